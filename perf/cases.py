@@ -1,0 +1,329 @@
+"""The work that a user of this library has it do, as measurable cases.
+
+A case is one pass through the public entry points (paper_2204_01205_amd.binding): a spectral
+convolution (eq. (3) of arXiv 2204.01205) or an FNO block (eq. (2)), forward alone as in inference or
+forward and backward as in training, or a whole network (lift, blocks, projection; in training also the
+relative L2 misfit, every adjoint and the Adam update).  `listed()` names the cases that stand for the
+uses, `draw()` gives more of the same ranges, `prepare()` makes what a program holds before the call
+(inputs, weights, buffers, workspace), `run()` is the pass, `work()` the bytes and operations it cannot
+do without and `tolerance()` how far two correct fp32 implementations may differ.
+"""
+import math
+
+import torch
+
+from paper_2204_01205_amd import binding as B
+
+OPS = ("conv", "conv_train", "block", "block_train", "network", "network_train")
+
+
+def _case(name, op, batch, c_in, width, grid, modes, rule=0, act=1, planned=False, mse=False, lift="none",
+          blocks=0, hidden=0):
+    """batch entries, c_in -> width channels (a block: c_in == width; a network: c_in is what the lift
+    reads), grid Nx Ny Nz Nt, kept modes per side on x, y, z and their count on t.
+    planned: the twiddle tables are written once and kept with the workspace (a serving program);
+    mse: the block's backward starts from the target of a mean squared error instead of a cotangent;
+    lift: "channel" (input given on the whole grid) or "time" (input without a time axis)."""
+    case = dict(op=op, batch=batch, c_in=c_in, width=width, nx=grid[0], ny=grid[1], nz=grid[2], nt=grid[3],
+                mx=modes[0], my=modes[1], mz=modes[2], mt=modes[3], rule=rule, act=act, planned=planned, mse=mse,
+                lift=lift, blocks=blocks, hidden=hidden)
+    return case if name is None else dict(name=name, **case)
+
+
+def listed():
+    return [
+        # the smallest workload of the configurations: a call bound by latency and launches
+        _case("conv_16", "conv", 1, 8, 8, (16, 16, 16, 8), (4, 4, 4, 3)),
+        # a layer embedded in a model of the user's own: other widths in and out, sizes without a power of
+        # two, the symmetric mode rule; forward and both gradients
+        _case("conv_train_odd", "conv_train", 2, 12, 16, (30, 27, 21, 14), (6, 5, 4, 5), rule=1),
+        # a small surrogate served in small batches, the plan kept between calls
+        _case("block_serve", "block", 4, 16, 16, (28, 24, 20, 10), (5, 4, 4, 4), planned=True),
+        # a block of moderate size at the width of the paper
+        _case("block_64", "block", 2, 20, 20, (64, 64, 64, 16), (12, 12, 12, 8)),
+        # one GPU's share of the paper's weak scaling runs, 64 x 64 x 64 points and 20 time steps: training
+        _case("block_train_64x20", "block_train", 1, 20, 20, (64, 64, 64, 20), (12, 12, 12, 8)),
+        # a wider model on a ragged grid: training with the symmetric mode rule
+        _case("block_train_wide", "block_train", 1, 32, 32, (50, 45, 40, 24), (8, 7, 6, 8), rule=1, mse=True),
+        # one training step of the network at the paper's training samples: the input has no time axis
+        _case("net_train_60", "network_train", 1, 2, 20, (60, 60, 64, 30), (12, 12, 12, 8), lift="time", blocks=4,
+              hidden=128),
+        # inference at the grid of the full reservoir model (a prime z axis)
+        _case("net_263", "network", 1, 2, 20, (68, 118, 263, 16), (12, 16, 24, 8), planned=True, lift="time",
+              blocks=4, hidden=128),
+        # inference of the benchmark network: input with coordinate channels on the whole grid
+        _case("net_128", "network", 1, 5, 20, (128, 128, 64, 32), (16, 16, 12, 9), lift="channel", blocks=4,
+              hidden=128),
+        # and one training step of it
+        _case("net_train_128", "network_train", 1, 5, 20, (128, 128, 64, 32), (16, 16, 12, 9), lift="channel",
+              blocks=4, hidden=128),
+        # the largest training step of a block (batch 4, mean squared error)
+        _case("block_train_128", "block_train", 4, 20, 20, (128, 128, 128, 16), (16, 16, 16, 9), mse=True),
+        # the largest grid one GPU holds: inference of a block
+        _case("block_256", "block", 1, 20, 20, (256, 256, 128, 32), (24, 24, 16, 9)),
+    ]
+
+
+def draw(rng):
+    """One more case of the same ranges: any operation, axis lengths spread over their logarithm with odd
+    ones among them, the time lengths of the configurations as often as any other."""
+    def spread(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    while True:
+        op = rng.choice(OPS)
+        nx, ny, nz = spread(12, 160), spread(12, 160), spread(8, 160)
+        if rng.random() < 0.5:                     # grids are often made of round numbers
+            nx, ny, nz = (max(8, 4 * round(n / 4)) for n in (nx, ny, nz))
+        nt = rng.choice((8, 10, 12, 16, 20, 24, 30, 32, 40, 48)) if rng.random() < 0.75 else rng.randint(5, 48)
+        width = rng.choice((8, 16, 20, 20, 20, 24, 32)) if rng.random() < 0.75 else rng.randint(4, 32)
+        batch = rng.choice((1, 1, 2, 3, 4))
+        rule = 1 if rng.random() < 0.25 else 0
+        modes = [max(1, min(int(n * rng.uniform(0.1, 0.22)), (n - rule) // 2)) for n in (nx, ny, nz)]
+        modes.append(max(1, min(int(round(nt * rng.uniform(0.25, 0.5))), nt // 2 + 1, 16)))
+        case = _case(None, op, batch, width, width, (nx, ny, nz, nt), modes, rule=rule, planned=rng.random() < 0.25)
+        if op.startswith("conv"):
+            case.update(c_in=rng.choice((width, width, max(2, width // 2))), act=0)
+        elif op.startswith("block"):
+            case.update(act=0 if rng.random() < 0.15 else 1, mse=op == "block_train" and rng.random() < 0.5)
+        else:
+            lift = rng.choice(("time", "channel"))
+            case.update(lift=lift, c_in=rng.randint(1, 3) if lift == "time" else rng.randint(2, 6), batch=min(batch, 2),
+                        blocks=rng.choice((2, 4)), hidden=rng.choice((64, 128)))
+        kept = _kept(case)[1]
+        values = case["batch"] * case["width"] * nx * ny * nz * nt
+        weights = max(1, case["blocks"]) * 2 * case["c_in" if op.startswith("conv") else "width"] * case["width"] * kept
+        # the (z, t) planes that every version of the layer covers (a z axis that is no multiple of 4 with
+        # all channels of up to 64 rows), and what the card holds comfortably
+        plane = nz * (nt + 2 * modes[3] + 2) <= 14000
+        if nz % 4 and width * min(nz, 64) * (nt + 1 + 2 * modes[3]) > 15500:
+            plane = False
+        if plane and values * max(1, case["blocks"]) <= 8e8 and weights <= 3e8:
+            return case
+
+
+def _kept(case):
+    counts = [2 * case[m] + case["rule"] for m in ("mx", "my", "mz")] + [case["mt"]]
+    return counts, counts[0] * counts[1] * counts[2] * counts[3]
+
+
+def _points(case):
+    return case["nx"] * case["ny"] * case["nz"] * case["nt"]
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(int(seed))
+    batch, width, grid = case["batch"], case["width"], (case["nx"], case["ny"], case["nz"], case["nt"])
+    modes = (case["mx"], case["my"], case["mz"], case["mt"])
+    counts, kept = _kept(case)
+    op, train, network = case["op"], case["op"].endswith("train"), case["op"].startswith("network")
+    c_in = width if network else case["c_in"]       # channels that the spectral layers read
+
+    def normal(*shape, std=1.0):
+        return torch.randn(shape, device="cuda", generator=gen).mul_(std)
+
+    def empty(*shape):
+        return torch.empty(shape, device="cuda")
+
+    def spectral():                                  # Re, Im ~ N(0, 1 / (Cin Cout))
+        return torch.view_as_complex(normal(c_in, width, *counts, 2, std=(c_in * width) ** -0.5))
+
+    flags = (B.FNO_FLAG_MSE_TARGET if case["mse"] else 0) | (B.FNO_FLAG_TABLES_READY if case["planned"] else 0)
+    desc = B.make_desc(batch, c_in, width, grid, modes, case["rule"], case["act"], flags)
+    kind = ((B.FNO_OP_SPECTRAL_CONV_BWD if train else B.FNO_OP_SPECTRAL_CONV_FWD) if op.startswith("conv")
+            else (B.FNO_OP_BLOCK_BWD if train else B.FNO_OP_BLOCK_FWD))
+    s = dict(case=case, desc=desc, ws=B.alloc_workspace(desc, kind))
+    if case["planned"]:
+        B.fno_plan_tables(desc, kind, s["ws"])
+
+    def field(channels):
+        return normal(batch, channels, *grid)
+
+    def spectrum():
+        return torch.empty((batch, c_in) + tuple(counts), dtype=torch.complex64, device="cuda")
+
+    if not network:
+        s.update(x=field(c_in), R=spectral(), out=empty(batch, width, *grid))
+        if op.startswith("block"):
+            s.update(W=normal(width, width, std=width ** -0.5), b=normal(width, std=0.1))
+        if train:
+            s.update(xh=spectrum(), g=field(width), gx=torch.empty_like(s["x"]), gR=torch.empty_like(s["R"]))
+            if op.startswith("block"):
+                s.update(z=torch.empty_like(s["out"]), gW=torch.empty_like(s["W"]), gb=torch.empty_like(s["b"]))
+        return s
+
+    ci, hidden, nblocks, nt = case["c_in"], case["hidden"], case["blocks"], case["nt"]
+    time_lift = case["lift"] == "time"
+    s["a"] = normal(batch, ci, *(grid[:3] if time_lift else grid))
+    # the parameters: lift, projection, then (R, W, b) of every block
+    params = [normal(width, ci, std=ci ** -0.5), normal(width, std=0.1)]
+    if time_lift:
+        params += [normal(nt), normal(nt, std=0.3)]
+    params += [normal(hidden, width, std=width ** -0.5), normal(hidden, std=0.1), normal(1, hidden, std=hidden ** -0.5),
+               normal(1, std=0.1)]
+    for _ in range(nblocks):
+        params += [spectral(), normal(width, width, std=width ** -0.5), normal(width, std=0.1)]
+    s["params"], s["u"] = params, empty(batch, 1, *grid)
+    nv = nblocks + 1 if train else 2                 # training keeps every block's input, inference two fields
+    s["v"] = [empty(batch, width, *grid) for _ in range(nv)]
+    if train:
+        s.update(y=field(1), gu=torch.empty_like(s["u"]), loss=empty(1), step=1000)
+        s["z"] = [empty(batch, width, *grid) for _ in range(nblocks)]
+        s["xh"] = [spectrum() for _ in range(nblocks)]
+        s["gv"] = [empty(batch, width, *grid) for _ in range(2)]
+        s["grads"] = [torch.empty_like(p) for p in params]
+        # the optimiser's moments in the middle of a training run
+        s["moments"] = [(normal(f.numel(), std=3e-5), normal(f.numel(), std=1e-4).square_().add_(1e-9))
+                        for f in map(_flat, params)]
+        scratch = max(B.fno_pointwise_bwd_workspace_bytes(width, hidden, 1), B.fno_rel_l2_workspace_bytes(),
+                      B.fno_time_lift_bwd_workspace_bytes(ci, width, nt) if time_lift
+                      else B.fno_pointwise_bwd_workspace_bytes(ci, 0, width))
+        s["scratch"] = empty(scratch // 4 + 2)
+    return s
+
+
+def _flat(p):
+    return (torch.view_as_real(p) if p.is_complex() else p).reshape(-1)
+
+
+def run(s):
+    case = s["case"]
+    return {"conv": _conv, "conv_train": _conv_train, "block": _block, "block_train": _block_train,
+            "network": _network, "network_train": _network_train}[case["op"]](s, case)
+
+
+def _conv(s, case):
+    B.fno_spectral_conv_fwd(s["desc"], s["x"], s["R"], s["out"], None, s["ws"])
+    return s["out"]
+
+
+def _conv_train(s, case):
+    B.fno_spectral_conv_fwd(s["desc"], s["x"], s["R"], s["out"], s["xh"], s["ws"])
+    B.fno_spectral_conv_bwd(s["desc"], s["x"], s["xh"], s["R"], s["g"], s["gx"], s["gR"], s["ws"])
+    return s["out"], s["gx"], s["gR"]
+
+
+def _block(s, case):
+    B.fno_block_fwd(s["desc"], s["x"], s["R"], s["W"], s["b"], s["out"], None, None, s["ws"])
+    return s["out"]
+
+
+def _block_train(s, case):
+    B.fno_block_fwd(s["desc"], s["x"], s["R"], s["W"], s["b"], s["out"], s["z"], s["xh"], s["ws"])
+    B.fno_block_bwd(s["desc"], s["x"], s["R"], s["W"], s["z"], s["xh"], s["g"], s["gx"], s["gR"], s["gW"], s["gb"],
+                    s["ws"])
+    return s["out"], s["gx"], s["gR"], s["gW"], s["gb"]
+
+
+def _split(params, case):
+    """(lift parameters, projection parameters, [(R, W, b)] per block) of a network's flat list."""
+    nl = 4 if case["lift"] == "time" else 2
+    body = params[nl + 4:]
+    return params[:nl], params[nl:nl + 4], [body[3 * k: 3 * k + 3] for k in range(case["blocks"])]
+
+
+def _lift(s, case, lift, out):
+    batch, ci, width = case["batch"], case["c_in"], case["width"]
+    if case["lift"] == "time":
+        wc, bc, wt, bt = lift
+        B.fno_time_lift(batch, ci, width, case["nx"] * case["ny"] * case["nz"], case["nt"], s["a"], wt, bt, wc, bc, out)
+    else:
+        B.fno_pointwise_linear(batch, ci, width, _points(case), s["a"], lift[0], lift[1], out)
+
+
+def _network(s, case):
+    lift, (w1, b1, w2, b2), blocks = _split(s["params"], case)
+    v = s["v"]
+    _lift(s, case, lift, v[0])
+    for k, (R, W, b) in enumerate(blocks):
+        B.fno_block_fwd(s["desc"], v[k & 1], R, W, b, v[(k + 1) & 1], None, None, s["ws"])
+    B.fno_pointwise_mlp2(case["batch"], case["width"], case["hidden"], 1, _points(case), v[len(blocks) & 1], w1, b1, w2,
+                         b2, s["u"])
+    return s["u"]
+
+
+def _network_train(s, case):
+    batch, ci, width, hidden, points = case["batch"], case["c_in"], case["width"], case["hidden"], _points(case)
+    lift, (w1, b1, w2, b2), blocks = _split(s["params"], case)
+    glift, (gw1, gb1, gw2, gb2), gblocks = _split(s["grads"], case)
+    v, scratch, desc, ws = s["v"], s["scratch"], s["desc"], s["ws"]
+    _lift(s, case, lift, v[0])
+    for k, (R, W, b) in enumerate(blocks):
+        B.fno_block_fwd(desc, v[k], R, W, b, v[k + 1], s["z"][k], s["xh"][k], ws)
+    B.fno_pointwise_mlp2(batch, width, hidden, 1, points, v[-1], w1, b1, w2, b2, s["u"])
+    B.fno_rel_l2_loss(s["u"].numel(), s["u"], s["y"], s["loss"], s["gu"], scratch)
+    gin, gout = s["gv"]
+    B.fno_pointwise_mlp2_bwd(batch, width, hidden, 1, points, v[-1], w1, b1, w2, s["gu"], gin, gw1, gb1, gw2, gb2,
+                             scratch)
+    for k in reversed(range(len(blocks))):
+        R, W, b = blocks[k]
+        gR, gW, gb = gblocks[k]
+        B.fno_block_bwd(desc, v[k], R, W, s["z"][k], s["xh"][k], gin, gout, gR, gW, gb, ws)
+        gin, gout = gout, gin
+    if case["lift"] == "time":
+        wc, bc, wt, bt = lift
+        gwc, gbc, gwt, gbt = glift
+        B.fno_time_lift_bwd(batch, ci, width, case["nx"] * case["ny"] * case["nz"], case["nt"], s["a"], wt, bt, wc, gin,
+                            gwt, gbt, gwc, gbc, scratch)
+    else:
+        B.fno_pointwise_linear_bwd(batch, ci, width, points, s["a"], lift[0], gin, None, glift[0], glift[1], scratch)
+    s["step"] += 1
+    for p, g, (m, q) in zip(s["params"], s["grads"], s["moments"]):
+        p, g = _flat(p), _flat(g)
+        B.fno_adam_step(p.numel(), p, g, m, q, 1e-3, 0.9, 0.999, 1e-8, s["step"])
+    return s["loss"], s["u"], s["grads"], s["params"]
+
+
+def work(case):
+    """Bytes: every tensor that enters or leaves a call of the pass once per call, nothing in between.
+    Operations: the kept-mode products, the channel maps, and fast transforms of the length of each axis
+    over the data that is left at that axis (t, z, y, x in turn)."""
+    counts, kept = _kept(case)
+    batch, width, n = case["batch"], case["width"], _points(case)
+    op, train, network = case["op"], case["op"].endswith("train"), case["op"].startswith("network")
+    ci = width if network else case["c_in"]
+    nx, ny, nz, nt = (case[k] for k in ("nx", "ny", "nz", "nt"))
+    lx, ly, lz, mt = counts
+
+    def lg(v):
+        return max(1.0, math.log2(v))
+
+    # one transform of a real field of one channel to its kept modes, or back
+    dft = (2.5 * n * lg(nt) + 5.0 * nx * ny * mt * (nz * lg(nz)) + 5.0 * nx * lz * mt * (ny * lg(ny))
+           + 5.0 * ly * lz * mt * (nx * lg(nx)))
+    mix = 8.0 * batch * ci * width * kept
+    weights, spec = 8.0 * ci * width * kept, 8.0 * batch * ci * kept
+    fin, fout = 4.0 * batch * ci * n, 4.0 * batch * width * n
+    fwd_b, fwd_f = fin + fout + weights, batch * (ci + width) * dft + mix
+    bwd_b, bwd_f = fin + fout + 2 * weights + spec, batch * (ci + width) * dft + 2 * mix
+    if not op.startswith("conv"):
+        fwd_f += batch * n * width * (2.0 * width + 20)
+        bwd_b += 2 * fout                            # the pre-activation and the block's input
+        bwd_f += batch * n * width * (4.0 * width + 30)
+    if train:
+        fwd_b += spec + (0 if op.startswith("conv") else fout)
+    layers = max(1, case["blocks"])
+    nbytes, flops = layers * (fwd_b + (bwd_b if train else 0)), layers * (fwd_f + (bwd_f if train else 0))
+    if network:
+        a = 4.0 * batch * case["c_in"] * (n // nt if case["lift"] == "time" else n)
+        u, hid = 4.0 * batch * n, case["hidden"]
+        nbytes += a + fout + fout + u                # lift, projection
+        flops += batch * n * (2.0 * case["c_in"] * width + hid * (2.0 * width + 22))
+        if train:
+            nbytes += 3 * u + (2 * fout + u) + (fout + a)         # misfit, adjoint of the projection, of the lift
+            flops += batch * n * (2.0 * case["c_in"] * width + hid * (6.0 * width + 30))
+            nbytes += 28.0 * (layers * (2.0 * ci * width * kept + width * width))     # Adam: four arrays in, three out
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    # fp32 throughout.  Measured against the same path in float64: the tensors of one layer or block are off
+    # by 1e-7 to 3.2e-7 of their norm and 1.5e-6 of their scale at most, the output of a network of four
+    # blocks by 1.5e-6 to 2.4e-6 (2e-5 at most), its gradients by 1e-6 to 9e-6 (1.2e-3 at most, single
+    # entries of a spectral weight's gradient).  About four times that is stated.
+    if case["op"] == "network_train":
+        return {"rel": 4e-5, "max": 5e-3}
+    if case["op"] == "network":
+        return {"rel": 1e-5, "max": 1e-4}
+    return {"rel": 1.5e-6, "max": 1e-5}
