@@ -319,11 +319,14 @@ def work(case):
 
 def tolerance(case):
     # fp32 throughout.  Measured against the same path in float64: the tensors of one layer or block are off
-    # by 1e-7 to 3.2e-7 of their norm and 1.5e-6 of their scale at most, the output of a network of four
+    # by 1e-7 to 3.2e-7 of their norm, single values by 3e-6 of their scale (by 4e-5 in a spectral weight's
+    # gradient, whose modes next to a large mean feel the mean's rounding), the output of a network of four
     # blocks by 1.5e-6 to 2.4e-6 (2e-5 at most), its gradients by 1e-6 to 9e-6 (1.2e-3 at most, single
     # entries of a spectral weight's gradient).  About four times that is stated.
     if case["op"] == "network_train":
         return {"rel": 4e-5, "max": 5e-3}
     if case["op"] == "network":
         return {"rel": 1e-5, "max": 1e-4}
-    return {"rel": 1.5e-6, "max": 1e-5}
+    if case["op"] == "block_train":
+        return {"rel": 1.5e-6, "max": 2e-4}
+    return {"rel": 1.5e-6, "max": 2e-5}
