@@ -30,7 +30,8 @@ struct Plan {
   int64_t K;             // kept modes per (batch, channel)
   int64_t Npts;          // grid points per (batch, channel)
   // workspace offsets in bytes
-  size_t off_ztab, off_twt, off_tw[3], off_twf[2], off_a1, off_a2, off_s1, off_s2, off_s3, off_gz, off_part, total;
+  bool folded;           // the folded z table is there
+  size_t off_ztab, off_twt, off_tw[3], off_twf[2], off_fold, off_a1, off_a2, off_s1, off_s2, off_s3, off_gz, off_part, total;
   int part_blocks;
 };
 
@@ -119,6 +120,9 @@ int make_plan(const fno_desc* d, bool need_block, bool need_bwd_block, Plan* p) 
     p->off_twf[a] = p->off_tw[a];
     if (p->axf[a].P != p->ax[a].P) { p->off_twf[a] = off; off = align_up(off + (size_t)p->axf[a].L * p->axf[a].P * 8); }
   }
+  p->folded = fno::tz_fwd_fold_fits(p->ax[2], p->Nt, p->mt);
+  p->off_fold = off;
+  if (p->folded) off = align_up(off + fno::fold_plan(p->ax[2]).floats * 4);
   const size_t bc = (size_t)p->B * Cm;
   p->off_a1 = off; off = align_up(off + bc * p->N[0] * p->N[1] * p->L[2] * p->mt * 8);
   p->off_a2 = off; off = align_up(off + bc * p->N[0] * p->L[1] * p->L[2] * p->mt * 8);
@@ -209,6 +213,10 @@ int build_tables(const Plan& p, void* ws, hipStream_t s, bool tables_ready = fal
   for (int a = 0; a < 2; ++a)
     if (p.off_twf[a] != p.off_tw[a])
       ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_twf[a]), p.axf[a].N, p.axf[a].L, p.axf[a].npos, p.axf[a].P};
+  if (p.folded) {
+    const fno::FoldPlan f = fno::fold_plan(p.ax[2]);
+    ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_fold), p.ax[2].N, -f.rows, 0, f.stride};
+  }
   FNO_HIP(fno::launch_plan_tables(ts, s));
   return FNO_OK;
 }
@@ -219,7 +227,7 @@ int forward_chain(const Plan& p, void* ws, const float* field, int C, float2* sp
   float2* a1 = at<float2>(ws, p.off_a1);
   float2* a2 = at<float2>(ws, p.off_a2);
   FNO_STAGE(FNO_STAGE_TZ_FWD, s, fno::launch_tz_fwd(field, a1, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]),
-                             bc * p.N[0] * p.N[1], p.ax[2], p.Nt, p.mt, s));
+                             p.folded ? at<float>(ws, p.off_fold) : nullptr, bc * p.N[0] * p.N[1], p.ax[2], p.Nt, p.mt, s));
   const int64_t in_y = (int64_t)p.L[2] * p.mt;
   FNO_STAGE(FNO_STAGE_Y_FWD, s, fno::launch_axis_fwd(a1, a2, at<float2>(ws, p.off_twf[1]), bc * p.N[0], p.axf[1], in_y, s));
   const int64_t in_x = in_y * p.L[1];

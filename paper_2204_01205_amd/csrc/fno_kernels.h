@@ -18,14 +18,32 @@ struct AxisPlan {
 // Fill the twiddle tables:  tw[j*P + n2] = exp(-2 pi i k_j n2 / N)  for an AxisPlan, and
 // twt[kt*Nt + n] = exp(-2 pi i kt n / Nt) for the real axis.
 // Twiddle tables of a plan, written by one launch.  Axis table: L > 0, [L][P] entries
-// w_N^(k_j n2); t table: L = 0, [npos][N] entries w_N^(kt n).
+// w_N^(k_j n2); t table: L = 0, [npos][N] entries w_N^(kt n); folded table: L = -rows, P = stride
+// (see FoldPlan).
 struct TableDesc { float2* tw; int N, L, npos, P; };
-struct TableSet { TableDesc t[6]; int n; };
+struct TableSet { TableDesc t[8]; int n; };
+
+// z table of the folded product (fno_tz_fwd_fold.hip), for the frequencies k = 0 .. kmax of an axis of
+// length N and its pairs of rows n, N - 1 - n (nu = n + 1/2): cos(2 pi k nu / N) [rows][stride], halved
+// where a row is its own pair, then sin(2 pi k nu / N) [rows][stride], then exp(i pi k / N) [rows].
+struct FoldPlan {
+  int rows;        // kmax + 1, padded to whole row tiles
+  int pairs;       // ceil(N / 2)
+  int stride;      // floats per row
+  size_t floats;   // of the whole table
+};
+FoldPlan fold_plan(AxisPlan az);
 hipError_t launch_plan_tables(const TableSet& ts, hipStream_t s);
 
 // Forward (t, z): x[planes][Nz][Nt] real  ->  out[planes][Lz][mt] complex.
-hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const float2* twz,
+// ztab: the folded table of the z axis, or null where tz_fwd_fold_fits() says no.
+hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const float2* twz, const float* ztab,
                          int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s);
+
+// The same for any lengths (see fno_tz_fwd_fold.hip); ztab: the folded table of the z axis.
+bool tz_fwd_fold_fits(AxisPlan az, int Nt, int mt);
+hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, const float* ztab,
+                              int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s);
 
 // Complex pruned transform along the middle axis of [outer][N|L][inner].
 hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int64_t outer,

@@ -23,7 +23,7 @@ namespace {
 // ------------------------------------------------------------------------------------------
 // All tables of a plan in one launch: blockIdx.y picks the table.  An axis table holds
 // w_N^(k_j n2) for the kept frequencies k_j and the residue classes n2 < P; the t table (L = 0)
-// holds w_Nt^(kt n) for kt < npos (= mt), n < N (= Nt).
+// holds w_Nt^(kt n) for kt < npos (= mt), n < N (= Nt); the folded table is described at FoldPlan.
 __global__ void plan_tables_kernel(TableSet ts) {
   const TableDesc t = ts.t[blockIdx.y];
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -36,6 +36,23 @@ __global__ void plan_tables_kernel(TableSet ts) {
     double s, c;
     sincospi(-2.0 * double(r) / double(t.N), &s, &c);
     t.tw[idx] = make_float2(float(c), float(s));
+  } else if (t.L < 0) {
+    const int rows = -t.L, stride = t.P;
+    if (idx >= rows * stride) return;
+    const int k = idx / stride, n = idx - k * stride;
+    float* f = reinterpret_cast<float*>(t.tw);
+    double s = 0.0, c = 0.0;
+    if (2 * n < t.N) {
+      const long long r = ((long long)k * (2 * n + 1)) % (2LL * t.N);      // angle pi r / N
+      sincospi(double(r) / double(t.N), &s, &c);
+      if (2 * n + 1 == t.N) c *= 0.5;
+    }
+    f[idx] = float(c);
+    f[rows * stride + idx] = float(s);
+    if (n == 0) {
+      sincospi(double(k % (2 * t.N)) / double(t.N), &s, &c);
+      reinterpret_cast<float2*>(f + 2 * rows * stride)[k] = make_float2(float(c), float(s));
+    }
   } else {
     if (idx >= t.N * t.npos) return;
     const int kt = idx / t.N, n = idx % t.N;
@@ -184,120 +201,6 @@ __global__ __launch_bounds__(kThreads) void tz_fwd_kernel(
     const float2* base = T + (p * mt + kt) * sT + Pz * mj;
     const float2* w = twz + jz * Pz;
     out[((plane0 + p) * Lz + jz) * mt + kt] = combine_terms(w, base, 1, Pz);
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// Forward (t, z) for a z axis with no power of two in its length (the z transform is a dense
-// truncated DFT) and Nt a multiple of 4.  Rows are read straight from memory (one float4 run per
-// thread) for the real-to-complex t stage; the z stage, out[jz][(p,kt)] = sum_n w[jz][n]
-// T[(p,kt)][n], is a matrix product on 16x16x4 fp32 MFMA tiles (lane l supplies A[l%16][l/16] and
-// B[l/16][l%16], holds rows 4 (l/16) + v of column l%16): the 16 columns are the kt bins of
-// 16/mt planes, the z rows (K) are dealt to the four waves, whose partial sums meet in LDS.
-// ------------------------------------------------------------------------------------------
-constexpr int kDenseMT = 3;     // row tiles (16 kept z-frequencies each) per sweep
-// row stride in complex values, 4 mod 16: the 16 lanes of a K step read 4 columns x 4 rows that
-// fall on distinct banks
-__host__ __device__ inline int tzd_row_stride(int Nz) { return Nz + ((20 - (Nz & 15)) & 15); }
-
-__global__ __launch_bounds__(kThreads) void tz_fwd_dense_kernel(
-    const float* __restrict__ x, float2* __restrict__ out, const float2* __restrict__ twt,
-    const float2* __restrict__ twz, long long planes, int Nz, int Nt, int Lz, int mt, int ppb, int alias) {
-  HIP_DYNAMIC_SHARED(float, smem)
-  const int sT = tzd_row_stride(Nz);
-  float2* T = reinterpret_cast<float2*>(smem);                 // [16][sT]
-  // [4][kDenseMT * 16][16] partial sums; when one sweep covers all kept z-frequencies they take
-  // T's place once the sweep has read it (alias = 1), which halves the block's LDS
-  float2* P = alias ? T : T + 16 * sT;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
-  const long long plane0 = xcd_contiguous_item(blockIdx.x, gridDim.x) * ppb;   // grid: a multiple of 8
-  if (plane0 >= planes) return;
-  const int np = (int)min((long long)ppb, planes - plane0);
-  const int ncol = np * mt;
-
-  // t stage: one thread per z-row, every kept bin
-  for (int row = tid; row < np * Nz; row += kThreads) {
-    const int p = row / Nz, z = row - p * Nz;
-    const float4* xr = reinterpret_cast<const float4*>(x + ((plane0 + p) * Nz + z) * (long long)Nt);
-    float2 acc[16];
-#pragma unroll
-    for (int kt = 0; kt < 16; ++kt) acc[kt] = make_float2(0.f, 0.f);
-    for (int n = 0; n < Nt; n += 4) {
-      const float4 v = xr[n >> 2];
-#pragma unroll
-      for (int kt = 0; kt < 16; ++kt) {
-        if (kt < mt) {
-          const float2* wp = twt + kt * Nt + n;
-          const float2 w0 = wp[0], w1 = wp[1], w2 = wp[2], w3 = wp[3];
-          acc[kt].x = fmaf(v.x, w0.x, acc[kt].x); acc[kt].y = fmaf(v.x, w0.y, acc[kt].y);
-          acc[kt].x = fmaf(v.y, w1.x, acc[kt].x); acc[kt].y = fmaf(v.y, w1.y, acc[kt].y);
-          acc[kt].x = fmaf(v.z, w2.x, acc[kt].x); acc[kt].y = fmaf(v.z, w2.y, acc[kt].y);
-          acc[kt].x = fmaf(v.w, w3.x, acc[kt].x); acc[kt].y = fmaf(v.w, w3.y, acc[kt].y);
-        }
-      }
-    }
-#pragma unroll
-    for (int kt = 0; kt < 16; ++kt)
-      if (kt < mt) T[(p * mt + kt) * sT + z] = acc[kt];
-  }
-  __syncthreads();
-
-  // z stage
-  const int nmt = (Lz + 15) >> 4, ksteps = (Nz + 3) >> 2;
-  for (int mg = 0; mg < nmt; mg += kDenseMT) {
-    v4f re[kDenseMT], im[kDenseMT];
-#pragma unroll
-    for (int m = 0; m < kDenseMT; ++m) {
-      re[m] = v4f{0.f, 0.f, 0.f, 0.f};
-      im[m] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
-    for (int s0 = w; s0 < ksteps; s0 += 8) {           // two K steps per pass: their loads go out together
-      float2 bv[2], av[2][kDenseMT];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int n = 4 * (s0 + 4 * u) + lk;
-        const bool nok = n < Nz;
-        bv[u] = (nok && lr < ncol) ? T[lr * sT + n] : make_float2(0.f, 0.f);
-#pragma unroll
-        for (int m = 0; m < kDenseMT; ++m) {
-          const int jz = (mg + m) * 16 + lr;
-          av[u][m] = (nok && jz < Lz) ? twz[jz * Nz + n] : make_float2(0.f, 0.f);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int m = 0; m < kDenseMT; ++m) {
-          re[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][m].x, bv[u].x, re[m], 0, 0, 0);
-          re[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av[u][m].y, bv[u].y, re[m], 0, 0, 0);
-          im[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][m].x, bv[u].y, im[m], 0, 0, 0);
-          im[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][m].y, bv[u].x, im[m], 0, 0, 0);
-        }
-    }
-    if (alias) __syncthreads();                          // every wave is done reading T
-#pragma unroll
-    for (int m = 0; m < kDenseMT; ++m)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        P[(w * (kDenseMT * 16) + m * 16 + 4 * lk + v) * 16 + lr] = make_float2(re[m][v], im[m][v]);
-    __syncthreads();
-    for (int idx = tid; idx < np * (kDenseMT * 16) * mt; idx += kThreads) {
-      const int kt = idx % mt;
-      const int jzl = (idx / mt) % (kDenseMT * 16);
-      const int p = idx / (mt * kDenseMT * 16);
-      const int jz = mg * 16 + jzl;
-      if (jz < Lz) {
-        const int col = p * mt + kt;
-        float2 sum = make_float2(0.f, 0.f);
-#pragma unroll
-        for (int ww = 0; ww < kThreads / 64; ++ww) {
-          const float2 v = P[(ww * (kDenseMT * 16) + jzl) * 16 + col];
-          sum.x += v.x; sum.y += v.y;
-        }
-        out[((plane0 + p) * Lz + jz) * mt + kt] = sum;
-      }
-    }
-    __syncthreads();
   }
 }
 
@@ -854,7 +757,8 @@ hipError_t launch_plan_tables(const TableSet& ts, hipStream_t s) {
   if (ts.n <= 0) return hipSuccess;
   int most = 1;
   for (int i = 0; i < ts.n; ++i) {
-    const int n = ts.t[i].L > 0 ? ts.t[i].L * ts.t[i].P : ts.t[i].N * ts.t[i].npos;
+    const int L = ts.t[i].L;
+    const int n = L != 0 ? (L > 0 ? L : -L) * ts.t[i].P : ts.t[i].N * ts.t[i].npos;
     if (n > most) most = n;
   }
   hipLaunchKernelGGL(plan_tables_kernel, dim3((most + 255) / 256, ts.n), dim3(256), 0, s, ts);
@@ -873,7 +777,7 @@ size_t tz_fast_lds(AxisPlan az, int Nt, int mt, int ppb) {
   return ((size_t)tz_fast_region(az, Nt, mt, ppb) + tw_floats) * 4;
 }
 
-hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const float2* twz,
+hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const float2* twz, const float* ztab,
                          int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s) {
   if (planes <= 0) return hipSuccess;
   // in-register t stage: the power-of-two lengths, and 30 (the time steps of the paper's training samples)
@@ -928,20 +832,7 @@ hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const f
 #undef FNO_TZF_S
     return hipGetLastError();
   }
-  if (az.M == 1 && Nt % 4 == 0 && mt <= 16 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-    const int ppb = 16 / mt;
-    const size_t t_bytes = (size_t)16 * tzd_row_stride(az.N) * 8;
-    const size_t p_bytes = (size_t)(kThreads / 64) * kDenseMT * 16 * 16 * 8;
-    const int alias = az.L <= kDenseMT * 16;      // one sweep: the partial sums reuse the rows' LDS
-    const size_t lds = alias ? (t_bytes > p_bytes ? t_bytes : p_bytes) : t_bytes + p_bytes;
-    const int64_t nblk = (((planes + ppb - 1) / ppb + 7) / 8) * 8;
-    if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (lds <= (size_t)(150 * 1024)) {
-      hipLaunchKernelGGL(tz_fwd_dense_kernel, dim3((unsigned)nblk), dim3(kThreads), lds, s, x, out, twt, twz,
-                         (long long)planes, az.N, Nt, az.L, mt, ppb, alias);
-      return hipGetLastError();
-    }
-  }
+  if (ztab != nullptr && tz_fwd_fold_fits(az, Nt, mt)) return launch_tz_fwd_fold(x, out, twt, ztab, planes, az, Nt, mt, s);
   int ppb = 1;
   // enough rows to occupy the block, within an LDS share that keeps several blocks per CU
   while (ppb * 2 * az.N <= 2 * kThreads && tz_fwd_lds(az, Nt, mt, ppb * 2) <= (size_t)(32 * 1024)) ppb *= 2;

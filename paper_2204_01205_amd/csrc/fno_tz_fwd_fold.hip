@@ -1,0 +1,304 @@
+// Forward (t, z) stage of the transform chain (F of eq. (3) of arXiv 2204.01205 along the last two
+// axes) for any axis lengths, as two chained real matrix products on the matrix cores.
+//
+// A plane of Nz x Nt reals goes to its kept bins in two contractions.  Over t: T[n][c] =
+// sum_t x[n][t] cs[t][c], c running over the cos and -sin columns of the kept bins.  Over z, folded
+// about the middle of the axis: with nu = n + 1/2 and the row pairs E[n] = T[n] + T[Nz-1-n],
+// O[n] = T[n] - T[Nz-1-n],
+//   X[+-k] = exp(+-i pi k / Nz) (C[k] -+ i S[k]),   C[k] = sum_n cos(2 pi k nu / Nz) E[n],
+//                                                    S[k] = sum_n sin(2 pi k nu / Nz) O[n],
+// n over the ceil(Nz / 2) pairs: both matrices are real, every pair of rows and every pair of
+// frequencies shares its products (a quarter of the multiply-adds of the plain complex sum), and no
+// row is special (an odd Nz pairs its middle row with itself, at half the weight).
+//
+// Both run on v_mfma_f32_16x16x4 (full fp32; lane l supplies A[l%16][l/16] and B[l/16][l%16] and holds
+// rows 4 (l/16) + v of column l%16).  One wave owns a plane: it folds 16 row pairs as they arrive from
+// memory (four lanes read 64 contiguous bytes of a row), turns them over t, and the accumulator
+// registers of that product are, as they stand, the right operand of the product over z (register v of
+// lane group g is row 4 g + v of the contraction, so the table operand is read in that order).  No
+// tile of the plane passes through LDS, no wave waits for another; LDS holds only the z table, which
+// a block's waves share over all planes they walk.
+//
+// What bounds it: the matrix cores at 32 cycles per instruction (a 263 x 16 plane with 49 frequencies and
+// 8 bins: 9 tiles of 8 + 16 instructions) next to one read of the field.  Measured against the kernels it
+// replaced (mixed-radix and dense complex sums on tiles staged in LDS): 263 x 16 planes, 2.7 GB read,
+// 2.20 -> 0.78 ms; 64 x 20, 0.42 GB, 0.25 -> 0.12 ms; 40 x 24, 0.28 GB, 0.16 -> 0.09 ms; 8 x 35, 0.18 GB,
+// 0.21 ms with one plane per tile -> 0.09 ms with four.
+#include "fno_device.h"
+
+namespace fno {
+
+namespace {
+
+template <int W> struct vec_of;
+template <> struct vec_of<1> { typedef float type; };
+template <> struct vec_of<2> { typedef v2f type; };
+template <> struct vec_of<3> { typedef float type __attribute__((ext_vector_type(3))); };
+template <> struct vec_of<4> { typedef v4f type; };
+
+// W consecutive floats at a 4-byte aligned address
+template <int W, bool STREAM>
+__device__ __forceinline__ void load_run(const float* p, float (&v)[W]) {
+  if constexpr (W == 1) {
+    v[0] = ld_once<STREAM>(p);
+  } else {
+    typedef typename vec_of<W>::type vec;
+    typedef vec unaligned __attribute__((aligned(4)));
+    vec q;
+    if constexpr (STREAM) q = __builtin_nontemporal_load(reinterpret_cast<const unaligned*>(p));
+    else q = *reinterpret_cast<const unaligned*>(p);
+#pragma unroll
+    for (int c = 0; c < W; ++c) v[c] = q[c];
+  }
+}
+
+__device__ __forceinline__ float swap_pair(float v) {      // the value of lane ^ 1
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
+}
+
+// registers of a variant (two row tiles in flight and folded, the t table, the accumulators, the z
+// table's operands and the addresses), and the waves per SIMD they allow
+constexpr int fold_regs(int KS, int CT, int MT, int PP) {
+  return KS * (4 + CT) + 8 * MT * CT * PP + (CT == 2 ? 16 : 6) * MT + 32;
+}
+constexpr int fold_waves(int KS, int CT, int MT, int PP) {
+  const int regs = fold_regs(KS, CT, MT, PP);
+  return regs <= 64 ? 8 : (regs <= 72 ? 6 : (regs <= 96 ? 5 : (regs <= 128 ? 4 : (regs <= 168 ? 3 : 2))));
+}
+
+// A row of Nt = 16 J + r floats (1 <= r <= 16): J runs of 16 (four per lane group) and a tail in which
+// lane group g takes W = ceil(r / 4) floats from min(W g, r - W), so that no lane reads past its row;
+// entries a lower group has already taken meet zeros in the t table.
+// PP planes of at most 16 / PP row pairs share a tile: row 4 g + v of it is pair (4 / PP) g + v % (4 / PP) of
+// plane v / (4 / PP), so that each register of the first product belongs to one plane.
+template <int J, int W, int CT, int MT, int PP, bool STREAM>
+__global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void tz_fwd_fold_kernel(
+    const float* __restrict__ x, float* __restrict__ out, const float2* __restrict__ twt,
+    const float* __restrict__ ztab, long long planes, int Nz, int Nt, int Lz, int npos, int mt, int mrows,
+    int pairs, int stride, int ngroups, int mgroups) {
+  HIP_DYNAMIC_SHARED(float, smem)
+  constexpr int KS = 4 * J + W;                 // K steps of the product over t
+  float* COS = smem;                            // [16 MT][stride]
+  float* SIN = smem + 16 * MT * stride;         // [16 MT][stride]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // uniform: plane addresses stay scalar
+  const int c = lane & 15, g = lane >> 4;
+  // blocks that share planes but not frequencies or columns sit on one XCD next to each other
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+  const int grp = local % ngroups;
+  const int m0 = 16 * MT * (grp % mgroups), c0 = 16 * CT * (grp / mgroups);
+  {
+    const float4* cs = reinterpret_cast<const float4*>(ztab + (long long)m0 * stride);
+    const float4* sn = reinterpret_cast<const float4*>(ztab + (long long)(mrows + m0) * stride);
+    const int n4 = (16 * MT * stride) >> 2;
+    for (int i = tid; i < n4; i += kThreads) {
+      reinterpret_cast<float4*>(COS)[i] = cs[i];
+      reinterpret_cast<float4*>(SIN)[i] = sn[i];
+    }
+  }
+  float2* ROT = reinterpret_cast<float2*>(SIN + 16 * MT * stride);      // [16 MT]
+  if (tid < 16 * MT) ROT[tid] = reinterpret_cast<const float2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
+  const int r = Nt - 16 * J;
+  const int t0 = min(W * g, r - W);             // start of this lane group's tail
+  float tb[CT][KS];                             // t table, the right operand of every K step
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int col = c0 + 16 * ct + c, kt = col >> 1;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int t = s < 4 * J ? 16 * (s >> 2) + 4 * g + (s & 3) : 16 * J + t0 + (s - 4 * J);
+      const bool dup = s >= 4 * J && t < 16 * J + W * g;
+      float v = 0.f;
+      if (kt < mt && !dup) {
+        const float2 w = twt[kt * Nt + t];
+        v = (col & 1) ? w.y : w.x;
+      }
+      tb[ct][s] = v;
+    }
+  }
+  const float sgn = (c & 1) ? -1.f : 1.f;
+  __syncthreads();
+
+  // each XCD walks a contiguous eighth of the planes, its waves interleaved inside it
+  const long long per_x = (planes + 7) >> 3;
+  const long long pe = min(planes, (long long)(xcd + 1) * per_x);
+  const long long nwl = (long long)((gridDim.x >> 3) / ngroups) * (kThreads / 64) * PP;
+  long long p = (long long)xcd * per_x + ((long long)(local / ngroups) * (kThreads / 64) + wave) * PP;
+  if (p >= pe) return;
+  const int ntile = PP > 1 ? 1 : (pairs + 15) >> 4;
+  constexpr int VP = 4 / PP;                    // registers of a lane that belong to one plane
+  const int lp = (c & 3) / VP, ln = VP * (c >> 2) + (c & (VP - 1));      // plane and pair of tile row c (PP > 1)
+
+  float va[KS], vb[KS];                         // this lane's part of row n and of row Nz - 1 - n
+  auto load_tile = [&](long long plane, int tile) {
+    const int n = min(PP > 1 ? ln : 16 * tile + c, pairs - 1);
+    const int first = PP > 1 ? min(lp, (int)min((long long)PP, planes - plane) - 1) * Nz : 0;      // row of the lane's plane
+    const float* base = x + plane * (Nz * Nt);
+    const float* ra = base + (first + n) * Nt;
+    const float* rb = base + (first + Nz - 1 - n) * Nt;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      float qa[4], qb[4];
+      load_run<4, STREAM>(ra + 16 * j + 4 * g, qa);
+      load_run<4, STREAM>(rb + 16 * j + 4 * g, qb);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { va[4 * j + u] = qa[u]; vb[4 * j + u] = qb[u]; }
+    }
+    float qa[W], qb[W];
+    load_run<W, STREAM>(ra + 16 * J + t0, qa);
+    load_run<W, STREAM>(rb + 16 * J + t0, qb);
+#pragma unroll
+    for (int u = 0; u < W; ++u) { va[4 * J + u] = qa[u]; vb[4 * J + u] = qb[u]; }
+  };
+  load_tile(p, 0);
+  for (; p < pe; p += nwl) {
+    v4f accC[PP][MT][CT], accS[PP][MT][CT];
+#pragma unroll
+    for (int q = 0; q < PP; ++q)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          accC[q][m][ct] = v4f{0.f, 0.f, 0.f, 0.f};
+          accS[q][m][ct] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+    for (int tile = 0; tile < ntile; ++tile) {
+      float e[KS], o[KS];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) { e[s] = va[s] + vb[s]; o[s] = va[s] - vb[s]; }
+      if (tile + 1 < ntile) load_tile(p, tile + 1);
+      else if (p + nwl < pe) load_tile(p + nwl, 0);
+      float ca[MT][VP], sa[MT][VP];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        typedef typename vec_of<VP>::type vec;
+        const int at = (16 * m + c) * stride + 16 * tile + VP * g;
+        const vec cq = *reinterpret_cast<const vec*>(COS + at), sq = *reinterpret_cast<const vec*>(SIN + at);
+#pragma unroll
+        for (int v = 0; v < VP; ++v) {
+          if constexpr (VP == 1) { ca[m][v] = cq; sa[m][v] = sq; }
+          else { ca[m][v] = cq[v]; sa[m][v] = sq[v]; }
+        }
+      }
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        v4f dE = {0.f, 0.f, 0.f, 0.f}, dO = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          dE = __builtin_amdgcn_mfma_f32_16x16x4f32(e[s], tb[ct][s], dE, 0, 0, 0);
+          dO = __builtin_amdgcn_mfma_f32_16x16x4f32(o[s], tb[ct][s], dO, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            v4f& C = accC[v / VP][m][ct];
+            v4f& S = accS[v / VP][m][ct];
+            C = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[m][v % VP], dE[v], C, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[m][v % VP], dO[v], S, 0, 0, 0);
+          }
+      }
+    }
+    // X[+-k] from C, S: real and imaginary parts sit in neighbouring lanes
+    // the phases and the store offsets are worked out again for every plane, not kept in registers
+    int g4 = 4 * g;
+    asm volatile("" : "+v"(g4)::"memory");
+#pragma unroll
+    for (int q = 0; q < PP; ++q) {
+      if (PP > 1 && p + q >= pe) break;
+      float* dst = out + (p + q) * (Lz * mt * 2);
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int kl = 16 * m + g4 + v, k = m0 + kl;
+          const float2 w = ROT[kl];
+          const float ws = sgn * w.y;
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const int col = c0 + 16 * ct + c;
+            const float sp = sgn * swap_pair(accS[q][m][ct][v]);
+            const float xp = accC[q][m][ct][v] + sp, xm = accC[q][m][ct][v] - sp;
+            const float yp = fmaf(-ws, swap_pair(xp), xp * w.x);
+            const float ym = fmaf(ws, swap_pair(xm), xm * w.x);
+            if (col < 2 * mt) {
+              if (k < npos) dst[k * mt * 2 + col] = yp;
+              if (k >= 1 && k <= Lz - npos) dst[(Lz - k) * mt * 2 + col] = ym;
+            }
+          }
+        }
+    }
+  }
+}
+
+constexpr size_t kFoldLds = 78 * 1024;      // two blocks per CU
+
+size_t fold_lds(const FoldPlan& f, int MT) { return (size_t)(2 * 16 * MT * f.stride + 2 * 16 * MT) * 4; }
+
+}  // namespace
+
+FoldPlan fold_plan(AxisPlan az) {
+  FoldPlan f;
+  const int kmax = az.npos - 1 > az.L - az.npos ? az.npos - 1 : az.L - az.npos;
+  f.rows = kmax + 1 <= 16 ? 16 : (kmax + 1 + 31) / 32 * 32;    // whole groups of the kernel's row tiles
+  f.pairs = (az.N + 1) / 2;
+  f.stride = (f.pairs + 15) / 16 * 16 + 4;      // 4 floats beside whole tiles: rows spread over the LDS banks
+  f.floats = (size_t)2 * f.rows * f.stride + 2 * f.rows;
+  return f;
+}
+
+// Nt up to 64 in registers; one or two row tiles of frequencies and column tiles of bins per block
+bool tz_fwd_fold_fits(AxisPlan az, int Nt, int mt) {
+  const FoldPlan f = fold_plan(az);
+  const int MT = f.rows >= 32 ? 2 : 1;
+  return Nt <= 64 && mt <= 64 && fold_lds(f, MT) <= kFoldLds;
+}
+
+hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, const float* ztab, int64_t planes,
+                              AxisPlan az, int Nt, int mt, hipStream_t s) {
+  const FoldPlan f = fold_plan(az);
+  const int CT = 2 * mt <= 16 ? 1 : 2, MT = f.rows >= 32 ? 2 : 1;
+  const int mgroups = (f.rows + 16 * MT - 1) / (16 * MT), cgroups = (2 * mt + 16 * CT - 1) / (16 * CT);
+  const int ngroups = mgroups * cgroups;
+  const size_t lds = fold_lds(f, MT);
+  // resident blocks only: each loads the z table once and walks planes
+  const int J = (Nt - 1) / 16, r = Nt - 16 * J, W = (r + 3) / 4;
+  const int PP = f.pairs <= 4 ? 4 : (f.pairs <= 8 ? 2 : 1);      // then also MT = 1: no more frequencies than rows
+  int64_t per_cu = fold_waves(4 * J + W, CT, MT, PP);
+  if (per_cu > (int64_t)(160 * 1024 / lds)) per_cu = (int64_t)(160 * 1024 / lds);
+  int64_t per_x = ((planes + 7) / 8 + 4 * PP - 1) / (4 * PP);
+  if (per_x > 32 * per_cu) per_x = 32 * per_cu;
+  const dim3 grid((unsigned)(8 * per_x * ngroups));
+  const bool stream = planes * (int64_t)az.N * Nt * 4 >= kStreamBytes;
+#define FNO_TZD_S(JV, WV, CTV, MTV, PPV, STRV)                                                                  \
+  hipLaunchKernelGGL((tz_fwd_fold_kernel<JV, WV, CTV, MTV, PPV, STRV>), grid, dim3(kThreads), lds, s, x,         \
+                     reinterpret_cast<float*>(out), twt, ztab, (long long)planes, az.N, Nt, az.L, az.npos, mt,  \
+                     f.rows, f.pairs, f.stride, ngroups, mgroups)
+#define FNO_TZD_M(JV, WV, CTV, MTV, PPV)                                                                \
+  do {                                                                                                  \
+    if (stream) FNO_TZD_S(JV, WV, CTV, MTV, PPV, true); else FNO_TZD_S(JV, WV, CTV, MTV, PPV, false);   \
+  } while (0)
+#define FNO_TZD_P(JV, WV, CTV)                                                                          \
+  do {                                                                                                  \
+    if (PP == 4) FNO_TZD_M(JV, WV, CTV, 1, 4); else if (PP == 2) FNO_TZD_M(JV, WV, CTV, 1, 2);          \
+    else if (MT == 1) FNO_TZD_M(JV, WV, CTV, 1, 1); else FNO_TZD_M(JV, WV, CTV, 2, 1);                  \
+  } while (0)
+#define FNO_TZD_C(JV, WV)                                               \
+  do {                                                                  \
+    if (CT == 1) FNO_TZD_P(JV, WV, 1); else FNO_TZD_P(JV, WV, 2);       \
+  } while (0)
+#define FNO_TZD_W(JV)                                                                         \
+  do {                                                                                        \
+    if (W == 1) FNO_TZD_C(JV, 1); else if (W == 2) FNO_TZD_C(JV, 2);                          \
+    else if (W == 3) FNO_TZD_C(JV, 3); else FNO_TZD_C(JV, 4);                                 \
+  } while (0)
+  if (J == 0) FNO_TZD_W(0); else if (J == 1) FNO_TZD_W(1); else if (J == 2) FNO_TZD_W(2); else FNO_TZD_W(3);
+#undef FNO_TZD_W
+#undef FNO_TZD_C
+#undef FNO_TZD_P
+#undef FNO_TZD_M
+#undef FNO_TZD_S
+  return hipGetLastError();
+}
+
+}  // namespace fno

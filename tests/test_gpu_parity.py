@@ -758,3 +758,28 @@ def test_network_with_time_lift_training_gradients_match_oracle():
     GT = 5 * TOL
     for name, got in (("gWt", gwt), ("gbt", gbt), ("gWc", gwc), ("gbc", gbc)):
         assert rel(host(got), ref[name]) <= GT, name
+
+
+@pytest.mark.parametrize("nz,mz,nt,mt,rule", [
+    (1, 0, 5, 3, 1),          # one row, paired with itself; a row shorter than the tail's four lane groups x 2
+    (2, 1, 1, 1, 0),          # one pair, one time step
+    (8, 3, 35, 15, 0),        # four planes of 4 pairs per tile, 74 planes: the last tile is half empty
+    (5, 2, 6, 3, 1),          # four planes of 3 pairs, the middle row its own pair
+    (12, 4, 20, 10, 1),       # two planes of 6 pairs per tile, 37 planes, 20 columns
+    (15, 3, 7, 4, 0),         # odd z: the middle row at half weight, two planes of 8 pairs per tile
+    (31, 7, 13, 7, 1),        # exactly one tile of 16 pairs
+    (33, 15, 17, 9, 0),       # one pair into a second tile, all 16 frequency rows; a tail of one step; 18 columns
+    (34, 16, 20, 10, 0),      # 17 frequency rows: two row tiles, the second nearly empty
+    (71, 33, 33, 16, 1),      # 34 frequency rows: two groups of row tiles; 32 columns
+    (70, 5, 63, 32, 0),       # 64 columns: two column groups; three whole runs of 16 steps and a tail of 15
+    (263, 24, 45, 3, 0),      # long axes on both sides
+])
+def test_folded_forward_transform_at_the_edges_of_its_tiles(nz, mz, nt, mt, rule):
+    """Forward (t, z) stage for lengths without a fast split, at the edges of the row tiles, frequency
+    tiles, column tiles and of the tail of a row; 37 planes are no multiple of a block's or an XCD's share."""
+    grid = (37, 2, nz, nt) if rule == 0 else (37, 1, nz, nt)
+    L = Layer(1, 1, 1, grid, (1, 1, mz, mt) if rule == 0 else (1, 0, mz, mt), rule)
+    y, xh = gpu_spectral_fwd(L)
+    yo, xho = O.spectral_conv_fwd(L.x, L.R, L.spec, return_xhat=True)
+    assert rel(xh, xho) <= TOL
+    assert rel(y, yo) <= TOL
