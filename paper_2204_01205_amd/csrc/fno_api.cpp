@@ -105,7 +105,7 @@ int make_plan(const fno_desc* d, bool need_block, bool need_bwd_block, Plan* p) 
       if (m > fno::kMaxFftM || p->N[2] % m) continue;
       az.M = m; az.P = p->N[2] / m;
       ok = fno::tz_fwd_fits(az, p->Nt, p->mt) &&
-           (fno::zt_mfma_fits(az, p->Nt, p->mt, Cm, Cm) || fno::zt_inv_fits(az, p->Nt, p->mt, Cm));
+           (fno::zt_tile_fits(az, p->Nt, p->mt, Cm, Cm) || fno::zt_inv_fits(az, p->Nt, p->mt, Cm));
     }
     if (!ok) { set_detail("an Nz x Nt plane with this many channels does not fit the LDS tiles"); return FNO_EUNSUPPORTED; }
     p->ax[2] = az;
@@ -245,7 +245,8 @@ int inverse_chain(const Plan& p, void* ws, const float2* spec, int C, float* out
   const int64_t in_x = in_y * p.L[1];
   FNO_STAGE(FNO_STAGE_X_INV, s, fno::launch_axis_inv(spec, a2, at<float2>(ws, p.off_tw[0]), bc, p.ax[0], in_x, s));
   FNO_STAGE(FNO_STAGE_Y_INV, s, fno::launch_axis_inv(a2, a1, at<float2>(ws, p.off_tw[1]), bc * p.N[0], p.ax[1], in_y, s));
-  FNO_STAGE(FNO_STAGE_ZT_INV, s, fno::launch_zt_inv(a1, out, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]), p.B, C,
+  FNO_STAGE(FNO_STAGE_ZT_INV, s, fno::launch_zt_inv(a1, out, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]),
+                             p.folded ? at<float>(ws, p.off_fold) : nullptr, p.B, C,
                              p.N[0], p.N[1], p.ax[2], p.Nt, p.mt, ep, at<float>(ws, p.off_ztab), s));
   return FNO_OK;
 }

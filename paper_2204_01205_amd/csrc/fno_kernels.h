@@ -72,8 +72,9 @@ struct Epilogue {
 
 // Inverse (z, t) of a[B*Co planes][Lz][mt] plus epilogue  out = act(ys + W u + bias).
 // `tables` is kZtTablesBytes of scratch (16-byte aligned) for the kernel's per-call tables.
+// ztab: the folded table of the z axis, or null where there is none.
 hipError_t launch_zt_inv(const float2* a, float* out, const float2* twt, const float2* twz,
-                         int B, int Co, int Nx, int Ny, AxisPlan az, int Nt, int mt,
+                         const float* ztab, int B, int Co, int Nx, int Ny, AxisPlan az, int Nt, int mt,
                          Epilogue ep, float* tables, hipStream_t s);
 
 // gz = g * act'(z) (g = gout or the MSE gradient against a target), written to gz_out;
@@ -130,6 +131,7 @@ constexpr size_t kZtTablesBytes = 512 * 1024;
 bool tz_fwd_fits(AxisPlan az, int Nt, int mt);
 bool zt_inv_fits(AxisPlan az, int Nt, int mt, int Co);
 bool axis_fits(AxisPlan ax);
-bool zt_mfma_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
+// with zt_inv_fits(): the planes of z and t, and the channels, that are accepted
+bool zt_tile_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
 
 }  // namespace fno

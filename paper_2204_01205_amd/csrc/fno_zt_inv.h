@@ -1,4 +1,4 @@
-// Internal to libfno: what the three inverse (z, t) kernels share -- the epilogue arguments, the
+// Internal to libfno: what the inverse (z, t) kernels share -- the epilogue arguments, the
 // host-side sizing rules of their LDS tiles, and the entry points of their translation units.
 #pragma once
 #include "fno_device.h"
@@ -40,11 +40,13 @@ inline size_t zt_inv_lds(AxisPlan az, int Nt, int mt, int Co) {
   return ((vy + 3) & ~(size_t)3) * 4 + (size_t)kMaxCo * kMaxCo * 4;
 }
 
-// Tile of the matrix-core kernel: Q residue classes whose Rz = Q*M rows times Nt points make
-// 128..512 points (64..256 threads, two points each) and whose Q adjacent rows span at least 128 bytes.
-// Rows per tile for NW waves: each wave covers 128 points.  Returns Q = rows / M, or 0.
-// t-tile of the matrix-core kernels for an axis of length Nt: 16 or 32 points, the axis itself or
-// the next tile width above an even length; 0 when neither fits
+// The rule of zt_tile_fits(): a tile of Q residue classes, Rz = Q*M rows, of 128 points for each of NW waves,
+// whose spectrum, V and tables fit the LDS.  It bounds, with zt_inv_fits(), the shapes that are accepted: those
+// that only this rule admits are within the folded kernel's reach, or, where its table or a single group of
+// channels is too large for it, within the generic kernel's at up to 160 KB of LDS (checked by enumeration over
+// the lengths, kept counts and widths).
+// t-tile for an axis of length Nt: 16 or 32 points, the axis itself or the next tile width above an even length;
+// 0 when neither fits
 inline int mfma_tile_nt(int Nt) {
   if (Nt == 16 || Nt == 32) return Nt;
   if (Nt % 2 != 0 || Nt < 10 || Nt > 32) return 0;
@@ -117,18 +119,19 @@ inline int mfma_nw(AxisPlan az, int Nt, int mt, int Co, int Cu) {
 // (defined in fno_zt_inv.hip).
 hipError_t launch_zt_tables(float* blob, int groups, const float2* twt, const float2* twz, const float* W,
                             int w_so, int w_si, const float* bias, int Co, int Cu, int CP, int mt, int NT,
-                            int nt_act, int Lz, int Pz, int Q, int blob_floats, hipStream_t s);
+                            int Lz, int Pz, int Q, int blob_floats, hipStream_t s);
 
-// Each launcher sets *taken when its kernel covers the shape and has been launched.
+// The column kernels' launchers set *taken when the kernel covers the shape and has been launched.
 hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, const float2* twz, int B, int Co,
                              int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, float* tables, hipStream_t s,
                              bool* taken);
 hipError_t launch_zt_inv_col16(const float2* a, float* out, const float2* twt, const float2* twz, int B, int Co,
                                int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, float* tables, hipStream_t s,
                                bool* taken);
-hipError_t launch_zt_inv_mfma(const float2* a, float* out, const float2* twt, const float2* twz, int B, int Co,
-                              int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, float* tables, hipStream_t s,
-                              bool* taken);
+// Cu: input channels of the linear term, 0 without one.
+bool zt_inv_fold_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
+hipError_t launch_zt_inv_fold(const float2* a, float* out, const float2* twt, const float* ztab, int64_t ncols, int Co,
+                              int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, hipStream_t s);
 hipError_t launch_zt_inv_generic(const float2* a, float* out, const float2* twt, const float2* twz, int64_t ncols,
                                  int Co, int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, hipStream_t s);
 

@@ -1,5 +1,14 @@
-// Inverse (z, t) + block epilogue, column variant on the matrix cores (see fno_zt_inv.hip for
-// what the stage computes and fno_zt_inv_mfma.hip for the lane layout of the 4x4x1 MFMA blocks).
+// Inverse (z, t) + block epilogue, column variant on the matrix cores (see fno_zt_inv.hip for what the
+// stage computes).
+//
+// Per grid point the pre-activation is one inner product of length Cu + 2 mt:
+//     z[o] = b[o] + sum_i W[o][i] u[i]  +  sum_kt ( Re V[o][kt] cos(th) - Im V[o][kt] sin(th) )
+// i.e. the channel-linear term of eq. (2) and the complex-to-real step over t share the accumulator.
+// v_mfma_f32_4x4x1 (16 independent 4x4 outer products per wave, full fp32) fits it without padding.  An
+// MFMA block is 4 consecutive t of one z-row ("quad") times 4 channels: lane 4b+i supplies the A value at
+// t = 4 quad + i (u of the current input channel, or the twiddle), lane 4b+j supplies the B value of
+// channel 4T+j (W[4T+j][i] or V[4T+j][row][kt]), and lane 4b+j receives, in its four result registers,
+// channel 4T+j at the quad's four t: one float4 of the output.
 #include "fno_zt_inv.h"
 #include <type_traits>
 
@@ -20,9 +29,9 @@ namespace {
 // the pre-activation is stored as well), EPI = -1 reads it from the arguments.  With a fixed
 // epilogue every half step issues the same number of loads and stores on every path, which the
 // compiler's wait counts for the prefetched u values rely on.
-template <int CT, bool FULL, int MTC, int LZC, int NPC, int EPI, bool STREAM>
+template <int CT, int MTC, int LZC, int NPC, int EPI, bool STREAM>
 __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
-    const float2* __restrict__ a, float* __restrict__ out, int Co_rt, int NxNy, int Nz, int Lz_rt,
+    const float2* __restrict__ a, float* __restrict__ out, int NxNy, int Nz, int Lz_rt,
     int nposz_rt, int mt_rt, int inv_mt, int a_floats, int a_stride4, int v_stride,
     const float* __restrict__ blob, int blob_floats, EpiArgs ep) {
   HIP_DYNAMIC_SHARED(float, smem)
@@ -35,8 +44,8 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
   constexpr int CP = 4 * CT;
   constexpr int CI = CP;
   constexpr int nthr = 64 * NW;
-  const int Co = FULL ? CP : Co_rt;
-  const int Cu = FULL ? CI : ep.Cu;
+  constexpr int Co = CP;
+  constexpr int Cu = CI;
   const int Pz = Nz / MZ;
   const float2* A = reinterpret_cast<const float2*>(smem);      // [Co][Lz][mt], padded channel stride
   float2* V = reinterpret_cast<float2*>(smem + a_floats);       // [CP][MZ][mt], padded channel stride
@@ -80,10 +89,6 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
   const int zkt = tid - zo * mt;
   const float2* asrc = A + zo * (2 * a_stride4) + zkt;
   float2* vdst = V + zo * v_stride + zkt;
-  if (!FULL) {
-    // channels of the padding tiles: finite values so the unused MFMA columns stay harmless
-    for (int idx = tid; idx < (CP - Co) * v_stride; idx += nthr) V[Co * v_stride + idx] = make_float2(0.f, 0.f);
-  }
   const float* BI = reinterpret_cast<const float*>(TW + Pz * Lz);      // bias, padded to CP
   // u values of the two slots (lane 4b+i takes t = 4 quad + i): loaded one step ahead, each
   // slot's registers refilled as soon as its W part has used them
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
     for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
       for (int i = 0; i < CI; ++i)
-        if (FULL || i < Cu) xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + sl * NT]);
+        xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + sl * NT]);
   }
   asm volatile("" ::: "memory");
   // everything issued so far has landed (the first u values too: the bias step below reads LDS that
@@ -213,14 +218,12 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
           for (int ii = 0; ii < IB; ++ii)
 #pragma unroll
             for (int T = 0; T < CT; ++T)
-              wv[ii][T] = (FULL || i0 + ii < Cu) ? Wt[(i0 + ii) * CP + 4 * T + j4] : 0.f;
+              wv[ii][T] = Wt[(i0 + ii) * CP + 4 * T + j4];
 #pragma unroll
           for (int ii = 0; ii < IB; ++ii) {
-            if (FULL || i0 + ii < Cu) {
 #pragma unroll
-              for (int T = 0; T < CT; ++T)
-                acc[T] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i0 + ii][sl], wv[ii][T], acc[T], 0, 0, 0);
-            }
+            for (int T = 0; T < CT; ++T)
+              acc[T] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i0 + ii][sl], wv[ii][T], acc[T], 0, 0, 0);
           }
         }
         // this slot's u values of the next step
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
         if constexpr (PREFETCH) {
 #pragma unroll
           for (int i = 0; i < CI; ++i)
-            if (FULL || i < Cu) xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (n2 + 2) * NT]);
+            xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (n2 + 2) * NT]);
         }
         asm volatile("" ::: "memory");
       }
@@ -238,21 +241,18 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col_kernel(
         float* zp = ep.zsave + (b * Co + j4) * Npts + poff;
 #pragma unroll
         for (int T = 0; T < CT; ++T)
-          if (FULL || 4 * T + j4 < Co)
-            st_once<STREAM>(reinterpret_cast<v4f*>(zp + (4 * T) * Npts), acc[T]);
+          st_once<STREAM>(reinterpret_cast<v4f*>(zp + (4 * T) * Npts), acc[T]);
       }
       if (act) {
 #pragma unroll
         for (int T = 0; T < CT; ++T)
-          if (FULL || 4 * T + j4 < Co)
-            st_once<STREAM>(reinterpret_cast<v4f*>(op + (4 * T) * Npts),
+          st_once<STREAM>(reinterpret_cast<v4f*>(op + (4 * T) * Npts),
                             v4f{gelu_fast_f(acc[T][0]), gelu_fast_f(acc[T][1]), gelu_fast_f(acc[T][2]),
                                 gelu_fast_f(acc[T][3])});
       } else {
 #pragma unroll
         for (int T = 0; T < CT; ++T)
-          if (FULL || 4 * T + j4 < Co)
-            st_once<STREAM>(reinterpret_cast<v4f*>(op + (4 * T) * Npts), acc[T]);
+          st_once<STREAM>(reinterpret_cast<v4f*>(op + (4 * T) * Npts), acc[T]);
       }
     }
   };
@@ -268,9 +268,14 @@ hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, con
   *taken = false;
   const EpiArgs& e = ep;
   const int CT = (Co + 3) / 4 <= 2 ? 2 : ((Co + 3) / 4 <= 5 ? 5 : 8);
-  // Column kernel (Nt = 32, 16-point z FFT): the spectrum of a column is staged once instead of
-  // once per tile.  Taken when two blocks fit a CU's LDS, else the per-tile kernel below.
-  if (Nt == 32 && az.M == 16 && az.P >= 2 && az.P % 2 == 0 &&
+  // Nt = 32, a 16-point z FFT and 8 or 20 channels in and out: rows of one whole 128-byte line, which the folded
+  // kernel's tiles of 16 t halve.  Measured per block forward and back, this kernel against the folded one: 20
+  // channels, 64 x 64 x 32 x 32, 0.43 against 0.62 ms; 64 x 64 x 64 x 32 with 12 t bins 1.08 and 1.07; 8 channels,
+  // 64 x 64 x 128 x 32, 0.57 and 0.76.  Widths that leave channel tiles part empty are 1.3 to 1.6 times faster
+  // there, and so are 8 channels without the linear term (0.13 and 0.08 ms forward).  Taken when two blocks fit a
+  // CU's LDS.
+  const bool full = Co == 4 * CT && (ep.u == nullptr ? CT == 5 : ep.Cu == 4 * CT);
+  if (full && Nt == 32 && az.M == 16 && az.P >= 2 && az.P % 2 == 0 &&
       (az.P & (az.P - 1)) == 0 && CT <= 5 && Co * mt <= 512 && (az.L * mt) % 2 == 0 && B <= 65535) {
     const int Cu = ep.u ? ep.Cu : 0;
     const int a_stride4 = zt_mfma_astride4(az, mt);
@@ -279,36 +284,35 @@ hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, con
     const int blob_floats = zt_mfma_blob(az, Nt, mt, Co, Cu, az.P);
     const size_t lds = ((size_t)a_floats + 2 * 4 * CT * v_stride + blob_floats) * 4;
     if (Cu <= 4 * CT && lds <= (size_t)(79 * 1024) && (size_t)blob_floats * 4 <= kZtTablesBytes) {
-      const bool full = (Co == 4 * CT) && (ep.u == nullptr || ep.Cu == 4 * CT);
       const int inv_mt = (65536 + mt - 1) / mt;
       hipError_t terr = launch_zt_tables(tables, 1, twt, twz, ep.u ? ep.W : nullptr, ep.w_so, ep.w_si, ep.bias, Co,
-                                         Cu, 4 * CT, mt, Nt, Nt, az.L, az.P, az.P, blob_floats, s);
+                                         Cu, 4 * CT, mt, Nt, az.L, az.P, az.P, blob_floats, s);
       if (terr != hipSuccess) return terr;
       const dim3 grid((unsigned)NxNy, (unsigned)B);
-#define FNO_ZTC_S(CTV, FULLV, MTV, LZV, NPV, EPIV, STRV)                                                     \
-  hipLaunchKernelGGL((zt_inv_col_kernel<CTV, FULLV, MTV, LZV, NPV, EPIV, STRV>), grid, dim3(512), lds, s, a, out, \
-                     Co, NxNy, az.N, az.L, az.npos, mt, inv_mt, a_floats, a_stride4, v_stride, tables,       \
+#define FNO_ZTC_S(CTV, MTV, LZV, NPV, EPIV, STRV)                                                     \
+  hipLaunchKernelGGL((zt_inv_col_kernel<CTV, MTV, LZV, NPV, EPIV, STRV>), grid, dim3(512), lds, s, a, out, \
+                     NxNy, az.N, az.L, az.npos, mt, inv_mt, a_floats, a_stride4, v_stride, tables,       \
                      blob_floats, e)
       // u is read once and the results are written once: as streams when they are larger than the caches
       const bool stream = (int64_t)B * Co * NxNy * az.N * Nt * 4 >= kStreamBytes;
-#define FNO_ZTC(CTV, FULLV, MTV, LZV, NPV, EPIV)                  \
+#define FNO_ZTC(CTV, MTV, LZV, NPV, EPIV)                  \
   do {                                                            \
-    if (stream) FNO_ZTC_S(CTV, FULLV, MTV, LZV, NPV, EPIV, true); \
-    else FNO_ZTC_S(CTV, FULLV, MTV, LZV, NPV, EPIV, false);       \
+    if (stream) FNO_ZTC_S(CTV, MTV, LZV, NPV, EPIV, true); \
+    else FNO_ZTC_S(CTV, MTV, LZV, NPV, EPIV, false);       \
   } while (0)
       // the shape of the large workloads (width 20, 9 kept t bins, 32 kept z frequencies) with its three
       // epilogues: forward, forward that keeps the pre-activation, and the adjoint's linear one
       const int epi = (e.act ? 1 : 0) | (e.zsave != nullptr ? 2 : 0);
-      if (CT == 5 && full && mt == 9 && az.L == 32 && az.npos == 16 && e.u != nullptr && epi != 2) {
-        if (epi == 1) FNO_ZTC(5, true, 9, 32, 16, 1);
-        else if (epi == 3) FNO_ZTC(5, true, 9, 32, 16, 3);
-        else FNO_ZTC(5, true, 9, 32, 16, 0);
-      } else if (CT == 5 && full && mt == 9 && az.L == 24 && az.npos == 12 && e.u != nullptr && epi != 2) {
-        if (epi == 1) FNO_ZTC(5, true, 9, 24, 12, 1);
-        else if (epi == 3) FNO_ZTC(5, true, 9, 24, 12, 3);
-        else FNO_ZTC(5, true, 9, 24, 12, 0);
-      } else if (CT == 2) { if (full) FNO_ZTC(2, true, 0, 0, 0, -1); else FNO_ZTC(2, false, 0, 0, 0, -1); }
-      else { if (full) FNO_ZTC(5, true, 0, 0, 0, -1); else FNO_ZTC(5, false, 0, 0, 0, -1); }
+      if (CT == 5 && mt == 9 && az.L == 32 && az.npos == 16 && e.u != nullptr && epi != 2) {
+        if (epi == 1) FNO_ZTC(5, 9, 32, 16, 1);
+        else if (epi == 3) FNO_ZTC(5, 9, 32, 16, 3);
+        else FNO_ZTC(5, 9, 32, 16, 0);
+      } else if (CT == 5 && mt == 9 && az.L == 24 && az.npos == 12 && e.u != nullptr && epi != 2) {
+        if (epi == 1) FNO_ZTC(5, 9, 24, 12, 1);
+        else if (epi == 3) FNO_ZTC(5, 9, 24, 12, 3);
+        else FNO_ZTC(5, 9, 24, 12, 0);
+      } else if (CT == 2) FNO_ZTC(2, 0, 0, 0, -1);
+      else FNO_ZTC(5, 0, 0, 0, -1);
 #undef FNO_ZTC
 #undef FNO_ZTC_S
       *taken = true;

@@ -1,6 +1,6 @@
 // Inverse (z, t) + block epilogue, column variant on the matrix cores for a t axis of 16 points
-// (see fno_zt_inv.hip for what the stage computes, fno_zt_inv_mfma.hip for the lane layout of the
-// 4x4x1 MFMA blocks and fno_zt_inv_col.hip for the 32-point column variant this one follows).
+// (see fno_zt_inv.hip for what the stage computes and fno_zt_inv_col.hip for the lane layout of the 4x4x1
+// MFMA blocks and the 32-point column variant this one follows).
 #include "fno_zt_inv.h"
 #include <type_traits>
 
@@ -19,9 +19,9 @@ namespace {
 // z = Pz n1 + 2 pair + class.  Launch: grid (NxNy, B), 512 threads; Pz a multiple of 4.
 // The table blob is the one of zt_tables_kernel with Q = Pz.  MTC, LZC, NPC, EPI as in the
 // 32-point variant.
-template <int CT, bool FULL, int MTC, int LZC, int NPC, int EPI, bool STREAM>
+template <int CT, int MTC, int LZC, int NPC, int EPI, bool STREAM>
 __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
-    const float2* __restrict__ a, float* __restrict__ out, int Co_rt, int NxNy, int Nz, int Lz_rt,
+    const float2* __restrict__ a, float* __restrict__ out, int NxNy, int Nz, int Lz_rt,
     int nposz_rt, int mt_rt, int inv_mt, int a_floats, int a_stride4, int v_stride,
     const float* __restrict__ blob, int blob_floats, EpiArgs ep) {
   HIP_DYNAMIC_SHARED(float, smem)
@@ -37,8 +37,8 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
   constexpr int NSUB = (CT + TS - 1) / TS;          // passes per pair
   constexpr int nthr = 64 * NW;
   constexpr int ZB = 4;                             // z-stage terms whose LDS reads go out together
-  const int Co = FULL ? CP : Co_rt;
-  const int Cu = FULL ? CI : ep.Cu;
+  constexpr int Co = CP;
+  constexpr int Cu = CI;
   const int Pz = Nz / MZ;
   const float2* A = reinterpret_cast<const float2*>(smem);      // [Co][Lz][mt], padded channel stride
   float2* V = reinterpret_cast<float2*>(smem + a_floats);       // [4 TS][2 MZ][mt], padded channel stride
@@ -79,10 +79,6 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
       }
     }
   }
-  if (!FULL) {
-    // channel slots of V that no z stage writes feed unused MFMA columns: give them finite values
-    for (int idx = tid; idx < 4 * TS * v_stride; idx += nthr) V[idx] = make_float2(0.f, 0.f);
-  }
   const float* BI = reinterpret_cast<const float*>(TW + Pz * Lz);      // bias, padded to CP
   // u values of a pair (lane 4b+i takes t = 4 quad + i), two register sets: even and odd pairs
   float xv[CI][2];
@@ -93,7 +89,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
     for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
       for (int i = 0; i < CI; ++i)
-        if (FULL || i < Cu) xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * sl) * NT]);
+        xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * sl) * NT]);
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
@@ -108,7 +104,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
     constexpr bool PREFETCH = decltype(prefetch_tag)::value;
     constexpr int T0 = SUB * TS;                                    // first channel tile of the pass
     constexpr int NTL = (SUB == NSUB - 1) ? CT - T0 : TS;           // its channel tiles
-    const int nch = FULL ? 4 * NTL : min(4 * NTL, Co - 4 * T0);     // channels that exist in the pass
+    constexpr int nch = 4 * NTL;
     // z stage: item (class, channel, kt) collects the kept z-frequencies with their twiddles into
     // MZ bins; an inverse FFT over n1 gives the rows z = Pz n1 + 2 pair + class
     {
@@ -225,14 +221,12 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
         for (int ii = 0; ii < IB; ++ii)
 #pragma unroll
           for (int T = 0; T < NTL; ++T)
-            wv[ii][T] = (FULL || i0 + ii < Cu) ? Wt[(i0 + ii) * CP + 4 * (T0 + T) + j4] : 0.f;
+            wv[ii][T] = Wt[(i0 + ii) * CP + 4 * (T0 + T) + j4];
 #pragma unroll
         for (int ii = 0; ii < IB; ++ii) {
-          if (FULL || i0 + ii < Cu) {
 #pragma unroll
-            for (int T = 0; T < NTL; ++T)
-              acc[T] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i0 + ii][sl], wv[ii][T], acc[T], 0, 0, 0);
-          }
+          for (int T = 0; T < NTL; ++T)
+            acc[T] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i0 + ii][sl], wv[ii][T], acc[T], 0, 0, 0);
         }
       }
       if constexpr (SUB == NSUB - 1) {
@@ -241,7 +235,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
         if constexpr (PREFETCH) {
 #pragma unroll
           for (int i = 0; i < CI; ++i)
-            if (FULL || i < Cu) xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * (pair + 2)) * NT]);
+            xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * (pair + 2)) * NT]);
         }
         asm volatile("" ::: "memory");
       }
@@ -253,20 +247,17 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
       float* zp = ep.zsave + (b * Co + 4 * T0 + j4) * Npts + poff;
 #pragma unroll
       for (int T = 0; T < NTL; ++T)
-        if (FULL || 4 * (T0 + T) + j4 < Co)
           st_once<STREAM>(reinterpret_cast<v4f*>(zp + (4 * T) * Npts), acc[T]);
     }
     if (act) {
 #pragma unroll
       for (int T = 0; T < NTL; ++T)
-        if (FULL || 4 * (T0 + T) + j4 < Co)
           st_once<STREAM>(reinterpret_cast<v4f*>(op + (4 * T) * Npts),
                           v4f{gelu_fast_f(acc[T][0]), gelu_fast_f(acc[T][1]), gelu_fast_f(acc[T][2]),
                               gelu_fast_f(acc[T][3])});
     } else {
 #pragma unroll
       for (int T = 0; T < NTL; ++T)
-        if (FULL || 4 * (T0 + T) + j4 < Co)
           st_once<STREAM>(reinterpret_cast<v4f*>(op + (4 * T) * Npts), acc[T]);
     }
   };
@@ -306,44 +297,41 @@ hipError_t launch_zt_inv_col16(const float2* a, float* out, const float2* twt, c
   const size_t lds = ((size_t)a_floats + 2 * 4 * TS * v_stride + blob_floats) * 4;
   // two blocks per CU
   if (Cu > 4 * CT || lds > (size_t)(80 * 1024 - 512) || (size_t)blob_floats * 4 > kZtTablesBytes) return hipSuccess;
-  const bool full = (Co == 4 * CT) && (ep.u == nullptr || ep.Cu == 4 * CT);
   const int inv_mt = (65536 + mt - 1) / mt;
   // the shapes of the named workloads (width 20; 9 kept t bins and 32 kept z frequencies, or 8 and 24)
   // with their three epilogues: forward, forward that keeps the pre-activation, the adjoint's linear one
   const int epi = (e.act ? 1 : 0) | (e.zsave != nullptr ? 2 : 0);
-  const bool named = CT == 5 && full && e.u != nullptr && epi != 2;
+  const bool named = Co == 20 && e.u != nullptr && e.Cu == 20 && epi != 2;
   const bool shape_a = named && mt == 9 && az.L == 32 && az.npos == 16;
   const bool shape_b = named && mt == 8 && az.L == 24 && az.npos == 12;
-  // other widths above 8, with run-time counts, do not fit the register budget of two blocks per
-  // CU: the per-tile kernel takes them
-  if (!(shape_a || shape_b || CT == 2)) return hipSuccess;
+  // Everything else is faster on the folded kernel (8 channels, 64 x 64 x 64 x 16, one block forward and back:
+  // 0.22 ms with run-time counts here, 0.16 there).
+  if (!(shape_a || shape_b)) return hipSuccess;
   hipError_t terr = launch_zt_tables(tables, 1, twt, twz, ep.u ? ep.W : nullptr, ep.w_so, ep.w_si, ep.bias, Co,
-                                     Cu, 4 * CT, mt, Nt, Nt, az.L, az.P, az.P, blob_floats, s);
+                                     Cu, 4 * CT, mt, Nt, az.L, az.P, az.P, blob_floats, s);
   if (terr != hipSuccess) return terr;
   const dim3 grid((unsigned)NxNy, (unsigned)B);
-#define FNO_ZTC16_S(CTV, FULLV, MTV, LZV, NPV, EPIV, STRV)                                                     \
-  hipLaunchKernelGGL((zt_inv_col16_kernel<CTV, FULLV, MTV, LZV, NPV, EPIV, STRV>), grid, dim3(512), lds, s, a,   \
-                     out, Co, NxNy, az.N, az.L, az.npos, mt, inv_mt, a_floats, a_stride4, v_stride, tables,  \
+#define FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, STRV)                                                     \
+  hipLaunchKernelGGL((zt_inv_col16_kernel<CTV, MTV, LZV, NPV, EPIV, STRV>), grid, dim3(512), lds, s, a,   \
+                     out, NxNy, az.N, az.L, az.npos, mt, inv_mt, a_floats, a_stride4, v_stride, tables,  \
                      blob_floats, e)
   // u and the result as streams when they are larger than the caches, except in the launch that also
   // stores the pre-activation: with three streams per point it measured 4 % slower with the hint,
   // the other two epilogues 2-5 % faster
   const bool stream = e.zsave == nullptr && (int64_t)B * Co * NxNy * az.N * Nt * 4 >= kStreamBytes;
-#define FNO_ZTC16(CTV, FULLV, MTV, LZV, NPV, EPIV)                  \
+#define FNO_ZTC16(CTV, MTV, LZV, NPV, EPIV)                  \
   do {                                                              \
-    if (stream) FNO_ZTC16_S(CTV, FULLV, MTV, LZV, NPV, EPIV, true); \
-    else FNO_ZTC16_S(CTV, FULLV, MTV, LZV, NPV, EPIV, false);       \
+    if (stream) FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, true); \
+    else FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, false);       \
   } while (0)
   if (shape_a) {
-    if (epi == 1) FNO_ZTC16(5, true, 9, 32, 16, 1);
-    else if (epi == 3) FNO_ZTC16(5, true, 9, 32, 16, 3);
-    else FNO_ZTC16(5, true, 9, 32, 16, 0);
-  } else if (shape_b) {
-    if (epi == 1) FNO_ZTC16(5, true, 8, 24, 12, 1);
-    else if (epi == 3) FNO_ZTC16(5, true, 8, 24, 12, 3);
-    else FNO_ZTC16(5, true, 8, 24, 12, 0);
+    if (epi == 1) FNO_ZTC16(5, 9, 32, 16, 1);
+    else if (epi == 3) FNO_ZTC16(5, 9, 32, 16, 3);
+    else FNO_ZTC16(5, 9, 32, 16, 0);
   } else {
-    if (full) FNO_ZTC16(2, true, 0, 0, 0, -1); else FNO_ZTC16(2, false, 0, 0, 0, -1);
+    if (epi == 1) FNO_ZTC16(5, 8, 24, 12, 1);
+    else if (epi == 3) FNO_ZTC16(5, 8, 24, 12, 3);
+    else FNO_ZTC16(5, 8, 24, 12, 0);
   }
 #undef FNO_ZTC16
 #undef FNO_ZTC16_S

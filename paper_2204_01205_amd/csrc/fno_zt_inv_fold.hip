@@ -1,0 +1,501 @@
+// Inverse (z, t) + block epilogue for any axis lengths (see fno_zt_inv.hip for what the stage computes), as
+// chained matrix products on the matrix cores: the counterpart of fno_tz_fwd_fold.hip.
+//
+// With nu = n + 1/2 and the kept frequencies k = 0 .. kmax of the z axis folded into
+//   E[k] = a'[k] + a'[-k],  O[k] = i (a'[k] - a'[-k]),  a'[+-k] = exp(-+i pi k / Nz) a[+-k],
+// the rows of a pair are V[n] = C[n] + S[n] and V[Nz-1-n] = C[n] - S[n] with
+//   C[n] = sum_k cos(2 pi k nu / Nz) E[k],   S[n] = sum_k sin(2 pi k nu / Nz) O[k]:
+// both matrices are real, and a pair of rows shares its products.  A row's points then follow as
+// sum_c cs[t][c] V[n][c] over the 2 mt - 1 real columns c (the imaginary part of bin 0 does not enter).
+//
+// Both products run on v_mfma_f32_16x16x4 (full fp32; lane l supplies A[l%16][l/16] and B[l/16][l%16] and
+// holds rows 4 (l/16) + v of column l%16).  Four output channels share a tile of the first: its row 4 g + v is
+// column c = 4 tau + g of channel v, its columns are 16 row pairs.  Register v of the result then holds, as it
+// stands, one K step of channel v's product over c, whose result gives a lane W consecutive t of one row: the
+// layout in which u is read and the output written.  The channel-linear term joins in that layout too:
+// v_mfma_f32_4x4x1 with W[4T+i][.] as the left and a lane's own point as the right operand leaves four output
+// channels of that point in the lane.
+//
+// One wave works a tile of 16 row pairs x 4 W points of t for all output channels, its u values in registers.
+// LDS holds E and O of the block's columns, folded once per column by the waves that share it, and per wave the
+// cos / sin entries of its row pairs.  After the fold no wave waits for another.  A last tile of at most eight
+// pairs puts the second rows of its pairs into the idle half of the lanes.
+//
+// What bounds it: issue, then the overlap of a wave's loads with its products.  fp32 matrix instructions and vector
+// instructions share one datapath (measured: their times add up, within a wave and between waves), and a tile of
+// 32 rows x 16 points x 20 channels takes about 20 thousand cycles of the first and 13 thousand of the second (half
+// of them GELU); without its arithmetic the kernel takes 1.17 ms for 263 x 16 planes (5.4 GB), without its loads
+// 1.39 ms, together 1.68 ms.  u in registers allows two waves per SIMD; streaming u past accumulators for all output
+// channels takes as many.  Measured against the kernels it replaced (mixed-radix or dense sums with LDS staging, and
+// 4x4x1 tiles of one residue class), milliseconds: 20 channels, 68 x 118 columns of 263 x 16 3.95 -> 1.68; one block
+// forward and back: 20 channels, 64^3 x 20 0.89 -> 0.68, x 30 0.95 -> 0.81, 32 channels, 50 x 45 x 40 x 24
+// 1.19 -> 0.54, 16 channels, 64^3 x 16 0.42 -> 0.33, 12 channels, 64 x 64 x 48 x 16 0.52 -> 0.21.
+#include "fno_zt_inv.h"
+
+namespace fno {
+
+namespace {
+
+struct FoldInv {
+  long long ncols, Npts;
+  int Co, NxNy, Nz, Nt, Lz, npos, mt;
+  int K1, ks;            // folded frequencies, K steps of the product over them
+  int R;                 // tiles of columns: ceil((2 mt - 1) / 4)
+  int pairs, stride, mrows;      // of the folded table (FoldPlan)
+  int ntile, tt;         // tiles of row pairs and of t
+  int half_last;         // both rows of the last tile's pairs fit its 16 columns
+  int ntask;             // tiles of t inside tiles of row pairs; one row at a time: rows n, then rows Nz-1-n of whole tiles
+  int ct, nchunk;        // groups of four output channels per block, blocks per column
+  int wc_shift;          // log2 of the waves that share a column
+  unsigned items;        // blocks with work
+  unsigned inv_mt;       // ceil(2^32 / mt): division by multiplication, exact for the counts here
+};
+
+template <int W> struct run_of;
+template <> struct run_of<1> { typedef float type; };
+template <> struct run_of<2> { typedef v2f type; };
+template <> struct run_of<3> { typedef float type __attribute__((ext_vector_type(3))); };
+template <> struct run_of<4> { typedef v4f type; };
+
+// W consecutive floats at a 4-byte aligned address
+template <int W, bool STREAM>
+__device__ __forceinline__ void load_run(const char* p, float (&v)[W]) {
+  typedef typename run_of<W>::type vec;
+  typedef vec unaligned __attribute__((aligned(4)));
+  vec q;
+  if constexpr (STREAM) q = __builtin_nontemporal_load(reinterpret_cast<const unaligned*>(p));
+  else q = *reinterpret_cast<const unaligned*>(p);
+  if constexpr (W == 1) v[0] = q;
+  else {
+#pragma unroll
+    for (int c = 0; c < W; ++c) v[c] = q[c];
+  }
+}
+template <int W, bool STREAM>
+__device__ __forceinline__ void store_run(char* p, const float (&v)[W]) {
+  typedef typename run_of<W>::type vec;
+  typedef vec unaligned __attribute__((aligned(4)));
+  vec q;
+  if constexpr (W == 1) q = v[0];
+  else {
+#pragma unroll
+    for (int c = 0; c < W; ++c) q[c] = v[c];
+  }
+  if constexpr (STREAM) __builtin_nontemporal_store(q, reinterpret_cast<unaligned*>(p));
+  else *reinterpret_cast<unaligned*>(p) = q;
+}
+
+constexpr int fold_inv_ns(int W, int CI) { return 2 * W * CI <= 160 ? 2 : 1; }
+// smallest channel count that runs with CI register slots: the slots from there on may be empty
+constexpr int fold_inv_low(int CI) { return CI <= 8 ? 1 : (CI == 32 ? 25 : CI - 3); }
+
+// Where a lane's points of one task lie.
+template <int NU> struct FoldTile {
+  int n;                 // pair of rows
+  bool second;           // one row per lane: it is Nz-1-n
+  bool half;             // both rows of the pairs in one set of 16 columns (uniform)
+  int ti;                // tile of t
+  int voff[NU];          // byte offsets of the lane's W points inside a column of one channel
+  bool keep[NU];         // the lane stores
+};
+template <int NU, int W>
+__device__ __forceinline__ FoldTile<NU> fold_inv_place(const FoldInv& f, int task, bool active) {
+  FoldTile<NU> q;
+  const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int t1 = task / f.tt, rt = t1 < f.ntile ? t1 : t1 - f.ntile;
+  q.ti = task - t1 * f.tt;
+  q.half = f.half_last && rt == f.ntile - 1;
+  q.second = q.half ? c >= 8 : t1 >= f.ntile;
+  q.n = 16 * rt + (q.half ? c & 7 : c);
+  const int t0 = min(W * (4 * q.ti + g), f.Nt - W), nr = min(q.n, f.pairs - 1);
+  const bool own = 2 * q.n + 1 == f.Nz;        // the middle row of an odd axis: stored once
+  q.voff[0] = ((q.second ? f.Nz - 1 - nr : nr) * f.Nt + t0) * 4;
+  q.keep[0] = active && q.n < f.pairs && !(q.second && own);
+  if constexpr (NU == 2) {
+    q.voff[1] = q.half ? q.voff[0] : ((f.Nz - 1 - nr) * f.Nt + t0) * 4;
+    q.keep[1] = q.keep[0] && !own && !q.half;
+  }
+  return q;
+}
+
+// u of the lane's points, every input channel (up: channel 0 of the column)
+template <int NU, int W, int CI, bool STREAM>
+__device__ __forceinline__ void fold_inv_load_u(const int (&voff)[NU], const char* up, int Cu, long long chan_bytes,
+                                                float (&u)[CI > 0 ? CI : 1][NU][W]) {
+#pragma unroll
+  for (int i = 0; i < CI; ++i) {
+    if (i < fold_inv_low(CI) || i < Cu) {
+#pragma unroll
+      for (int s = 0; s < NU; ++s) load_run<W, STREAM>(up + (size_t)voff[s], u[i][s]);
+      up += chan_bytes;
+      asm volatile("" : "+s"(up));               // one running base, not one per channel
+    } else {
+#pragma unroll
+      for (int s = 0; s < NU; ++s)
+#pragma unroll
+        for (int v = 0; v < W; ++v) u[i][s][v] = 0.f;
+    }
+  }
+}
+
+// C and S of NR tiles of columns (stride R1 float2 apart): the operands of the next K step are read while this
+// one's products run.  last: the lane's entry of the last K step, which may reach past the folded frequencies
+// (its lanes there read the last one again, against zeros in ZT).
+template <int NR>
+__device__ __forceinline__ void fold_inv_z(const float2* eo, int R1, const float2* zt, int ks, int last, v4f (&C)[NR],
+                                           v4f (&S)[NR]) {
+  const int lane = threadIdx.x & 63;
+  float2 e[NR], z = zt[lane];
+#pragma unroll
+  for (int h = 0; h < NR; ++h) {
+    e[h] = eo[h * R1 + (ks > 1 ? lane : last)];
+    C[h] = v4f{0.f, 0.f, 0.f, 0.f};
+    S[h] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll 2
+  for (int s = 1; s < ks; ++s) {
+    const int at = s + 1 < ks ? 64 * s + lane : last;
+    float2 en[NR];
+    const float2 zn = zt[64 * s + lane];
+#pragma unroll
+    for (int h = 0; h < NR; ++h) en[h] = eo[h * R1 + at];
+#pragma unroll
+    for (int h = 0; h < NR; ++h) {
+      C[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].x, z.x, C[h], 0, 0, 0);
+      S[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].y, z.y, S[h], 0, 0, 0);
+    }
+    z = zn;
+#pragma unroll
+    for (int h = 0; h < NR; ++h) e[h] = en[h];
+  }
+#pragma unroll
+  for (int h = 0; h < NR; ++h) {
+    C[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].x, z.x, C[h], 0, 0, 0);
+    S[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].y, z.y, S[h], 0, 0, 0);
+  }
+}
+
+// One K step of the four channels' products over t, for the first rows of the pairs and (both) the second ones.
+template <int NS>
+__device__ __forceinline__ void fold_inv_t(float tb, v4f C, v4f S, bool both, v4f (&d2)[4][NS]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) d2[v][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(tb, C[v] + S[v], d2[v][0], 0, 0, 0);
+  if constexpr (NS == 2)
+    if (both)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d2[v][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(tb, C[v] - S[v], d2[v][1], 0, 0, 0);
+}
+
+// One task.  NS = 2: both rows of the lane's pair; NS = 1: one of them.
+template <int NS, int W, int CI, bool STREAM>
+__device__ __forceinline__ void fold_inv_tile(const FoldInv& f, const EpiArgs& ep, float* __restrict__ out,
+                                              const float* __restrict__ ztab, const float2* EO, float2* ZT,
+                                              const float* TB, const float* WL, const float4* BL, long long first,
+                                              int o0, const FoldTile<NS>& q,
+                                              float (&u)[CI > 0 ? CI : 1][NS][W], const char* up, const int (&vnext)[NS],
+                                              bool more) {
+  const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  // cos / sin of the tile's row pairs; the middle row of an odd axis is its own pair, stored at half weight
+  constexpr int ZB = 8;
+  const float wc = 2 * q.n + 1 == f.Nz ? 2.f : 1.f, ws = q.second ? -1.f : 1.f;
+  const bool both = NS == 2 && !q.half;          // uniform
+  const float* zc = ztab + (long long)g * f.stride + q.n;
+  const long long zs = (long long)f.mrows * f.stride;
+  float cv[ZB], sv[ZB];
+#pragma unroll
+  for (int s = 0; s < ZB; ++s) {
+    const bool ok = 4 * s + g < f.K1;
+    cv[s] = ok ? zc[4 * s * f.stride] : 0.f;
+    sv[s] = ok ? zc[zs + 4 * s * f.stride] : 0.f;
+  }
+#pragma unroll
+  for (int s = 0; s < ZB; ++s)
+    if (s < f.ks) ZT[64 * s + lane] = make_float2(cv[s] * wc, sv[s] * ws);
+  for (int s = ZB; s < f.ks; ++s) {
+    const bool ok = 4 * s + g < f.K1;
+    const float cw = ok ? zc[4 * s * f.stride] : 0.f, sw = ok ? zc[zs + 4 * s * f.stride] : 0.f;
+    ZT[64 * s + lane] = make_float2(cw * wc, sw * ws);
+  }
+  __builtin_amdgcn_wave_barrier();
+  const int last = min(4 * (f.ks - 1) + g, f.K1 - 1) * 16 + c;
+  const int R1 = f.K1 * 16;
+  const float* tbp = TB + q.ti * f.R * 64 + lane;
+  for (int T = 0; T < f.ct; ++T) {
+    const int o = o0 + 4 * T;
+    v4f d2[4][NS];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) d2[v][s] = v4f{0.f, 0.f, 0.f, 0.f};
+    const float2* eot = EO + T * f.R * R1;
+    int r = 0;
+    for (; r + 2 <= f.R; r += 2) {
+      v4f C[2], S[2];
+      const float tb0 = tbp[64 * r], tb1 = tbp[64 * r + 64];
+      fold_inv_z<2>(eot + r * R1, R1, ZT, f.ks, last, C, S);
+      fold_inv_t<NS>(tb0, C[0], S[0], both, d2);
+      fold_inv_t<NS>(tb1, C[1], S[1], both, d2);
+    }
+    if (r < f.R) {
+      v4f C[1], S[1];
+      const float tb = tbp[64 * r];
+      fold_inv_z<1>(eot + r * R1, R1, ZT, f.ks, last, C, S);
+      fold_inv_t<NS>(tb, C[0], S[0], both, d2);
+    }
+    // four channels of a point side by side, the bias, and the channel-linear term on top
+    const float4 bias = BL[T];
+    v4f acc[NS][W];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int v = 0; v < W; ++v)
+        acc[s][v] = v4f{d2[0][s][v] + bias.x, d2[1][s][v] + bias.y, d2[2][s][v] + bias.z, d2[3][s][v] + bias.w};
+    if constexpr (CI > 0) {
+      const float* wl = WL + T * (CI * 4) + (lane & 3);
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        if (s == 0 || both)
+#pragma unroll
+          for (int i = 0; i < CI; ++i) {
+            const float wv = wl[4 * i];
+#pragma unroll
+            for (int v = 0; v < W; ++v)
+              acc[s][v] = __builtin_amdgcn_mfma_f32_4x4x1f32(wv, u[i][s][v], acc[s][v], 0, 0, 0);
+          }
+    }
+    // the next task's u values are on their way while this one's last channels are finished
+    if (CI > 0 && T + 1 == f.ct && more) fold_inv_load_u<NS, W, CI, STREAM>(vnext, up, ep.Cu, f.Npts * 4, u);
+    const long long base = first + o * f.Npts;
+    auto store4 = [&](float* dst) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (o + w < f.Co) {
+          char* op = reinterpret_cast<char*>(dst + base + w * f.Npts);
+#pragma unroll
+          for (int s = 0; s < NS; ++s) {
+            float y[W];
+#pragma unroll
+            for (int v = 0; v < W; ++v) y[v] = acc[s][v][w];
+            if (q.keep[s]) store_run<W, STREAM>(op + (size_t)q.voff[s], y);
+          }
+        }
+      }
+    };
+    if (ep.zsave != nullptr) store4(ep.zsave);
+    if (ep.act) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        if (s == 0 || both)
+#pragma unroll
+          for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int v = 0; v < W; ++v) acc[s][v][w] = gelu_fast_f(acc[s][v][w]);
+    }
+    store4(out);
+  }
+}
+
+// waves per SIMD: u, the two accumulator sets and about 50 registers of operands and addresses
+constexpr int fold_inv_waves(int W, int CI) {
+  const int ns = fold_inv_ns(W, CI), regs = ns * W * CI + ns * 16 + ns * W * 4 + 50;
+  return regs <= 128 ? 4 : (regs <= 168 ? 3 : 2);
+}
+
+template <int W, int CI, bool STREAM>
+__global__ __launch_bounds__(kThreads, fold_inv_waves(W, CI)) void zt_inv_fold_kernel(
+    const float2* __restrict__ a, float* __restrict__ out, const float2* __restrict__ twt,
+    const float* __restrict__ ztab, FoldInv f, EpiArgs ep) {
+  HIP_DYNAMIC_SHARED(float4, smem4)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const long long item = xcd_contiguous_item(blockIdx.x, gridDim.x);      // grid: a multiple of 8
+  if (item >= (long long)f.items) return;
+  // the blocks of one column follow each other on one XCD, whose L2 serves their second read of u
+  const long long group = item / f.nchunk;
+  const int chunk = (int)(item - group * f.nchunk);
+  const int o0 = chunk * f.ct * 4;
+  const int wc = 1 << f.wc_shift, cb = 4 >> f.wc_shift;
+  const int cl = wave >> f.wc_shift, wl = wave & (wc - 1);
+  const bool active = group * cb + cl < f.ncols;
+  const long long col = min(group * cb + cl, f.ncols - 1);
+
+  const int eo_col = f.ct * f.R * f.K1 * 16;                     // float2 per column
+  float2* EO = reinterpret_cast<float2*>(smem4);                 // [cb][ct][R][K1][16]
+  float2* ZT = EO + cb * eo_col;                                 // [4][ks][64]
+  float* TB = reinterpret_cast<float*>(ZT + 4 * f.ks * 64);      // [tt][R][64]
+  float* BL = TB + f.tt * f.R * 64;                              // [ct][4]
+  float* WL = BL + 4 * f.ct;                                     // [ct][CI][4]
+  EO += cl * eo_col;
+  ZT += wave * f.ks * 64;
+
+  constexpr int NS = fold_inv_ns(W, CI);
+  const long long b = col / f.NxNy, xy = col - b * f.NxNy;
+  const long long first = b * f.Co * f.Npts + xy * f.Nz * (long long)f.Nt;      // the column in channel 0 of out
+  const char* up = CI > 0 ? reinterpret_cast<const char*>(ep.u + b * ep.Cu * f.Npts + xy * f.Nz * (long long)f.Nt) : nullptr;
+  float u[CI > 0 ? CI : 1][NS][W];
+  // the u values of the wave's first task are on their way while E and O are made
+  FoldTile<NS> q = fold_inv_place<NS, W>(f, min(wl, f.ntask - 1), active);
+  if constexpr (CI > 0) fold_inv_load_u<NS, W, CI, STREAM>(q.voff, up, ep.Cu, f.Npts * 4, u);
+  // E and O of this wave's channels of its column; a lane takes one (k, kt), both parts.  Columns of the tile past
+  // the 2 mt - 1 real ones, and channels past the last, are zeros.
+  {
+    const float2* src = a + ((b * f.Co + o0) * f.NxNy + xy) * (long long)(f.Lz * f.mt);
+    const long long ostride = (long long)f.NxNy * f.Lz * f.mt;
+    const float2* rot = reinterpret_cast<const float2*>(ztab + (long long)2 * f.mrows * f.stride);
+    const int R1 = f.K1 * 16, real = 2 * f.mt - 1;
+    for (int i0 = 0; i0 < f.K1 * f.mt; i0 += 64) {
+      const int idx = min(i0 + lane, f.K1 * f.mt - 1);         // lanes past the end repeat the last entry
+      const int k = f.mt > 1 ? (int)__umulhi((unsigned)idx, f.inv_mt) : idx, kt = idx - k * f.mt;
+      const bool has_p = k < f.npos, has_q = k >= 1 && k <= f.Lz - f.npos;
+      const int off_p = has_p ? idx : 0, off_q = has_q ? (f.Lz - k) * f.mt + kt : 0;
+      const float2 w = rot[k];
+      // bin 0 has no imaginary part: its place takes the first padding column
+      const int c_re = kt == 0 ? 0 : 2 * kt - 1, c_im = kt == 0 ? real : 2 * kt;
+      float2* d_re = EO + (c_re >> 2) * R1 + 16 * k + 4 * (c_re & 3);
+      float2* d_im = EO + (c_im >> 2) * R1 + 16 * k + 4 * (c_im & 3);
+      constexpr int UB = 4;
+      for (int c0 = wl * UB; c0 < 4 * f.ct; c0 += UB * wc) {   // the four channels of a tile
+        float2 p[UB], q[UB];
+#pragma unroll
+        for (int h = 0; h < UB; ++h) {
+          const float2* so = src + min(c0 + h, f.Co - 1 - o0) * ostride;
+          p[h] = so[off_p];
+          q[h] = so[off_q];
+        }
+        const int at = (c0 >> 2) * f.R * R1;
+#pragma unroll
+        for (int h = 0; h < UB; ++h) {
+          const bool in = o0 + c0 + h < f.Co, ip = in && has_p, iq = in && has_q;
+          const float px = ip ? p[h].x : 0.f, py = ip ? p[h].y : 0.f, qx = iq ? q[h].x : 0.f, qy = iq ? q[h].y : 0.f;
+          const float sx = px + qx, dx = px - qx, sy = py + qy, dy = py - qy;
+          float2 im = make_float2(fmaf(-w.y, dx, w.x * sy), fmaf(w.y, sy, w.x * dx));
+          if (kt == 0) im = make_float2(0.f, 0.f);
+          d_re[at + h] = make_float2(fmaf(w.y, dy, w.x * sx), fmaf(w.y, sx, -w.x * dy));
+          d_im[at + h] = im;
+          if (4 * f.R > real + 1 && kt == 0) {                 // two more padding columns
+            EO[at + h + (f.R - 1) * R1 + 16 * k + 8] = make_float2(0.f, 0.f);
+            EO[at + h + (f.R - 1) * R1 + 16 * k + 12] = make_float2(0.f, 0.f);
+          }
+        }
+      }
+    }
+  }
+  // table of the product over t: entry (tile, r, lane) is cs[t][4 r + lane / 16] at the t of tile row lane % 16
+  for (int i = tid; i < f.tt * f.R * 64; i += kThreads) {
+    const int l = i & 63, q = i >> 6;
+    const int ti = q / f.R, r = q - ti * f.R;
+    const int m = l & 15, cc = 4 * r + (l >> 4), kt = (cc + 1) >> 1;
+    const int t = min(W * (4 * ti + (m >> 2)), f.Nt - W) + (m & 3);
+    float v = 0.f;
+    if (cc < 2 * f.mt - 1 && (m & 3) < W) {
+      const float2 w = twt[kt * f.Nt + t];
+      v = (cc & 1) || cc == 0 ? w.x : w.y;
+    }
+    TB[i] = v;
+  }
+  for (int i = tid; i < 4 * f.ct; i += kThreads)
+    BL[i] = (ep.bias != nullptr && o0 + i < f.Co) ? ep.bias[o0 + i] : 0.f;
+  if constexpr (CI > 0) {
+    for (int i = tid; i < f.ct * CI * 4; i += kThreads) {
+      const int T = i / (4 * CI), ii = (i >> 2) - T * CI, o = o0 + 4 * T + (i & 3);
+      WL[i] = (ii < ep.Cu && o < f.Co) ? ep.W[o * ep.w_so + ii * ep.w_si] : 0.f;
+    }
+  }
+  __syncthreads();
+
+  const float4* BL4 = reinterpret_cast<const float4*>(BL);
+  for (int task = wl; task < f.ntask; task += wc) {
+    const bool more = task + wc < f.ntask;
+    const FoldTile<NS> qn = fold_inv_place<NS, W>(f, more ? task + wc : task, active);
+    fold_inv_tile<NS, W, CI, STREAM>(f, ep, out, ztab, EO, ZT, TB, WL, BL4, first, o0, q, u, up, qn.voff, more);
+    q = qn;
+  }
+}
+
+int fold_inv_bucket(int Cu) { return Cu <= 0 ? 0 : (Cu <= 8 ? 8 : (Cu <= 20 ? (Cu + 3) / 4 * 4 : (Cu <= 24 ? 24 : 32))); }
+int fold_inv_run(int Nt, int tt) { return (Nt + 4 * tt - 1) / (4 * tt); }      // points of t per lane
+
+// everything but the number of columns; false where no split fits the LDS
+bool fold_inv_geometry(AxisPlan az, int Nt, int mt, int Co, int Cu, FoldInv* out, size_t* lds) {
+  if (Co > kMaxCo || Cu > 32 || (int64_t)az.N * Nt > (1 << 28) || !tz_fwd_fold_fits(az, Nt, mt)) return false;
+  const FoldPlan fp = fold_plan(az);
+  FoldInv f{};
+  f.Co = Co; f.Nz = az.N; f.Nt = Nt; f.Lz = az.L; f.npos = az.npos; f.mt = mt;
+  f.K1 = 1 + (az.npos - 1 > az.L - az.npos ? az.npos - 1 : az.L - az.npos);
+  f.ks = (f.K1 + 3) / 4;
+  f.R = (2 * mt - 1 + 3) / 4;
+  f.pairs = fp.pairs; f.stride = fp.stride; f.mrows = fp.rows;
+  f.ntile = (f.pairs + 15) / 16;
+  f.tt = (Nt + 15) / 16;
+  const int W = fold_inv_run(Nt, f.tt), CI = fold_inv_bucket(Cu);
+  f.inv_mt = mt > 1 ? (unsigned)((0x100000000ull + mt - 1) / mt) : 0;
+  f.half_last = f.pairs - 16 * (f.ntile - 1) <= 8;
+  f.ntask = (f.ntile + (fold_inv_ns(W, CI) == 1 ? f.ntile - f.half_last : 0)) * f.tt;
+  const int CT = (Co + 3) / 4;
+  // Waves per column: two tasks each, so that the second one's u values load under the first (64 x 20, one block
+  // forward and back: 0.71 ms with one task per wave, 0.68 with two); more waves when the columns of a block then
+  // fit the LDS share of its resident waves; then fewer output channels per block.
+  const int wc0 = f.ntask >= 8 ? 2 : (f.ntask >= 4 ? 1 : 0);
+  for (int nchunk = 1; nchunk <= CT; ++nchunk) {
+    f.ct = (CT + nchunk - 1) / nchunk;
+    f.nchunk = (CT + f.ct - 1) / f.ct;
+    for (const size_t cap : {(size_t)160 * 1024 / fold_inv_waves(W, CI), (size_t)80 * 1024})
+      for (f.wc_shift = wc0; f.wc_shift <= 2; ++f.wc_shift) {
+        const size_t fl = (size_t)(4 >> f.wc_shift) * f.ct * f.R * f.K1 * 32 + (size_t)4 * f.ks * 128 +
+                          (size_t)f.tt * f.R * 64 + 4 * f.ct + (size_t)f.ct * CI * 4;
+        if (fl * 4 > cap) continue;
+        *out = f;
+        *lds = fl * 4;
+        return true;
+      }
+  }
+  return false;
+}
+
+}  // namespace
+
+bool zt_inv_fold_fits(AxisPlan az, int Nt, int mt, int Co, int Cu) {
+  FoldInv f;
+  size_t lds;
+  return fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds);
+}
+
+hipError_t launch_zt_inv_fold(const float2* a, float* out, const float2* twt, const float* ztab, int64_t ncols, int Co,
+                              int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, hipStream_t s) {
+  FoldInv f{};
+  size_t lds = 0;
+  const int Cu = e.u != nullptr ? e.Cu : 0;
+  if (!fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds)) return hipErrorInvalidValue;
+  f.ncols = ncols; f.NxNy = NxNy; f.Npts = (int64_t)NxNy * az.N * Nt;
+  const int W = fold_inv_run(Nt, f.tt), CI = fold_inv_bucket(Cu);
+  const int cb = 4 >> f.wc_shift;
+  const int64_t items = (ncols + cb - 1) / cb * f.nchunk;
+  const int64_t nblk = (items + 7) / 8 * 8;
+  if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
+  f.items = (unsigned)items;
+  // Whole rows per tile: its 16 rows are one run of memory, and streams pay as everywhere (263 x 16: 6.9 -> 6.7 ms
+  // over four blocks).  Tiles of part of a row leave lines half written, which plain stores let the L2 complete
+  // (64 x 20, one block forward and back: 0.89 ms streamed, 0.74 ms plain; 64 x 30: 5.3 and 3.4 ms over four).
+  const bool stream = f.tt == 1 && ncols * (int64_t)Co * az.N * Nt * 4 >= kStreamBytes;
+#define FNO_ZF_S(WV, CIV, STRV)                                                                                      \
+  hipLaunchKernelGGL((zt_inv_fold_kernel<WV, CIV, STRV>), dim3((unsigned)nblk), dim3(kThreads), lds, s, a, out, twt, \
+                     ztab, f, e)
+#define FNO_ZF_C(WV, CIV) do { if (stream) FNO_ZF_S(WV, CIV, true); else FNO_ZF_S(WV, CIV, false); } while (0)
+#define FNO_ZF_W(WV)                                                              \
+  switch (CI) {                                                                   \
+    case 0: FNO_ZF_C(WV, 0); break;                                               \
+    case 8: FNO_ZF_C(WV, 8); break;                                               \
+    case 12: FNO_ZF_C(WV, 12); break;                                             \
+    case 16: FNO_ZF_C(WV, 16); break;                                             \
+    case 20: FNO_ZF_C(WV, 20); break;                                             \
+    case 24: FNO_ZF_C(WV, 24); break;                                             \
+    default: FNO_ZF_C(WV, 32); break;                                             \
+  }
+  if (W == 1) FNO_ZF_W(1) else if (W == 2) FNO_ZF_W(2) else if (W == 3) FNO_ZF_W(3) else FNO_ZF_W(4)
+#undef FNO_ZF_W
+#undef FNO_ZF_C
+#undef FNO_ZF_S
+  return hipGetLastError();
+}
+
+}  // namespace fno

@@ -783,3 +783,47 @@ def test_folded_forward_transform_at_the_edges_of_its_tiles(nz, mz, nt, mt, rule
     yo, xho = O.spectral_conv_fwd(L.x, L.R, L.spec, return_xhat=True)
     assert rel(xh, xho) <= TOL
     assert rel(y, yo) <= TOL
+
+
+@pytest.mark.parametrize("c, nz, mz, nt, mt, rule", [
+    (1, 1, 0, 1, 1, 1),         # one point per column
+    (3, 5, 2, 3, 2, 1),         # half a tile: three pairs and their mirrored rows, the middle row its own pair
+    (8, 16, 4, 8, 3, 0),        # eight pairs: a half tile with every lane at work
+    (9, 18, 9, 17, 9, 0),       # nine pairs: one past the half tile; a second tile of t with one new step; 17 of 20 columns
+    (20, 33, 8, 16, 8, 1),      # one pair past a whole tile, symmetric rule
+    (20, 49, 12, 30, 8, 0),     # two tiles (nine pairs in the second), overlapping runs of four steps at the end of a row
+    (17, 64, 12, 20, 6, 0),     # runs of three steps; three empty channels in the last group
+    (21, 40, 6, 24, 8, 1),      # more than 20 channels: one row of a pair at a time, then runs of three steps
+    (32, 35, 17, 31, 16, 0),    # every channel, the largest column count, one row of a pair at a time; odd z
+    (24, 40, 5, 10, 5, 0),      # 24 channels, runs of three: both rows again
+    (5, 70, 33, 63, 32, 0),     # 63 columns in 16 tiles, four tiles of t, more than eight K steps
+    (4, 128, 60, 48, 24, 0),    # the folded spectrum of all channels past half a CU's LDS
+    (3, 12, 3, 70, 5, 0),       # t axis past the folded kernel: the generic one
+    (2, 35, 6, 66, 4, 1),       # same, dense z stage
+    (20, 256, 128, 10, 1, 0),   # table of the folded kernel past the LDS: the generic one, at more than 64 KiB
+])
+def test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule):
+    """Inverse (z, t) stage with every epilogue (forward, forward with the pre-activation, adjoint, none) at the edges of
+    the tiles of row pairs, of t, of columns and of channels; 7 and 14 columns are no multiple of a block's share.
+    A batch entry of NaNs leaves the other entry, whose columns share blocks with it, as it was."""
+    L = Layer(1, c, c, (7, 1, nz, nt), (2, 0, mz, mt), 1) if rule else Layer(1, c, c, (7, 2, nz, nt), (2, 1, mz, mt))
+    out, z, xh = gpu_block_fwd(L)
+    oo, zo, xho = O.block_fwd(L.x, L.R, L.W, L.b, L.spec)
+    assert rel(out, oo) <= TOL and rel(z, zo) <= TOL
+    y, _ = gpu_spectral_fwd(L)
+    assert rel(y, O.spectral_conv_fwd(L.x, L.R, L.spec)) <= TOL
+    g = synth.normal_field(3, synth.T_GOUT, 1, c, L.spec.grid)
+    ref = O.block_bwd(L.x, L.R, L.W, L.b, g, L.spec)
+    gx = torch.empty((1, c) + L.spec.grid, device="cuda")
+    B.fno_block_bwd(L.desc, dev(L.x), dev(L.R), dev(L.W), dev(z), dev(xh), dev(g), gx, None, None, None,
+                    B.alloc_workspace(L.desc, B.FNO_OP_BLOCK_BWD))
+    torch.cuda.synchronize()
+    assert rel(host(gx), ref["gx"]) <= TOL
+
+    two = B.make_desc(2, c, c, L.spec.grid, L.spec.modes, rule, B.FNO_ACT_GELU)
+    x2 = dev(np.concatenate([np.full_like(L.x, np.nan), L.x]))
+    out2 = torch.empty_like(x2)
+    B.fno_block_fwd(two, x2, dev(L.R), dev(L.W), dev(L.b), out2, None, None, B.alloc_workspace(two, B.FNO_OP_BLOCK_FWD))
+    torch.cuda.synchronize()
+    assert np.isnan(host(out2[0])).all()
+    assert np.array_equal(host(out2[1]), out[0])
