@@ -38,20 +38,22 @@ __global__ void plan_tables_kernel(TableSet ts) {
     t.tw[idx] = make_float2(float(c), float(s));
   } else if (t.L < 0) {
     const int rows = -t.L, stride = t.P;
-    if (idx >= rows * stride) return;
-    const int k = idx / stride, n = idx - k * stride;
+    if (idx >= rows * (stride + 1)) return;
+    const bool phase = idx >= rows * stride;             // the last `rows` entries: exp(i pi k / N)
+    const int k = phase ? idx - rows * stride : idx / stride, n = phase ? 0 : idx - k * stride;
     float* f = reinterpret_cast<float*>(t.tw);
     double s = 0.0, c = 0.0;
     if (2 * n < t.N) {
-      const long long r = ((long long)k * (2 * n + 1)) % (2LL * t.N);      // angle pi r / N
+      // angle pi r / N; k and 2 n + 1 are below 2^13
+      const unsigned r = ((unsigned)k * (phase ? 1u : 2u * n + 1u)) % (2u * t.N);
       sincospi(double(r) / double(t.N), &s, &c);
-      if (2 * n + 1 == t.N) c *= 0.5;
+      if (2 * n + 1 == t.N && !phase) c *= 0.5;
     }
-    f[idx] = float(c);
-    f[rows * stride + idx] = float(s);
-    if (n == 0) {
-      sincospi(double(k % (2 * t.N)) / double(t.N), &s, &c);
+    if (phase) {
       reinterpret_cast<float2*>(f + 2 * rows * stride)[k] = make_float2(float(c), float(s));
+    } else {
+      f[idx] = float(c);
+      f[rows * stride + idx] = float(s);
     }
   } else {
     if (idx >= t.N * t.npos) return;
@@ -630,37 +632,47 @@ __device__ __forceinline__ float mode_scale(long long k, int mt, int Nt, float i
   return single ? invN : 2.0f * invN;
 }
 
-constexpr int kMixB = 4;   // batch entries held per pass (backward mix)
+constexpr int kMixU = 4;   // input (backward: output) channels whose loads go out together
 
 // One thread: one mode, KO output channels, KB batch entries per pass; R is read exactly once,
-// the input spectrum once per group of KO output channels (launch: grid.y = ceil(Co / KO)).
+// the input spectrum once per group of KO output channels (launch: grid.y = ceil(Co / KO)).  Large spectra are bound
+// by the read of R, small ones by the chain of round trips over the input channels, hence U of them per trip (one where
+// four batch entries fill the registers and waves abound: 8 % faster there).  16 channels, 2048 modes, batch 4: 25 -> 9 us;
+// 20 channels, 110592 modes, one entry: 103 -> 75 us; two 117 -> 84 us.
 template <int KB, int KO, bool STREAM>
 __global__ __launch_bounds__(kThreads) void mix_fwd_kernel(
     const float2* __restrict__ xh, const float2* __restrict__ R, float2* __restrict__ yh, int B,
     int Ci, int Co, long long K, int mt, int Nt, float invN) {
-  const long long k = (long long)blockIdx.x * kThreads + threadIdx.x;
+  const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const int o0 = blockIdx.y * KO;
   if (k >= K) return;
   const float sc = mode_scale(k, mt, Nt, invN);
+  constexpr int U = KB >= 4 && STREAM ? 1 : kMixU;
   for (int b0 = 0; b0 < B; b0 += KB) {
     float2 acc[KB][KO];
 #pragma unroll
     for (int u = 0; u < KB; ++u)
 #pragma unroll
       for (int v = 0; v < KO; ++v) acc[u][v] = make_float2(0.f, 0.f);
-    for (int i = 0; i < Ci; ++i) {
-      float2 xv[KB];
+    for (int i0 = 0; i0 < Ci; i0 += U) {
+      float2 xv[U][KB], r[U][KO];
 #pragma unroll
-      for (int u = 0; u < KB; ++u)
-        xv[u] = (b0 + u < B) ? xh[((long long)(b0 + u) * Ci + i) * K + k] : make_float2(0.f, 0.f);
+      for (int h = 0; h < U; ++h) {
+        const int i = i0 + h;
 #pragma unroll
-      for (int v = 0; v < KO; ++v) {
-        if (o0 + v < Co) {
-          const float2 r = ld_once2<STREAM>(&R[((long long)i * Co + o0 + v) * K + k]);
+        for (int u = 0; u < KB; ++u)
+          xv[h][u] = (i < Ci && b0 + u < B) ? xh[((long long)(b0 + u) * Ci + i) * K + k] : make_float2(0.f, 0.f);
 #pragma unroll
-          for (int u = 0; u < KB; ++u) acc[u][v] = cfma(xv[u], r, acc[u][v]);
-        }
+        for (int v = 0; v < KO; ++v)
+          r[h][v] = (i < Ci && o0 + v < Co) ? ld_once2<STREAM>(&R[((long long)i * Co + o0 + v) * K + k])
+                                            : make_float2(0.f, 0.f);
       }
+#pragma unroll
+      for (int h = 0; h < U; ++h)
+#pragma unroll
+        for (int v = 0; v < KO; ++v)
+#pragma unroll
+          for (int u = 0; u < KB; ++u) acc[u][v] = cfma(xv[h][u], r[h][v], acc[u][v]);
     }
 #pragma unroll
     for (int u = 0; u < KB; ++u)
@@ -671,63 +683,77 @@ __global__ __launch_bounds__(kThreads) void mix_fwd_kernel(
   }
 }
 
-// One thread: one mode k, kMixI input channels, the batch in chunks of kMixB; the gradient
-// spectrum gh is then read once per kMixI input channels.
+// One thread: one mode k, kMixI input channels, the batch KB entries at a time; the gradient spectrum gh is then
+// read once per kMixI input channels.
 constexpr int kMixI = 4;
-template <bool STREAM>
+template <int KB, bool STREAM>
 __global__ __launch_bounds__(kThreads) void mix_bwd_kernel(
     const float2* __restrict__ xh, const float2* __restrict__ R, const float2* __restrict__ gh,
     float2* __restrict__ gR, float2* __restrict__ gxh, int B, int Ci, int Co, long long K, int mt,
     int Nt, float invN, int accumulate) {
-  const long long k = (long long)blockIdx.x * kThreads + threadIdx.x;
+  const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const int i0 = blockIdx.y * kMixI;
   if (k >= K) return;
   const float sc = mode_scale(k, mt, Nt, invN);
-  for (int b0 = 0; b0 < B; b0 += kMixB) {
-    float2 xv[kMixB][kMixI], gx[kMixB][kMixI];
+  constexpr int U = KB >= 4 ? (STREAM ? 1 : 2) : kMixU;
+  for (int b0 = 0; b0 < B; b0 += KB) {
+    const bool add = gR != nullptr && (b0 > 0 || accumulate);
+    float2 xv[KB][kMixI], gx[KB][kMixI];
 #pragma unroll
-    for (int u = 0; u < kMixB; ++u)
+    for (int u = 0; u < KB; ++u)
 #pragma unroll
       for (int v = 0; v < kMixI; ++v) {
         gx[u][v] = make_float2(0.f, 0.f);
         xv[u][v] = (b0 + u < B && i0 + v < Ci) ? xh[((long long)(b0 + u) * Ci + i0 + v) * K + k]
                                                : make_float2(0.f, 0.f);
       }
-    for (int o = 0; o < Co; ++o) {
-      float2 r[kMixI], gr[kMixI], gy[kMixB];
+    for (int o0 = 0; o0 < Co; o0 += U) {
+      float2 r[U][kMixI], gr[U][kMixI], gy[U][KB];
 #pragma unroll
-      for (int v = 0; v < kMixI; ++v) {
-        const long long ridx = ((long long)(i0 + v) * Co + o) * K + k;
-        r[v] = i0 + v < Ci ? ld_once2<STREAM>(&R[ridx]) : make_float2(0.f, 0.f);
-        gr[v] = (gR != nullptr && (b0 > 0 || accumulate) && i0 + v < Ci) ? gR[ridx] : make_float2(0.f, 0.f);
-      }
-#pragma unroll
-      for (int u = 0; u < kMixB; ++u) {
-        gy[u] = b0 + u < B ? gh[((long long)(b0 + u) * Co + o) * K + k] : make_float2(0.f, 0.f);
-        gy[u].x *= sc; gy[u].y *= sc;
-      }
-#pragma unroll
-      for (int u = 0; u < kMixB; ++u)
+      for (int h = 0; h < U; ++h) {
+        const int o = o0 + h;
 #pragma unroll
         for (int v = 0; v < kMixI; ++v) {
-          gr[v] = cfmac(gy[u], xv[u][v], gr[v]);        // conj(xh) * gy
-          gx[u][v] = cfmac(gy[u], r[v], gx[u][v]);      // conj(R) * gy
+          const long long ridx = ((long long)(i0 + v) * Co + o) * K + k;
+          const bool on = o < Co && i0 + v < Ci;
+          r[h][v] = on ? ld_once2<STREAM>(&R[ridx]) : make_float2(0.f, 0.f);
+          gr[h][v] = (on && add) ? gR[ridx] : make_float2(0.f, 0.f);
         }
-      if (gR != nullptr) {
 #pragma unroll
-        for (int v = 0; v < kMixI; ++v)
-          if (i0 + v < Ci) st_once2<STREAM>(&gR[((long long)(i0 + v) * Co + o) * K + k], gr[v]);
+        for (int u = 0; u < KB; ++u)
+          gy[h][u] = (o < Co && b0 + u < B) ? gh[((long long)(b0 + u) * Co + o) * K + k] : make_float2(0.f, 0.f);
+      }
+#pragma unroll
+      for (int h = 0; h < U; ++h) {
+        const int o = o0 + h;
+#pragma unroll
+        for (int u = 0; u < KB; ++u) { gy[h][u].x *= sc; gy[h][u].y *= sc; }
+#pragma unroll
+        for (int u = 0; u < KB; ++u)
+#pragma unroll
+          for (int v = 0; v < kMixI; ++v) {
+            gr[h][v] = cfmac(gy[h][u], xv[u][v], gr[h][v]);        // conj(xh) * gy
+            gx[u][v] = cfmac(gy[h][u], r[h][v], gx[u][v]);         // conj(R) * gy
+          }
+        if (gR != nullptr) {
+#pragma unroll
+          for (int v = 0; v < kMixI; ++v)
+            if (o < Co && i0 + v < Ci) st_once2<STREAM>(&gR[((long long)(i0 + v) * Co + o) * K + k], gr[h][v]);
+        }
       }
     }
     if (gxh != nullptr) {
 #pragma unroll
-      for (int u = 0; u < kMixB; ++u)
+      for (int u = 0; u < KB; ++u)
 #pragma unroll
         for (int v = 0; v < kMixI; ++v)
           if (b0 + u < B && i0 + v < Ci) gxh[((long long)(b0 + u) * Ci + i0 + v) * K + k] = gx[u][v];
     }
   }
 }
+
+// threads per block of the mode mix: 64 where 256 would leave CUs without a block
+int mix_threads(int64_t K, int groups) { return (K + kThreads - 1) / kThreads * groups < 512 ? 64 : kThreads; }
 
 size_t tz_fwd_lds(AxisPlan az, int Nt, int mt, int ppb) {
   size_t s_floats = (size_t)ppb * az.N * (Nt + 1);
@@ -758,7 +784,7 @@ hipError_t launch_plan_tables(const TableSet& ts, hipStream_t s) {
   int most = 1;
   for (int i = 0; i < ts.n; ++i) {
     const int L = ts.t[i].L;
-    const int n = L != 0 ? (L > 0 ? L : -L) * ts.t[i].P : ts.t[i].N * ts.t[i].npos;
+    const int n = L > 0 ? L * ts.t[i].P : (L < 0 ? -L * (ts.t[i].P + 1) : ts.t[i].N * ts.t[i].npos);
     if (n > most) most = n;
   }
   hipLaunchKernelGGL(plan_tables_kernel, dim3((most + 255) / 256, ts.n), dim3(256), 0, s, ts);
@@ -895,7 +921,8 @@ hipError_t launch_axis_inv(const float2* in, float2* out, const float2* tw, int6
 
 hipError_t launch_mix_fwd(const float2* xh, const float2* R, float2* yh, int B, int Ci, int Co,
                           int64_t K, int mt, int Nt, double invN, hipStream_t s) {
-  const int64_t nb = (K + kThreads - 1) / kThreads;
+  const int thr = mix_threads(K, (Co + 3) / 4);
+  const int64_t nb = (K + thr - 1) / thr;
   if (nb > 0x7fffffffLL || Co > 65535) return hipErrorInvalidValue;
   // four output channels and up to four batch entries per thread (a tile of one or two entries for
   // batches that small: 3 % faster than four with unused rows); wider output tiles (10 or 20
@@ -903,7 +930,7 @@ hipError_t launch_mix_fwd(const float2* xh, const float2* R, float2* yh, int B, 
   // R is read once per call: as a stream when it is larger than the caches
   const bool stream = (int64_t)Ci * Co * K * 8 >= kStreamBytes;
 #define FNO_MIX(KBV, STRV)                                                                                  \
-  hipLaunchKernelGGL((mix_fwd_kernel<KBV, 4, STRV>), dim3((unsigned)nb, (unsigned)((Co + 3) / 4)), dim3(kThreads), \
+  hipLaunchKernelGGL((mix_fwd_kernel<KBV, 4, STRV>), dim3((unsigned)nb, (unsigned)((Co + 3) / 4)), dim3(thr), \
                      0, s, xh, R, yh, B, Ci, Co, (long long)K, mt, Nt, (float)invN)
 #define FNO_MIX_B(STRV)                                                                      \
   do {                                                                                       \
@@ -918,14 +945,20 @@ hipError_t launch_mix_fwd(const float2* xh, const float2* R, float2* yh, int B, 
 hipError_t launch_mix_bwd(const float2* xh, const float2* R, const float2* gh, float2* gR,
                           float2* gxh, int B, int Ci, int Co, int64_t K, int mt, int Nt,
                           double invN, int accumulate, hipStream_t s) {
-  const int64_t nb = (K + kThreads - 1) / kThreads;
+  const int groups = (Ci + kMixI - 1) / kMixI, thr = mix_threads(K, groups);
+  const int64_t nb = (K + thr - 1) / thr;
   if (nb > 0x7fffffffLL || Ci > 4 * 65535) return hipErrorInvalidValue;
-  if ((int64_t)Ci * Co * K * 8 >= kStreamBytes)
-    hipLaunchKernelGGL(mix_bwd_kernel<true>, dim3((unsigned)nb, (unsigned)((Ci + kMixI - 1) / kMixI)), dim3(kThreads), 0,
-                       s, xh, R, gh, gR, gxh, B, Ci, Co, (long long)K, mt, Nt, (float)invN, accumulate);
-  else
-    hipLaunchKernelGGL(mix_bwd_kernel<false>, dim3((unsigned)nb, (unsigned)((Ci + kMixI - 1) / kMixI)), dim3(kThreads), 0,
-                       s, xh, R, gh, gR, gxh, B, Ci, Co, (long long)K, mt, Nt, (float)invN, accumulate);
+  const bool stream = (int64_t)Ci * Co * K * 8 >= kStreamBytes;
+#define FNO_MIXB(KBV, STRV)                                                                                          \
+  hipLaunchKernelGGL((mix_bwd_kernel<KBV, STRV>), dim3((unsigned)nb, (unsigned)groups), dim3(thr), 0, s, xh, R, gh,  \
+                     gR, gxh, B, Ci, Co, (long long)K, mt, Nt, (float)invN, accumulate)
+#define FNO_MIXB_B(STRV)                                                                        \
+  do {                                                                                          \
+    if (B == 1) FNO_MIXB(1, STRV); else if (B == 2) FNO_MIXB(2, STRV); else FNO_MIXB(4, STRV);  \
+  } while (0)
+  if (stream) FNO_MIXB_B(true); else FNO_MIXB_B(false);
+#undef FNO_MIXB_B
+#undef FNO_MIXB
   return hipGetLastError();
 }
 
