@@ -219,35 +219,43 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
   }
 }
 
-// Sum of the partial slots in a fixed order (same bits on every run): 64 pairs per block, the
-// slots dealt round-robin to kRedGroups threads per pair, whose sums are added in group order.
-constexpr int kRedGroups = 16;
-__global__ __launch_bounds__(64 * kRedGroups) void reduce_partials_kernel(
-    const double* __restrict__ part, int nblk, int Co, int Ci, float* __restrict__ gW,
-    float* __restrict__ gb, int accumulate) {
-  __shared__ double sums[kRedGroups][64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int q = blockIdx.x * 64 + lane;
-  const int npairs = Co * Ci + Co;
+// Sum over the partial slots part[slot][q] in a fixed order (same bits on every run): kRedPairs sums per block, the
+// slots dealt round-robin to kRedGroups threads per sum, whose sums are added in group order.  Returns the total in
+// group 0.  What bounds it is the latency of a thread's chain of loads, so the chain is short: 4096 slots of 420 sums
+// take 12 us (31 us with 64 sums and 16 groups per block), 512 slots of 2945 sums 8 us (126 us with one thread per sum).
+constexpr int kRedPairs = 16, kRedGroups = 64;
+__device__ __forceinline__ double sum_slots(const double* __restrict__ part, int nslots, int n, int q) {
+  __shared__ double sums[kRedGroups][kRedPairs];
+  const int c = threadIdx.x % kRedPairs, grp = threadIdx.x / kRedPairs;
   double s = 0.0;
-  if (q < npairs) {
+  if (q < n) {
     const double* p = part + q;
-    int blk = grp;
-    for (; blk + 7 * kRedGroups < nblk; blk += 8 * kRedGroups) {
+    int slot = grp;
+    for (; slot + 7 * kRedGroups < nslots; slot += 8 * kRedGroups) {
       double v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(long long)(blk + u * kRedGroups) * npairs];
+      for (int u = 0; u < 8; ++u) v[u] = p[(long long)(slot + u * kRedGroups) * n];
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; blk < nblk; blk += kRedGroups) s += p[(long long)blk * npairs];
+    for (; slot < nslots; slot += kRedGroups) s += p[(long long)slot * n];
   }
-  sums[grp][lane] = s;
+  sums[grp][c] = s;
   __syncthreads();
-  if (grp == 0 && q < npairs) {
-    double t = 0.0;
+  double t = 0.0;
+  if (grp == 0)
 #pragma unroll
-    for (int g = 0; g < kRedGroups; ++g) t += sums[g][lane];
+    for (int g = 0; g < kRedGroups; ++g) t += sums[g][c];
+  return t;
+}
+
+__global__ __launch_bounds__(kRedPairs * kRedGroups) void reduce_partials_kernel(
+    const double* __restrict__ part, int nblk, int Co, int Ci, float* __restrict__ gW,
+    float* __restrict__ gb, int accumulate) {
+  const int q = blockIdx.x * kRedPairs + threadIdx.x % kRedPairs;
+  const int npairs = Co * Ci + Co;
+  const double t = sum_slots(part, nblk, npairs, q);
+  if (threadIdx.x < kRedPairs && q < npairs) {
     // accumulate: the sums are added to what gW and gb hold (a step over several calls)
     if (q < Co * Ci) { if (gW != nullptr) gW[q] = float(accumulate ? t + double(gW[q]) : t); }
     else if (gb != nullptr) gb[q - Co * Ci] = float(accumulate ? t + double(gb[q - Co * Ci]) : t);
@@ -320,16 +328,14 @@ __global__ void transpose_kernel(const float* __restrict__ w, float* __restrict_
   if (idx < rows * cols) wt[(idx % cols) * rows + idx / cols] = w[idx];
 }
 
-// out[q] = sum over blocks of part[blk][q], blocks in order (same bits on every run); the result
-// goes to four destinations by ranges of q (any of them may be null)
-__global__ __launch_bounds__(kThreads) void reduce_ranges_kernel(
+// The totals over the slots go to four destinations by ranges of q (any of them may be null).
+__global__ __launch_bounds__(kRedPairs * kRedGroups) void reduce_ranges_kernel(
     const double* __restrict__ part, int nblk, int n0, int n1, int n2, int n3, float* __restrict__ d0,
     float* __restrict__ d1, float* __restrict__ d2, float* __restrict__ d3) {
-  const int q = blockIdx.x * kThreads + threadIdx.x;
+  const int q = blockIdx.x * kRedPairs + threadIdx.x % kRedPairs;
   const int npairs = n0 + n1 + n2 + n3;
-  if (q >= npairs) return;
-  double s = 0.0;
-  for (int b = 0; b < nblk; ++b) s += part[(long long)b * npairs + q];
+  const double s = sum_slots(part, nblk, npairs, q);
+  if (threadIdx.x >= kRedPairs || q >= npairs) return;
   if (q < n0) { if (d0 != nullptr) d0[q] = (float)s; }
   else if (q < n0 + n1) { if (d1 != nullptr) d1[q - n0] = (float)s; }
   else if (q < n0 + n1 + n2) { if (d2 != nullptr) d2[q - n0 - n1] = (float)s; }
@@ -755,12 +761,27 @@ __global__ __launch_bounds__(kThreads) void rel_l2_partial_kernel(
   }
 }
 
-// loss = sqrt(Sd) / sqrt(Sy); scale = 1 / (sqrt(Sd) sqrt(Sy)) for the gradient (0 when Sd = 0)
-__global__ void rel_l2_final_kernel(const double* __restrict__ part, int nblk, float* __restrict__ loss,
-                                    double* __restrict__ scale) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// loss = sqrt(Sd) / sqrt(Sy); scale = 1 / (sqrt(Sd) sqrt(Sy)) for the gradient (0 when Sd = 0).  One block; the
+// partials in a fixed order (a thread's share, then lanes as a tree, then waves): 5 us, 83 us with a single thread.
+__global__ __launch_bounds__(kThreads) void rel_l2_final_kernel(const double* __restrict__ part, int nblk,
+                                                                float* __restrict__ loss, double* __restrict__ scale) {
+  __shared__ double sd[kThreads / 64], sy[kThreads / 64];
   double a = 0.0, b = 0.0;
-  for (int i = 0; i < nblk; ++i) { a += part[2 * i]; b += part[2 * i + 1]; }
+#pragma unroll
+  for (int u = 0; u < kLossBlocks / kThreads; ++u) {
+    const int i = threadIdx.x + u * kThreads;
+    if (i < nblk) { a += part[2 * i]; b += part[2 * i + 1]; }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    a += __shfl_xor(a, off);
+    b += __shfl_xor(b, off);
+  }
+  if ((threadIdx.x & 63) == 0) { sd[threadIdx.x >> 6] = a; sy[threadIdx.x >> 6] = b; }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  a = 0.0; b = 0.0;
+  for (int w = 0; w < kThreads / 64; ++w) { a += sd[w]; b += sy[w]; }
   const double nd = sqrt(a), ny = sqrt(b);
   if (loss != nullptr) *loss = (float)(nd / ny);
   *scale = nd > 0.0 ? 1.0 / (nd * ny) : 0.0;
@@ -1039,8 +1060,8 @@ hipError_t launch_bwd_pointwise(const float* z, const float* gout, const float* 
 hipError_t launch_reduce_partials(const double* part, int nblk, int Co, int Ci, float* gW,
                                   float* gb, int accumulate, hipStream_t s) {
   const int npairs = Co * Ci + Co;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((npairs + 63) / 64), dim3(64 * kRedGroups), 0, s, part,
-                     nblk, Co, Ci, gW, gb, accumulate);
+  hipLaunchKernelGGL(reduce_partials_kernel, dim3((npairs + kRedPairs - 1) / kRedPairs),
+                     dim3(kRedPairs * kRedGroups), 0, s, part, nblk, Co, Ci, gW, gb, accumulate);
   return hipGetLastError();
 }
 
@@ -1190,7 +1211,7 @@ hipError_t launch_rel_l2(int64_t n, const float* pred, const float* target, floa
   if (nblk > kLossBlocks) nblk = kLossBlocks;
   double* scale = ws + 2 * kLossBlocks;
   hipLaunchKernelGGL(rel_l2_partial_kernel, dim3(nblk), dim3(kThreads), 0, s, (long long)n, pred, target, ws);
-  hipLaunchKernelGGL(rel_l2_final_kernel, dim3(1), dim3(64), 0, s, ws, nblk, loss, scale);
+  hipLaunchKernelGGL(rel_l2_final_kernel, dim3(1), dim3(kThreads), 0, s, ws, nblk, loss, scale);
   if (grad != nullptr) {
     int64_t gb = (n + kThreads - 1) / kThreads;
     if (gb > 65536) gb = 65536;
@@ -1231,8 +1252,8 @@ hipError_t launch_pointwise_linear_bwd(int B, int Ci, int Co, int64_t N, const f
     const size_t lds = (size_t)(Co + Ci) * (kBwdTile + 1) * 4;
     hipLaunchKernelGGL(bwd_pointwise_kernel, dim3((unsigned)nblk), dim3(kThreads), lds, s, g, g, x,
                        (float*)nullptr, part, B, Ci, Co, (long long)N, 0, 0, 0.f);
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((Co * Ci + Co + 63) / 64), dim3(64 * kRedGroups), 0, s,
-                       part, nblk, Co, Ci, gW, gb, 0);
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((Co * Ci + Co + kRedPairs - 1) / kRedPairs),
+                       dim3(kRedPairs * kRedGroups), 0, s, part, nblk, Co, Ci, gW, gb, 0);
   }
   if (gx != nullptr) {
     float* wt = reinterpret_cast<float*>(part + (size_t)2048 * (Co * Ci + Co));
@@ -1260,8 +1281,8 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
     if (Ci <= 21) { if (co == 1) FNO_MLPB(11, 1); else FNO_MLPB(11, 4); }
     else { if (co == 1) FNO_MLPB(16, 1); else FNO_MLPB(16, 4); }
 #undef FNO_MLPB
-    hipLaunchKernelGGL(reduce_ranges_kernel, dim3((nsum + kThreads - 1) / kThreads), dim3(kThreads), 0, s, part,
-                       nblk, H * Ci, H, Co * H, Co, gW1, gb1, gW2, gb2);
+    hipLaunchKernelGGL(reduce_ranges_kernel, dim3((nsum + kRedPairs - 1) / kRedPairs),
+                       dim3(kRedPairs * kRedGroups), 0, s, part, nblk, H * Ci, H, Co * H, Co, gW1, gb1, gW2, gb2);
     return hipGetLastError();
   }
   size_t lds_floats = (size_t)(Ci + Co + 2 * kMlpChunk) * (kThreads + 1);
@@ -1277,8 +1298,8 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
   else
     hipLaunchKernelGGL((mlp2_bwd_kernel<32>), dim3((unsigned)nblk), dim3(kThreads), lds, s, B, Ci, H, Co,
                        (long long)N, x, W1, b1, W2, g, gx, part);
-  hipLaunchKernelGGL(reduce_ranges_kernel, dim3((nsum + kThreads - 1) / kThreads), dim3(kThreads), 0, s, part,
-                     nblk, H * Ci, H, Co * H, Co, gW1, gb1, gW2, gb2);
+  hipLaunchKernelGGL(reduce_ranges_kernel, dim3((nsum + kRedPairs - 1) / kRedPairs),
+                     dim3(kRedPairs * kRedGroups), 0, s, part, nblk, H * Ci, H, Co * H, Co, gW1, gb1, gW2, gb2);
   return hipGetLastError();
 }
 
