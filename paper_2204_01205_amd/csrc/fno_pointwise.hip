@@ -219,6 +219,191 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
   }
 }
 
+// The same step for every other width up to 32, any point count and alignment, and c_in != c_out (the adjoint of the
+// lift).  The kernel above keeps all of gW in a wave's accumulators, which 32 channels do not fit; here the output
+// channels are dealt to `ngrp` waves of a block (OT tiles of 4 each), which share x through the cache.  Layout and
+// products are those of the kernel above; rows need not be aligned (4-byte aligned 16-byte loads), a batch entry's
+// ragged last step takes single values, and channels past the end read the last one and count as zero.  The fp32
+// accumulators take kBwdChain steps (128 terms, as many as one chain of the tiled kernel below) and are then added
+// over the wave's 16 lane blocks, half of them sent away at each level, into doubles of which every lane keeps a
+// sixteenth.  erff and expf as in the tiled kernel.
+// 5 -> 20 channels at 33.5 M points: 0.77 ms = 4.4 TB/s (1.9 ms tiled); 32 -> 32 at 2.16 M points with GELU: 0.43 ms
+// (0.67 ms tiled), where x comes from the cache for three of the four waves that share it.
+constexpr int kBwdChain = 32;
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+
+// one level of the sum over lane blocks: N values per lane to N / 2 (an odd N: all are added, both lanes keep them)
+template <int N>
+__device__ __forceinline__ void fold_level(float* v, bool upper, int mask) {
+  if constexpr (N % 2 == 0) {
+#pragma unroll
+    for (int q = 0; q < N / 2; ++q) {
+      const float keep = upper ? v[q + N / 2] : v[q], send = upper ? v[q] : v[q + N / 2];
+      v[q] = keep + __shfl_xor(send, mask);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] += __shfl_xor(v[q], mask);
+  }
+}
+constexpr int fold_count(int n) { return n % 2 == 0 ? n / 2 : n; }
+
+template <int OT, int IT, bool STREAM>
+__global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
+    const float* __restrict__ z, const float* __restrict__ gout, const float* __restrict__ x,
+    float* __restrict__ gz_out, double* __restrict__ part, int B, int Ci, int Co, long long N, int act,
+    int mse_target, float mse_scale, int ngrp) {
+  constexpr int R0 = 4 * OT * IT, R1 = fold_count(R0), R2 = fold_count(R1), R3 = fold_count(R2), R4 = fold_count(R3);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j4 = lane & 3, blk = lane >> 2;
+  const int per_block = (kThreads / 64) / ngrp;            // point ranges per block
+  const int o0 = (wave % ngrp) * 4 * OT;
+  const bool need_z = act || mse_target;
+  long long orow[OT], irow[IT];
+  bool olive[OT], ilive[IT];
+#pragma unroll
+  for (int T = 0; T < OT; ++T) {
+    const int o = o0 + 4 * T + j4;
+    olive[T] = o < Co;
+    orow[T] = (long long)(olive[T] ? o : Co - 1) * N;
+  }
+#pragma unroll
+  for (int T = 0; T < IT; ++T) {
+    const int i = 4 * T + j4;
+    ilive[T] = i < Ci;
+    irow[T] = (long long)(ilive[T] ? i : Ci - 1) * N;
+  }
+  v4f acc[OT][IT];
+  float gbacc[OT];
+  double sum[R4], gbsum[OT];
+#pragma unroll
+  for (int q = 0; q < R4; ++q) sum[q] = 0.0;
+#pragma unroll
+  for (int a = 0; a < OT; ++a) {
+    gbacc[a] = 0.f;
+    gbsum[a] = 0.0;
+#pragma unroll
+    for (int c = 0; c < IT; ++c) acc[a][c] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  auto flush = [&]() {
+    float v[R0];
+#pragma unroll
+    for (int a = 0; a < OT; ++a) {
+      gbsum[a] += (double)gbacc[a];
+      gbacc[a] = 0.f;
+#pragma unroll
+      for (int c = 0; c < IT; ++c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[(a * IT + c) * 4 + i] = acc[a][c][i];
+        acc[a][c] = v4f{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    fold_level<R0>(v, blk & 1, 4);
+    fold_level<R1>(v, blk & 2, 8);
+    fold_level<R2>(v, blk & 4, 16);
+    fold_level<R3>(v, blk & 8, 32);
+#pragma unroll
+    for (int q = 0; q < R4; ++q) sum[q] += (double)v[q];
+  };
+
+  const long long steps_per_b = (N + 63) >> 6;
+  const long long steps = steps_per_b * B;
+  // as above: each XCD walks a contiguous eighth of the steps
+  const long long per_x = (steps + 7) >> 3;
+  const long long xs = (long long)(blockIdx.x & 7) * per_x;
+  const long long xe = xs + per_x < steps ? xs + per_x : steps;
+  const long long wl = (long long)(blockIdx.x >> 3) * per_block + wave / ngrp;
+  const long long nwl = (long long)(gridDim.x >> 3) * per_block;
+  int chain = 0;
+  for (long long s = xs + wl; s < xe; s += nwl) {
+    const long long bb = s / steps_per_b;
+    const long long p0 = (s - bb * steps_per_b) * 64;
+    const long long p = p0 + 4 * blk;
+    const bool whole = p0 + 64 <= N;                       // the same for the whole wave
+    const long long ob = bb * Co * N, ib = bb * Ci * N;
+    v4f zq[OT], gq[OT], xq[IT];
+    if (whole) {
+#pragma unroll
+      for (int T = 0; T < OT; ++T) {
+        zq[T] = need_z ? (v4f)ld_once<STREAM>(reinterpret_cast<const v4fu*>(z + ob + orow[T] + p)) : v4f{0.f, 0.f, 0.f, 0.f};
+        gq[T] = ld_once<STREAM>(reinterpret_cast<const v4fu*>(gout + ob + orow[T] + p));
+      }
+#pragma unroll
+      for (int T = 0; T < IT; ++T) xq[T] = *reinterpret_cast<const v4fu*>(x + ib + irow[T] + p);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const long long pu = p + u < N ? p + u : N - 1;
+#pragma unroll
+        for (int T = 0; T < OT; ++T) {
+          zq[T][u] = need_z ? z[ob + orow[T] + pu] : 0.f;
+          gq[T][u] = gout[ob + orow[T] + pu];
+        }
+#pragma unroll
+        for (int T = 0; T < IT; ++T) xq[T][u] = p + u < N ? x[ib + irow[T] + pu] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int T = 0; T < OT; ++T) {
+      v4f g = gq[T];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (act) {
+          const float zv = zq[T][u];
+          if (mse_target) g[u] = mse_scale * (gelu_f(zv) - g[u]);
+          g[u] *= gelu_prime_f(zv);
+        } else if (mse_target) {
+          g[u] = mse_scale * (zq[T][u] - g[u]);
+        }
+        if (!olive[T] || (!whole && p + u >= N)) g[u] = 0.f;
+      }
+      if (gz_out != nullptr && olive[T]) {
+        float* dst = gz_out + ob + orow[T] + p;
+        if (whole) {
+          st_once<STREAM>(reinterpret_cast<v4fu*>(dst), (v4fu)g);
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (p + u < N) dst[u] = g[u];
+        }
+      }
+      gbacc[T] += (g[0] + g[1]) + (g[2] + g[3]);
+      gq[T] = g;
+    }
+#pragma unroll
+    for (int T = 0; T < IT; ++T)
+      if (!ilive[T]) xq[T] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int a = 0; a < OT; ++a)
+#pragma unroll
+        for (int c = 0; c < IT; ++c)
+          acc[a][c] = __builtin_amdgcn_mfma_f32_4x4x1f32(gq[a][u], xq[c][u], acc[a][c], 0, 0, 0);
+    if (++chain == kBwdChain) {
+      chain = 0;
+      flush();
+    }
+  }
+  flush();
+  // where this lane's sums stand in (tile row, tile column, row in the tile); lanes that share them write the same
+  const int base = (R0 % 2 == 0 && (blk & 1) ? R0 / 2 : 0) + (R1 % 2 == 0 && (blk & 2) ? R1 / 2 : 0) +
+                   (R2 % 2 == 0 && (blk & 4) ? R2 / 2 : 0) + (R3 % 2 == 0 && (blk & 8) ? R3 / 2 : 0);
+  double* dst = part + ((long long)blockIdx.x * per_block + wave / ngrp) * (Co * Ci + Co);
+#pragma unroll
+  for (int q = 0; q < R4; ++q) {
+    const int r = base + q, tile = r >> 2;
+    const int o = o0 + 4 * (tile / IT) + (r & 3), i = 4 * (tile % IT) + j4;
+    if (o < Co && i < Ci) dst[o * Ci + i] = sum[q];
+  }
+#pragma unroll
+  for (int a = 0; a < OT; ++a) {
+    double t = gbsum[a];
+    t += __shfl_xor(t, 4); t += __shfl_xor(t, 8); t += __shfl_xor(t, 16); t += __shfl_xor(t, 32);
+    if (blk == 0 && olive[a]) dst[Co * Ci + o0 + 4 * a + j4] = t;
+  }
+}
+
 // Sum over the partial slots part[slot][q] in a fixed order (same bits on every run): kRedPairs sums per block, the
 // slots dealt round-robin to kRedGroups threads per sum, whose sums are added in group order.  Returns the total in
 // group 0.  What bounds it is the latency of a thread's chain of loads, so the chain is short: 4096 slots of 420 sums
@@ -1019,6 +1204,38 @@ int bwd_pointwise_blocks(int B, int64_t N) {
   return 4096;
 }
 
+// The tiles of the wide kernel for these widths, at most max_slots point ranges of partial sums; false: the widths do
+// not fit it.  The waves of a block share out gW so that a wave's accumulators, the values of a step and the sums in
+// doubles fit 256 registers (4 x 8 tiles per wave spilled 82 of them).
+bool launch_bwd_wide(const float* z, const float* gout, const float* x, float* gz_out, double* part, int* nslots,
+                     int max_slots, int B, int Ci, int Co, int64_t N, int act, int mse_target, double mse_scale,
+                     hipStream_t s) {
+  if (Ci > 32 || Co > 32) return false;
+  const int ot = Ci <= 8 ? (Co <= 8 ? 2 : Co <= 20 ? 5 : 4) : (Ci <= 24 && Co <= 24 ? 3 : 2);
+  const int it = Ci <= 8 ? 2 : (ot == 3 ? 6 : 8);
+  const int ngrp = Co <= 4 * ot ? 1 : Co <= 8 * ot ? 2 : 4, per_block = 4 / ngrp;
+  const int64_t steps = ((N + 63) / 64) * B;
+  int64_t nb = ((steps + per_block - 1) / per_block + 7) / 8 * 8;       // a multiple of 8: the kernel's step ranges
+  if (nb > max_slots / per_block) nb = max_slots / per_block;
+  if (nb > 1024) nb = 1024;
+  *nslots = (int)nb * per_block;
+  const bool stream = (int64_t)B * Co * N * 4 >= kStreamBytes;
+#define FNO_BPX(OTV, ITV)                                                                                         \
+  do {                                                                                                            \
+    if (stream)                                                                                                   \
+      hipLaunchKernelGGL((bwd_pointwise_wide_kernel<OTV, ITV, true>), dim3((unsigned)nb), dim3(kThreads), 0, s, z, gout, \
+                         x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);      \
+    else                                                                                                          \
+      hipLaunchKernelGGL((bwd_pointwise_wide_kernel<OTV, ITV, false>), dim3((unsigned)nb), dim3(kThreads), 0, s, z, gout, \
+                         x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);      \
+  } while (0)
+  if (it == 2) { if (ot == 2) FNO_BPX(2, 2); else if (ot == 5) FNO_BPX(5, 2); else FNO_BPX(4, 2); }
+  else if (it == 6) FNO_BPX(3, 6);
+  else FNO_BPX(2, 8);
+#undef FNO_BPX
+  return true;
+}
+
 hipError_t launch_bwd_pointwise(const float* z, const float* gout, const float* x, float* gz_out,
                                 double* part, int* nslots, int B, int Ci, int Co, int64_t N, int act,
                                 int mse_target, double mse_scale, hipStream_t s) {
@@ -1048,6 +1265,9 @@ hipError_t launch_bwd_pointwise(const float* z, const float* gout, const float* 
     }
     return hipGetLastError();
   }
+  if (launch_bwd_wide(z, gout, x, gz_out, part, nslots, bwd_pointwise_blocks(B, N), B, Ci, Co, N, act, mse_target,
+                      mse_scale, s))
+    return hipGetLastError();
   const int64_t tiles = (int64_t)B * ((N + kBwdTile - 1) / kBwdTile);
   const int nblk = (int)(tiles < 2048 ? tiles : 2048);
   *nslots = nblk;
@@ -1246,12 +1466,15 @@ hipError_t launch_pointwise_linear_bwd(int B, int Ci, int Co, int64_t N, const f
   if (Co * Ci + Co > kBwdPairs * kThreads || Ci > 32) return hipErrorInvalidValue;
   if (N <= 0) return hipErrorInvalidValue;
   double* part = static_cast<double*>(ws);
-  const int64_t tiles = (int64_t)B * ((N + kBwdTile - 1) / kBwdTile);
-  const int nblk = (int)(tiles < 2048 ? tiles : 2048);
   if (gW != nullptr || gb != nullptr) {
-    const size_t lds = (size_t)(Co + Ci) * (kBwdTile + 1) * 4;
-    hipLaunchKernelGGL(bwd_pointwise_kernel, dim3((unsigned)nblk), dim3(kThreads), lds, s, g, g, x,
-                       (float*)nullptr, part, B, Ci, Co, (long long)N, 0, 0, 0.f);
+    int nblk = 0;
+    if (!launch_bwd_wide(g, g, x, nullptr, part, &nblk, 2048, B, Ci, Co, N, 0, 0, 0.0, s)) {
+      const int64_t tiles = (int64_t)B * ((N + kBwdTile - 1) / kBwdTile);
+      nblk = (int)(tiles < 2048 ? tiles : 2048);
+      const size_t lds = (size_t)(Co + Ci) * (kBwdTile + 1) * 4;
+      hipLaunchKernelGGL(bwd_pointwise_kernel, dim3((unsigned)nblk), dim3(kThreads), lds, s, g, g, x,
+                         (float*)nullptr, part, B, Ci, Co, (long long)N, 0, 0, 0.f);
+    }
     hipLaunchKernelGGL(reduce_partials_kernel, dim3((Co * Ci + Co + kRedPairs - 1) / kRedPairs),
                        dim3(kRedPairs * kRedGroups), 0, s, part, nblk, Co, Ci, gW, gb, 0);
   }

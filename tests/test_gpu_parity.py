@@ -827,3 +827,38 @@ def test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule):
     torch.cuda.synchronize()
     assert np.isnan(host(out2[0])).all()
     assert np.array_equal(host(out2[1]), out[0])
+
+
+@pytest.mark.parametrize("c_in, c_out, npts, batch", [
+    (1, 1, 3, 1), (8, 8, 64, 2), (5, 20, 65, 2), (8, 32, 127, 1), (9, 12, 66, 3), (24, 24, 193, 1), (7, 25, 640, 2),
+    (25, 8, 130, 1), (26, 16, 129, 2), (32, 32, 1001, 1), (32, 17, 64, 1),
+    (5, 8, 64 * (2048 * 32 + 700) + 13, 1),      # more than one fp32 chain per wave, ragged end
+])
+def test_sums_over_points_of_every_tile_shape(c_in, c_out, npts, batch):
+    """gW = sum g x^T and gb = sum g (the adjoint of a pointwise linear map) at the edges of the kernel's channel
+    tiles and point steps, on tensors that are only 4-byte aligned where a row's length makes them so."""
+    gen = torch.Generator(device="cuda").manual_seed(c_in * 1000 + c_out)
+    x = torch.randn((batch, c_in, npts), device="cuda", generator=gen)
+    g = torch.randn((batch, c_out, npts), device="cuda", generator=gen) + 0.1
+    w = torch.randn((c_out, c_in), device="cuda", generator=gen)
+    gW, gb = torch.empty_like(w), torch.empty(c_out, device="cuda")
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(c_in, 0, c_out) // 4 + 2, device="cuda")
+    B.fno_pointwise_linear_bwd(batch, c_in, c_out, npts, x, w, g, None, gW, gb, ws)
+    torch.cuda.synchronize()
+    xd, gd = x.cpu().double().numpy(), g.cpu().double().numpy()
+    want = sum(gd[k] @ xd[k].T for k in range(batch))
+    # fp32 chains of at most 128 terms (then doubles): an entry is off by a few 2^-24 of its terms' root sum square
+    scale = np.sqrt(sum((gd[k] ** 2) @ (xd[k] ** 2).T for k in range(batch)))
+    assert np.max(np.abs(host(gW) - want) / np.maximum(scale, np.abs(want))) <= TOL
+    assert rel(host(gb), gd.sum(axis=(0, 2))) <= TOL
+
+
+@pytest.mark.parametrize("case", [
+    (1, 32, 32, (3, 2, 32, 16), (1, 1, 4, 4), 0),      # width 32, 48 whole steps
+    (2, 20, 20, (3, 3, 12, 7), (1, 1, 3, 3), 0),       # width 20, 756 points: a ragged last step
+    (1, 28, 28, (3, 5, 6, 7), (1, 2, 2, 3), 0),        # a padded channel tile, rows that are not 16-byte aligned
+    (1, 13, 13, (3, 3, 9, 5), (1, 1, 2, 2), 0),        # odd width
+])
+def test_block_adjoint_for_widths_and_point_counts_off_the_tiles(case):
+    for activation in (B.FNO_ACT_GELU, B.FNO_ACT_IDENTITY):
+        test_block_fwd_and_bwd_match_oracle(case, activation)
