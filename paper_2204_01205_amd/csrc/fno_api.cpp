@@ -31,6 +31,7 @@ struct Plan {
   int64_t Npts;          // grid points per (batch, channel)
   // workspace offsets in bytes
   bool folded;           // the folded z table is there
+  bool ax_folded[2];     // x, y as folded products: off_tw holds the folded table
   size_t off_ztab, off_twt, off_tw[3], off_twf[2], off_fold, off_a1, off_a2, off_s1, off_s2, off_s3, off_gz, off_part, total;
   int part_blocks;
 };
@@ -115,10 +116,17 @@ int make_plan(const fno_desc* d, bool need_block, bool need_bwd_block, Plan* p) 
   size_t off = 0;
   p->off_ztab = off; off = align_up(off + fno::kZtTablesBytes);
   p->off_twt = off; off = align_up(off + (size_t)p->mt * p->Nt * 8);
-  for (int a = 0; a < 3; ++a) { p->off_tw[a] = off; off = align_up(off + (size_t)p->ax[a].L * p->ax[a].P * 8); }
+  const int64_t inner_y = (int64_t)p->L[2] * p->mt, planes = (int64_t)p->B * Cm;
+  p->ax_folded[0] = fno::axis_fold_fits(p->ax[0], planes, inner_y * p->L[1]);
+  p->ax_folded[1] = fno::axis_fold_fits(p->ax[1], planes * p->N[0], inner_y);
+  for (int a = 0; a < 3; ++a) {
+    p->off_tw[a] = off;
+    off = align_up(off + (a < 2 && p->ax_folded[a] ? fno::fold_plan(p->ax[a]).floats * 4
+                                                   : (size_t)p->ax[a].L * p->ax[a].P * 8));
+  }
   for (int a = 0; a < 2; ++a) {
     p->off_twf[a] = p->off_tw[a];
-    if (p->axf[a].P != p->ax[a].P) { p->off_twf[a] = off; off = align_up(off + (size_t)p->axf[a].L * p->axf[a].P * 8); }
+    if (!p->ax_folded[a] && p->axf[a].P != p->ax[a].P) { p->off_twf[a] = off; off = align_up(off + (size_t)p->axf[a].L * p->axf[a].P * 8); }
   }
   p->folded = fno::tz_fwd_fold_fits(p->ax[2], p->Nt, p->mt);
   p->off_fold = off;
@@ -208,8 +216,14 @@ int build_tables(const Plan& p, void* ws, hipStream_t s, bool tables_ready = fal
   if (tables_ready) return FNO_OK;
   fno::TableSet ts{};
   ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_twt), p.Nt, 0, p.mt, 1};
-  for (int a = 0; a < 3; ++a)
-    ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_tw[a]), p.ax[a].N, p.ax[a].L, p.ax[a].npos, p.ax[a].P};
+  for (int a = 0; a < 3; ++a) {
+    if (a < 2 && p.ax_folded[a]) {
+      const fno::FoldPlan f = fno::fold_plan(p.ax[a]);
+      ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_tw[a]), p.ax[a].N, -f.rows, 0, f.stride};
+    } else {
+      ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_tw[a]), p.ax[a].N, p.ax[a].L, p.ax[a].npos, p.ax[a].P};
+    }
+  }
   for (int a = 0; a < 2; ++a)
     if (p.off_twf[a] != p.off_tw[a])
       ts.t[ts.n++] = fno::TableDesc{at<float2>(ws, p.off_twf[a]), p.axf[a].N, p.axf[a].L, p.axf[a].npos, p.axf[a].P};
@@ -221,6 +235,18 @@ int build_tables(const Plan& p, void* ws, hipStream_t s, bool tables_ready = fal
   return FNO_OK;
 }
 
+// x (a = 0) or y stage on the kernels that the plan laid the tables out for
+hipError_t axis_fwd(const Plan& p, void* ws, int a, const float2* in, float2* out, int64_t outer, int64_t inner,
+                    hipStream_t s) {
+  if (p.ax_folded[a]) return fno::launch_axis_fwd_fold(in, out, at<float>(ws, p.off_tw[a]), outer, p.ax[a], inner, s);
+  return fno::launch_axis_fwd(in, out, at<float2>(ws, p.off_twf[a]), outer, p.axf[a], inner, s);
+}
+hipError_t axis_inv(const Plan& p, void* ws, int a, const float2* in, float2* out, int64_t outer, int64_t inner,
+                    hipStream_t s) {
+  if (p.ax_folded[a]) return fno::launch_axis_inv_fold(in, out, at<float>(ws, p.off_tw[a]), outer, p.ax[a], inner, s);
+  return fno::launch_axis_inv(in, out, at<float2>(ws, p.off_tw[a]), outer, p.ax[a], inner, s);
+}
+
 // real field [B*C][grid] -> kept spectrum [B*C][K]
 int forward_chain(const Plan& p, void* ws, const float* field, int C, float2* spec, hipStream_t s) {
   const int64_t bc = (int64_t)p.B * C;
@@ -229,9 +255,9 @@ int forward_chain(const Plan& p, void* ws, const float* field, int C, float2* sp
   FNO_STAGE(FNO_STAGE_TZ_FWD, s, fno::launch_tz_fwd(field, a1, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]),
                              p.folded ? at<float>(ws, p.off_fold) : nullptr, bc * p.N[0] * p.N[1], p.ax[2], p.Nt, p.mt, s));
   const int64_t in_y = (int64_t)p.L[2] * p.mt;
-  FNO_STAGE(FNO_STAGE_Y_FWD, s, fno::launch_axis_fwd(a1, a2, at<float2>(ws, p.off_twf[1]), bc * p.N[0], p.axf[1], in_y, s));
+  FNO_STAGE(FNO_STAGE_Y_FWD, s, axis_fwd(p, ws, 1, a1, a2, bc * p.N[0], in_y, s));
   const int64_t in_x = in_y * p.L[1];
-  FNO_STAGE(FNO_STAGE_X_FWD, s, fno::launch_axis_fwd(a2, spec, at<float2>(ws, p.off_twf[0]), bc, p.axf[0], in_x, s));
+  FNO_STAGE(FNO_STAGE_X_FWD, s, axis_fwd(p, ws, 0, a2, spec, bc, in_x, s));
   return FNO_OK;
 }
 
@@ -243,8 +269,8 @@ int inverse_chain(const Plan& p, void* ws, const float2* spec, int C, float* out
   float2* a2 = at<float2>(ws, p.off_a2);
   const int64_t in_y = (int64_t)p.L[2] * p.mt;
   const int64_t in_x = in_y * p.L[1];
-  FNO_STAGE(FNO_STAGE_X_INV, s, fno::launch_axis_inv(spec, a2, at<float2>(ws, p.off_tw[0]), bc, p.ax[0], in_x, s));
-  FNO_STAGE(FNO_STAGE_Y_INV, s, fno::launch_axis_inv(a2, a1, at<float2>(ws, p.off_tw[1]), bc * p.N[0], p.ax[1], in_y, s));
+  FNO_STAGE(FNO_STAGE_X_INV, s, axis_inv(p, ws, 0, spec, a2, bc, in_x, s));
+  FNO_STAGE(FNO_STAGE_Y_INV, s, axis_inv(p, ws, 1, a2, a1, bc * p.N[0], in_y, s));
   FNO_STAGE(FNO_STAGE_ZT_INV, s, fno::launch_zt_inv(a1, out, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]),
                              p.folded ? at<float>(ws, p.off_fold) : nullptr, p.B, C,
                              p.N[0], p.N[1], p.ax[2], p.Nt, p.mt, ep, at<float>(ws, p.off_ztab), s));

@@ -21,9 +21,9 @@ struct AxisPlan {
 // w_N^(k_j n2); t table: L = 0, [npos][N] entries w_N^(kt n); folded table: L = -rows, P = stride
 // (see FoldPlan).
 struct TableDesc { float2* tw; int N, L, npos, P; };
-struct TableSet { TableDesc t[8]; int n; };
+struct TableSet { TableDesc t[10]; int n; };
 
-// z table of the folded product (fno_tz_fwd_fold.hip), for the frequencies k = 0 .. kmax of an axis of
+// Table of the folded products (fno_tz_fwd_fold.hip, fno_zt_inv_fold.hip, fno_axis_fold.hip), for the frequencies k = 0 .. kmax of an axis of
 // length N and its pairs of rows n, N - 1 - n (nu = n + 1/2): cos(2 pi k nu / N) [rows][stride], halved
 // where a row is its own pair, then sin(2 pi k nu / N) [rows][stride], then exp(i pi k / N) [rows].
 struct FoldPlan {
@@ -50,6 +50,12 @@ hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int6
                            AxisPlan ax, int64_t inner, hipStream_t s);
 hipError_t launch_axis_inv(const float2* in, float2* out, const float2* tw, int64_t outer,
                            AxisPlan ax, int64_t inner, hipStream_t s);
+// The same as folded matrix products (fno_axis_fold.hip); tab: the folded table of the axis.
+bool axis_fold_fits(AxisPlan ax, int64_t outer, int64_t inner);
+hipError_t launch_axis_fwd_fold(const float2* in, float2* out, const float* tab, int64_t outer, AxisPlan ax,
+                                int64_t inner, hipStream_t s);
+hipError_t launch_axis_inv_fold(const float2* in, float2* out, const float* tab, int64_t outer, AxisPlan ax,
+                                int64_t inner, hipStream_t s);
 
 // Per-mode channel mix.  scale_t[kt] = c_kt / N is applied to the result.
 hipError_t launch_mix_fwd(const float2* xh, const float2* R, float2* yh, int B, int Ci, int Co,

@@ -862,3 +862,18 @@ def test_sums_over_points_of_every_tile_shape(c_in, c_out, npts, batch):
 def test_block_adjoint_for_widths_and_point_counts_off_the_tiles(case):
     for activation in (B.FNO_ACT_GELU, B.FNO_ACT_IDENTITY):
         test_block_fwd_and_bwd_match_oracle(case, activation)
+
+
+@pytest.mark.parametrize("case", [
+    # x and y axes at the edges of the folded products' tiles: 1, 8, 16, 17, 33 and 48 folded frequencies
+    (1, 2, 3, (45, 118, 4, 5), (7, 16, 1, 2), 0),      # odd length; 2 x 59 with 17 folded frequencies
+    (1, 2, 2, (31, 33, 3, 4), (15, 16, 1, 1), 1),      # every frequency kept, symmetric rule: 16 and 17, inner of 3
+    (1, 1, 1, (106, 94, 2, 3), (47, 32, 1, 2), 0),     # 48 and 33 folded frequencies
+    (2, 2, 2, (64, 32, 4, 8), (12, 15, 2, 3), 0),      # short powers of two
+    (1, 1, 2, (2, 66, 4, 4), (1, 33, 1, 2), 0),        # two points; every frequency of an even length
+    (1, 1, 1, (1, 7, 4, 4), (0, 0, 1, 2), 1),          # one point; one frequency
+    (3, 4, 2, (96, 72, 9, 6), (9, 10, 2, 3), 0),       # the FFT kernels on x, folded on y; two tiles per wave
+])
+def test_folded_axis_products_match_oracle(case):
+    test_spectral_conv_fwd_matches_oracle(case)
+    test_spectral_conv_bwd_matches_oracle(case)
