@@ -25,7 +25,8 @@ struct TableSet { TableDesc t[10]; int n; };
 
 // Table of the folded products (fno_tz_fwd_fold.hip, fno_zt_inv_fold.hip, fno_axis_fold.hip), for the frequencies k = 0 .. kmax of an axis of
 // length N and its pairs of rows n, N - 1 - n (nu = n + 1/2): cos(2 pi k nu / N) [rows][stride], halved
-// where a row is its own pair, then sin(2 pi k nu / N) [rows][stride], then exp(i pi k / N) [rows].
+// where a row is its own pair, then sin(2 pi k nu / N) [rows][stride], then exp(i pi k / N) [rows], a pair of doubles
+// each.
 struct FoldPlan {
   int rows;        // kmax + 1, padded to whole row tiles
   int pairs;       // ceil(N / 2)

@@ -50,7 +50,7 @@ __global__ void plan_tables_kernel(TableSet ts) {
       if (2 * n + 1 == t.N && !phase) c *= 0.5;
     }
     if (phase) {
-      reinterpret_cast<float2*>(f + 2 * rows * stride)[k] = make_float2(float(c), float(s));
+      reinterpret_cast<double2*>(f + 2 * rows * stride)[k] = make_double2(c, s);
     } else {
       f[idx] = float(c);
       f[rows * stride + idx] = float(s);

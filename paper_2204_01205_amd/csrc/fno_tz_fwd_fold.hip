@@ -97,7 +97,10 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
     }
   }
   float2* ROT = reinterpret_cast<float2*>(SIN + 16 * MT * stride);      // [16 MT]
-  if (tid < 16 * MT) ROT[tid] = reinterpret_cast<const float2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
+  if (tid < 16 * MT) {
+    const double2 w = reinterpret_cast<const double2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
+    ROT[tid] = make_float2((float)w.x, (float)w.y);
+  }
   const int r = Nt - 16 * J;
   const int t0 = min(W * g, r - W);             // start of this lane group's tail
   float tb[CT][KS];                             // t table, the right operand of every K step
@@ -243,7 +246,7 @@ FoldPlan fold_plan(AxisPlan az) {
   f.rows = kmax + 1 <= 16 ? 16 : (kmax + 1 + 31) / 32 * 32;    // whole groups of the kernel's row tiles
   f.pairs = (az.N + 1) / 2;
   f.stride = (f.pairs + 15) / 16 * 16 + 4;      // 4 floats beside whole tiles: rows spread over the LDS banks
-  f.floats = (size_t)2 * f.rows * f.stride + 2 * f.rows;
+  f.floats = (size_t)2 * f.rows * f.stride + 4 * f.rows;
   return f;
 }
 

@@ -341,14 +341,14 @@ __global__ __launch_bounds__(kThreads, fold_inv_waves(W, CI)) void zt_inv_fold_k
   {
     const float2* src = a + ((b * f.Co + o0) * f.NxNy + xy) * (long long)(f.Lz * f.mt);
     const long long ostride = (long long)f.NxNy * f.Lz * f.mt;
-    const float2* rot = reinterpret_cast<const float2*>(ztab + (long long)2 * f.mrows * f.stride);
+    const double2* rot = reinterpret_cast<const double2*>(ztab + (long long)2 * f.mrows * f.stride);
     const int R1 = f.K1 * 16, real = 2 * f.mt - 1;
     for (int i0 = 0; i0 < f.K1 * f.mt; i0 += 64) {
       const int idx = min(i0 + lane, f.K1 * f.mt - 1);         // lanes past the end repeat the last entry
       const int k = f.mt > 1 ? (int)__umulhi((unsigned)idx, f.inv_mt) : idx, kt = idx - k * f.mt;
       const bool has_p = k < f.npos, has_q = k >= 1 && k <= f.Lz - f.npos;
       const int off_p = has_p ? idx : 0, off_q = has_q ? (f.Lz - k) * f.mt + kt : 0;
-      const float2 w = rot[k];
+      const float2 w = make_float2((float)rot[k].x, (float)rot[k].y);
       // bin 0 has no imaginary part: its place takes the first padding column
       const int c_re = kt == 0 ? 0 : 2 * kt - 1, c_im = kt == 0 ? real : 2 * kt;
       float2* d_re = EO + (c_re >> 2) * R1 + 16 * k + 4 * (c_re & 3);
