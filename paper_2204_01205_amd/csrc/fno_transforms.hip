@@ -858,7 +858,8 @@ hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const f
 #undef FNO_TZF_S
     return hipGetLastError();
   }
-  if (ztab != nullptr && tz_fwd_fold_fits(az, Nt, mt)) return launch_tz_fwd_fold(x, out, twt, ztab, planes, az, Nt, mt, s);
+  if (ztab != nullptr && tz_fwd_fold_fits(az, Nt, mt) && tz_fwd_fold_pays(az, Nt))
+    return launch_tz_fwd_fold(x, out, twt, ztab, planes, az, Nt, mt, s);
   int ppb = 1;
   // enough rows to occupy the block, within an LDS share that keeps several blocks per CU
   while (ppb * 2 * az.N <= 2 * kThreads && tz_fwd_lds(az, Nt, mt, ppb * 2) <= (size_t)(32 * 1024)) ppb *= 2;

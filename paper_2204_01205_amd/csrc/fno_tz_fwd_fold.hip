@@ -19,11 +19,14 @@
 // tile of the plane passes through LDS, no wave waits for another; LDS holds only the z table, which
 // a block's waves share over all planes they walk.
 //
+// The sums stay in fp32 but in short chains: two over t, blocks of eight pairs over z that are added up as they come,
+// and the turn by the phase is in double.  One chain of Nz / 2 terms was off by up to 1.7 times what the FFT over z
+// that these kernels replaced is off by (128 x 20: 1.18e-7 with the FFT, 1.75e-7 in one chain, 1.07e-7 now).
+//
 // What bounds it: the matrix cores at 32 cycles per instruction (a 263 x 16 plane with 49 frequencies and
 // 8 bins: 9 tiles of 8 + 16 instructions) next to one read of the field.  Measured against the kernels it
-// replaced (mixed-radix and dense complex sums on tiles staged in LDS): 263 x 16 planes, 2.7 GB read,
-// 2.20 -> 0.78 ms; 64 x 20, 0.42 GB, 0.25 -> 0.12 ms; 40 x 24, 0.28 GB, 0.16 -> 0.09 ms; 8 x 35, 0.18 GB,
-// 0.21 ms with one plane per tile -> 0.09 ms with four.
+// replaced (mixed-radix and dense complex sums on tiles staged in LDS), us on 1536 columns: 64 x 20, 20 channels, 93 -> 53;
+// 128 x 24 202 -> 179; 80 x 40 375 -> 145; 263 x 16, 6 channels, 293 -> 102; two entries of 8 x 40 113 -> 44.
 #include "fno_device.h"
 
 namespace fno {
@@ -59,7 +62,7 @@ __device__ __forceinline__ float swap_pair(float v) {      // the value of lane 
 // registers of a variant (two row tiles in flight and folded, the t table, the accumulators, the z
 // table's operands and the addresses), and the waves per SIMD they allow
 constexpr int fold_regs(int KS, int CT, int MT, int PP) {
-  return KS * (4 + CT) + 8 * MT * CT * PP + (CT == 2 ? 16 : 6) * MT + 32;
+  return KS * (4 + CT) + 8 * MT * CT * PP + (CT == 2 ? 16 : 6) * MT + 48;
 }
 constexpr int fold_waves(int KS, int CT, int MT, int PP) {
   const int regs = fold_regs(KS, CT, MT, PP);
@@ -96,11 +99,8 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
       reinterpret_cast<float4*>(SIN)[i] = sn[i];
     }
   }
-  float2* ROT = reinterpret_cast<float2*>(SIN + 16 * MT * stride);      // [16 MT]
-  if (tid < 16 * MT) {
-    const double2 w = reinterpret_cast<const double2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
-    ROT[tid] = make_float2((float)w.x, (float)w.y);
-  }
+  double2* ROT = reinterpret_cast<double2*>(SIN + 16 * MT * stride);    // [16 MT]
+  if (tid < 16 * MT) ROT[tid] = reinterpret_cast<const double2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
   const int r = Nt - 16 * J;
   const int t0 = min(W * g, r - W);             // start of this lane group's tail
   float tb[CT][KS];                             // t table, the right operand of every K step
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
       tb[ct][s] = v;
     }
   }
-  const float sgn = (c & 1) ? -1.f : 1.f;
+  const double sgn = (c & 1) ? -1.0 : 1.0;
   __syncthreads();
 
   // each XCD walks a contiguous eighth of the planes, its waves interleaved inside it
@@ -185,21 +185,42 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
       }
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        v4f dE = {0.f, 0.f, 0.f, 0.f}, dO = {0.f, 0.f, 0.f, 0.f};
+        const v4f zero = {0.f, 0.f, 0.f, 0.f};
+        v4f dE = zero, dO = zero, dE1 = zero, dO1 = zero;        // two chains each: even and odd steps
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-          dE = __builtin_amdgcn_mfma_f32_16x16x4f32(e[s], tb[ct][s], dE, 0, 0, 0);
-          dO = __builtin_amdgcn_mfma_f32_16x16x4f32(o[s], tb[ct][s], dO, 0, 0, 0);
+          v4f& E = s & 1 ? dE1 : dE;
+          v4f& O = s & 1 ? dO1 : dO;
+          E = __builtin_amdgcn_mfma_f32_16x16x4f32(e[s], tb[ct][s], E, 0, 0, 0);
+          O = __builtin_amdgcn_mfma_f32_16x16x4f32(o[s], tb[ct][s], O, 0, 0, 0);
         }
+        if constexpr (KS > 1) { dE += dE1; dO += dO1; }
+        if constexpr (PP > 1) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+          for (int v = 0; v < 4; ++v) {
+            v4f& C = accC[v / VP][0][ct];
+            v4f& S = accS[v / VP][0][ct];
+            C = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[0][v % VP], dE[v], C, 0, 0, 0);
+            S = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[0][v % VP], dO[v], S, 0, 0, 0);
+          }
+        } else {
 #pragma unroll
           for (int m = 0; m < MT; ++m) {
-            v4f& C = accC[v / VP][m][ct];
-            v4f& S = accS[v / VP][m][ct];
-            C = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[m][v % VP], dE[v], C, 0, 0, 0);
-            S = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[m][v % VP], dO[v], S, 0, 0, 0);
+            v4f pc[2], ps[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              pc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[m][2 * h], dE[2 * h], zero, 0, 0, 0);
+              ps[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[m][2 * h], dO[2 * h], zero, 0, 0, 0);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              pc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[m][2 * h + 1], dE[2 * h + 1], pc[h], 0, 0, 0);
+              ps[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[m][2 * h + 1], dO[2 * h + 1], ps[h], 0, 0, 0);
+            }
+            accC[0][m][ct] += pc[0] + pc[1];
+            accS[0][m][ct] += ps[0] + ps[1];
           }
+        }
       }
     }
     // X[+-k] from C, S: real and imaginary parts sit in neighbouring lanes
@@ -215,18 +236,19 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int kl = 16 * m + g4 + v, k = m0 + kl;
-          const float2 w = ROT[kl];
-          const float ws = sgn * w.y;
+          const double2 w = ROT[kl];
+          const double ws = sgn * w.y;
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct) {
             const int col = c0 + 16 * ct + c;
-            const float sp = sgn * swap_pair(accS[q][m][ct][v]);
-            const float xp = accC[q][m][ct][v] + sp, xm = accC[q][m][ct][v] - sp;
-            const float yp = fmaf(-ws, swap_pair(xp), xp * w.x);
-            const float ym = fmaf(ws, swap_pair(xm), xm * w.x);
+            const float fc = accC[q][m][ct][v], fs = accS[q][m][ct][v];
+            const double C = fc, is = sgn * swap_pair(fs);       // this part of C and -i S, and the other part
+            const double D = swap_pair(fc), it = sgn * fs;
+            const double yp = fma(C + is, w.x, -ws * (D - it));
+            const double ym = fma(C - is, w.x, ws * (D + it));
             if (col < 2 * mt) {
-              if (k < npos) dst[k * mt * 2 + col] = yp;
-              if (k >= 1 && k <= Lz - npos) dst[(Lz - k) * mt * 2 + col] = ym;
+              if (k < npos) dst[k * mt * 2 + col] = (float)yp;
+              if (k >= 1 && k <= Lz - npos) dst[(Lz - k) * mt * 2 + col] = (float)ym;
             }
           }
         }
@@ -236,7 +258,7 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
 
 constexpr size_t kFoldLds = 78 * 1024;      // two blocks per CU
 
-size_t fold_lds(const FoldPlan& f, int MT) { return (size_t)(2 * 16 * MT * f.stride + 2 * 16 * MT) * 4; }
+size_t fold_lds(const FoldPlan& f, int MT) { return (size_t)(2 * 16 * MT * f.stride + 4 * 16 * MT) * 4; }
 
 }  // namespace
 
@@ -248,6 +270,15 @@ FoldPlan fold_plan(AxisPlan az) {
   f.stride = (f.pairs + 15) / 16 * 16 + 4;      // 4 floats beside whole tiles: rows spread over the LDS banks
   f.floats = (size_t)2 * f.rows * f.stride + 4 * f.rows;
   return f;
+}
+
+// Short rows of a z axis with a power of two in its length: a wave has few bytes to ask for per load and mostly empty K
+// steps, and the mixed-radix kernel is as fast or faster.  us on 4096 columns of 8 channels, that kernel against this
+// one: z of 24 (two entries), t of 5, 8, 12, 14: 19, 27, 35, 49 and 40, 40, 45, 49; z of 48, t of 5, 9, 12: 19, 30, 43
+// and 32, 36, 38; z of 72, t of 7, 8, 12: 33, 40, 55 and 42, 43, 50; z of 120, t of 5, 9, 12: 51, 82, 101 and 78, 84, 85.
+bool tz_fwd_fold_pays(AxisPlan az, int Nt) {
+  if (az.M < 4) return true;
+  return !(Nt <= 7 || (Nt <= 9 && (az.N <= 48 || az.N > 96)) || (Nt <= 12 && az.N <= 24));
 }
 
 // Nt up to 64 in registers; one or two row tiles of frequencies and column tiles of bins per block
