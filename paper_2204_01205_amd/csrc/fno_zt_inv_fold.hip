@@ -16,6 +16,11 @@
 // v_mfma_f32_4x4x1 with W[4T+i][.] as the left and a lane's own point as the right operand leaves four output
 // channels of that point in the lane.
 //
+// Rounding: E and O are folded and turned in double, once per column; the sums over k run from the highest frequency
+// down, in four chains where no u is held (a convolution; the channel-linear term outweighs them in a block).  With an
+// fp32 phase and one chain a 128 x 20 plane was off by 1.31e-7, against 1.06e-7 for the FFT over z that these kernels
+// replaced and 1.10e-7 now, at 1 % more time; after all axes a convolution is no further off than it was with the FFTs.
+//
 // One wave works a tile of 16 row pairs x 4 W points of t for all output channels, its u values in registers.
 // LDS holds E and O of the block's columns, folded once per column by the waves that share it, and per wave the
 // cos / sin entries of its row pairs.  After the fold no wave waits for another.  A last tile of at most eight
@@ -138,40 +143,57 @@ __device__ __forceinline__ void fold_inv_load_u(const int (&voff)[NU], const cha
   }
 }
 
-// C and S of NR tiles of columns (stride R1 float2 apart): the operands of the next K step are read while this
-// one's products run.  last: the lane's entry of the last K step, which may reach past the folded frequencies
-// (its lanes there read the last one again, against zeros in ZT).
-template <int NR>
+// C and S of NR tiles of columns (stride R1 float2 apart), each in CH chains: the operands of the next K step are read
+// while this one's products run.  From the highest frequencies down, so that the large low ones join the sums last.
+// last: the lane's entry of the last K step, which may reach past the folded frequencies (its lanes there read the last
+// one again, against zeros in ZT).
+template <int NR, int CH>
 __device__ __forceinline__ void fold_inv_z(const float2* eo, int R1, const float2* zt, int ks, int last, v4f (&C)[NR],
                                            v4f (&S)[NR]) {
   const int lane = threadIdx.x & 63;
-  float2 e[NR], z = zt[lane];
+  v4f c[CH][NR], s[CH][NR];
+  float2 e[NR], z = zt[64 * (ks - 1) + lane];
 #pragma unroll
   for (int h = 0; h < NR; ++h) {
-    e[h] = eo[h * R1 + (ks > 1 ? lane : last)];
-    C[h] = v4f{0.f, 0.f, 0.f, 0.f};
-    S[h] = v4f{0.f, 0.f, 0.f, 0.f};
+    e[h] = eo[h * R1 + last];
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) c[ch][h] = s[ch][h] = v4f{0.f, 0.f, 0.f, 0.f};
   }
-#pragma unroll 2
-  for (int s = 1; s < ks; ++s) {
-    const int at = s + 1 < ks ? 64 * s + lane : last;
+  auto step = [&](v4f (&cc)[NR], v4f (&ss)[NR], int k) {
+    const int at = 64 * max(k - 1, 0) + lane;
+    const float2 zn = zt[at];
     float2 en[NR];
-    const float2 zn = zt[64 * s + lane];
 #pragma unroll
     for (int h = 0; h < NR; ++h) en[h] = eo[h * R1 + at];
 #pragma unroll
     for (int h = 0; h < NR; ++h) {
-      C[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].x, z.x, C[h], 0, 0, 0);
-      S[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].y, z.y, S[h], 0, 0, 0);
+      cc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].x, z.x, cc[h], 0, 0, 0);
+      ss[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].y, z.y, ss[h], 0, 0, 0);
     }
     z = zn;
 #pragma unroll
     for (int h = 0; h < NR; ++h) e[h] = en[h];
+  };
+  int k = ks - 1;
+  if constexpr (CH == 1) {
+#pragma unroll 2
+    for (; k > 0; --k) step(c[0], s[0], k);
+  } else {
+    for (; k >= CH; k -= CH)
+#pragma unroll
+      for (int ch = 0; ch < CH; ++ch) step(c[ch], s[ch], k - ch);
+#pragma unroll
+    for (int ch = 0; ch + 1 < CH; ++ch)
+      if (k > 0) step(c[ch], s[ch], k--);
   }
 #pragma unroll
-  for (int h = 0; h < NR; ++h) {
-    C[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].x, z.x, C[h], 0, 0, 0);
-    S[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].y, z.y, S[h], 0, 0, 0);
+  for (int h = 0; h < NR; ++h) {                 // the lowest frequencies: nothing left to read
+    c[CH - 1][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].x, z.x, c[CH - 1][h], 0, 0, 0);
+    s[CH - 1][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[h].y, z.y, s[CH - 1][h], 0, 0, 0);
+    C[h] = c[0][h];
+    S[h] = s[0][h];
+#pragma unroll
+    for (int ch = 1; ch < CH; ++ch) { C[h] += c[ch][h]; S[h] += s[ch][h]; }
   }
 }
 
@@ -228,19 +250,23 @@ __device__ __forceinline__ void fold_inv_tile(const FoldInv& f, const EpiArgs& e
 #pragma unroll
       for (int s = 0; s < NS; ++s) d2[v][s] = v4f{0.f, 0.f, 0.f, 0.f};
     const float2* eot = EO + T * f.R * R1;
-    int r = 0;
-    for (; r + 2 <= f.R; r += 2) {
-      v4f C[2], S[2];
-      const float tb0 = tbp[64 * r], tb1 = tbp[64 * r + 64];
-      fold_inv_z<2>(eot + r * R1, R1, ZT, f.ks, last, C, S);
-      fold_inv_t<NS>(tb0, C[0], S[0], both, d2);
-      fold_inv_t<NS>(tb1, C[1], S[1], both, d2);
+    int r = f.R;                                 // from the highest bins of t down
+    if (CI == 0 || (r & 1)) {
+      for (; r > (CI == 0 ? 0 : f.R - 1); --r) {
+        v4f C[1], S[1];
+        const float tb = tbp[64 * (r - 1)];
+        fold_inv_z<1, CI == 0 ? 4 : 1>(eot + (r - 1) * R1, R1, ZT, f.ks, last, C, S);
+        fold_inv_t<NS>(tb, C[0], S[0], both, d2);
+      }
     }
-    if (r < f.R) {
-      v4f C[1], S[1];
-      const float tb = tbp[64 * r];
-      fold_inv_z<1>(eot + r * R1, R1, ZT, f.ks, last, C, S);
-      fold_inv_t<NS>(tb, C[0], S[0], both, d2);
+    if constexpr (CI > 0) {
+      for (; r >= 2; r -= 2) {
+        v4f C[2], S[2];
+        const float tb0 = tbp[64 * (r - 2)], tb1 = tbp[64 * (r - 1)];
+        fold_inv_z<2, 1>(eot + (r - 2) * R1, R1, ZT, f.ks, last, C, S);
+        fold_inv_t<NS>(tb1, C[1], S[1], both, d2);
+        fold_inv_t<NS>(tb0, C[0], S[0], both, d2);
+      }
     }
     // four channels of a point side by side, the bias, and the channel-linear term on top
     const float4 bias = BL[T];
@@ -348,7 +374,7 @@ __global__ __launch_bounds__(kThreads, fold_inv_waves(W, CI)) void zt_inv_fold_k
       const int k = f.mt > 1 ? (int)__umulhi((unsigned)idx, f.inv_mt) : idx, kt = idx - k * f.mt;
       const bool has_p = k < f.npos, has_q = k >= 1 && k <= f.Lz - f.npos;
       const int off_p = has_p ? idx : 0, off_q = has_q ? (f.Lz - k) * f.mt + kt : 0;
-      const float2 w = make_float2((float)rot[k].x, (float)rot[k].y);
+      const double2 w = rot[k];
       // bin 0 has no imaginary part: its place takes the first padding column
       const int c_re = kt == 0 ? 0 : 2 * kt - 1, c_im = kt == 0 ? real : 2 * kt;
       float2* d_re = EO + (c_re >> 2) * R1 + 16 * k + 4 * (c_re & 3);
@@ -366,11 +392,12 @@ __global__ __launch_bounds__(kThreads, fold_inv_waves(W, CI)) void zt_inv_fold_k
 #pragma unroll
         for (int h = 0; h < UB; ++h) {
           const bool in = o0 + c0 + h < f.Co, ip = in && has_p, iq = in && has_q;
-          const float px = ip ? p[h].x : 0.f, py = ip ? p[h].y : 0.f, qx = iq ? q[h].x : 0.f, qy = iq ? q[h].y : 0.f;
-          const float sx = px + qx, dx = px - qx, sy = py + qy, dy = py - qy;
-          float2 im = make_float2(fmaf(-w.y, dx, w.x * sy), fmaf(w.y, sy, w.x * dx));
+          // folded and turned in double: one rounding each
+          const double px = ip ? p[h].x : 0.f, py = ip ? p[h].y : 0.f, qx = iq ? q[h].x : 0.f, qy = iq ? q[h].y : 0.f;
+          const double sx = px + qx, dx = px - qx, sy = py + qy, dy = py - qy;
+          float2 im = make_float2((float)fma(-w.y, dx, w.x * sy), (float)fma(w.y, sy, w.x * dx));
           if (kt == 0) im = make_float2(0.f, 0.f);
-          d_re[at + h] = make_float2(fmaf(w.y, dy, w.x * sx), fmaf(w.y, sx, -w.x * dy));
+          d_re[at + h] = make_float2((float)fma(w.y, dy, w.x * sx), (float)fma(w.y, sx, -w.x * dy));
           d_im[at + h] = im;
           if (4 * f.R > real + 1 && kt == 0) {                 // two more padding columns
             EO[at + h + (f.R - 1) * R1 + 16 * k + 8] = make_float2(0.f, 0.f);

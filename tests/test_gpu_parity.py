@@ -914,3 +914,22 @@ def test_folded_forward_transform_sums_in_short_chains(nz, mz, nt, mt):
     want = np.einsum("kn,bnt->bkt", np.exp(-2j * np.pi * (np.outer(k, n) % nz) / nz), bins)
     roundings = 2 + (nt / 2 + 1) / 2 + 1 + 1 + 4.5 + (np.ceil(nz / 16) + 1) / 2 + 1
     assert rel(xh.reshape(want.shape), want) <= 1.1 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
+
+
+@pytest.mark.parametrize("nz, mz, nt, mt", [(64, 11, 20, 8), (96, 17, 20, 8), (128, 23, 10, 4), (160, 28, 24, 9),
+                                            (263, 47, 20, 8)])
+def test_folded_inverse_transform_sums_in_short_chains(nz, mz, nt, mt):
+    """The same count for the inverse (z, t) stage of a convolution: four chains over the folded frequencies, one over
+    the 2 mt - 1 columns of t; beside them the mode mix, the folded spectrum, the two tables, the joined chains and the
+    two rows of a pair.  One chain over z and a phase in fp32 are 1.15 to 1.4 times further off."""
+    L = Layer(64, 1, 1, (1, 1, nz, nt), (0, 0, mz, mt), 1)
+    L.R = np.ones_like(L.R)
+    y, xh = gpu_spectral_fwd(L)
+    k, n = np.array(O.mode_lists(L.spec)[2]), np.arange(nz)
+    theta = 2 * np.pi * (np.outer(np.arange(mt), np.arange(nt)) % nt) / nt
+    c = np.where((np.arange(mt) == 0) | (2 * np.arange(mt) == nt), 1.0, 2.0) * float(np.float32(1.0 / (nz * nt)))
+    rows = np.einsum("kn,bkt->bnt", np.exp(2j * np.pi * (np.outer(k, n) % nz) / nz),
+                     xh.astype(np.complex128).reshape(64, len(k), mt) * c)
+    want = rows.real @ np.cos(theta) - rows.imag @ np.sin(theta)
+    roundings = 6 + ((mz + 1) / 4 + 1) / 2 + mt
+    assert rel(y.reshape(want.shape), want) <= 1.1 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
