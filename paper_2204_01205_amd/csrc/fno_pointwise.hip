@@ -224,26 +224,27 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
 // channels are dealt to `ngrp` waves of a block (OT tiles of 4 each), which share x through the cache.  Layout and
 // products are those of the kernel above; rows need not be aligned (4-byte aligned 16-byte loads), a batch entry's
 // ragged last step takes single values, and channels past the end read the last one and count as zero.  The fp32
-// accumulators take kBwdChain steps (128 terms, as many as one chain of the tiled kernel below) and are then added
-// over the wave's 16 lane blocks, half of them sent away at each level, into doubles of which every lane keeps a
-// sixteenth.  erff and expf as in the tiled kernel.
+// accumulators take kBwdChain steps (128 terms, as many as one chain of the tiled kernel below) and then go to doubles,
+// which are added over the wave's 16 lane blocks, half of them sent away at each level: every lane keeps a sixteenth.
+// erff and expf as in the tiled kernel.
 // 5 -> 20 channels at 33.5 M points: 0.77 ms = 4.4 TB/s (1.9 ms tiled); 32 -> 32 at 2.16 M points with GELU: 0.43 ms
 // (0.67 ms tiled), where x comes from the cache for three of the four waves that share it.
 constexpr int kBwdChain = 32;
 typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
 
-// one level of the sum over lane blocks: N values per lane to N / 2 (an odd N: all are added, both lanes keep them)
-template <int N>
-__device__ __forceinline__ void fold_level(float* v, bool upper, int mask) {
+// one level of the sum over lane blocks, in double: N values per lane to N / 2 (an odd N: all are added, both lanes keep
+// them)
+template <int N, class T>
+__device__ __forceinline__ void fold_level(const T* v, double* out, bool upper, int mask) {
   if constexpr (N % 2 == 0) {
 #pragma unroll
     for (int q = 0; q < N / 2; ++q) {
-      const float keep = upper ? v[q + N / 2] : v[q], send = upper ? v[q] : v[q + N / 2];
-      v[q] = keep + __shfl_xor(send, mask);
+      const T keep = upper ? v[q + N / 2] : v[q], send = upper ? v[q] : v[q + N / 2];
+      out[q] = (double)keep + (double)__shfl_xor(send, mask);
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < N; ++q) v[q] += __shfl_xor(v[q], mask);
+    for (int q = 0; q < N; ++q) out[q] = (double)v[q] + (double)__shfl_xor(v[q], mask);
   }
 }
 constexpr int fold_count(int n) { return n % 2 == 0 ? n / 2 : n; }
@@ -298,12 +299,13 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
         acc[a][c] = v4f{0.f, 0.f, 0.f, 0.f};
       }
     }
-    fold_level<R0>(v, blk & 1, 4);
-    fold_level<R1>(v, blk & 2, 8);
-    fold_level<R2>(v, blk & 4, 16);
-    fold_level<R3>(v, blk & 8, 32);
+    double w[R1];
+    fold_level<R0>(v, w, blk & 1, 4);
+    fold_level<R1>(w, w, blk & 2, 8);
+    fold_level<R2>(w, w, blk & 4, 16);
+    fold_level<R3>(w, w, blk & 8, 32);
 #pragma unroll
-    for (int q = 0; q < R4; ++q) sum[q] += (double)v[q];
+    for (int q = 0; q < R4; ++q) sum[q] += w[q];
   };
 
   const long long steps_per_b = (N + 63) >> 6;

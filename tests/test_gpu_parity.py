@@ -853,6 +853,25 @@ def test_sums_over_points_of_every_tile_shape(c_in, c_out, npts, batch):
     assert rel(host(gb), gd.sum(axis=(0, 2))) <= TOL
 
 
+@pytest.mark.parametrize("c_in, c_out", [(5, 8), (24, 24), (32, 7)])
+def test_sums_over_points_reach_doubles_after_128_terms(c_in, c_out):
+    """Whole numbers whose 128-term chains stay below 2^24 (128 x 255 x 255 < 8.4e6) and are therefore exact in fp32,
+    while the 2048 terms of a wave's 16 lane blocks are not: every sum of products comes out exact, where the halves of
+    the points cancel to what a rounding of the partial sums would drown."""
+    npts = 64 * 2048 * 32                                # one chain per wave
+    gen = torch.Generator(device="cuda").manual_seed(c_in)
+    x = torch.randint(0, 256, (1, c_in, npts), device="cuda", generator=gen).float()
+    g = torch.randint(0, 256, (1, c_out, npts), device="cuda", generator=gen).float()
+    g[:, :, npts // 2:] *= -1.0
+    gW, gb = torch.empty((c_out, c_in), device="cuda"), torch.empty(c_out, device="cuda")
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(c_in, 0, c_out) // 4 + 2, device="cuda")
+    B.fno_pointwise_linear_bwd(1, c_in, c_out, npts, x, torch.zeros_like(gW), g, None, gW, gb, ws)
+    torch.cuda.synchronize()
+    want = torch.stack([(g[0, o].double() * x[0].double()).sum(1) for o in range(c_out)])
+    assert torch.equal(gW, want.float())
+    assert torch.equal(gb, g[0].double().sum(1).float())
+
+
 @pytest.mark.parametrize("case", [
     (1, 32, 32, (3, 2, 32, 16), (1, 1, 4, 4), 0),      # width 32, 48 whole steps
     (2, 20, 20, (3, 3, 12, 7), (1, 1, 3, 3), 0),       # width 20, 756 points: a ragged last step
