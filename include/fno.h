@@ -130,6 +130,7 @@ int fno_spectral_conv_bwd(const fno_desc* desc, const float* x, const float* xha
  *   W  in float [Cout][Cin]     b  in float [Cout], nullable (= 0)
  *   out        out float [B][Cout][grid]
  *   z_save     out float [B][Cout][grid], nullable: the pre-activation, needed by fno_block_bwd
+ *              (one of out and z_save may be x itself, the block in place; no other overlap)
  *   xhat_save  out cfloat, nullable, as above */
 int fno_block_fwd(const fno_desc* desc, const float* x, const float* R, const float* W,
                   const float* b, float* out, float* z_save, float* xhat_save,

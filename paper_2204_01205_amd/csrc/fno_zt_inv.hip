@@ -44,6 +44,12 @@ __global__ void zt_tables_kernel(float* __restrict__ blob, const float2* __restr
   }
 }
 
+// Does [a, a + n) meet [b, b + n), n floats?
+bool overlap(const float* a, const float* b, int64_t n) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+  return a != nullptr && b != nullptr && (p < q ? q - p : p - q) < (uintptr_t)n * 4;
+}
+
 }  // namespace
 
 hipError_t launch_zt_tables(float* blob, int groups, const float2* twt, const float2* twz, const float* W,
@@ -81,7 +87,12 @@ hipError_t launch_zt_inv(const float2* a, float* out, const float2* twt, const f
     err = launch_zt_inv_col16(a, out, twt, twz, B, Co, NxNy, az, Nt, mt, e, tables, s, &taken);
     if (err != hipSuccess || taken) return err;
   }
-  if (ztab != nullptr && zt_inv_fold_fits(az, Nt, mt, Co, e.u != nullptr ? e.Cu : 0))
+  // A block in place (out or the pre-activation over u): the folded kernel reads the u of a point again after it may
+  // have been written, from the blocks of its other channel groups and from overlapping runs of t.  The column kernels
+  // and the generic one read every point before they write it, from one block.
+  const int64_t total = ncols * Co * (int64_t)az.N * Nt;
+  const bool in_place = overlap(e.u, out, total) || overlap(e.u, e.zsave, total);
+  if (!in_place && ztab != nullptr && zt_inv_fold_fits(az, Nt, mt, Co, e.u != nullptr ? e.Cu : 0))
     return launch_zt_inv_fold(a, out, twt, ztab, ncols, Co, NxNy, az, Nt, mt, e, s);
   return launch_zt_inv_generic(a, out, twt, twz, ncols, Co, NxNy, az, Nt, mt, e, s);
 }

@@ -952,3 +952,23 @@ def test_folded_inverse_transform_sums_in_short_chains(nz, mz, nt, mt):
     want = rows.real @ np.cos(theta) - rows.imag @ np.sin(theta)
     roundings = 6 + ((mz + 1) / 4 + 1) / 2 + mt
     assert rel(y.reshape(want.shape), want) <= 1.1 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
+
+
+@pytest.mark.parametrize("c, grid, modes, rule", [
+    (32, (5, 2, 35, 31), (1, 1, 17, 16), 0),     # channel groups in several blocks per column, overlapping runs of t
+    (20, (7, 2, 49, 30), (2, 1, 12, 8), 0),      # overlapping runs of t
+    (20, (6, 4, 64, 20), (1, 1, 12, 8), 0),
+    (20, (6, 3, 128, 16), (1, 1, 16, 9), 0),     # column kernels: 16 and 32 points of t
+    (20, (6, 3, 64, 32), (1, 1, 12, 9), 0),
+    (6, (5, 3, 12, 70), (1, 1, 3, 5), 0),        # generic kernel
+])
+@pytest.mark.parametrize("over", ["out", "z"])
+def test_block_in_place_matches_oracle(c, grid, modes, rule, over):
+    """out (or the saved pre-activation) over x itself: every point is read before it is written."""
+    L = Layer(1, c, c, grid, modes, rule)
+    oo, zo, _ = O.block_fwd(L.x, L.R, L.W, L.b, L.spec)
+    x, other = dev(L.x), torch.empty((1, c) + L.spec.grid, device="cuda")
+    out, z = (x, other) if over == "out" else (other, x)
+    B.fno_block_fwd(L.desc, x, dev(L.R), dev(L.W), dev(L.b), out, z, None, B.alloc_workspace(L.desc, B.FNO_OP_BLOCK_FWD))
+    torch.cuda.synchronize()
+    assert rel(host(out), oo) <= TOL and rel(host(z), zo) <= TOL
