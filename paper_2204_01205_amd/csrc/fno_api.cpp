@@ -116,9 +116,9 @@ int make_plan(const fno_desc* d, bool need_block, bool need_bwd_block, Plan* p) 
   size_t off = 0;
   p->off_ztab = off; off = align_up(off + fno::kZtTablesBytes);
   p->off_twt = off; off = align_up(off + (size_t)p->mt * p->Nt * 8);
-  const int64_t inner_y = (int64_t)p->L[2] * p->mt, planes = (int64_t)p->B * Cm;
-  p->ax_folded[0] = fno::axis_fold_fits(p->ax[0], planes, inner_y * p->L[1]);
-  p->ax_folded[1] = fno::axis_fold_fits(p->ax[1], planes * p->N[0], inner_y);
+  const int64_t inner_y = (int64_t)p->L[2] * p->mt;
+  p->ax_folded[0] = fno::axis_fold_fits(p->ax[0], inner_y * p->L[1]);
+  p->ax_folded[1] = fno::axis_fold_fits(p->ax[1], inner_y);
   for (int a = 0; a < 3; ++a) {
     p->off_tw[a] = off;
     off = align_up(off + (a < 2 && p->ax_folded[a] ? fno::fold_plan(p->ax[a]).floats * 4

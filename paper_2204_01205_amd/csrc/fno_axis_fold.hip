@@ -230,18 +230,28 @@ Tiles axis_tiles(int64_t outer, int64_t inner, int max_ct) {
   return t;
 }
 
+// Slabs of [N][inner] per launch: the kernels count tiles of 16 floats in 32 bits.  The rule of axis_fold_fits() cannot
+// ask for that, since one set of tables in a workspace serves every batch.
+int64_t slabs_per_launch(int64_t inner) { return ((1ll << 30) - 1) / ((2 * inner + 15) / 16); }
+
 int folded_count(AxisPlan ax) { return (ax.npos - 1 > ax.L - ax.npos ? ax.npos - 1 : ax.L - ax.npos) + 1; }
 
 }  // namespace
 
-bool axis_fold_fits(AxisPlan ax, int64_t outer, int64_t inner) {
+bool axis_fold_fits(AxisPlan ax, int64_t inner) {
   if (!axis_fold_pays(ax) || folded_count(ax) > 48) return false;
-  if (inner <= 0 || 2 * inner * ax.N >= (1ll << 30) || outer * ((2 * inner + 15) / 16) >= (1ll << 30)) return false;
+  if (inner <= 0 || 2 * inner * ax.N >= (1ll << 30)) return false;
   return fold_plan(ax).floats * 4 <= kAxisFoldLds;
 }
 
 hipError_t launch_axis_fwd_fold(const float2* in, float2* out, const float* tab, int64_t outer, AxisPlan ax,
                                 int64_t inner, hipStream_t s) {
+  const int64_t most = slabs_per_launch(inner);
+  if (outer > most) {
+    const hipError_t err = launch_axis_fwd_fold(in, out, tab, most, ax, inner, s);
+    if (err != hipSuccess) return err;
+    return launch_axis_fwd_fold(in + most * ax.N * inner, out + most * ax.L * inner, tab, outer - most, ax, inner, s);
+  }
   const FoldPlan f = fold_plan(ax);
   const Tiles t = axis_tiles(outer, inner, f.rows == 16 ? 2 : 1);
   const size_t lds = f.floats * 4;
@@ -264,6 +274,12 @@ hipError_t launch_axis_fwd_fold(const float2* in, float2* out, const float* tab,
 
 hipError_t launch_axis_inv_fold(const float2* in, float2* out, const float* tab, int64_t outer, AxisPlan ax,
                                 int64_t inner, hipStream_t s) {
+  const int64_t most = slabs_per_launch(inner);
+  if (outer > most) {
+    const hipError_t err = launch_axis_inv_fold(in, out, tab, most, ax, inner, s);
+    if (err != hipSuccess) return err;
+    return launch_axis_inv_fold(in + most * ax.L * inner, out + most * ax.N * inner, tab, outer - most, ax, inner, s);
+  }
   const FoldPlan f = fold_plan(ax);
   const int ks = (folded_count(ax) + 3) / 4;
   const Tiles t = axis_tiles(outer, inner, ks <= 4 ? 2 : 1);

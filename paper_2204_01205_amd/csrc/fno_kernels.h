@@ -53,7 +53,7 @@ hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int6
 hipError_t launch_axis_inv(const float2* in, float2* out, const float2* tw, int64_t outer,
                            AxisPlan ax, int64_t inner, hipStream_t s);
 // The same as folded matrix products (fno_axis_fold.hip); tab: the folded table of the axis.
-bool axis_fold_fits(AxisPlan ax, int64_t outer, int64_t inner);
+bool axis_fold_fits(AxisPlan ax, int64_t inner);
 hipError_t launch_axis_fwd_fold(const float2* in, float2* out, const float* tab, int64_t outer, AxisPlan ax,
                                 int64_t inner, hipStream_t s);
 hipError_t launch_axis_inv_fold(const float2* in, float2* out, const float* tab, int64_t outer, AxisPlan ax,

@@ -61,6 +61,17 @@ def test_workspace_sizes_and_config_table():
     assert B.fno_workspace_bytes(d, B.FNO_OP_BLOCK_FWD) < 0.25 * act_bytes
 
 
+def test_tables_take_the_same_room_for_every_batch():
+    """One set of tables in a workspace serves calls of any batch on the same grid and modes, so what stands before the
+    intermediates may not depend on the batch (2^30 slabs of the y stage here)."""
+    def total(batch):
+        return B.fno_workspace_bytes(B.make_desc(batch, 32, 32, (64, 6, 4, 1), (2, 2, 0, 1), 1), B.FNO_OP_SPECTRAL_CONV_FWD)
+
+    per_entry = total(2) - total(1)
+    for batch in (3, 1 << 10, 1 << 19, 1 << 20):
+        assert total(batch) - total(1) == (batch - 1) * per_entry
+
+
 def _status(fn, *args):
     return fn(*args)
 
