@@ -99,7 +99,7 @@ int make_plan(const fno_desc* d, bool need_block, bool need_bwd_block, Plan* p) 
   {
     AxisPlan az{p->N[2], p->L[2], p->npos[2], 1, p->N[2]};
     bool ok = false;
-    // 16 suits the tile of the matrix-core inverse kernel best; then larger, then smaller splits
+    // 16 is the FFT of the column and per-tile inverse kernels; then larger, then smaller splits
     const int order[6] = {16, 32, 8, 4, 2, 1};
     for (int c = 0; c < 6 && !ok; ++c) {
       const int m = order[c];

@@ -40,11 +40,9 @@ inline size_t zt_inv_lds(AxisPlan az, int Nt, int mt, int Co) {
   return ((vy + 3) & ~(size_t)3) * 4 + (size_t)kMaxCo * kMaxCo * 4;
 }
 
-// The rule of zt_tile_fits(): a tile of Q residue classes, Rz = Q*M rows, of 128 points for each of NW waves,
-// whose spectrum, V and tables fit the LDS.  It bounds, with zt_inv_fits(), the shapes that are accepted: those
-// that only this rule admits are within the folded kernel's reach, or, where its table or a single group of
-// channels is too large for it, within the generic kernel's at up to 160 KB of LDS (checked by enumeration over
-// the lengths, kept counts and widths).
+// Tile of the per-tile kernel: Q residue classes, Rz = Q*M rows, of 128 points for each of NW waves, whose spectrum, V
+// and tables fit the LDS.  zt_tile_fits() and zt_inv_fits() bound the shapes that are accepted: every one of them is
+// within the reach of the per-tile kernel or of the generic one, in place as well.
 // t-tile for an axis of length Nt: 16 or 32 points, the axis itself or the next tile width above an even length;
 // 0 when neither fits
 inline int mfma_tile_nt(int Nt) {
@@ -104,7 +102,7 @@ inline bool mfma_cfg_ok(AxisPlan az, int Nt, int mt, int Co, int Cu, int nw, siz
   const int q = mfma_q_nw(az, Nt, nw);
   const int CT = (Co + 3) / 4 <= 2 ? 2 : ((Co + 3) / 4 <= 5 ? 5 : 8);
   // the tile is staged in 16-byte pieces (L * mt even) and a thread owns at most two z-stage items
-  return q > 0 && (az.L * mt) % 2 == 0 && Co * mt * q <= (nw == 8 ? 512 : 512) && Co <= kMaxCo && Cu <= 4 * CT &&
+  return q > 0 && (az.L * mt) % 2 == 0 && Co * mt * q <= 512 && Co <= kMaxCo && Cu <= 4 * CT &&
          (nw == 4 || CT <= 5) && zt_mfma_lds(az, Nt, mt, Co, Cu, q) <= lds_cap;
 }
 
@@ -119,7 +117,7 @@ inline int mfma_nw(AxisPlan az, int Nt, int mt, int Co, int Cu) {
 // (defined in fno_zt_inv.hip).
 hipError_t launch_zt_tables(float* blob, int groups, const float2* twt, const float2* twz, const float* W,
                             int w_so, int w_si, const float* bias, int Co, int Cu, int CP, int mt, int NT,
-                            int Lz, int Pz, int Q, int blob_floats, hipStream_t s);
+                            int Nt, int Lz, int Pz, int Q, int blob_floats, hipStream_t s);
 
 // The column kernels' launchers set *taken when the kernel covers the shape and has been launched.
 hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, const float2* twz, int B, int Co,
@@ -129,6 +127,9 @@ hipError_t launch_zt_inv_col16(const float2* a, float* out, const float2* twt, c
                                int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, float* tables, hipStream_t s,
                                bool* taken);
 // Cu: input channels of the linear term, 0 without one.
+bool zt_inv_tile_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
+hipError_t launch_zt_inv_tile(const float2* a, float* out, const float2* twt, const float2* twz, int B, int Co,
+                              int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, float* tables, hipStream_t s);
 bool zt_inv_fold_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
 hipError_t launch_zt_inv_fold(const float2* a, float* out, const float2* twt, const float* ztab, int64_t ncols, int Co,
                               int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, hipStream_t s);

@@ -286,7 +286,7 @@ hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, con
     if (Cu <= 4 * CT && lds <= (size_t)(79 * 1024) && (size_t)blob_floats * 4 <= kZtTablesBytes) {
       const int inv_mt = (65536 + mt - 1) / mt;
       hipError_t terr = launch_zt_tables(tables, 1, twt, twz, ep.u ? ep.W : nullptr, ep.w_so, ep.w_si, ep.bias, Co,
-                                         Cu, 4 * CT, mt, Nt, az.L, az.P, az.P, blob_floats, s);
+                                         Cu, 4 * CT, mt, Nt, Nt, az.L, az.P, az.P, blob_floats, s);
       if (terr != hipSuccess) return terr;
       const dim3 grid((unsigned)NxNy, (unsigned)B);
 #define FNO_ZTC_S(CTV, MTV, LZV, NPV, EPIV, STRV)                                                     \

@@ -308,7 +308,7 @@ hipError_t launch_zt_inv_col16(const float2* a, float* out, const float2* twt, c
   // 0.22 ms with run-time counts here, 0.16 there).
   if (!(shape_a || shape_b)) return hipSuccess;
   hipError_t terr = launch_zt_tables(tables, 1, twt, twz, ep.u ? ep.W : nullptr, ep.w_so, ep.w_si, ep.bias, Co,
-                                     Cu, 4 * CT, mt, Nt, az.L, az.P, az.P, blob_floats, s);
+                                     Cu, 4 * CT, mt, Nt, Nt, az.L, az.P, az.P, blob_floats, s);
   if (terr != hipSuccess) return terr;
   const dim3 grid((unsigned)NxNy, (unsigned)B);
 #define FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, STRV)                                                     \

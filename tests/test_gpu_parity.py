@@ -829,6 +829,19 @@ def test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule):
     assert np.array_equal(host(out2[1]), out[0])
 
 
+@pytest.mark.parametrize("c, nz, mz, nt, mt, rule", [
+    # per-tile kernel: one residue class; padded channels; rows padded from 30 and 24 to 32 and from 12 to 16 points of t;
+    # eight channel tiles; several groups of residue classes, most z frequencies kept; an odd number of them
+    (20, 16, 4, 32, 8, 0), (7, 128, 30, 16, 9, 0), (18, 64, 12, 30, 9, 0), (13, 16, 8, 24, 11, 0), (24, 16, 3, 20, 7, 0),
+    (3, 256, 128, 12, 7, 0), (8, 512, 140, 16, 2, 0), (6, 32, 9, 16, 8, 1),
+    # generic kernel on short z axes: 8, 20 and 32 channels, a 32-channel convolution whose rows take V's place in LDS
+    (20, 8, 3, 24, 6, 0), (8, 12, 4, 48, 12, 0), (32, 9, 3, 20, 5, 1), (6, 27, 6, 33, 9, 1), (32, 7, 3, 6, 3, 1),
+    (4, 16, 4, 8, 3, 0),        # folded: eight pairs, a half tile with every lane at work
+])
+def test_inverse_transform_on_the_tile_and_generic_kernels(c, nz, mz, nt, mt, rule):
+    test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule)
+
+
 @pytest.mark.parametrize("c_in, c_out, npts, batch", [
     (1, 1, 3, 1), (8, 8, 64, 2), (5, 20, 65, 2), (8, 32, 127, 1), (9, 12, 66, 3), (24, 24, 193, 1), (7, 25, 640, 2),
     (25, 8, 130, 1), (26, 16, 129, 2), (32, 32, 1001, 1), (32, 17, 64, 1),
@@ -961,6 +974,9 @@ def test_folded_inverse_transform_sums_in_short_chains(nz, mz, nt, mt):
     (20, (6, 3, 128, 16), (1, 1, 16, 9), 0),     # column kernels: 16 and 32 points of t
     (20, (6, 3, 64, 32), (1, 1, 12, 9), 0),
     (6, (5, 3, 12, 70), (1, 1, 3, 5), 0),        # generic kernel
+    (32, (3, 2, 7, 6), (1, 1, 3, 3), 0),
+    (32, (5, 2, 32, 20), (1, 1, 2, 10), 0),      # per-tile kernel: no room for the generic one
+    (24, (5, 2, 64, 12), (1, 1, 8, 5), 0),
 ])
 @pytest.mark.parametrize("over", ["out", "z"])
 def test_block_in_place_matches_oracle(c, grid, modes, rule, over):
