@@ -225,7 +225,7 @@ int fno_pointwise_mlp2(int32_t batch, int32_t c_in, int32_t hidden, int32_t c_ou
 
 /* For callers that cannot allocate device memory or bring a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): fno_spectral_conv_fwd with the
- * workspace taken from a fixed array of FNO_STATIC_SCRATCH_BYTES bytes of device memory (and 1 MiB
+ * workspace taken from a fixed array of FNO_STATIC_SCRATCH_BYTES bytes of device memory (and 5 MiB
  * for tables) that the library owns (one copy per GPU it runs on, held until the process ends).  Arguments, layout,
  * results and error codes are those of fno_spectral_conv_fwd; the call allocates and frees
  * nothing.  Shapes whose fno_workspace_bytes(FNO_OP_SPECTRAL_CONV_FWD) exceeds the array are

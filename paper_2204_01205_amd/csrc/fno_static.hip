@@ -20,9 +20,9 @@ void set_status_detail(const char* text);
 namespace {
 
 // Room for the intermediates as declared, and beside it for the tables of the folded products: every shape that fits
-// without them fits with them.  The z table is at most 320 rows of 308 floats twice (its 32 rows of a block fit 78 KiB
-// of LDS, and there are no more rows than half the axis, 0.8 MB), those of x and y 40 KiB each.
-constexpr size_t kScratchBytes = FNO_STATIC_SCRATCH_BYTES + ((size_t)1 << 20);
+// without them fits with them.  The z table is at most 608 rows of 620 floats twice and their phases (16 of its rows
+// fit 78 KiB of LDS, and there are no more rows than half the axis, 3.1 MB), those of x and y 40 KiB each.
+constexpr size_t kScratchBytes = FNO_STATIC_SCRATCH_BYTES + ((size_t)5 << 20);
 constexpr int kMaxDevices = 64;
 
 // In host code this name is only a handle for hipGetSymbolAddress; the device address it

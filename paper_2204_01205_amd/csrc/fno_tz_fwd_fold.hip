@@ -272,26 +272,40 @@ FoldPlan fold_plan(AxisPlan az) {
   return f;
 }
 
-// Short rows of a z axis with a power of two in its length: a wave has few bytes to ask for per load and mostly empty K
-// steps, and the mixed-radix kernel is as fast or faster.  us on 4096 columns of 8 channels, that kernel against this
-// one: z of 24 (two entries), t of 5, 8, 12, 14: 19, 27, 35, 49 and 40, 40, 45, 49; z of 48, t of 5, 9, 12: 19, 30, 43
-// and 32, 36, 38; z of 72, t of 7, 8, 12: 33, 40, 55 and 42, 43, 50; z of 120, t of 5, 9, 12: 51, 82, 101 and 78, 84, 85.
-bool tz_fwd_fold_pays(AxisPlan az, int Nt) {
+// Whether these kernels are the faster ones, against the mixed-radix kernel for a z axis with a power of two in its
+// length (M = 4: the four-point FFT leaves long residue sums, so the line lies further out there).
+//
+// Short rows: a wave has few bytes to ask for per load and mostly empty K steps.  us on 4096 columns of 8 channels,
+// mixed radix against this one: z of 24 (two entries), t of 5, 8, 12, 14: 19, 27, 35, 49 and 40, 40, 45, 49; z of 48,
+// t of 5, 9, 12: 19, 30, 43 and 32, 36, 38; z of 72, t of 7, 8, 12: 33, 40, 55 and 42, 43, 50; z of 120, t of 5, 9, 12:
+// 51, 82, 101 and 78, 84, 85.
+//
+// Many frequencies: the product over z is worked for every group of 32 rows of the table, and the one over t is worked
+// again for each, where the FFT costs the same for any number of frequencies.  us on 576 columns of 4 channels, mixed
+// radix against this one: z of 128 with t of 10 and 5 bins, 7, 19, 32, 64 kept per side: 11.9, 13.6, 15.0, 20.1 and
+// 10.8, 14.5, 20.6, 28.2; z of 256 with t of 24 and 12 bins, 15, 38, 128 per side: 48, 53, 77 and 30, 56, 125; z of 160
+// with t of 48 and 16 bins, 9, 20, 80 per side: 88, 92, 106 and 33, 39, 81.  Over 10.8 thousand shapes on 576 columns (z
+// of 8 to 512, t of 8 to 48, 4 to 32 channels) 15 % were more than a tenth slower here than mixed radix without this part
+// of the rule, 2 % are with it (and 2 % more than a tenth slower than here); over 2.9 thousand on 4096 columns 11 and 3 %
+// (1 %).
+bool tz_fwd_fold_pays(AxisPlan az, int Nt, int mt) {
   if (az.M < 4) return true;
-  return !(Nt <= 7 || (Nt <= 9 && (az.N <= 48 || az.N > 96)) || (Nt <= 12 && az.N <= 24));
+  if (Nt <= 7 || (Nt <= 9 && (az.N <= 48 || az.N > 96)) || (Nt <= 12 && az.N <= 24)) return false;
+  const int rows = fold_plan(az).rows;
+  if (az.M == 4) return rows <= 32 || mt > 4;
+  return rows <= 16 || Nt > 36 || (rows <= 32 && mt > 4);
 }
 
-// Nt up to 64 in registers; one or two row tiles of frequencies and column tiles of bins per block
+// Nt up to 64 in registers; one or two row tiles of frequencies and column tiles of bins per block (one, where the table
+// of two does not leave room for two blocks on a CU: z axes of more than 608 points)
 bool tz_fwd_fold_fits(AxisPlan az, int Nt, int mt) {
-  const FoldPlan f = fold_plan(az);
-  const int MT = f.rows >= 32 ? 2 : 1;
-  return Nt <= 64 && mt <= 64 && fold_lds(f, MT) <= kFoldLds;
+  return Nt <= 64 && mt <= 64 && fold_lds(fold_plan(az), 1) <= kFoldLds;
 }
 
 hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, const float* ztab, int64_t planes,
                               AxisPlan az, int Nt, int mt, hipStream_t s) {
   const FoldPlan f = fold_plan(az);
-  const int CT = 2 * mt <= 16 ? 1 : 2, MT = f.rows >= 32 ? 2 : 1;
+  const int CT = 2 * mt <= 16 ? 1 : 2, MT = f.rows >= 32 && fold_lds(f, 2) <= kFoldLds ? 2 : 1;
   const int mgroups = (f.rows + 16 * MT - 1) / (16 * MT), cgroups = (2 * mt + 16 * CT - 1) / (16 * CT);
   const int ngroups = mgroups * cgroups;
   const size_t lds = fold_lds(f, MT);

@@ -842,6 +842,18 @@ def test_inverse_transform_on_the_tile_and_generic_kernels(c, nz, mz, nt, mt, ru
     test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule)
 
 
+@pytest.mark.parametrize("c, nz, mz, nt, mt", [
+    (2, 611, 30, 4, 2), (1, 1215, 300, 3, 2), (2, 609, 304, 5, 3),      # folded, one row tile per block
+    (3, 128, 64, 10, 5), (2, 160, 30, 24, 4), (2, 256, 100, 20, 9),     # mixed radix: many frequencies
+    (2, 512, 40, 14, 4), (3, 640, 20, 8, 3),
+])
+def test_forward_transform_of_long_z_axes(c, nz, mz, nt, mt):
+    L = Layer(2, c, c, (3, 2, nz, nt), (1, 1, mz, mt))
+    y, xh = gpu_spectral_fwd(L)
+    yo, xho = O.spectral_conv_fwd(L.x, L.R, L.spec, return_xhat=True)
+    assert rel(xh, xho) <= TOL and rel(y, yo) <= TOL
+
+
 @pytest.mark.parametrize("c_in, c_out, npts, batch", [
     (1, 1, 3, 1), (8, 8, 64, 2), (5, 20, 65, 2), (8, 32, 127, 1), (9, 12, 66, 3), (24, 24, 193, 1), (7, 25, 640, 2),
     (25, 8, 130, 1), (26, 16, 129, 2), (32, 32, 1001, 1), (32, 17, 64, 1),
@@ -931,7 +943,8 @@ def test_folded_axis_products_round_only_their_table_and_their_result(n, m):
 
 
 @pytest.mark.parametrize("nz, mz, nt, mt", [(21, 3, 14, 5), (40, 7, 14, 5), (64, 11, 20, 8), (80, 14, 24, 9),
-                                            (100, 18, 10, 4), (128, 23, 40, 16), (160, 28, 48, 16), (263, 47, 20, 8)])
+                                            (100, 18, 10, 4), (128, 23, 40, 16), (160, 28, 48, 16), (263, 47, 20, 8), (611, 30, 4, 2),
+                                            (801, 30, 8, 2)])
 def test_folded_forward_transform_sums_in_short_chains(nz, mz, nt, mt):
     """The error of the forward (t, z) stage is that of two chains of Nt / 2 terms over t and of blocks of eight pairs
     over z.  A rounding has an rms of 0.42 x 2^-24 of its value; a chain of n terms of equal size rounds partial sums
