@@ -36,14 +36,6 @@ bool axis_fold_pays(AxisPlan ax) { return ax.M <= 4 || ax.N == 32; }
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ double swap_pair(double v) {    // the value of lane ^ 1: the other part of a complex number
-  typedef int v2i __attribute__((ext_vector_type(2)));
-  v2i b = __builtin_bit_cast(v2i, v);
-  b[0] = __builtin_amdgcn_mov_dpp(b[0], 0xB1, 0xF, 0xF, true);
-  b[1] = __builtin_amdgcn_mov_dpp(b[1], 0xB1, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, b);
-}
-
 __device__ __forceinline__ void stage_table(const float* __restrict__ tab, float* smem, int floats) {
   for (int i = threadIdx.x; i < (floats >> 2); i += kThreads)
     reinterpret_cast<float4*>(smem)[i] = reinterpret_cast<const float4*>(tab)[i];

@@ -69,6 +69,62 @@ __device__ __forceinline__ void st_once2(float2* p, float2 v) {
   st_once<STREAM>(reinterpret_cast<v2f*>(p), v2f{v.x, v.y});
 }
 
+// W consecutive floats at a 4-byte aligned address (ld_once and st_once of a vector take its own alignment: a template
+// argument drops a type's aligned attribute).  Three go as two and one, which the compiler joins to a 12-byte
+// access where the target has one; a vector of three elements may be widened to 16 bytes, past the run.
+template <int W> struct run_of;
+template <> struct run_of<1> { typedef float type; };
+template <> struct run_of<2> { typedef v2f type; };
+template <> struct run_of<4> { typedef v4f type; };
+template <int W, bool STREAM>
+__device__ __forceinline__ void load_run(const void* p, float* v) {
+  if constexpr (W == 3) {
+    load_run<2, STREAM>(p, v);
+    load_run<1, STREAM>(static_cast<const float*>(p) + 2, v + 2);
+  } else {
+    typedef typename run_of<W>::type vec;
+    typedef vec unaligned __attribute__((aligned(4)));
+    vec q;
+    if constexpr (STREAM) q = __builtin_nontemporal_load(static_cast<const unaligned*>(p));
+    else q = *static_cast<const unaligned*>(p);
+    if constexpr (W == 1) v[0] = q;
+    else {
+#pragma unroll
+      for (int c = 0; c < W; ++c) v[c] = q[c];
+    }
+  }
+}
+template <int W, bool STREAM>
+__device__ __forceinline__ void store_run(void* p, const float* v) {
+  if constexpr (W == 3) {
+    store_run<2, STREAM>(p, v);
+    store_run<1, STREAM>(static_cast<float*>(p) + 2, v + 2);
+  } else {
+    typedef typename run_of<W>::type vec;
+    typedef vec unaligned __attribute__((aligned(4)));
+    vec q;
+    if constexpr (W == 1) q = v[0];
+    else {
+#pragma unroll
+      for (int c = 0; c < W; ++c) q[c] = v[c];
+    }
+    if constexpr (STREAM) __builtin_nontemporal_store(q, static_cast<unaligned*>(p));
+    else *static_cast<unaligned*>(p) = q;
+  }
+}
+
+// the value of lane ^ 1: the other part of a complex number
+__device__ __forceinline__ float swap_pair(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double swap_pair(double v) {
+  typedef int v2i __attribute__((ext_vector_type(2)));
+  v2i b = __builtin_bit_cast(v2i, v);
+  b[0] = __builtin_amdgcn_mov_dpp(b[0], 0xB1, 0xF, 0xF, true);
+  b[1] = __builtin_amdgcn_mov_dpp(b[1], 0xB1, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, b);
+}
+
 // Thread blocks are dealt to the chip's eight XCDs round robin.  For a grid padded to a multiple of
 // eight blocks this is the work item of block `bid` under which every XCD walks a contiguous eighth
 // of the items, so that the memory it has in flight at one time spans an eighth of the pages

@@ -33,32 +33,6 @@ namespace fno {
 
 namespace {
 
-template <int W> struct vec_of;
-template <> struct vec_of<1> { typedef float type; };
-template <> struct vec_of<2> { typedef v2f type; };
-template <> struct vec_of<3> { typedef float type __attribute__((ext_vector_type(3))); };
-template <> struct vec_of<4> { typedef v4f type; };
-
-// W consecutive floats at a 4-byte aligned address
-template <int W, bool STREAM>
-__device__ __forceinline__ void load_run(const float* p, float (&v)[W]) {
-  if constexpr (W == 1) {
-    v[0] = ld_once<STREAM>(p);
-  } else {
-    typedef typename vec_of<W>::type vec;
-    typedef vec unaligned __attribute__((aligned(4)));
-    vec q;
-    if constexpr (STREAM) q = __builtin_nontemporal_load(reinterpret_cast<const unaligned*>(p));
-    else q = *reinterpret_cast<const unaligned*>(p);
-#pragma unroll
-    for (int c = 0; c < W; ++c) v[c] = q[c];
-  }
-}
-
-__device__ __forceinline__ float swap_pair(float v) {      // the value of lane ^ 1
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
-}
-
 // registers of a variant (two row tiles in flight and folded, the t table, the accumulators, the z
 // table's operands and the addresses), and the waves per SIMD they allow
 constexpr int fold_regs(int KS, int CT, int MT, int PP) {
@@ -174,7 +148,7 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
       float ca[MT][VP], sa[MT][VP];
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        typedef typename vec_of<VP>::type vec;
+        typedef typename run_of<VP>::type vec;
         const int at = (16 * m + c) * stride + 16 * tile + VP * g;
         const vec cq = *reinterpret_cast<const vec*>(COS + at), sq = *reinterpret_cast<const vec*>(SIN + at);
 #pragma unroll
@@ -331,9 +305,11 @@ hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, co
     if (PP == 4) FNO_TZD_M(JV, WV, CTV, 1, 4); else if (PP == 2) FNO_TZD_M(JV, WV, CTV, 1, 2);          \
     else if (MT == 1) FNO_TZD_M(JV, WV, CTV, 1, 1); else FNO_TZD_M(JV, WV, CTV, 2, 1);                  \
   } while (0)
-#define FNO_TZD_C(JV, WV)                                               \
-  do {                                                                  \
-    if (CT == 1) FNO_TZD_P(JV, WV, 1); else FNO_TZD_P(JV, WV, 2);       \
+  // more than eight bins (CT = 2) need 16 points of t at least: no variant of shorter rows
+#define FNO_TZD_C(JV, WV)                                                           \
+  do {                                                                              \
+    if constexpr ((JV) > 0 || (WV) == 4) { if (CT == 2) { FNO_TZD_P(JV, WV, 2); break; } } \
+    FNO_TZD_P(JV, WV, 1);                                                           \
   } while (0)
 #define FNO_TZD_W(JV)                                                                         \
   do {                                                                                        \

@@ -56,40 +56,6 @@ struct FoldInv {
   unsigned inv_mt;       // ceil(2^32 / mt): division by multiplication, exact for the counts here
 };
 
-template <int W> struct run_of;
-template <> struct run_of<1> { typedef float type; };
-template <> struct run_of<2> { typedef v2f type; };
-template <> struct run_of<3> { typedef float type __attribute__((ext_vector_type(3))); };
-template <> struct run_of<4> { typedef v4f type; };
-
-// W consecutive floats at a 4-byte aligned address
-template <int W, bool STREAM>
-__device__ __forceinline__ void load_run(const char* p, float (&v)[W]) {
-  typedef typename run_of<W>::type vec;
-  typedef vec unaligned __attribute__((aligned(4)));
-  vec q;
-  if constexpr (STREAM) q = __builtin_nontemporal_load(reinterpret_cast<const unaligned*>(p));
-  else q = *reinterpret_cast<const unaligned*>(p);
-  if constexpr (W == 1) v[0] = q;
-  else {
-#pragma unroll
-    for (int c = 0; c < W; ++c) v[c] = q[c];
-  }
-}
-template <int W, bool STREAM>
-__device__ __forceinline__ void store_run(char* p, const float (&v)[W]) {
-  typedef typename run_of<W>::type vec;
-  typedef vec unaligned __attribute__((aligned(4)));
-  vec q;
-  if constexpr (W == 1) q = v[0];
-  else {
-#pragma unroll
-    for (int c = 0; c < W; ++c) q[c] = v[c];
-  }
-  if constexpr (STREAM) __builtin_nontemporal_store(q, reinterpret_cast<unaligned*>(p));
-  else *reinterpret_cast<unaligned*>(p) = q;
-}
-
 constexpr int fold_inv_ns(int W, int CI) { return 2 * W * CI <= 160 ? 2 : 1; }
 // smallest channel count that runs with CI register slots: the slots from there on may be empty
 constexpr int fold_inv_low(int CI) { return CI <= 8 ? 1 : (CI == 32 ? 25 : CI - 3); }
