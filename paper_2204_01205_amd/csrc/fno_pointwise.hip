@@ -11,101 +11,7 @@ namespace {
 // ------------------------------------------------------------------------------------------
 // Backward pointwise: gz = g * act'(z); partial sums for gb and gW
 // ------------------------------------------------------------------------------------------
-constexpr int kBwdTile = 256;      // points per tile (= threads)
-constexpr int kBwdPairs = 5;       // sums per thread: covers Cout*(Cin+1) up to 1280
-
-__global__ __launch_bounds__(kThreads) void bwd_pointwise_kernel(
-    const float* __restrict__ z, const float* __restrict__ gout, const float* __restrict__ x,
-    float* __restrict__ gz_out, double* __restrict__ part, int B, int Ci, int Co, long long N,
-    int act, int mse_target, float mse_scale) {
-  HIP_DYNAMIC_SHARED(float, smem)
-  const int sR = kBwdTile + 1;
-  float* Gs = smem;                 // [Co][sR]
-  float* Xs = smem + Co * sR;       // [Ci][sR]
-  const int tid = threadIdx.x;
-  const long long tiles_per_b = (N + kBwdTile - 1) / kBwdTile;
-  const long long ntiles = tiles_per_b * B;
-  const int npairs = Co * Ci + Co;
-  // each thread owns up to kBwdPairs of the Co*Ci + Co sums (checked on the host)
-  double acc[kBwdPairs];
-#pragma unroll
-  for (int h = 0; h < kBwdPairs; ++h) acc[h] = 0.0;
-  for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const long long b = tile / tiles_per_b;
-    const long long p = (tile % tiles_per_b) * kBwdTile + tid;
-    const bool live = p < N;
-    for (int o0 = 0; o0 < Co; o0 += 8) {          // eight channels per pass: their loads go out together
-      float zv[8], g[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bool on = live && o0 + u < Co;
-        const long long e = (b * Co + o0 + u) * N + p;
-        zv[u] = (on && (act || mse_target)) ? z[e] : 0.f;
-        g[u] = on ? gout[e] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (o0 + u < Co) {
-          float gv = 0.f;
-          if (live) {
-            float gg = g[u];
-            if (mse_target) gg = mse_scale * ((act ? gelu_f(zv[u]) : zv[u]) - gg);
-            gv = act ? gg * gelu_prime_f(zv[u]) : gg;
-            if (gz_out != nullptr) gz_out[(b * Co + o0 + u) * N + p] = gv;
-          }
-          Gs[(o0 + u) * sR + tid] = gv;
-        }
-      }
-    }
-    for (int i0 = 0; i0 < Ci; i0 += 8) {
-      float xv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) xv[u] = (live && i0 + u < Ci) ? x[(b * Ci + i0 + u) * N + p] : 0.f;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (i0 + u < Ci) Xs[(i0 + u) * sR + tid] = xv[u];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < kBwdPairs; ++h) {
-      const int q = tid + h * kThreads;
-      if (q < npairs) {
-        float s = 0.f;
-        if (q < Co * Ci) {
-          const float* gr = Gs + (q / Ci) * sR;
-          const float* xr = Xs + (q % Ci) * sR;
-          float s1 = 0.f;
-          for (int t = 0; t < kBwdTile; t += 8) {    // eight terms per pass: their LDS reads go out together
-            float gq[8], xq[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { gq[u] = gr[t + u]; xq[u] = xr[t + u]; }
-#pragma unroll
-            for (int u = 0; u < 8; u += 2) { s = fmaf(gq[u], xq[u], s); s1 = fmaf(gq[u + 1], xq[u + 1], s1); }
-          }
-          s += s1;
-        } else {
-          const float* gr = Gs + (q - Co * Ci) * sR;
-          float s1 = 0.f;
-          for (int t = 0; t < kBwdTile; t += 8) {
-            float gq[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) gq[u] = gr[t + u];
-#pragma unroll
-            for (int u = 0; u < 8; u += 2) { s += gq[u]; s1 += gq[u + 1]; }
-          }
-          s += s1;
-        }
-        acc[h] += double(s);
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int h = 0; h < kBwdPairs; ++h)
-    if (tid + h * kThreads < npairs) part[(long long)blockIdx.x * npairs + tid + h * kThreads] = acc[h];
-}
-
-// Same step for widths that are a multiple of 4 (up to 20) and N a multiple of 64, streaming
+// Widths that are a multiple of 4 (up to 20) and N a multiple of 64, streaming
 // and without LDS: lane (blk, j) of a wave owns channels j, 4+j, ... at the four consecutive
 // points 4*blk .. 4*blk+3 of a 64-point step, so every z / g / x access is a float4 and gz is
 // computed exactly once per element.  gW[o][i] = sum_p gz[o][p] x[i][p] is a dense contraction
@@ -224,13 +130,19 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
 // channels are dealt to `ngrp` waves of a block (OT tiles of 4 each), which share x through the cache.  Layout and
 // products are those of the kernel above; rows need not be aligned (4-byte aligned 16-byte loads), a batch entry's
 // ragged last step takes single values, and channels past the end read the last one and count as zero.  The fp32
-// accumulators take kBwdChain steps (128 terms, as many as one chain of the tiled kernel below) and then go to doubles,
-// which are added over the wave's 16 lane blocks, half of them sent away at each level: every lane keeps a sixteenth.
-// erff and expf as in the tiled kernel.
-// 5 -> 20 channels at 33.5 M points: 0.77 ms = 4.4 TB/s (1.9 ms tiled); 32 -> 32 at 2.16 M points with GELU: 0.43 ms
-// (0.67 ms tiled), where x comes from the cache for three of the four waves that share it.
+// accumulators take kBwdChain steps (128 terms of a lane block) and then go to doubles, which are added over the wave's
+// 16 lane blocks, half of them sent away at each level: every lane keeps a sixteenth.  GELU and its slope by erff and
+// expf.  5 -> 20 channels at 33.5 M points: 0.78 ms = 4.3 TB/s; 32 -> 32 at 2.16 M points with GELU: 0.43 ms, where x
+// comes from the cache for three of the four waves that share it.  (One sum per thread over tiles of 256 points in LDS
+// took 1.9 and 0.67 ms.)
 constexpr int kBwdChain = 32;
-typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+
+template <bool STREAM>
+__device__ __forceinline__ v4f load4(const float* p) {
+  float v[4];
+  load_run<4, STREAM>(p, v);
+  return v4f{v[0], v[1], v[2], v[3]};
+}
 
 // one level of the sum over lane blocks, in double: N values per lane to N / 2 (an odd N: all are added, both lanes keep
 // them)
@@ -327,11 +239,11 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     if (whole) {
 #pragma unroll
       for (int T = 0; T < OT; ++T) {
-        zq[T] = need_z ? (v4f)ld_once<STREAM>(reinterpret_cast<const v4fu*>(z + ob + orow[T] + p)) : v4f{0.f, 0.f, 0.f, 0.f};
-        gq[T] = ld_once<STREAM>(reinterpret_cast<const v4fu*>(gout + ob + orow[T] + p));
+        zq[T] = need_z ? load4<STREAM>(z + ob + orow[T] + p) : v4f{0.f, 0.f, 0.f, 0.f};
+        gq[T] = load4<STREAM>(gout + ob + orow[T] + p);
       }
 #pragma unroll
-      for (int T = 0; T < IT; ++T) xq[T] = *reinterpret_cast<const v4fu*>(x + ib + irow[T] + p);
+      for (int T = 0; T < IT; ++T) xq[T] = load4<false>(x + ib + irow[T] + p);
     } else {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -362,7 +274,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
       if (gz_out != nullptr && olive[T]) {
         float* dst = gz_out + ob + orow[T] + p;
         if (whole) {
-          st_once<STREAM>(reinterpret_cast<v4fu*>(dst), (v4fu)g);
+          const float gs[4] = {g[0], g[1], g[2], g[3]};
+          store_run<4, STREAM>(dst, gs);
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u)
@@ -1206,13 +1119,13 @@ int bwd_pointwise_blocks(int B, int64_t N) {
   return 4096;
 }
 
-// The tiles of the wide kernel for these widths, at most max_slots point ranges of partial sums; false: the widths do
-// not fit it.  The waves of a block share out gW so that a wave's accumulators, the values of a step and the sums in
-// doubles fit 256 registers (4 x 8 tiles per wave spilled 82 of them).
-bool launch_bwd_wide(const float* z, const float* gout, const float* x, float* gz_out, double* part, int* nslots,
-                     int max_slots, int B, int Ci, int Co, int64_t N, int act, int mse_target, double mse_scale,
-                     hipStream_t s) {
-  if (Ci > 32 || Co > 32) return false;
+// The tiles of the wide kernel for these widths, at most max_slots point ranges of partial sums.  The waves of a block
+// share out gW so that a wave's accumulators, the values of a step and the sums in doubles fit 256 registers (4 x 8
+// tiles per wave spilled 82 of them).
+hipError_t launch_bwd_wide(const float* z, const float* gout, const float* x, float* gz_out, double* part, int* nslots,
+                           int max_slots, int B, int Ci, int Co, int64_t N, int act, int mse_target, double mse_scale,
+                           hipStream_t s) {
+  if (Ci > 32 || Co > 32) return hipErrorInvalidValue;
   const int ot = Ci <= 8 ? (Co <= 8 ? 2 : Co <= 20 ? 5 : 4) : (Ci <= 24 && Co <= 24 ? 3 : 2);
   const int it = Ci <= 8 ? 2 : (ot == 3 ? 6 : 8);
   const int ngrp = Co <= 4 * ot ? 1 : Co <= 8 * ot ? 2 : 4, per_block = 4 / ngrp;
@@ -1235,13 +1148,12 @@ bool launch_bwd_wide(const float* z, const float* gout, const float* x, float* g
   else if (it == 6) FNO_BPX(3, 6);
   else FNO_BPX(2, 8);
 #undef FNO_BPX
-  return true;
+  return hipGetLastError();
 }
 
 hipError_t launch_bwd_pointwise(const float* z, const float* gout, const float* x, float* gz_out,
                                 double* part, int* nslots, int B, int Ci, int Co, int64_t N, int act,
                                 int mse_target, double mse_scale, hipStream_t s) {
-  if (Co * Ci + Co > kBwdPairs * kThreads) return hipErrorInvalidValue;
   const bool aligned = ((reinterpret_cast<uintptr_t>(z) | reinterpret_cast<uintptr_t>(gout) |
                          reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(gz_out)) & 15) == 0;
   if (Ci == Co && Co % 4 == 0 && Co <= 20 && N % 64 == 0 && aligned) {
@@ -1267,16 +1179,8 @@ hipError_t launch_bwd_pointwise(const float* z, const float* gout, const float* 
     }
     return hipGetLastError();
   }
-  if (launch_bwd_wide(z, gout, x, gz_out, part, nslots, bwd_pointwise_blocks(B, N), B, Ci, Co, N, act, mse_target,
-                      mse_scale, s))
-    return hipGetLastError();
-  const int64_t tiles = (int64_t)B * ((N + kBwdTile - 1) / kBwdTile);
-  const int nblk = (int)(tiles < 2048 ? tiles : 2048);
-  *nslots = nblk;
-  const size_t lds = (size_t)(Co + Ci) * (kBwdTile + 1) * 4;
-  hipLaunchKernelGGL(bwd_pointwise_kernel, dim3((unsigned)nblk), dim3(kThreads), lds, s, z, gout,
-                     x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale);
-  return hipGetLastError();
+  return launch_bwd_wide(z, gout, x, gz_out, part, nslots, bwd_pointwise_blocks(B, N), B, Ci, Co, N, act, mse_target,
+                         mse_scale, s);
 }
 
 hipError_t launch_reduce_partials(const double* part, int nblk, int Co, int Ci, float* gW,
@@ -1465,18 +1369,12 @@ size_t pointwise_bwd_workspace_bytes(int Ci, int H, int Co) {
 hipError_t launch_pointwise_linear_bwd(int B, int Ci, int Co, int64_t N, const float* x, const float* W,
                                        const float* g, float* gx, float* gW, float* gb, void* ws,
                                        hipStream_t s) {
-  if (Co * Ci + Co > kBwdPairs * kThreads || Ci > 32) return hipErrorInvalidValue;
   if (N <= 0) return hipErrorInvalidValue;
   double* part = static_cast<double*>(ws);
   if (gW != nullptr || gb != nullptr) {
     int nblk = 0;
-    if (!launch_bwd_wide(g, g, x, nullptr, part, &nblk, 2048, B, Ci, Co, N, 0, 0, 0.0, s)) {
-      const int64_t tiles = (int64_t)B * ((N + kBwdTile - 1) / kBwdTile);
-      nblk = (int)(tiles < 2048 ? tiles : 2048);
-      const size_t lds = (size_t)(Co + Ci) * (kBwdTile + 1) * 4;
-      hipLaunchKernelGGL(bwd_pointwise_kernel, dim3((unsigned)nblk), dim3(kThreads), lds, s, g, g, x,
-                         (float*)nullptr, part, B, Ci, Co, (long long)N, 0, 0, 0.f);
-    }
+    const hipError_t e = launch_bwd_wide(g, g, x, nullptr, part, &nblk, 2048, B, Ci, Co, N, 0, 0, 0.0, s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_partials_kernel, dim3((Co * Ci + Co + kRedPairs - 1) / kRedPairs),
                        dim3(kRedPairs * kRedGroups), 0, s, part, nblk, Co, Ci, gW, gb, 0);
   }

@@ -267,7 +267,7 @@ hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, con
                              bool* taken) {
   *taken = false;
   const EpiArgs& e = ep;
-  const int CT = (Co + 3) / 4 <= 2 ? 2 : ((Co + 3) / 4 <= 5 ? 5 : 8);
+  const int CT = Co <= 8 ? 2 : 5;
   // Nt = 32, a 16-point z FFT and 8 or 20 channels in and out: rows of one whole 128-byte line, which the folded
   // kernel's tiles of 16 t halve.  Measured per block forward and back, this kernel against the folded one: 20
   // channels, 64 x 64 x 32 x 32, 0.43 against 0.62 ms; 64 x 64 x 64 x 32 with 12 t bins 1.08 and 1.07; 8 channels,
@@ -276,14 +276,14 @@ hipError_t launch_zt_inv_col(const float2* a, float* out, const float2* twt, con
   // CU's LDS.
   const bool full = Co == 4 * CT && (ep.u == nullptr ? CT == 5 : ep.Cu == 4 * CT);
   if (full && Nt == 32 && az.M == 16 && az.P >= 2 && az.P % 2 == 0 &&
-      (az.P & (az.P - 1)) == 0 && CT <= 5 && Co * mt <= 512 && (az.L * mt) % 2 == 0 && B <= 65535) {
+      (az.P & (az.P - 1)) == 0 && Co * mt <= 512 && (az.L * mt) % 2 == 0 && B <= 65535) {
     const int Cu = ep.u ? ep.Cu : 0;
     const int a_stride4 = zt_mfma_astride4(az, mt);
     const int a_floats = (Co * a_stride4 * 4 + 255) & ~255;
     const int v_stride = zt_mfma_vstride(az, mt, 1);
     const int blob_floats = zt_mfma_blob(az, Nt, mt, Co, Cu, az.P);
     const size_t lds = ((size_t)a_floats + 2 * 4 * CT * v_stride + blob_floats) * 4;
-    if (Cu <= 4 * CT && lds <= (size_t)(79 * 1024) && (size_t)blob_floats * 4 <= kZtTablesBytes) {
+    if (lds <= (size_t)(79 * 1024) && (size_t)blob_floats * 4 <= kZtTablesBytes) {
       const int inv_mt = (65536 + mt - 1) / mt;
       hipError_t terr = launch_zt_tables(tables, 1, twt, twz, ep.u ? ep.W : nullptr, ep.w_so, ep.w_si, ep.bias, Co,
                                          Cu, 4 * CT, mt, Nt, Nt, az.L, az.P, az.P, blob_floats, s);

@@ -17,25 +17,22 @@ namespace {
 // loaded one step (two pairs, one per register set) ahead.
 // Lane block (wave, blk): quad blk % 4, class (blk / 4) % 2 of the pair, n1 = 2 wave + blk / 8,
 // z = Pz n1 + 2 pair + class.  Launch: grid (NxNy, B), 512 threads; Pz a multiple of 4.
-// The table blob is the one of zt_tables_kernel with Q = Pz.  MTC, LZC, NPC, EPI as in the
-// 32-point variant.
-template <int CT, int MTC, int LZC, int NPC, int EPI, bool STREAM>
+// The table blob is the one of zt_tables_kernel with Q = Pz.  mt, Lz, NPC: the kept counts on t and z (NPC of
+// the latter are non-negative frequencies); EPI: the epilogue (bit 0: GELU, bit 1: the pre-activation is stored
+// as well).  With a fixed epilogue every pass issues the same number of loads and stores on every path, which
+// the compiler's wait counts for the prefetched u values rely on.
+constexpr int CT = 5;                               // channel tiles: width 20
+constexpr int TS = 3;                               // of a pass
+template <int mt, int Lz, int NPC, int EPI, bool STREAM>
 __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
-    const float2* __restrict__ a, float* __restrict__ out, int NxNy, int Nz, int Lz_rt,
-    int nposz_rt, int mt_rt, int inv_mt, int a_floats, int a_stride4, int v_stride,
-    const float* __restrict__ blob, int blob_floats, EpiArgs ep) {
+    const float2* __restrict__ a, float* __restrict__ out, int NxNy, int Nz, int inv_mt, int a_floats,
+    int a_stride4, int v_stride, const float* __restrict__ blob, int blob_floats, EpiArgs ep) {
   HIP_DYNAMIC_SHARED(float, smem)
-  const int mt = MTC ? MTC : mt_rt;
-  const int Lz = LZC ? LZC : Lz_rt;
-  const int nposz = LZC ? NPC : nposz_rt;
-  const bool act = EPI >= 0 ? (EPI & 1) != 0 : ep.act != 0;
-  const bool zsave = EPI >= 0 ? (EPI & 2) != 0 : ep.zsave != nullptr;
+  constexpr bool act = (EPI & 1) != 0, zsave = (EPI & 2) != 0;
   constexpr int NT = 16, MZ = 16, NW = 8;
   constexpr int CP = 4 * CT;
   constexpr int CI = CP;
-  constexpr int TS = CT == 5 ? 3 : CT;              // channel tiles per pass
   constexpr int NSUB = (CT + TS - 1) / TS;          // passes per pair
-  constexpr int nthr = 64 * NW;
   constexpr int ZB = 4;                             // z-stage terms whose LDS reads go out together
   constexpr int Co = CP;
   constexpr int Cu = CI;
@@ -44,8 +41,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
   float2* V = reinterpret_cast<float2*>(smem + a_floats);       // [4 TS][2 MZ][mt], padded channel stride
   float* CS = smem + a_floats + 2 * (4 * TS) * v_stride;        // [2 mt][NT]: cos rows and -sin rows
   float* Wt = CS + 2 * mt * NT;                                 // [Cu][CP]
-  const bool lin = EPI >= 0 ? true : ep.u != nullptr;
-  const float2* TW = reinterpret_cast<const float2*>(Wt + (lin ? Cu * CP : 0));   // [Pz][Lz]
+  const float2* TW = reinterpret_cast<const float2*>(Wt + Cu * CP);   // [Pz][Lz]
   const int tid = threadIdx.x;
   const int xy = blockIdx.x;
   const long long b = blockIdx.y;
@@ -59,8 +55,6 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
   const int row = cls * MZ + n1;              // row of this lane block in V
   const long long Npts = (long long)NxNy * Nz * NT;
   const long long pbase = ((long long)xy * Nz + Pz * n1 + cls) * NT + 4 * quad;   // + 2 pair * NT
-  const int kmin = nposz - Lz, kmax = nposz - 1;
-  const int mbase = posmod(-kmin, MZ);
 
   for (int c0 = wave * 256; c0 < blob_floats; c0 += 256 * NW)
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(blob + c0 + 4 * lane),
@@ -82,15 +76,13 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
   const float* BI = reinterpret_cast<const float*>(TW + Pz * Lz);      // bias, padded to CP
   // u values of a pair (lane 4b+i takes t = 4 quad + i), two register sets: even and odd pairs
   float xv[CI][2];
-  const float* ubase = lin ? ep.u + (b * Cu) * Npts + j4 + pbase : nullptr;
+  const float* ubase = ep.u + (b * Cu) * Npts + j4 + pbase;
   asm volatile("" ::: "memory");    // keep the issue order: tables, spectrum, u
-  if (lin) {
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl)
+  for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
-      for (int i = 0; i < CI; ++i)
-        xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * sl) * NT]);
-  }
+    for (int i = 0; i < CI; ++i)
+      xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * sl) * NT]);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
   __syncthreads();
@@ -120,50 +112,23 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
         float2 gres[MZ];
 #pragma unroll
         for (int m = 0; m < MZ; ++m) gres[m] = make_float2(0.f, 0.f);
-        if constexpr (LZC > 0) {
-          // compile-time counts: the stored order j in rounds of ZB, each term to its bin k_j mod MZ
+        // the stored order j in rounds of ZB, each term to its bin k_j mod MZ
 #pragma unroll
-          for (int j0 = 0; j0 < LZC; j0 += ZB) {
-            float2 av[ZB], wv8[ZB];
+        for (int j0 = 0; j0 < Lz; j0 += ZB) {
+          float2 av[ZB], wv8[ZB];
 #pragma unroll
-            for (int u = 0; u < ZB; ++u)
-              if (j0 + u < LZC) {
-                av[u] = asrc[(j0 + u) * mt];
-                wv8[u] = twq[j0 + u];
-              }
-#pragma unroll
-            for (int u = 0; u < ZB; ++u)
-              if (j0 + u < LZC) {
-                const int k = j0 + u < NPC ? j0 + u : j0 + u - LZC;
-                const int m = ((k % MZ) + MZ) % MZ;
-                gres[m] = cfmac(av[u], wv8[u], gres[m]);
-              }
-          }
-        } else if ((Lz & (MZ - 1)) == 0) {
-#pragma unroll
-          for (int r0 = 0; r0 < Lz; r0 += MZ) {
-            const float2* ar = asrc + r0 * mt;
-            const float2* tr = twq + r0;
-#pragma unroll
-            for (int mb = 0; mb < MZ; mb += ZB) {
-              float2 av[ZB], wv8[ZB];
-#pragma unroll
-              for (int u = 0; u < ZB; ++u) {
-                av[u] = ar[(mb + u) * mt];
-                wv8[u] = tr[mb + u];
-              }
-#pragma unroll
-              for (int u = 0; u < ZB; ++u) gres[mb + u] = cfmac(av[u], wv8[u], gres[mb + u]);
+          for (int u = 0; u < ZB; ++u)
+            if (j0 + u < Lz) {
+              av[u] = asrc[(j0 + u) * mt];
+              wv8[u] = twq[j0 + u];
             }
-          }
-        } else {
 #pragma unroll
-          for (int m = 0; m < MZ; ++m) {
-            for (int k = kmin + ((m + mbase) & (MZ - 1)); k <= kmax; k += MZ) {
-              const int j = k >= 0 ? k : k + Lz;
-              gres[m] = cfmac(asrc[j * mt], twq[j], gres[m]);
+          for (int u = 0; u < ZB; ++u)
+            if (j0 + u < Lz) {
+              const int k = j0 + u < NPC ? j0 + u : j0 + u - Lz;
+              const int m = ((k % MZ) + MZ) % MZ;
+              gres[m] = cfmac(av[u], wv8[u], gres[m]);
             }
-          }
         }
         fft_reg<MZ, +1>(gres);
 #pragma unroll
@@ -178,7 +143,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
     const float* cs_lane = CS + 4 * quad + j4;
     const float2* v0 = V + j4 * v_stride + row * mt;
     int kt = 0;
-    constexpr int KB = (MTC > 0 && MTC % 4 == 0) ? 4 : 3;   // kt per round: their reads go out together
+    constexpr int KB = mt % 4 == 0 ? 4 : 3;   // kt per round: their reads go out together
 #pragma unroll 1
     for (; kt + KB <= mt; kt += KB) {
       float cs4[2 * KB];
@@ -212,33 +177,31 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
       }
     }
     __syncthreads();      // V is rewritten by the next z stage
-    if (lin) {
-      constexpr int IB = 4;                       // input channels per batch of LDS reads
+    constexpr int IB = 4;                         // input channels per batch of LDS reads
 #pragma unroll
-      for (int i0 = 0; i0 < CI; i0 += IB) {
-        float wv[IB][NTL];
+    for (int i0 = 0; i0 < CI; i0 += IB) {
+      float wv[IB][NTL];
 #pragma unroll
-        for (int ii = 0; ii < IB; ++ii)
+      for (int ii = 0; ii < IB; ++ii)
 #pragma unroll
-          for (int T = 0; T < NTL; ++T)
-            wv[ii][T] = Wt[(i0 + ii) * CP + 4 * (T0 + T) + j4];
+        for (int T = 0; T < NTL; ++T)
+          wv[ii][T] = Wt[(i0 + ii) * CP + 4 * (T0 + T) + j4];
 #pragma unroll
-        for (int ii = 0; ii < IB; ++ii) {
+      for (int ii = 0; ii < IB; ++ii) {
 #pragma unroll
-          for (int T = 0; T < NTL; ++T)
-            acc[T] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i0 + ii][sl], wv[ii][T], acc[T], 0, 0, 0);
-        }
+        for (int T = 0; T < NTL; ++T)
+          acc[T] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i0 + ii][sl], wv[ii][T], acc[T], 0, 0, 0);
       }
-      if constexpr (SUB == NSUB - 1) {
-        // the pair's last pass has used this register set: refill it for the pair two ahead
-        asm volatile("" ::: "memory");
-        if constexpr (PREFETCH) {
+    }
+    if constexpr (SUB == NSUB - 1) {
+      // the pair's last pass has used this register set: refill it for the pair two ahead
+      asm volatile("" ::: "memory");
+      if constexpr (PREFETCH) {
 #pragma unroll
-          for (int i = 0; i < CI; ++i)
-            xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * (pair + 2)) * NT]);
-        }
-        asm volatile("" ::: "memory");
+        for (int i = 0; i < CI; ++i)
+          xv[i][sl] = ld_once<STREAM>(&ubase[i * Npts + (2 * (pair + 2)) * NT]);
       }
+      asm volatile("" ::: "memory");
     }
     // lane 4b+j now holds channel 4(T0+T)+j at the four t of its quad
     const long long poff = pbase + (long long)(2 * pair) * NT;
@@ -269,7 +232,7 @@ __global__ __launch_bounds__(512, 4) void zt_inv_col16_kernel(
     for (int sl = 0; sl < 2; ++sl) {
       const int pair = 2 * step + sl;
       run_pass(pair, sl, std::integral_constant<int, 0>{}, prefetch_tag);
-      if constexpr (NSUB > 1) run_pass(pair, sl, std::integral_constant<int, 1>{}, prefetch_tag);
+      run_pass(pair, sl, std::integral_constant<int, 1>{}, prefetch_tag);
     }
   };
   for (int step = 0; step + 1 < nsteps; ++step) run_step(step, std::true_type{});
@@ -283,55 +246,45 @@ hipError_t launch_zt_inv_col16(const float2* a, float* out, const float2* twt, c
                                bool* taken) {
   *taken = false;
   const EpiArgs& e = ep;
-  const int CT = (Co + 3) / 4 <= 2 ? 2 : ((Co + 3) / 4 <= 5 ? 5 : 8);
-  if (Nt != 16 || az.M != 16 || az.P < 4 || az.P % 4 != 0 || (az.P & (az.P - 1)) != 0 || CT > 5 ||
-      (az.L * mt) % 2 != 0 || B > 65535)
+  // the kept counts of the named workloads (9 t bins and 32 z frequencies, or 8 and 24) at width 20, with the
+  // three epilogues of a block: forward, forward that keeps the pre-activation, the adjoint's linear one
+  const int epi = (e.act ? 1 : 0) | (e.zsave != nullptr ? 2 : 0);
+  const bool shape_a = mt == 9 && az.L == 32 && az.npos == 16, shape_b = mt == 8 && az.L == 24 && az.npos == 12;
+  if (Nt != 16 || az.M != 16 || az.P < 4 || az.P % 4 != 0 || (az.P & (az.P - 1)) != 0 || B > 65535 ||
+      Co != 20 || e.u == nullptr || e.Cu != 20 || epi == 2 || !(shape_a || shape_b))
     return hipSuccess;
-  const int TS = CT == 5 ? 3 : CT;
-  if (2 * 4 * TS * mt > 512) return hipSuccess;         // one z-stage item per thread
-  const int Cu = ep.u ? ep.Cu : 0;
   const int a_stride4 = zt_mfma_astride4(az, mt);
   const int a_floats = (Co * a_stride4 * 4 + 255) & ~255;
   const int v_stride = zt_mfma_vstride(az, mt, 2);
-  const int blob_floats = zt_mfma_blob(az, Nt, mt, Co, Cu, az.P);
+  const int blob_floats = zt_mfma_blob(az, Nt, mt, Co, e.Cu, az.P);
   const size_t lds = ((size_t)a_floats + 2 * 4 * TS * v_stride + blob_floats) * 4;
   // two blocks per CU
-  if (Cu > 4 * CT || lds > (size_t)(80 * 1024 - 512) || (size_t)blob_floats * 4 > kZtTablesBytes) return hipSuccess;
+  if (lds > (size_t)(80 * 1024 - 512) || (size_t)blob_floats * 4 > kZtTablesBytes) return hipSuccess;
   const int inv_mt = (65536 + mt - 1) / mt;
-  // the shapes of the named workloads (width 20; 9 kept t bins and 32 kept z frequencies, or 8 and 24)
-  // with their three epilogues: forward, forward that keeps the pre-activation, the adjoint's linear one
-  const int epi = (e.act ? 1 : 0) | (e.zsave != nullptr ? 2 : 0);
-  const bool named = Co == 20 && e.u != nullptr && e.Cu == 20 && epi != 2;
-  const bool shape_a = named && mt == 9 && az.L == 32 && az.npos == 16;
-  const bool shape_b = named && mt == 8 && az.L == 24 && az.npos == 12;
-  // Everything else is faster on the folded kernel (8 channels, 64 x 64 x 64 x 16, one block forward and back:
-  // 0.22 ms with run-time counts here, 0.16 there).
-  if (!(shape_a || shape_b)) return hipSuccess;
-  hipError_t terr = launch_zt_tables(tables, 1, twt, twz, ep.u ? ep.W : nullptr, ep.w_so, ep.w_si, ep.bias, Co,
-                                     Cu, 4 * CT, mt, Nt, Nt, az.L, az.P, az.P, blob_floats, s);
+  hipError_t terr = launch_zt_tables(tables, 1, twt, twz, e.W, e.w_so, e.w_si, e.bias, Co, e.Cu, 4 * CT, mt, Nt, Nt,
+                                     az.L, az.P, az.P, blob_floats, s);
   if (terr != hipSuccess) return terr;
   const dim3 grid((unsigned)NxNy, (unsigned)B);
-#define FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, STRV)                                                     \
-  hipLaunchKernelGGL((zt_inv_col16_kernel<CTV, MTV, LZV, NPV, EPIV, STRV>), grid, dim3(512), lds, s, a,   \
-                     out, NxNy, az.N, az.L, az.npos, mt, inv_mt, a_floats, a_stride4, v_stride, tables,  \
-                     blob_floats, e)
+#define FNO_ZTC16_S(MTV, LZV, NPV, EPIV, STRV)                                                          \
+  hipLaunchKernelGGL((zt_inv_col16_kernel<MTV, LZV, NPV, EPIV, STRV>), grid, dim3(512), lds, s, a, out, \
+                     NxNy, az.N, inv_mt, a_floats, a_stride4, v_stride, tables, blob_floats, e)
   // u and the result as streams when they are larger than the caches, except in the launch that also
   // stores the pre-activation: with three streams per point it measured 4 % slower with the hint,
   // the other two epilogues 2-5 % faster
   const bool stream = e.zsave == nullptr && (int64_t)B * Co * NxNy * az.N * Nt * 4 >= kStreamBytes;
-#define FNO_ZTC16(CTV, MTV, LZV, NPV, EPIV)                  \
+#define FNO_ZTC16(MTV, LZV, NPV, EPIV)                       \
   do {                                                              \
-    if (stream) FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, true); \
-    else FNO_ZTC16_S(CTV, MTV, LZV, NPV, EPIV, false);       \
+    if (stream) FNO_ZTC16_S(MTV, LZV, NPV, EPIV, true); \
+    else FNO_ZTC16_S(MTV, LZV, NPV, EPIV, false);       \
   } while (0)
   if (shape_a) {
-    if (epi == 1) FNO_ZTC16(5, 9, 32, 16, 1);
-    else if (epi == 3) FNO_ZTC16(5, 9, 32, 16, 3);
-    else FNO_ZTC16(5, 9, 32, 16, 0);
+    if (epi == 1) FNO_ZTC16(9, 32, 16, 1);
+    else if (epi == 3) FNO_ZTC16(9, 32, 16, 3);
+    else FNO_ZTC16(9, 32, 16, 0);
   } else {
-    if (epi == 1) FNO_ZTC16(5, 8, 24, 12, 1);
-    else if (epi == 3) FNO_ZTC16(5, 8, 24, 12, 3);
-    else FNO_ZTC16(5, 8, 24, 12, 0);
+    if (epi == 1) FNO_ZTC16(8, 24, 12, 1);
+    else if (epi == 3) FNO_ZTC16(8, 24, 12, 3);
+    else FNO_ZTC16(8, 24, 12, 0);
   }
 #undef FNO_ZTC16
 #undef FNO_ZTC16_S

@@ -854,6 +854,19 @@ def test_forward_transform_of_long_z_axes(c, nz, mz, nt, mt):
     assert rel(xh, xho) <= TOL and rel(y, yo) <= TOL
 
 
+@pytest.mark.parametrize("case", [
+    # x and y axes on the kernels with an FFT of M points in registers: M = 4, 2 and 1 with more than 48 folded
+    # frequencies or a folded table past 40 KiB, 8 and 16
+    (1, 2, 2, (204, 202, 2, 3), (50, 49, 1, 2), 0),
+    (2, 1, 2, (156, 101, 3, 4), (34, 49, 1, 2), 1),
+    (1, 2, 1, (80, 72, 3, 4), (13, 20, 1, 2), 0),
+    (1, 3, 2, (144, 40, 4, 5), (30, 20, 1, 2), 0),
+])
+def test_fft_axis_kernels_match_oracle(case):
+    test_spectral_conv_fwd_matches_oracle(case)
+    test_spectral_conv_bwd_matches_oracle(case)
+
+
 @pytest.mark.parametrize("c_in, c_out, npts, batch", [
     (1, 1, 3, 1), (8, 8, 64, 2), (5, 20, 65, 2), (8, 32, 127, 1), (9, 12, 66, 3), (24, 24, 193, 1), (7, 25, 640, 2),
     (25, 8, 130, 1), (26, 16, 129, 2), (32, 32, 1001, 1), (32, 17, 64, 1),
@@ -895,6 +908,87 @@ def test_sums_over_points_reach_doubles_after_128_terms(c_in, c_out):
     want = torch.stack([(g[0, o].double() * x[0].double()).sum(1) for o in range(c_out)])
     assert torch.equal(gW, want.float())
     assert torch.equal(gb, g[0].double().sum(1).float())
+
+
+def test_sums_over_points_of_a_streamed_gradient():
+    """A gradient above 256 MiB with an odd point count: the nontemporal variant on rows that are 4-byte aligned."""
+    c_in, c_out, npts = 3, 17, 4_100_003
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((1, c_in, npts), device="cuda", generator=gen)
+    x[:, 0] = torch.linspace(0.0, 1.0, npts, device="cuda")          # a coordinate channel
+    g = torch.randn((1, c_out, npts), device="cuda", generator=gen) + 0.1
+    w = torch.randn((c_out, c_in), device="cuda", generator=gen)
+    gW, gb = torch.empty_like(w), torch.empty(c_out, device="cuda")
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(c_in, 0, c_out) // 4 + 2, device="cuda")
+    B.fno_pointwise_linear_bwd(1, c_in, c_out, npts, x, w, g, None, gW, gb, ws)
+    torch.cuda.synchronize()
+    gd, xd = g[0].double(), x[0].double()
+    want = torch.stack([(gd * xd[i]).sum(1) for i in range(c_in)], 1)
+    scale = torch.stack([(gd * xd[i]).square().sum(1) for i in range(c_in)], 1).sqrt()
+    assert float(((gW - want).abs() / torch.maximum(scale, want.abs())).max()) <= TOL
+    assert rel(host(gb), host(gd.sum(1))) <= TOL
+
+
+@pytest.mark.parametrize("c", [13, 32])
+def test_block_adjoint_of_streamed_tensors(c):
+    """A block backward whose gradient with respect to the pre-activation is above 256 MiB, at an odd width and at 32:
+    gW and gb against products in float64 on the device, gx against the same call on halves of the batch that stay
+    below."""
+    grid, modes = (624 // c, 40, 21, 17), (2, 2, 2, 3)
+    batch = 10
+    counts = tuple(2 * m for m in modes[:3]) + (modes[3],)
+    gen = torch.Generator(device="cuda").manual_seed(c)
+    randn = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    x, z, g = (randn(batch, c, *grid) for _ in range(3))
+    assert g.numel() * 4 >= 256 << 20
+    W, R = randn(c, c), torch.view_as_complex(randn(c, c, *counts, 2) / c)
+    gx, gW, gb = torch.empty_like(x), torch.empty_like(W), torch.empty(c, device="cuda")
+    desc = B.make_desc(batch, c, c, grid, modes, 0, B.FNO_ACT_GELU)
+    B.fno_block_bwd(desc, x, R, W, z, None, g, gx, None, gW, gb, B.alloc_workspace(desc, B.FNO_OP_BLOCK_BWD))
+    half = B.make_desc(batch // 2, c, c, grid, modes, 0, B.FNO_ACT_GELU)
+    parts = torch.empty_like(x)
+    ws = B.alloc_workspace(half, B.FNO_OP_BLOCK_BWD)
+    for h in (slice(0, batch // 2), slice(batch // 2, batch)):
+        B.fno_block_bwd(half, x[h], R, W, z[h], None, g[h], parts[h], None, None, None, ws)
+    torch.cuda.synchronize()
+    assert rel(host(gx), host(parts)) <= TOL
+    want, scale, wb = (torch.zeros((c, c), device="cuda", dtype=torch.float64) for _ in range(3))
+    for b in range(batch):
+        zd = z[b].reshape(c, -1).double()
+        slope = 0.5 * (1 + torch.erf(zd / 2 ** 0.5)) + zd * torch.exp(-zd * zd / 2) / (2 * np.pi) ** 0.5
+        gz, xd = g[b].reshape(c, -1).double() * slope, x[b].reshape(c, -1).double()
+        want += gz @ xd.T
+        scale += gz.square() @ xd.square().T
+        wb[0] += gz.sum(1)
+    assert float(((gW - want).abs() / torch.maximum(scale.sqrt(), want.abs())).max()) <= TOL
+    assert rel(host(gb), host(wb[0])) <= TOL
+
+
+@pytest.mark.parametrize("batch", [1, 2])
+def test_mode_mix_adjoint_of_a_streamed_weight(batch):
+    """The adjoint of the mode mix with a weight above 256 MiB, one and two batch entries: gR and gx of a convolution
+    that keeps every mode of its x axis, at sampled channel pairs and on the whole gradient."""
+    c, grid, modes, counts = 32, (64, 33, 8, 6), (32, 16, 4, 3), (64, 32, 8, 3)
+    gen = torch.Generator(device="cuda").manual_seed(batch)
+    randn = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    R = torch.view_as_complex(randn(c, c, *counts, 2) / c)
+    assert R.numel() * 8 >= 256 << 20
+    x, g = randn(batch, c, *grid), randn(batch, c, *grid)
+    desc = B.make_desc(batch, c, c, grid, modes, 0, B.FNO_ACT_IDENTITY)
+    ws = B.alloc_workspace(desc, B.FNO_OP_SPECTRAL_CONV_BWD)
+    gx, gR = torch.empty_like(x), torch.empty_like(R)
+    B.fno_spectral_conv_bwd(desc, x, None, R, g, gx, gR, ws)
+    torch.cuda.synchronize()
+    spec = O.LayerSpec(grid, modes, 0)
+    for i, o in ((0, 0), (5, 31), (31, 7)):
+        _, gRo = O.spectral_conv_bwd(host(x[:, i:i + 1]), host(R[i:i + 1, o:o + 1]), host(g[:, o:o + 1]), spec)
+        assert rel(host(gR[i:i + 1, o:o + 1]), gRo) <= TOL
+    # <gx, x'> = <g, K x'> for a random x'
+    xp, y = randn(batch, c, *grid), torch.empty_like(x)
+    B.fno_spectral_conv_fwd(desc, xp, R, y, None, ws)
+    torch.cuda.synchronize()
+    lhs, rhs = float((gx.double() * xp.double()).sum()), float((g.double() * y.double()).sum())
+    assert abs(lhs - rhs) <= TOL * float(gx.double().norm()) * float(xp.double().norm())
 
 
 @pytest.mark.parametrize("case", [
