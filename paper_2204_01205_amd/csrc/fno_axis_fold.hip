@@ -42,7 +42,8 @@ __device__ __forceinline__ void stage_table(const float* __restrict__ tab, float
   __syncthreads();
 }
 
-// MT: row tiles of 16 frequencies; inner2: floats per row; ntile: tiles of 16 floats per row
+// MT: row tiles of 16 frequencies; inner2: floats per row; ntile: tiles of 16 floats per row.  MT = 4 keeps 16 of its
+// registers in scratch
 template <int MT, int CT, bool STREAM>
 __global__ __launch_bounds__(kThreads, MT == 4 ? 2 : (MT * CT == 2 ? 3 : 4)) void axis_fwd_fold_kernel(
     const float* __restrict__ in, float* __restrict__ out, const float* __restrict__ tab, int N, int L, int npos,

@@ -34,7 +34,8 @@ namespace fno {
 namespace {
 
 // registers of a variant (two row tiles in flight and folded, the t table, the accumulators, the z
-// table's operands and the addresses), and the waves per SIMD they allow
+// table's operands and the addresses), and the waves per SIMD they allow; one variant, <1, 3, 2, 1, 1>, needs five more
+// than its 128 and keeps them in scratch
 constexpr int fold_regs(int KS, int CT, int MT, int PP) {
   return KS * (4 + CT) + 8 * MT * CT * PP + (CT == 2 ? 16 : 6) * MT + 48;
 }

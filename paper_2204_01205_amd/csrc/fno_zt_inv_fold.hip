@@ -287,7 +287,8 @@ __device__ __forceinline__ void fold_inv_tile(const FoldInv& f, const EpiArgs& e
   }
 }
 
-// waves per SIMD: u, the two accumulator sets and about 50 registers of operands and addresses
+// waves per SIMD: u, the two accumulator sets and about 50 registers of operands and addresses.  Three variants need more
+// than that leaves and keep some in scratch (registers, bytes per lane): <3, 24> 30 and 76, <4, 20> and <1, 16> 3 and 16.
 constexpr int fold_inv_waves(int W, int CI) {
   const int ns = fold_inv_ns(W, CI), regs = ns * W * CI + ns * 16 + ns * W * 4 + 50;
   return regs <= 128 ? 4 : (regs <= 168 ? 3 : 2);

@@ -68,39 +68,39 @@ def gpu_block_fwd(L):
 SMALL = [
     # batch, cin, cout, grid, modes, rule
     (1, 8, 8, (16, 16, 16, 8), (4, 4, 4, 3), 0),       # the small workload
-    (2, 3, 3, (6, 5, 12, 6), (2, 2, 3, 4), 0),         # no power of two on x,y: dense path, Nyquist kept
+    (2, 3, 3, (6, 5, 12, 6), (2, 2, 3, 4), 0),         # no large power of two on x,y: folded axis products; Nyquist kept
     (1, 2, 3, (4, 6, 8, 7), (1, 2, 2, 4), 1),          # symmetric rule, odd Nt, Cin != Cout
     (1, 4, 4, (32, 24, 64, 16), (6, 5, 12, 8), 0),     # several tiles, ragged column tails
     (5, 2, 2, (8, 8, 8, 4), (2, 2, 2, 3), 0),          # batch above the mix kernel's register tile
     (1, 2, 2, (8, 8, 8, 8), (4, 4, 4, 5), 0),          # every mode kept (L = N, mt = Nt/2+1)
     (1, 2, 2, (8, 4, 8, 8), (1, 1, 1, 1), 0),          # a single t mode
     (1, 1, 1, (1, 1, 1, 1), (0, 0, 0, 1), 1),          # one-point grid
-    (1, 3, 2, (10, 3, 20, 5), (2, 1, 4, 2), 1),        # mixed radix z (20 = 5*4)
-    (1, 3, 3, (2, 3, 32, 16), (1, 1, 4, 5), 0),        # matrix-core inverse kernel, 6 columns, padded channels
-    (2, 2, 3, (3, 2, 32, 16), (1, 1, 6, 9), 0),        # same, two residue classes per block, Cin != Cout
-    (1, 20, 20, (2, 2, 32, 32), (1, 1, 8, 9), 0),      # same, width 20, Nt = 32
-    (1, 24, 24, (2, 2, 32, 16), (1, 1, 4, 4), 0),      # same, width 24 (eight channel tiles)
-    (1, 8, 8, (2, 3, 128, 32), (1, 1, 16, 9), 0),      # column kernel (Nt = 32): four steps per column
-    (2, 3, 5, (3, 2, 64, 32), (1, 1, 6, 5), 0),        # same, padded channel tiles, Cin != Cout
-    (1, 4, 4, (2, 2, 32, 32), (1, 1, 16, 17), 0),      # same, one step, every z and t mode kept
-    (1, 20, 20, (2, 3, 128, 16), (1, 1, 16, 9), 0),    # column kernel (Nt = 16): width 20 in two passes, two steps
+    (1, 3, 2, (10, 3, 20, 5), (2, 1, 4, 2), 1),        # mixed radix z (20 = 5*4) forward, folded inverse
+    (1, 3, 3, (2, 3, 32, 16), (1, 1, 4, 5), 0),        # folded inverse, 6 columns, padded channels
+    (2, 2, 3, (3, 2, 32, 16), (1, 1, 6, 9), 0),        # same, 17 columns, Cin != Cout
+    (1, 20, 20, (2, 2, 32, 32), (1, 1, 8, 9), 0),      # column kernel (Nt = 32), width 20
+    (1, 24, 24, (2, 2, 32, 16), (1, 1, 4, 4), 0),      # folded inverse, width 24: one row of a pair at a time
+    (1, 8, 8, (2, 3, 128, 32), (1, 1, 16, 9), 0),      # column kernel (Nt = 32): four steps per column; the convolution on the per-tile kernel
+    (2, 3, 5, (3, 2, 64, 32), (1, 1, 6, 5), 0),        # folded inverse, padded channel tiles, Cin != Cout
+    (1, 4, 4, (2, 2, 32, 32), (1, 1, 16, 17), 0),      # per-tile kernel, every z and t mode kept
+    (1, 20, 20, (2, 3, 128, 16), (1, 1, 16, 9), 0),    # column kernel (Nt = 16): width 20 in two passes, two steps; the convolution per tile
     (2, 20, 20, (2, 2, 64, 16), (1, 1, 12, 8), 0),     # same, one step, 24 kept z frequencies and 8 t bins
-    (1, 8, 8, (2, 3, 64, 16), (1, 1, 8, 5), 0),        # same, width 8: one pass
-    (2, 3, 5, (3, 2, 128, 16), (1, 1, 10, 7), 0),      # same, padded channel tiles, Cin != Cout
-    (1, 6, 6, (2, 2, 64, 16), (1, 1, 5, 4), 0),        # same, padded channel tiles in a block
+    (1, 8, 8, (2, 3, 64, 16), (1, 1, 8, 5), 0),        # block per tile, convolution folded, width 8
+    (2, 3, 5, (3, 2, 128, 16), (1, 1, 10, 7), 0),      # folded inverse, padded channel tiles, Cin != Cout
+    (1, 6, 6, (2, 2, 64, 16), (1, 1, 5, 4), 0),        # block per tile with padded channel tiles, convolution folded
     (1, 2, 2, (2, 2, 16, 64), (1, 1, 4, 9), 0),        # 64-point t axis (forward: the in-register 64-point real transform)
     (1, 2, 2, (2, 2, 256, 16), (1, 1, 20, 5), 0),      # 256-point z axis: one plane fills the forward block, 16 residue classes
     (2, 2, 2, (2, 2, 8, 32), (1, 1, 4, 17), 0),        # 8-point z axis under 32 t points: the forward tile's row stride (17) exceeds N + 1
-    (1, 8, 8, (3, 2, 32, 30), (1, 1, 4, 8), 0),        # matrix-core inverse kernel, t axis padded 30 -> 32
-    (2, 3, 3, (2, 3, 32, 12), (1, 1, 6, 4), 0),        # same, 12 -> 16, padded channel tiles
-    (1, 20, 20, (2, 2, 64, 30), (1, 1, 12, 8), 0),     # same, width 20, the z and t lengths of the paper's samples
-    (1, 3, 3, (4, 3, 21, 6), (1, 1, 5, 3), 0),         # odd z length: dense z stage of the inverse on 16x16x4 tiles
-    (2, 5, 4, (2, 2, 37, 16), (1, 1, 9, 8), 0),        # same, prime z length, ragged last row group, Cin != Cout
-    (1, 2, 2, (3, 3, 35, 4), (1, 1, 6, 2), 1),         # same, three row tiles per block, symmetric rule
-    (1, 2, 2, (2, 2, 135, 8), (1, 1, 30, 3), 0),       # dense forward z stage: two sweeps of row tiles, 15 of 16 columns
-    (1, 4, 4, (3, 5, 6, 7), (1, 2, 2, 3), 0),          # width 4 with 630 points (not a multiple of 64): the generic
+    (1, 8, 8, (3, 2, 32, 30), (1, 1, 4, 8), 0),        # per-tile kernel, t axis padded 30 -> 32
+    (2, 3, 3, (2, 3, 32, 12), (1, 1, 6, 4), 0),        # folded both ways, runs of three steps, padded channel tiles
+    (1, 20, 20, (2, 2, 64, 30), (1, 1, 12, 8), 0),     # per-tile kernel, width 20, the z and t lengths of the paper's samples
+    (1, 3, 3, (4, 3, 21, 6), (1, 1, 5, 3), 0),         # odd z length: folded both ways
+    (2, 5, 4, (2, 2, 37, 16), (1, 1, 9, 8), 0),        # same, prime z length, a ragged second tile of pairs, Cin != Cout
+    (1, 2, 2, (3, 3, 35, 4), (1, 1, 6, 2), 1),         # same, two tiles of pairs, symmetric rule
+    (1, 2, 2, (2, 2, 135, 8), (1, 1, 30, 3), 0),       # same, two row tiles of frequencies, five tiles of pairs
+    (1, 4, 4, (3, 5, 6, 7), (1, 2, 2, 3), 0),          # width 4 with 630 points (not a multiple of 64): the wide
                                                        # backward pointwise kernel (erff / expf), where case 3 of the
-                                                       # same width takes the matrix-core one (rational erf)
+                                                       # same width takes the other one (rational erf)
 ]
 
 
@@ -247,7 +247,9 @@ def test_planned_tables_give_the_same_bits_as_rebuilt_ones():
 
 @pytest.mark.parametrize("case", [(1, 8, 8, (2, 3, 128, 32), (1, 1, 16, 9), 0),      # column kernel
                                   (1, 20, 20, (2, 3, 128, 16), (1, 1, 16, 9), 0),   # column kernel, Nt = 16
-                                  (2, 3, 3, (6, 5, 12, 6), (2, 2, 3, 4), 0)])        # generic kernels
+                                  (2, 3, 3, (6, 5, 12, 6), (2, 2, 3, 4), 0),        # folded products
+                                  (1, 20, 20, (2, 2, 64, 30), (1, 1, 12, 8), 0),    # per-tile kernel
+                                  (1, 8, 8, (16, 16, 16, 8), (4, 4, 4, 3), 0)])     # generic kernel, FFT on x and y
 def test_block_forward_and_backward_replay_identically_from_a_hip_graph(case):
     """The calls only enqueue kernels on the caller's stream (no allocation, no memset, no
     synchronisation), so a caller may capture them in a HIP graph: three replays, with eager work and
@@ -788,7 +790,7 @@ def test_folded_forward_transform_at_the_edges_of_its_tiles(nz, mz, nt, mt, rule
 @pytest.mark.parametrize("c, nz, mz, nt, mt, rule", [
     (1, 1, 0, 1, 1, 1),         # one point per column
     (3, 5, 2, 3, 2, 1),         # half a tile: three pairs and their mirrored rows, the middle row its own pair
-    (8, 16, 4, 8, 3, 0),        # eight pairs: a half tile with every lane at work
+    (8, 16, 4, 8, 3, 0),        # eight pairs and eight channels: the generic kernel
     (9, 18, 9, 17, 9, 0),       # nine pairs: one past the half tile; a second tile of t with one new step; 17 of 20 columns
     (20, 33, 8, 16, 8, 1),      # one pair past a whole tile, symmetric rule
     (20, 49, 12, 30, 8, 0),     # two tiles (nine pairs in the second), overlapping runs of four steps at the end of a row
@@ -796,11 +798,13 @@ def test_folded_forward_transform_at_the_edges_of_its_tiles(nz, mz, nt, mt, rule
     (21, 40, 6, 24, 8, 1),      # more than 20 channels: one row of a pair at a time, then runs of three steps
     (32, 35, 17, 31, 16, 0),    # every channel, the largest column count, one row of a pair at a time; odd z
     (24, 40, 5, 10, 5, 0),      # 24 channels, runs of three: both rows again
-    (5, 70, 33, 63, 32, 0),     # 63 columns in 16 tiles, four tiles of t, more than eight K steps
-    (4, 128, 60, 48, 24, 0),    # the folded spectrum of all channels past half a CU's LDS
+    (5, 70, 33, 63, 32, 0),     # folded spectrum of four channels past half a CU's LDS: the generic kernel
+    (5, 70, 33, 20, 8, 0),      # more than eight K steps
+    (4, 40, 5, 63, 32, 0),      # 63 columns in 16 tiles, four tiles of t
+    (4, 128, 60, 48, 24, 0),    # as the case of 70: the generic kernel, with a 16-point FFT
     (3, 12, 3, 70, 5, 0),       # t axis past the folded kernel: the generic one
     (2, 35, 6, 66, 4, 1),       # same, dense z stage
-    (20, 256, 128, 10, 1, 0),   # table of the folded kernel past the LDS: the generic one, at more than 64 KiB
+    (20, 256, 128, 10, 1, 0),   # table of the folded kernel past the LDS: the per-tile one, rows padded to 16
 ])
 def test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule):
     """Inverse (z, t) stage with every epilogue (forward, forward with the pre-activation, adjoint, none) at the edges of
@@ -834,8 +838,11 @@ def test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule):
     # eight channel tiles; several groups of residue classes, most z frequencies kept; an odd number of them
     (20, 16, 4, 32, 8, 0), (7, 128, 30, 16, 9, 0), (18, 64, 12, 30, 9, 0), (13, 16, 8, 24, 11, 0), (24, 16, 3, 20, 7, 0),
     (3, 256, 128, 12, 7, 0), (8, 512, 140, 16, 2, 0), (6, 32, 9, 16, 8, 1),
-    # generic kernel on short z axes: 8, 20 and 32 channels, a 32-channel convolution whose rows take V's place in LDS
-    (20, 8, 3, 24, 6, 0), (8, 12, 4, 48, 12, 0), (32, 9, 3, 20, 5, 1), (6, 27, 6, 33, 9, 1), (32, 7, 3, 6, 3, 1),
+    # generic kernel: 20 channels; a 32-channel convolution whose rows take V's place in LDS (its block folded); 32 and 24
+    # channels under a t axis past the folded kernel
+    (20, 8, 3, 24, 6, 0), (32, 8, 3, 16, 5, 0), (32, 7, 3, 66, 4, 0), (24, 8, 3, 66, 4, 0),
+    # folded: short z axes without an FFT of eight points
+    (8, 12, 4, 48, 12, 0), (32, 9, 3, 20, 5, 1), (6, 27, 6, 33, 9, 1), (32, 7, 3, 6, 3, 1),
     (4, 16, 4, 8, 3, 0),        # folded: eight pairs, a half tile with every lane at work
 ])
 def test_inverse_transform_on_the_tile_and_generic_kernels(c, nz, mz, nt, mt, rule):
@@ -1007,10 +1014,11 @@ def test_block_adjoint_for_widths_and_point_counts_off_the_tiles(case):
     (1, 2, 3, (45, 118, 4, 5), (7, 16, 1, 2), 0),      # odd length; 2 x 59 with 17 folded frequencies
     (1, 2, 2, (31, 33, 3, 4), (15, 16, 1, 1), 1),      # every frequency kept, symmetric rule: 16 and 17, inner of 3
     (1, 1, 1, (106, 94, 2, 3), (47, 32, 1, 2), 0),     # 48 and 33 folded frequencies
-    (2, 2, 2, (64, 32, 4, 8), (12, 15, 2, 3), 0),      # short powers of two
+    (2, 2, 2, (64, 32, 4, 8), (12, 15, 2, 3), 0),      # 32 points folded, 64 on the FFT kernels
     (1, 1, 2, (2, 66, 4, 4), (1, 33, 1, 2), 0),        # two points; every frequency of an even length
     (1, 1, 1, (1, 7, 4, 4), (0, 0, 1, 2), 1),          # one point; one frequency
-    (3, 4, 2, (96, 72, 9, 6), (9, 10, 2, 3), 0),       # the FFT kernels on x, folded on y; two tiles per wave
+    (3, 4, 2, (96, 72, 9, 6), (9, 10, 2, 3), 0),       # 32- and 8-point FFTs
+    (2, 20, 2, (44, 60, 9, 16), (9, 10, 3, 8), 0),     # two tiles per wave
 ])
 def test_folded_axis_products_match_oracle(case):
     test_spectral_conv_fwd_matches_oracle(case)
