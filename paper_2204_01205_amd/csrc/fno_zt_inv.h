@@ -131,6 +131,10 @@ bool zt_inv_tile_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
 hipError_t launch_zt_inv_tile(const float2* a, float* out, const float2* twt, const float2* twz, int B, int Co,
                               int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, float* tables, hipStream_t s);
 bool zt_inv_fold_fits(AxisPlan az, int Nt, int mt, int Co, int Cu);
+// Of the folded kernel on a full chip: waves with a task per CU; matrix products of a tile, counted once per group of
+// channels that a block of its own serves.
+struct FoldInvLoad { int waves, products; };
+FoldInvLoad zt_inv_fold_load(AxisPlan az, int Nt, int mt, int Co, int Cu);
 hipError_t launch_zt_inv_fold(const float2* a, float* out, const float2* twt, const float* ztab, int64_t ncols, int Co,
                               int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, hipStream_t s);
 hipError_t launch_zt_inv_generic(const float2* a, float* out, const float2* twt, const float2* twz, int64_t ncols,

@@ -97,7 +97,20 @@ bool zt_inv_fold_pays(AxisPlan az, int Nt, int mt, int Co, int Cu, int64_t ncols
   // channels, 31.2 and 19.0; 128 x 32, 32 kept per side, 8 channels, 57 and 40; 128 x 16, 64 per side, 8 channels 63 and
   // 48, 12 channels 82 and 98, 32 per side 45 and 57, 24 channels 68 and 176.  4096 columns, with the linear term: 16 x
   // 32, 8 channels, 8 and 16 bins 1.2 and 1.2 to 1; 128 x 20, 20 channels, 5 and 10 bins, 0.82 to 1.
-  if (!few) return !(filled && (mt > 12 || (block && az.N <= 32 && Nt >= 20 && mt > 4)));
+  //
+  // Where the folded spectrum is large, one column fills a block's LDS: its four waves outnumber the column's tasks, or
+  // two such blocks are all that a CU holds.  4096 columns, per tile and folded, us: 64 x 16, 24 kept, 9 bins, 20 channels
+  // with the linear term 214 and 317; 32 x 24, 32 kept, 9 bins, 20 channels 142 and 256; 64 x 16, 64 kept, 9 bins, 8
+  // channels 75 and 164; 128 x 16, 128 kept, 9 bins, 6 channels 259 and 474; but (16 channels, padded to 20 per tile) 128
+  // x 24, 64 kept, 9 bins, 1024 columns, 194 and 141.  Over 1418 shapes of 1024 and 4096 columns, z of 32 to 256, t of 12
+  // to 32, 4 to 32 channels, 7 % were more than a tenth slower folded than per tile without this part, 2 % are with it
+  // (and under 1 % more than a tenth slower than folded).
+  if (!few) {
+    if (filled && (mt > 12 || (block && az.N <= 32 && Nt >= 20 && mt > 4))) return false;
+    const FoldInvLoad l = zt_inv_fold_load(az, Nt, mt, Co, Cu);
+    const bool same_pad = Co <= 20 && (Co + 3) / 4 * 4 == cp;
+    return !((l.waves < 8 && l.products > 60) || (l.waves <= 8 && same_pad && l.products > 92));
+  }
   if (az.N <= 16) return !(Co <= 20 || (Nt > 16 && !block));
   if (Co > 20 || mt <= 3) return true;
   const int k1 = 1 + (az.npos - 1 > az.L - az.npos ? az.npos - 1 : az.L - az.npos);

@@ -454,6 +454,16 @@ bool zt_inv_fold_fits(AxisPlan az, int Nt, int mt, int Co, int Cu) {
   return fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds);
 }
 
+FoldInvLoad zt_inv_fold_load(AxisPlan az, int Nt, int mt, int Co, int Cu) {
+  FoldInv f;
+  size_t lds;
+  if (!fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds)) return {0, 0};
+  const int waves = fold_inv_waves(fold_inv_run(Nt, f.tt), fold_inv_bucket(Cu)), room = (int)((size_t)160 * 1024 / lds);
+  const int wc = 1 << f.wc_shift;
+  return {(room < waves ? room : waves) * (4 / wc) * (f.ntask < wc ? f.ntask : wc),
+          (2 * mt + 2) / 4 * (2 * f.ks + 8) * f.nchunk};
+}
+
 hipError_t launch_zt_inv_fold(const float2* a, float* out, const float2* twt, const float* ztab, int64_t ncols, int Co,
                               int NxNy, AxisPlan az, int Nt, int mt, EpiArgs e, hipStream_t s) {
   FoldInv f{};

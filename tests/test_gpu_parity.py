@@ -850,6 +850,15 @@ def test_inverse_transform_on_the_tile_and_generic_kernels(c, nz, mz, nt, mt, ru
 
 
 @pytest.mark.parametrize("c, nz, mz, nt, mt", [
+    # folded spectra that leave a block of the folded kernel one column, on more columns than fill the chip: fewer tasks
+    # than waves; two blocks per CU
+    (20, 64, 12, 16, 9), (6, 128, 64, 16, 9),
+])
+def test_many_columns_of_a_large_folded_spectrum(c, nz, mz, nt, mt):
+    test_block_fwd_and_bwd_match_oracle((1, c, c, (28, 28, nz, nt), (1, 1, mz, mt), 0), B.FNO_ACT_GELU)
+
+
+@pytest.mark.parametrize("c, nz, mz, nt, mt", [
     (2, 611, 30, 4, 2), (1, 1215, 300, 3, 2), (2, 609, 304, 5, 3),      # folded, one row tile per block
     (3, 128, 64, 10, 5), (2, 160, 30, 24, 4), (2, 256, 100, 20, 9),     # mixed radix: many frequencies
     (2, 512, 40, 14, 4), (3, 640, 20, 8, 3),
