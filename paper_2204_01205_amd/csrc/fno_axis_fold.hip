@@ -32,7 +32,15 @@ constexpr size_t kAxisFoldLds = 40 * 1024;     // four resident blocks per CU
 // FFT kernels against these: 50 x 45 points 361 -> 134 (t of 24), 68 x 118 941 -> 438, 60 x 60 182 -> 117 (t of 30),
 // 32 x 32 127 -> 108; but 64 x 64 118 and 126, 48 x 48 113 and 136, 16 x 16 126 and 175, 72 x 88 358 and 386,
 // 120 x 104 410 and 410, 64 x 64 with 40 kept 315 and 370.
-bool axis_fold_pays(AxisPlan ax) { return ax.M <= 4 || ax.N == 32; }
+//
+// A short axis leaves most of the 16 pairs of a step and of the 16 frequencies of a tile empty, while a 4-point FFT with
+// few residues and few frequencies is next to nothing.  One axis there and back, 20 x 64 slabs of rows of 192 floats, us,
+// FFT kernels and these: 4 points 22 and 34, 12 points with 2, 4 and 10 kept 27 and 36, 27 and 36, 31 and 40, 20 points
+// with 4 kept 32 and 37; with 8 kept 38 and 40, with 18 49 and 45.  Rows of 12 floats: equal.
+bool axis_fold_pays(AxisPlan ax, int64_t inner) {
+  if (ax.M == 4 && ax.P * ax.L <= 32 && inner >= 48) return false;
+  return ax.M <= 4 || ax.N == 32;
+}
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -232,7 +240,7 @@ int folded_count(AxisPlan ax) { return (ax.npos - 1 > ax.L - ax.npos ? ax.npos -
 }  // namespace
 
 bool axis_fold_fits(AxisPlan ax, int64_t inner) {
-  if (!axis_fold_pays(ax) || folded_count(ax) > 48) return false;
+  if (!axis_fold_pays(ax, inner) || folded_count(ax) > 48) return false;
   if (inner <= 0 || 2 * inner * ax.N >= (1ll << 30)) return false;
   return fold_plan(ax).floats * 4 <= kAxisFoldLds;
 }
