@@ -43,7 +43,7 @@ hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const f
 
 // The same for any lengths (see fno_tz_fwd_fold.hip); ztab: the folded table of the z axis.
 bool tz_fwd_fold_fits(AxisPlan az, int Nt, int mt);
-bool tz_fwd_fold_pays(AxisPlan az, int Nt, int mt);
+bool tz_fwd_fold_pays(AxisPlan az, int Nt, int mt, int64_t planes);
 hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, const float* ztab,
                               int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s);
 

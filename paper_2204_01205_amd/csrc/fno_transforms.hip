@@ -858,7 +858,7 @@ hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const f
 #undef FNO_TZF_S
     return hipGetLastError();
   }
-  if (ztab != nullptr && tz_fwd_fold_fits(az, Nt, mt) && tz_fwd_fold_pays(az, Nt, mt))
+  if (ztab != nullptr && tz_fwd_fold_fits(az, Nt, mt) && tz_fwd_fold_pays(az, Nt, mt, planes))
     return launch_tz_fwd_fold(x, out, twt, ztab, planes, az, Nt, mt, s);
   int ppb = 1;
   // enough rows to occupy the block, within an LDS share that keeps several blocks per CU

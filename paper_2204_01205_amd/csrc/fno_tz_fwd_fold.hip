@@ -253,7 +253,11 @@ FoldPlan fold_plan(AxisPlan az) {
 // Short rows: a wave has few bytes to ask for per load and mostly empty K steps.  us on 4096 columns of 8 channels,
 // mixed radix against this one: z of 24 (two entries), t of 5, 8, 12, 14: 19, 27, 35, 49 and 40, 40, 45, 49; z of 48,
 // t of 5, 9, 12: 19, 30, 43 and 32, 36, 38; z of 72, t of 7, 8, 12: 33, 40, 55 and 42, 43, 50; z of 120, t of 5, 9, 12:
-// 51, 82, 101 and 78, 84, 85.
+// 51, 82, 101 and 78, 84, 85.  With few planes the chip is not full and the tiles that the other kernel stages in LDS are
+// its longer chain: us, mixed radix against this one, z of 24 with 3 kept, t of 4, 8, 12: 2048 planes 7.2, 8.7, 10.8 and
+// 6.7, 7.2, 7.2; 4608 planes 7.2, 8.6, 10.9 and 8.2, 8.5, 8.9; 9216 planes 7.5, 9.3, 11.4 and 9.8, 10.7, 11.1.  Of 588
+// shapes with z of 8 to 64 points and t of 4 to 12 that differ on 512 and 2048 planes, 466 are more than a tenth faster here
+// and 1 more than a tenth slower; on 4608 planes, with at most 32 points of z and more than 7 of t, 58 and 1 of 96.
 //
 // Many frequencies: the product over z is worked for every group of 32 rows of the table, and the one over t is worked
 // again for each, where the FFT costs the same for any number of frequencies.  us on 576 columns of 4 channels, mixed
@@ -263,9 +267,10 @@ FoldPlan fold_plan(AxisPlan az) {
 // of 8 to 512, t of 8 to 48, 4 to 32 channels) 15 % were more than a tenth slower here than mixed radix without this part
 // of the rule, 2 % are with it (and 2 % more than a tenth slower than here); over 2.9 thousand on 4096 columns 11 and 3 %
 // (1 %).
-bool tz_fwd_fold_pays(AxisPlan az, int Nt, int mt) {
+bool tz_fwd_fold_pays(AxisPlan az, int Nt, int mt, int64_t planes) {
   if (az.M < 4) return true;
-  if (Nt <= 7 || (Nt <= 9 && (az.N <= 48 || az.N > 96)) || (Nt <= 12 && az.N <= 24)) return false;
+  const bool few = (planes <= 3072 && az.N <= 64) || (planes <= 6144 && az.N <= 32 && Nt > 7);
+  if (!few && (Nt <= 7 || (Nt <= 9 && (az.N <= 48 || az.N > 96)) || (Nt <= 12 && az.N <= 24))) return false;
   const int rows = fold_plan(az).rows;
   if (az.M == 4) return rows <= 32 || mt > 4;
   return rows <= 16 || Nt > 36 || (rows <= 32 && mt > 4);

@@ -75,7 +75,7 @@ SMALL = [
     (1, 2, 2, (8, 8, 8, 8), (4, 4, 4, 5), 0),          # every mode kept (L = N, mt = Nt/2+1)
     (1, 2, 2, (8, 4, 8, 8), (1, 1, 1, 1), 0),          # a single t mode
     (1, 1, 1, (1, 1, 1, 1), (0, 0, 0, 1), 1),          # one-point grid
-    (1, 3, 2, (10, 3, 20, 5), (2, 1, 4, 2), 1),        # mixed radix z (20 = 5*4) forward, folded inverse
+    (1, 3, 2, (10, 3, 20, 5), (2, 1, 4, 2), 1),        # symmetric rule, Cin != Cout, every stage folded
     (1, 3, 3, (2, 3, 32, 16), (1, 1, 4, 5), 0),        # folded inverse, 6 columns, padded channels
     (2, 2, 3, (3, 2, 32, 16), (1, 1, 6, 9), 0),        # same, 17 columns, Cin != Cout
     (1, 20, 20, (2, 2, 32, 32), (1, 1, 8, 9), 0),      # column kernel (Nt = 32), width 20
@@ -865,6 +865,18 @@ def test_many_columns_of_a_large_folded_spectrum(c, nz, mz, nt, mt):
 ])
 def test_forward_transform_of_long_z_axes(c, nz, mz, nt, mt):
     L = Layer(2, c, c, (3, 2, nz, nt), (1, 1, mz, mt))
+    y, xh = gpu_spectral_fwd(L)
+    yo, xho = O.spectral_conv_fwd(L.x, L.R, L.spec, return_xhat=True)
+    assert rel(xh, xho) <= TOL and rel(y, yo) <= TOL
+
+
+@pytest.mark.parametrize("nz, mz, nt, mt", [(12, 2, 4, 2), (20, 4, 5, 2), (8, 2, 6, 3), (24, 4, 7, 3), (16, 3, 8, 3),
+                                            (32, 5, 5, 2), (10, 3, 5, 2)])
+@pytest.mark.parametrize("nx, ny", [(63, 61), (24, 32)])
+def test_forward_transform_of_short_rows(nx, ny, nz, mz, nt, mt):
+    """Many planes of short rows on the mixed-radix kernel, M = 4, 8, 16 and 32 (M = 2 is folded), few of them folded;
+    3072 planes are the most that are few."""
+    L = Layer(2, 2, 2, (nx, ny, nz, nt), (1, 1, mz, mt))
     y, xh = gpu_spectral_fwd(L)
     yo, xho = O.spectral_conv_fwd(L.x, L.R, L.spec, return_xhat=True)
     assert rel(xh, xho) <= TOL and rel(y, yo) <= TOL
