@@ -33,12 +33,15 @@ constexpr size_t kAxisFoldLds = 40 * 1024;     // four resident blocks per CU
 // 32 x 32 127 -> 108; but 64 x 64 118 and 126, 48 x 48 113 and 136, 16 x 16 126 and 175, 72 x 88 358 and 386,
 // 120 x 104 410 and 410, 64 x 64 with 40 kept 315 and 370.
 //
-// A short axis leaves most of the 16 pairs of a step and of the 16 frequencies of a tile empty, while a 4-point FFT with
-// few residues and few frequencies is next to nothing.  One axis there and back, 20 x 64 slabs of rows of 192 floats, us,
-// FFT kernels and these: 4 points 22 and 34, 12 points with 2, 4 and 10 kept 27 and 36, 27 and 36, 31 and 40, 20 points
-// with 4 kept 32 and 37; with 8 kept 38 and 40, with 18 49 and 45.  Rows of 12 floats: equal.
+// A short axis leaves most of the 16 pairs of a step and of the 16 frequencies of a tile empty, while a 2- or 4-point FFT
+// with few residues and few frequencies is next to nothing.  One axis there and back, 20 x 64 slabs of rows of 192 floats,
+// us, FFT kernels and these: 4 points 22 and 34, 6 points 24 and 35, 10 points with 2 and 4 kept 28 and 35, 29 and 35, 12
+// points with 4 and 10 kept 27 and 36, 31 and 40, 14 points with 2 kept 30 and 36, 20 and 28 points with 4 kept 32 and
+// 37, 37 and 38; 20 points with 8 kept 38 and 40, with 18 49 and 45.  Rows of 96 floats: 12 points with 4 kept 23 and 25,
+// 20 points with 4 kept 26 and 26, 28 points 28 and 27; of 12 floats: equal.
 bool axis_fold_pays(AxisPlan ax, int64_t inner) {
-  if (ax.M == 4 && ax.P * ax.L <= 32 && inner >= 48) return false;
+  const int terms = ax.P * ax.L;
+  if (ax.M > 1 && terms <= 32 && inner >= (terms <= 16 ? 48 : 80)) return false;
   return ax.M <= 4 || ax.N == 32;
 }
 

@@ -889,9 +889,11 @@ def test_forward_transform_of_short_rows(nx, ny, nz, mz, nt, mt):
     (2, 1, 2, (156, 101, 3, 4), (34, 49, 1, 2), 1),
     (1, 2, 1, (80, 72, 3, 4), (13, 20, 1, 2), 0),
     (1, 3, 2, (144, 40, 4, 5), (30, 20, 1, 2), 0),
-    # M = 4 with few residues and frequencies under rows of 48 values and more; one value less is folded
-    (2, 3, 2, (12, 20, 12, 16), (2, 3, 4, 8), 0),
-    (1, 2, 3, (20, 12, 12, 16), (3, 5, 3, 8), 0),
+    # M = 4 and 2 with few residues and frequencies under rows of 48 (80) values and more; one value less is folded
+    (2, 3, 2, (12, 20, 20, 16), (2, 3, 5, 8), 0),
+    (1, 2, 3, (20, 12, 12, 16), (3, 2, 3, 8), 0),
+    (1, 2, 2, (14, 10, 12, 16), (1, 1, 3, 8), 1),
+    (1, 2, 2, (6, 2, 12, 16), (2, 1, 3, 8), 0),
     (1, 2, 2, (4, 12, 47, 3), (1, 2, 23, 1), 1),
 ])
 def test_fft_axis_kernels_match_oracle(case):
