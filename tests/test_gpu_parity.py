@@ -182,6 +182,25 @@ def test_block_fwd_and_bwd_match_oracle(case, activation):
         assert torch.equal(gW, gW2) and torch.equal(gb, gb2) and torch.equal(gx, gx2)
 
 
+def test_forward_activation_over_its_whole_range():
+    # W = 1, R = 0: the pre-activation is x, and the output differs from float64 by the tail's fit (5.1e-8) and the roundings of
+    # its exponent (|z| T(|z|) times one unit of log2 T: at most 2.5e-7, near |z| = 4) and of the result
+    grid, modes, c = (16, 16, 16, 16), (2, 2, 2, 2), 4
+    n = c * 16 ** 4
+    x = torch.linspace(-45.0, 45.0, n, dtype=torch.float64).float()
+    x[:8] = torch.tensor([0.0, -0.0, 1e20, -1e20, 1e-30, -1e-30, 13.7, -13.7])
+    x = x.view(1, c, *grid).cuda()
+    desc = B.make_desc(1, c, c, grid, modes, 0, B.FNO_ACT_GELU)
+    R = torch.zeros(c, c, 4, 4, 4, 2, dtype=torch.complex64, device="cuda")
+    out = torch.empty_like(x)
+    B.fno_block_fwd(desc, x, R, torch.eye(c, device="cuda"), torch.zeros(c, device="cuda"), out, None, None,
+                    B.alloc_workspace(desc, B.FNO_OP_BLOCK_FWD))
+    z = x.double().cpu()
+    want = 0.5 * z * torch.erfc(-z / 2 ** 0.5)
+    over = (out.cpu().double() - want).abs() - (3.5e-7 + 6.0e-8 * want.abs())
+    assert float(over.max()) <= 0.0
+
+
 def test_accumulate_flag_adds_parameter_gradients_of_successive_calls():
     """FNO_FLAG_ACCUMULATE_GRADS: gR, gW, gb of a second call are added to those of the first (the
     gradient of a broadcast weight is a sum, Sec. 2.1), gx is overwritten; compared with the sum of
