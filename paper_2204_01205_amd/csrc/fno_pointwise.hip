@@ -18,23 +18,24 @@ namespace {
 // over points and runs on the matrix cores: v_mfma_f32_4x4x1 block blk adds the outer product
 // gz[4To..4To+3][p] x[4Ti..4Ti+3][p] of its point p to its own 4x4 partial tile; the 16 blocks,
 // the waves and the thread blocks are summed at the end (per-wave partials in double, fixed order).
+// GELU and its slope: the upper tail as in gelu_fast_f, with a polynomial of degree 7 (the tail itself enters the slope;
+// largest error of max(a, 1) T(a) 6.2e-8, least value -57 at 9.75), and the density from an exponential of its own.  19 issue
+// slots (each exponential counts two), as many as the rational form 7.1.26 of Abramowitz & Stegun that stood here; against
+// float64, of the norm under N(0, 1): 5.8e-8 on z Phi(z) and 7.2e-8 on the slope (8.5e-8 and 9.9e-8).
 __device__ __forceinline__ void gelu_and_grad_f(float z, float& val, float& grad) {
-  // Phi and phi from one exponential: with x = |z| / sqrt 2 and t = 1 / (1 + p x),
-  //   erfc(x) = t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-x^2)    (Abramowitz & Stegun 7.1.26, |error| <= 1.5e-7)
-  // and exp(-x^2) = exp(-z^2 / 2) is phi(z) up to its constant.  The a_i below are halved, so the
-  // polynomial times the exponential is the upper tail 1 - Phi(|z|).  23 issue slots (the reciprocal
-  // and the exponential count four each); against float64: at most 4.3e-7 absolute on z Phi(z), 3.0e-7 on the slope.
-  const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.23164190f, 1.0f));
-  float q = fmaf(t, 0.5307027145f, -0.7265760135f);
-  q = fmaf(t, q, 0.7107068705f);
-  q = fmaf(t, q, -0.1422483680f);
-  q = fmaf(t, q, 0.1274147960f);
-  q *= t;
-  const float e = __builtin_amdgcn_exp2f((z * z) * -0.72134752044f);    // exp(-z^2 / 2)
-  const float tail = q * e;
+  const float a = __builtin_amdgcn_fmed3f(fabsf(z), 0.0f, 9.75f);
+  float p = fmaf(a, 6.1192263e-06f, -3.2478307e-05f);
+  p = fmaf(a, p, -4.9471017e-04f);
+  p = fmaf(a, p, 7.5082830e-03f);
+  p = fmaf(a, p, -5.2784692e-02f);
+  p = fmaf(a, p, -4.5912030e-01f);
+  p = fmaf(a, p, -1.1511149f);
+  p = fmaf(a, p, -9.9999982e-01f);
+  const float tail = __builtin_amdgcn_exp2f(p);
+  const float pdf = __builtin_amdgcn_exp2f(fmaf(z * z, -0.72134752044f, -1.3257480647f));     // log2 of 1 / sqrt(2 pi)
   const float cdf = z < 0.f ? tail : 1.0f - tail;
   val = z * cdf;
-  grad = fmaf(z, 0.39894228040143267794f * e, cdf);
+  grad = fmaf(z, pdf, cdf);
 }
 
 template <int CT, bool STREAM>
@@ -553,131 +554,624 @@ __global__ __launch_bounds__(kThreads) void mlp2_bwd_kernel(
 // ------------------------------------------------------------------------------------------
 // The two-layer projection and its adjoint on the matrix cores
 // ------------------------------------------------------------------------------------------
-// v_mfma_f32_32x32x2 adds A (32x2) times B (2x32) to a 32x32 accumulator in full fp32.  Lane l
-// supplies A[l%32][l/32] and B[l/32][l%32]; register v of its accumulator holds the element in
-// row mfma_row(v, l/32), column l%32.
-//
-// A block of H/32 waves walks over tiles of 64 points (two column blocks of 32); wave w owns the
-// hidden units 32w .. 32w+31 and keeps their weights in registers, already in operand order.
-//   h   = [W1 | b1] [x ; 1]      K runs over the input channels and a row of ones
-//   gx  = W1^T gh                K runs over the wave's hidden units in accumulator order, so
-//                                the registers that hold gh are the B operand as they stand
-//   gW1 | gb1 = gh [x ; 1]^T     K runs over the points; gh goes through LDS to turn it
-// The activation, its slope and the products with W2 are the vector units' share.
+// Accumulators are 32 x 32: register v of lane l holds the element in row mfma_row(v, l/32), column l%32.
 typedef float v16f __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ int mfma_row(int v, int half) { return 8 * (v >> 2) + 4 * half + (v & 3); }
 
-constexpr int kMlpTile = 64;             // points per pass of a block
-constexpr int kMlpStage = 6;             // values a thread stages per pass
-constexpr int kMlpXS = kMlpTile + 1;     // row stride of the staged tile (odd: column reads spread over the banks)
-constexpr int kMlpTS = 33;               // row stride of a wave's 32x32 turn buffer
-constexpr int kMlpFlush = 16;            // passes between flushes of the fp32 weight-gradient accumulator
+// fp32 products on the bf16 matrix instructions: a float is the exact sum of three bf16 values (hi and mid rounded to nearest, lo what is left: 3 x 8 bits), and six of
+// the nine products of two such sums, added up in fp32, leave out less than 2^-25 of the product: less than one fp32
+// rounding.  v_mfma_f32_32x32x16_bf16 takes half the cycles of v_mfma_f32_32x32x2 for eight times the terms, so the six
+// cost three eighths of the fp32 instruction, and unlike it they run beside the vector unit's work.
+// Lane l supplies A[l%32][8 (l/32) + j] and B[8 (l/32) + j][l%32], j < 8; the accumulator is laid out as mfma_row says.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+__device__ __forceinline__ unsigned bf16_pair(float a, float b) {
+  const v2f v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+// the three parts of a and b, side by side
+__device__ __forceinline__ void bf16_split(float a, float b, unsigned (&part)[3]) {
+  part[0] = bf16_pair(a, b);
+  const float ra = a - bf16_low(part[0]), rb = b - bf16_high(part[0]);
+  part[1] = bf16_pair(ra, rb);
+  part[2] = bf16_pair(ra - bf16_low(part[1]), rb - bf16_high(part[1]));
+}
+__device__ __forceinline__ v16f mfma_bf16(u32x4 a, u32x4 b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// the six products, the small ones first
+constexpr int kSplitA[6] = {0, 2, 1, 0, 1, 0}, kSplitB[6] = {2, 0, 1, 1, 0, 0};
 
-template <int KS, int CO>
-__global__ __launch_bounds__(512) void mlp2_fwd_mfma_kernel(
+// u = W2 gelu(W1 x + b1) + b2.  A wave takes 32 points at a time through all hidden units, 32 of them per accumulator:
+// its x values are loaded in operand order straight from memory (slot s of lane l is channel 2 s + l/32, the bias a
+// channel of ones after the last), split once, and used against every group of hidden units, whose split weights the
+// block keeps in LDS.  Waves meet nowhere after the weights are there.
+//
+// What bounds it: the vector unit, 12 issue slots a hidden value (GELU and the product with W2) and a seventh of that for
+// loads and splits; it issues in 98 % of the cycles, the products' matrix instructions (38 %) run beside it, and the chip
+// holds 1.7 GHz.  20 -> 128 -> 1 at 4 million points 442 -> 312 us, off the measured rms error of the fp32 instruction
+// (2.2e-7, 1.1e-7 now); against the scalar kernel, which took the hidden and channel widths that one did not fit,
+// 20 -> 64 -> 1 862 -> 179 us, 32 -> 128 -> 1 at 2 million points 1352 -> 192 us.
+template <int NS, int CO>
+__global__ __launch_bounds__(kThreads, 4) void mlp2_fwd_split_kernel(
     int B, int Ci, int H, int Co, long long N, const float* __restrict__ x, const float* __restrict__ W1,
     const float* __restrict__ b1, const float* __restrict__ W2, const float* __restrict__ b2,
     float* __restrict__ y) {
-  HIP_DYNAMIC_SHARED(float, smem)
-  const int nthreads = blockDim.x, nw = nthreads >> 6;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, half = lane >> 5, c = lane & 31;
-  float* XS = smem;                          // [32][kMlpXS]: rows < Ci the tile, row Ci ones, the rest zero
-  float* YP = XS + 32 * kMlpXS;              // [nw][CO][kMlpTile] partial outputs of the waves
-  for (int e = tid; e < (32 - Ci) * kMlpXS; e += nthreads) XS[Ci * kMlpXS + e] = e < kMlpXS ? 1.f : 0.f;
-  float A1[KS], W2r[CO][16];
+  HIP_DYNAMIC_SHARED(float4, smem4)
+  constexpr int KB = (NS + 7) / 8;
+  constexpr int LOW = NS == 18 ? 32 : 2 * NS - 8;          // fewest channels that run with NS slots: those below are all there
+  const int NH = (H + 31) / 32;
+  u32x4* A = reinterpret_cast<u32x4*>(smem4);              // [NH][KB][3][64]
+  float4* W2S = reinterpret_cast<float4*>(A + NH * KB * 3 * 64);     // [CO][NH][8]: hidden units in order
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, c = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int e = tid; e < NH * KB * 64; e += kThreads) {
+    const int l = e & 63, g = e >> 6, kb = g % KB, k = (g / KB) * 32 + (l & 31);
+    unsigned part[4][3];
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    const int i = 2 * s + half, k = w * 32 + c;
-    A1[s] = i < Ci ? W1[k * Ci + i] : ((i == Ci && b1 != nullptr) ? b1[k] : 0.f);
+    for (int j = 0; j < 8; j += 2) {
+      float v[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int i = 2 * (8 * kb + j + q) + (l >> 5);
+        v[q] = k < H ? (i < Ci ? W1[k * Ci + i] : (i == Ci && b1 != nullptr ? b1[k] : 0.f)) : 0.f;
+      }
+      bf16_split(v[0], v[1], part[j / 2]);
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) A[(g * 3 + p) * 64 + l] = u32x4{part[0][p], part[1][p], part[2][p], part[3][p]};
   }
-#pragma unroll
-  for (int o = 0; o < CO; ++o)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) W2r[o][v] = o < Co ? W2[o * H + w * 32 + mfma_row(v, half)] : 0.f;
-  const long long tiles_per_b = (N + kMlpTile - 1) / kMlpTile;
-  const long long ntiles = tiles_per_b * B;
-  const int nstage = Ci * kMlpTile;
-  float pf[kMlpStage];
-  {
-    const long long t = blockIdx.x;
-    const long long b = t / tiles_per_b, p0 = (t - b * tiles_per_b) * kMlpTile;
-#pragma unroll
-    for (int r = 0; r < kMlpStage; ++r) {
-      const int e = tid + r * nthreads, row = e >> 6, col = e & 63;
-      pf[r] = (t < ntiles && e < nstage && p0 + col < N) ? x[(b * Ci + row) * N + p0 + col] : 0.f;
-    }
+  for (int e = tid; e < CO * NH * 32; e += kThreads) {
+    const int o = e / (NH * 32), k = e - o * NH * 32;
+    reinterpret_cast<float*>(W2S)[e] = (o < Co && k < H) ? W2[o * H + k] : 0.f;
   }
-  for (long long t = blockIdx.x; t < ntiles; t += gridDim.x) {
+  __syncthreads();
+
+  unsigned keep[NS], one[NS];                              // (v & keep) | one: what a slot past LOW holds
 #pragma unroll
-    for (int r = 0; r < kMlpStage; ++r) {
-      const int e = tid + r * nthreads, row = e >> 6, col = e & 63;
-      if (e < nstage) XS[row * kMlpXS + col] = pf[r];
-    }
-    __syncthreads();
-    {
-      const long long tn = t + gridDim.x;
-      const long long b = tn / tiles_per_b, p0 = (tn - b * tiles_per_b) * kMlpTile;
+  for (int s = 0; s < NS; ++s) {
+    const int i = 2 * s + half;
+    keep[s] = i < Ci ? ~0u : 0u;
+    one[s] = i == Ci ? 0x3f800000u : 0u;
+  }
+  float bias[CO];
 #pragma unroll
-      for (int r = 0; r < kMlpStage; ++r) {
-        const int e = tid + r * nthreads, row = e >> 6, col = e & 63;
-        pf[r] = (tn < ntiles && e < nstage && p0 + col < N) ? x[(b * Ci + row) * N + p0 + col] : 0.f;
+  for (int o = 0; o < CO; ++o) bias[o] = (b2 != nullptr && o < Co) ? b2[o] : 0.f;
+  // tiles of 32 points, the last of a batch entry ragged; lanes past its end repeat its last point
+  const long long tiles_per_b = (N + 31) >> 5;
+  long long t = (long long)blockIdx.x * (kThreads / 64) + wave;
+  const long long step = (long long)gridDim.x * (kThreads / 64);
+  long long b = t / tiles_per_b;
+  t -= b * tiles_per_b;
+  float v[NS];
+  auto load = [&](long long bb, long long tt) {
+    const long long p0 = tt << 5, col = min((long long)c, N - 1 - p0);
+    const float* xb = x + bb * Ci * N + p0;
+    const float *xh = xb + half * N + col, *xc = xb + col;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)                           // past the last channel: the last one, masked below
+      v[s] = (2 * s + 1 < LOW || 2 * s + 1 < Ci) ? xh[2 * s * N] : xc[min(2 * s, Ci - 1) * N];
+  };
+  if (b < B) load(b, t);
+  while (b < B) {
+    u32x4 xs[KB][3];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) {
+        unsigned part[3] = {0u, 0u, 0u};
+        const int s = 8 * kb + j;
+        if (s < NS) {
+          float q[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            q[h] = 2 * (s + h) + 1 < LOW ? v[s + h]
+                                         : __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, v[s + h]) & keep[s + h]) | one[s + h]);
+          bf16_split(q[0], q[1], part);
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p) xs[kb][p][j / 2] = part[p];
       }
-    }
-    const long long b = t / tiles_per_b, p0 = (t - b * tiles_per_b) * kMlpTile;
+    const long long bo = b, to = t;
+    for (t += step; t >= tiles_per_b && b < B; t -= tiles_per_b) ++b;
+    if (b < B) load(b, t);
+    float sum[CO];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const int pc = nb * 32 + c;
-      v16f hacc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < CO; ++o) sum[o] = 0.f;
+    auto hidden = [&](int hb) {
+      u32x4 a[KB][3];
 #pragma unroll
-      for (int s = 0; s < KS; ++s)
-        hacc = __builtin_amdgcn_mfma_f32_32x32x2f32(A1[s], XS[(2 * s + half) * kMlpXS + pc], hacc, 0, 0, 0);
-      float yp[CO];
+      for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int o = 0; o < CO; ++o) yp[o] = 0.f;
+        for (int p = 0; p < 3; ++p) a[kb][p] = A[((hb * KB + kb) * 3 + p) * 64 + lane];
+      v16f acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float a = gelu_fast_f(hacc[v]);
+      for (int r = 0; r < 6; ++r)
 #pragma unroll
-        for (int o = 0; o < CO; ++o) yp[o] = fmaf(W2r[o][v], a, yp[o]);
+        for (int kb = 0; kb < KB; ++kb) acc = mfma_bf16(a[kb][kSplitA[r]], xs[kb][kSplitB[r]], acc);
+      return acc;
+    };
+#pragma unroll 1
+    for (int hb = 0; hb < NH; ++hb) {
+      const v16f acc = hidden(hb);
+      float part[CO];
+#pragma unroll
+      for (int o = 0; o < CO; ++o) part[o] = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {                        // rows 8 q + 4 half + 0 .. 3
+        float g[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) g[w] = gelu_fast_f(acc[4 * q + w]);
+#pragma unroll
+        for (int o = 0; o < CO; ++o) {
+          const float4 w2 = W2S[(o * NH + hb) * 8 + 2 * q + half];
+          part[o] = fmaf(w2.x, g[0], part[o]);
+          part[o] = fmaf(w2.y, g[1], part[o]);
+          part[o] = fmaf(w2.z, g[2], part[o]);
+          part[o] = fmaf(w2.w, g[3], part[o]);
+        }
       }
 #pragma unroll
-      for (int o = 0; o < CO; ++o) {
-        yp[o] += __shfl_xor(yp[o], 32);
-        if (half == 0) YP[(w * CO + o) * kMlpTile + pc] = yp[o];
-      }
+      for (int o = 0; o < CO; ++o) sum[o] += part[o];
     }
-    __syncthreads();
-    for (int e = tid; e < Co * kMlpTile; e += nthreads) {
-      const int o = e >> 6, col = e & 63;
-      float sum = b2 != nullptr ? b2[o] : 0.f;
-      for (int ww = 0; ww < nw; ++ww) sum += YP[(ww * CO + o) * kMlpTile + col];
-      if (p0 + col < N) y[(b * Co + o) * N + p0 + col] = sum;
+    const long long p = (to << 5) + c;
+#pragma unroll
+    for (int o = 0; o < CO; ++o) {
+      sum[o] += __shfl_xor(sum[o], 32);
+      if (half == 0 && o < Co && p < N) y[(bo * Co + o) * N + p] = sum[o] + bias[o];
     }
   }
 }
 
-template <int KS, int CO>
+// The adjoint needs its own products split in registers, one hidden value at a time, so it uses two fp16 parts (2 x 11
+// bits, two vector instructions a value where three bf16 parts take five and a half) and all four products.  fp16 has
+// few exponents, so both operands are scaled by powers of two.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ void f16_split(float a, float b, unsigned (&part)[2]) {
+  const v2f v = {a, b};
+  const f16x2 hi = __builtin_convertvector(v, f16x2);
+  const v2f r = {fmaf((float)hi[0], -1.f, a), fmaf((float)hi[1], -1.f, b)};      // v_fma_mix_f32
+  part[0] = __builtin_bit_cast(unsigned, hi);
+  part[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(r, f16x2));
+}
+__device__ __forceinline__ v16f mfma_f16(u32x4 a, u32x4 b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+constexpr int kHalfA[4] = {1, 1, 0, 0}, kHalfB[4] = {1, 0, 1, 0};
+// the power of two that takes values up to v to 2^10 .. 2^11, where fp16 has room for values 16 times as large and for
+// the low parts of values 4096 times as small
+__device__ __forceinline__ int scale_exponent(float v) {
+  return 137 - (int)(__builtin_bit_cast(unsigned, v) >> 23 & 255u);
+}
+// the largest of a wave's non-negative values
+__device__ __forceinline__ float wave_max(float v) {
+  auto step = [&](auto ctrl, auto rows) {
+    const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl.value, rows.value, 0xf, false);
+    v = fmaxf(v, __builtin_bit_cast(float, o));
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});      // lanes 1, 2, 4, 8 to the left in rows of 16
+  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});      // the last lane of a row to the next row
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});      // that of the second row to the upper half
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+// 16-bit elements of LDS turned in reading: with rows of `stride` elements, lane l gets column l % 32 of rows
+// row0 + 8 (l/32) + 0 .. 7, two ds_read_b64_tr_b16 of four rows each (a group of 16 lanes reads 4 rows x 16 columns,
+// lane j of it the address of four elements of row j / 4, and keeps column j).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x4 lds_turned(const unsigned short* base, int row0, int stride) {
+  const int lane = threadIdx.x & 63;
+  const unsigned short* p = base + (row0 + 8 * (lane >> 5) + ((lane & 15) >> 2)) * stride + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+  const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * stride)));
+  return u32x4{a[0], a[1], b[0], b[1]};
+}
+
+// Adjoint of the projection to one channel.  A block walks over tiles of 64 points, staged split in LDS; wave (wh, wp)
+// takes 32 hidden units, whose split weights stay in its registers, and both column blocks of 32 points or (two waves
+// per group of hidden units, when these are few) one of them.  With d = gelu'(h), M = diag(W2) W1 and Y = g [x ; 1],
+//   h   = [W1 | b1] [x ; 1]
+//   gx  = g M^T d                      K runs over the hidden units in accumulator order: the parts of d are the right
+//                                      operand as they are packed
+//   gW1 | gb1 = diag(W2) d Y^T         K runs over the points; the parts of d are turned through LDS
+// so that neither g nor W2 multiplies anything per hidden value.  Every channel of M and of Y has a scale of its own.
+// Those of Y start anew with every flush of the accumulators and shrink, and the accumulators with them, when a tile
+// holds a value past fp16's range.
+//
+// The fp32 accumulator of gW1 takes kMlpFlush tiles and then goes to doubles, and takes -Y every other time: the
+// instruction's sums are rounded to nearest after a cut towards minus infinity some bits below (measured: 0.004 units of
+// the accumulator's last place on average; single products rounded in fp32 show none), which adds up over millions of
+// points (4 million: gW1 off by 4.2e-6), and cancels in the difference (2.4e-7; in fp32 6.8e-7).
+//
+// What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 1000 vector instructions
+// and 56 matrix instructions a wave and tile; the vector unit issues in 63 % of the cycles, the matrix unit in 26 %, 11 %
+// both.  20 -> 128 -> 1 at 4 million points, both ways' products on the fp32 instruction 1403 us, in three bf16 parts
+// 1095, now 950; against the scalar kernel (hidden or channel widths that the fp32 one did not fit) 20 -> 64 -> 1
+// 5637 -> 617 us, 32 -> 128 -> 1 at 2 million points 22300 -> 704 us.
+constexpr int kMlpTS = 36;               // row stride of turned tiles, in 16-bit elements: 18 banks, so that rows spread over all
+struct MlpBwd {
+  int B, Ci, H, nwh;                     // nwh: groups of 32 hidden units
+  long long N;
+};
+constexpr int kMlpFlush = 4;             // tiles between flushes of the fp32 weight-gradient accumulators
+constexpr int mlp_rows(int NS) { return NS == 4 ? 8 : (NS == 8 ? 16 : (NS == 12 ? 24 : 32)); }      // rows of gx
+// LDS floats of a wave: the parts of d of its column blocks, then its share of gx
+constexpr int mlp_region(int NS, int NPG) {
+  return mlp_rows(NS) * 64 > 64 / NPG * kMlpTS ? mlp_rows(NS) * 64 : 64 / NPG * kMlpTS;
+}
+template <int NS, int NPG>
+__global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
+    MlpBwd f, const float* __restrict__ x, const float* __restrict__ W1, const float* __restrict__ b1,
+    const float* __restrict__ W2, const float* __restrict__ g, float* __restrict__ gx, double* __restrict__ part) {
+  HIP_DYNAMIC_SHARED(float4, smem4)
+  constexpr int KB = NS > 8 ? 2 : 1, ROWS = mlp_rows(NS), REG = mlp_region(NS, NPG);
+  constexpr bool ALL = NS == 18;           // 32 input channels: no column left for gb1, the bias is where h starts
+  constexpr int PAIRS = NS < 16 ? NS : 16;
+  constexpr int SR = NPG == 2 ? PAIRS / 2 : (PAIRS + 2) / 3;     // most pairs of channels a wave stages: of two waves, or three
+  constexpr int NB = 2 / NPG;              // column blocks of a wave
+  const int Ci = f.Ci, H = f.H;
+  const long long N = f.N;
+  const int nthreads = blockDim.x, nw = nthreads >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, c = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp = w / f.nwh, wh = w - wp * f.nwh;
+  u32x4* XS = reinterpret_cast<u32x4*>(smem4);                               // [KB][3][2][64]: octets of channels of a point
+  unsigned short* YS = reinterpret_cast<unsigned short*>(XS + KB * 6 * 64);  // [2][64][kMlpTS]: channels of a point
+  float* GS = reinterpret_cast<float*>(YS + 2 * 64 * kMlpTS);                // [64]
+  int* ES = reinterpret_cast<int*>(GS + 64);                                 // [32] exponents of Y's scales
+  int* EM = ES + 32;                                                         // [32] of M's
+  float* BS = reinterpret_cast<float*>(EM + 32);                             // [256] b1
+  float* regions = BS + (ALL ? 256 : 0);
+  float* own = regions + w * REG;
+  unsigned short* T = reinterpret_cast<unsigned short*>(own);                // [NB][2][32][kMlpTS]
+  const int nsum = H * (Ci + 1) + H + 1;
+  const int np = ALL ? 16 : Ci / 2 + 1;    // pairs with the channel of ones
+  double* dst = part + (long long)blockIdx.x * nsum;       // gW1 | gb1 | gW2 | gb2
+  for (int e = tid; e < KB * 6 * 64; e += nthreads) XS[e] = u32x4{0u, 0u, 0u, 0u};
+  if constexpr (ALL)
+    for (int e = tid; e < 256; e += nthreads) BS[e] = b1 != nullptr && e < H ? b1[e] : 0.f;
+  // operands of h and gx; |M| of a channel is at most its largest |W1| times the largest |W2|
+  int m_exp = 0;
+  {
+    float m1 = 0.f, m2 = 0.f;
+#pragma unroll 8
+    for (int k = half; k < 32 * f.nwh; k += 2) m1 = fmaxf(m1, fabsf(W1[min(k, H - 1) * Ci + min(c, Ci - 1)]));
+    for (int k = lane; k < H; k += 64) m2 = fmaxf(m2, fabsf(W2[k]));
+    m1 = fmaxf(m1, __shfl_xor(m1, 32));
+    m_exp = scale_exponent(m1) + scale_exponent(wave_max(m2)) - 11;
+    if (tid < 32) EM[tid] = m_exp;
+  }
+  u32x4 a1[KB][3], am[2][2];
+  {
+    const int k = wh * 32 + c;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) {
+        float v[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int i = 16 * kb + 8 * half + j + q;
+          v[q] = k < H ? (i < Ci ? W1[k * Ci + i] : (i == Ci && b1 != nullptr ? b1[k] : 0.f)) : 0.f;
+        }
+        unsigned pt[3];
+        bf16_split(v[0], v[1], pt);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a1[kb][p][j / 2] = pt[p];
+      }
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      float m[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int kk = wh * 32 + mfma_row(v + q, half);
+        m[q] = (c < Ci && kk < H) ? (float)ldexp((double)W1[kk * Ci + c] * (double)W2[kk], m_exp) : 0.f;
+      }
+      unsigned pt[2];
+      f16_split(m[0], m[1], pt);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) am[v >> 3][p][(v & 7) / 2] = pt[p];
+    }
+  }
+  v16f accw;
+  double accd[16], accgd = 0.0;
+  float acc2[16], accg = 0.f, accb[ALL ? 16 : 1];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    accd[v] = 0.0;
+    acc2[v] = accw[v] = 0.f;
+  }
+#pragma unroll
+  for (int v = 0; v < (ALL ? 16 : 1); ++v) accb[v] = 0.f;
+
+  const long long tiles_per_b = (N + 63) >> 6;
+  long long t = blockIdx.x, b = t / tiles_per_b;
+  t -= b * tiles_per_b;
+  // a wave stages pairs of channels w, w + nw, ..; its lanes are the points
+  float pv[SR][2], pg;
+  // (lanes past the last point read it again, under g = 0; pairs past the last channel are not used)
+  auto load = [&]() {
+    const long long p = (t << 6) + lane, pc = min(p, N - 1);
+    const float* xb = x + b * Ci * N + pc;
+#pragma unroll
+    for (int r = 0; r < SR; ++r) {
+      const int i = 2 * (r * nw + w);
+      pv[r][0] = xb[min(i, Ci - 1) * N];
+      pv[r][1] = xb[min(i + 1, Ci - 1) * N];
+      if (i == Ci) pv[r][0] = 1.f;
+      if (i + 1 == Ci) pv[r][1] = 1.f;
+    }
+    pg = p < N ? g[b * N + pc] : 0.f;
+  };
+  if (b < f.B) load();
+  __syncthreads();                         // XS is clear
+  float sign = blockIdx.x & 1 ? -1.f : 1.f;                // of Y
+  int y_exp = 0;                           // of the lane's column of accw
+  auto flush = [&]() {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      accd[v] += ldexp((double)(sign * accw[v]), -y_exp);
+      accw[v] = 0.f;
+    }
+    accgd += (double)accg;
+    accg = 0.f;
+    sign = -sign;
+  };
+  int pass = 0, sc[SR][2];                 // scales of the channels that this wave stages
+#pragma unroll
+  for (int r = 0; r < SR; ++r) sc[r][0] = sc[r][1] = 0;
+  while (b < f.B) {
+    const float gp = pg, gs = pg * sign;
+#pragma unroll
+    for (int r = 0; r < SR; ++r) {
+      const int q = r * nw + w;
+      if (q < np) {
+        unsigned pt[3], py[2];
+        bf16_split(pv[r][0], pv[r][1], pt);
+        unsigned* xd = reinterpret_cast<unsigned*>(XS + ((q >> 3) * 6 + ((q >> 2) & 1)) * 64 + lane) + (q & 3);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) xd[p * 2 * 64 * 4] = pt[p];
+        const float y0 = gs * pv[r][0], y1 = gs * pv[r][1];
+        if (pass == 0 || __any(fmaxf(fabsf(ldexpf(y0, sc[r][0])), fabsf(ldexpf(y1, sc[r][1]))) > 32768.f)) {
+          const int e0 = scale_exponent(wave_max(fabsf(y0))), e1 = scale_exponent(wave_max(fabsf(y1)));
+          sc[r][0] = pass == 0 ? e0 : min(sc[r][0], e0);
+          sc[r][1] = pass == 0 ? e1 : min(sc[r][1], e1);
+          if (lane < 2) ES[2 * q + lane] = lane == 0 ? sc[r][0] : sc[r][1];
+        }
+        f16_split(ldexpf(y0, sc[r][0]), ldexpf(y1, sc[r][1]), py);
+        unsigned* yd = reinterpret_cast<unsigned*>(YS + lane * kMlpTS) + q;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) yd[p * 64 * (kMlpTS / 2)] = py[p];
+      }
+    }
+    if (w == 0) GS[lane] = pg;
+    __syncthreads();
+    const long long bo = b, po = (t << 6) + lane;
+    for (t += gridDim.x; t >= tiles_per_b && b < f.B; t -= tiles_per_b) ++b;
+    const bool more = b < f.B;
+    if (more) load();
+    {
+      const int e = ES[c];
+      if (__any(e != y_exp)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) accw[v] = ldexpf(accw[v], e - y_exp);
+        y_exp = e;
+      }
+    }
+    // Column block by column block.  The matrix instructions of one are dealt between the vector instructions of the
+    // other by hand: left alone, the compiler keeps them together, and a wave waits for its own chain of products.
+    v16f ga[NB], hacc[NB];
+    u32x4 xs[KB][3], dp[NB][2][2], dt[2], yt[2];
+    auto read_x = [&](int nb) {
+      const int pc = (NPG == 2 ? wp : nb) * 32 + c;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) xs[kb][p] = XS[((kb * 3 + p) * 2 + half) * 64 + pc];
+    };
+    auto clear = [](v16f& a) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) a[v] = 0.f;
+    };
+    auto hidden = [&](int nb, int r0, int r1) {            // products r0 .. r1 - 1 of 6 KB
+#pragma unroll
+      for (int r = 0; r < 6 * KB; ++r)
+        if (r >= r0 && r < r1) {
+          if (r == 0) {
+            if constexpr (ALL) {
+#pragma unroll
+              for (int v = 0; v < 16; v += 4) {
+                const float4 q = *reinterpret_cast<const float4*>(BS + wh * 32 + mfma_row(v, half));
+                hacc[nb][v] = q.x; hacc[nb][v + 1] = q.y; hacc[nb][v + 2] = q.z; hacc[nb][v + 3] = q.w;
+              }
+            } else {
+              clear(hacc[nb]);
+            }
+          }
+          hacc[nb] = mfma_bf16(a1[r % KB][kSplitA[r / KB]], xs[r % KB][kSplitB[r / KB]], hacc[nb]);
+        }
+    };
+    auto turned = [&](int nb, int m) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        dt[p] = lds_turned(T + (nb * 2 + p) * 32 * kMlpTS, 16 * m, kMlpTS);
+        yt[p] = lds_turned(YS + p * 64 * kMlpTS, (NPG == 2 ? wp : nb) * 32 + 16 * m, kMlpTS);
+      }
+    };
+    auto products = [&](int nb, int step) {                // eighth `step` of the sixteen products with d
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        if (s != step) continue;
+        if (s == 0) clear(ga[nb]);
+        if (s == 2) turned(nb, 0);
+        if (s < 4) {
+          ga[nb] = mfma_f16(am[0][kHalfA[s]], dp[nb][0][kHalfB[s]], ga[nb]);
+          ga[nb] = mfma_f16(am[1][kHalfA[s]], dp[nb][1][kHalfB[s]], ga[nb]);
+        } else {
+          constexpr int two[4] = {0, 2, 0, 2};
+          const int r = two[s - 4];
+          accw = mfma_f16(dt[kHalfA[r]], yt[kHalfB[r]], accw);
+          accw = mfma_f16(dt[kHalfA[r + 1]], yt[kHalfB[r + 1]], accw);
+          if (s == 5) turned(nb, 1);
+        }
+      }
+    };
+    auto slopes = [&](int nb, auto&& beside) {
+      const float gl = GS[(NPG == 2 ? wp : nb) * 32 + c];
+      accg += half == 0 ? gl : 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        beside(v / 2);
+        float d[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          float a;
+          gelu_and_grad_f(hacc[nb][v + q], a, d[q]);
+          acc2[v + q] = fmaf(gl, a, acc2[v + q]);
+          if constexpr (ALL) accb[v + q] = fmaf(gl, d[q], accb[v + q]);
+        }
+        unsigned pt[2];
+        f16_split(d[0], d[1], pt);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) dp[nb][v >> 3][p][(v & 7) / 2] = pt[p];
+        if ((v & 3) == 2) {                // rows 8 q + 4 half + 0 .. 3 of point c
+          const int q = v >> 2;
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+            *reinterpret_cast<uint2*>(T + ((nb * 2 + p) * 32 + c) * kMlpTS + 8 * q + 4 * half) =
+                make_uint2(dp[nb][q >> 1][p][2 * (q & 1)], dp[nb][q >> 1][p][2 * (q & 1) + 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    read_x(0);
+    hidden(0, 0, 6 * KB);
+    if constexpr (NB == 2 && ALL) {        // no registers for that
+      slopes(0, [](int) {});
+#pragma unroll
+      for (int u = 0; u < 8; ++u) products(0, u);
+      read_x(1);
+      hidden(1, 0, 6 * KB);
+      slopes(1, [](int) {});
+    } else if constexpr (NB == 2) {
+      read_x(1);
+      __builtin_amdgcn_sched_barrier(0);
+      slopes(0, [&](int u) { hidden(1, 6 * KB * u / 8, 6 * KB * (u + 1) / 8); });
+      slopes(1, [&](int u) { products(0, u); });
+    } else {
+      slopes(0, [](int) {});
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) products(NB - 1, u);
+    __builtin_amdgcn_wave_barrier();
+    if (gx != nullptr) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        float* share = own + 4 * half * 64 + (NPG == 2 ? wp : nb) * 32 + c;
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (mfma_row(v, 0) < ROWS) share[mfma_row(v, 0) * 64] = ga[nb][v];
+      }
+    }
+    __syncthreads();
+    if (gx != nullptr && po < N) {
+      const float* src = regions + (NPG == 2 ? half * f.nwh * REG : 0) + lane;
+      for (int i = w; i < Ci; i += nw) {
+        float sum = 0.f;
+#pragma unroll 4
+        for (int ww = 0; ww < f.nwh; ++ww) sum += src[ww * REG + i * 64];
+        gx[(bo * Ci + i) * N + po] = ldexpf(sum, -EM[i]) * gp;
+      }
+    }
+    if (++pass == kMlpFlush) {
+      pass = 0;
+      flush();
+    }
+  }
+  flush();
+  // the lanes of a row, then two waves with the same hidden units, meet in LDS in a fixed order
+  __syncthreads();
+  double* meet = reinterpret_cast<double*>(smem4) + wh * 64;
+  auto joined = [&](double v) {
+    if (NPG == 1) return v;
+    __syncthreads();
+    if (wp == 1) meet[lane] = v;
+    __syncthreads();
+    return wp == 0 ? v + meet[lane] : 0.0;
+  };
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int k = wh * 32 + mfma_row(v, half);
+    const double s = joined(accd[v]) * (k < H ? (double)W2[k] : 0.0);
+    if (wp == 0 && k < H) {
+      if (c < Ci) dst[k * Ci + c] = s;
+      else if (c == Ci) dst[H * Ci + k] = s;
+    }
+  }
+  auto row_sum = [&](const float (&a)[16]) {               // in lane l: over the lanes of register l / 2, half l % 2
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) own[66 * v + 33 * half + c] = a[v];
+    __builtin_amdgcn_wave_barrier();
+    double s = 0.0;
+    for (int j = 0; j < 32; ++j) s += (double)own[33 * c + j];
+    return joined(s);
+  };
+  const int k = wh * 32 + mfma_row(c >> 1, c & 1);
+  const bool mine = wp == 0 && half == 0 && k < H;
+  const double s2 = row_sum(acc2);
+  if (mine) dst[H * (Ci + 1) + k] = s2;
+  if constexpr (ALL) {
+    const double sb = row_sum(accb);
+    if (mine) dst[H * Ci + k] = sb * (double)W2[k];
+  }
+  double sg = accgd;
+#pragma unroll
+  for (int m = 1; m < 32; m <<= 1) sg += __shfl_xor(sg, m);
+  sg = joined(sg);
+  if (tid == 0) dst[H * (Ci + 1) + H] = sg;
+}
+
+// The adjoint of a projection to two to four channels, in fp32 throughout: v_mfma_f32_32x32x2, lane l supplies A[l%32][l/32]
+// and B[l/32][l%32].  As above, but gh = (W2^T g) gelu'(h) stands in the place of d and is not split.
+constexpr int kMlpTile = 64;             // points per pass of a block
+constexpr int kMlpStage = 6;             // values a thread stages per pass
+constexpr int kMlpXS = kMlpTile + 1;     // row stride of the staged tile (odd: column reads spread over the banks)
+constexpr int kMlpFlush32 = 16;          // passes between flushes of the fp32 weight-gradient accumulator
+constexpr int kMlpTurn = 33;               // row stride of a wave's 32x32 turn buffer
+
+template <int KS>
 __global__ __launch_bounds__(512) void mlp2_bwd_mfma_kernel(
     int B, int Ci, int H, int Co, long long N, const float* __restrict__ x, const float* __restrict__ W1,
     const float* __restrict__ b1, const float* __restrict__ W2, const float* __restrict__ g,
     float* __restrict__ gx, double* __restrict__ part) {
   HIP_DYNAMIC_SHARED(float, smem)
+  constexpr int CO = 4;
   const int nthreads = blockDim.x, nw = nthreads >> 6;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, half = lane >> 5, c = lane & 31;
   float* XS = smem;                                      // [32][kMlpXS]: tile, ones, zeros as above
   float* GS = XS + 32 * kMlpXS;                          // [CO][kMlpTile] upstream gradient of the tile
-  float* T = GS + CO * kMlpTile + w * (32 * kMlpTS);     // this wave's [32][kMlpTS] turn buffer
-  float* GXP = GS + CO * kMlpTile + nw * (32 * kMlpTS);  // [nw][Ci][kMlpXS] partial gx of the waves
-  float* W2S = GXP + nw * Ci * kMlpXS;                   // [CO][H], only when CO > 1 (else W2 sits in registers)
-  int acc_off = 32 * kMlpXS + CO * kMlpTile + nw * (32 * kMlpTS) + nw * Ci * kMlpXS + (CO > 1 ? CO * H : 0);
+  float* T = GS + CO * kMlpTile + w * (32 * kMlpTurn);     // this wave's [32][kMlpTurn] turn buffer
+  float* GXP = GS + CO * kMlpTile + nw * (32 * kMlpTurn);  // [nw][Ci][kMlpXS] partial gx of the waves
+  float* W2S = GXP + nw * Ci * kMlpXS;                   // [CO][H]
+  int acc_off = 32 * kMlpXS + CO * kMlpTile + nw * (32 * kMlpTurn) + nw * Ci * kMlpXS + CO * H;
   acc_off += acc_off & 1;
   double* ACC = reinterpret_cast<double*>(smem + acc_off);   // [nsum] gW1 | gb1 | gW2 | gb2
   const int nsum = H * (Ci + 1) + Co * H + Co;
   for (int q = tid; q < nsum; q += nthreads) ACC[q] = 0.0;
   for (int e = tid; e < (32 - Ci) * kMlpXS; e += nthreads) XS[Ci * kMlpXS + e] = e < kMlpXS ? 1.f : 0.f;
-  if constexpr (CO > 1)
-    for (int e = tid; e < CO * H; e += nthreads) W2S[e] = e < Co * H ? W2[e] : 0.f;
-  float A1[KS], A2[16], W2r[1][16];
+  for (int e = tid; e < CO * H; e += nthreads) W2S[e] = e < Co * H ? W2[e] : 0.f;
+  float A1[KS], A2[16];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     const int i = 2 * s + half, k = w * 32 + c;
@@ -687,7 +1181,6 @@ __global__ __launch_bounds__(512) void mlp2_bwd_mfma_kernel(
   for (int v = 0; v < 16; ++v) {
     const int k = w * 32 + mfma_row(v, half);
     A2[v] = c < Ci ? W1[k * Ci + c] : 0.f;
-    if constexpr (CO == 1) W2r[0][v] = W2[k];
   }
   const long long tiles_per_b = (N + kMlpTile - 1) / kMlpTile;
   const long long ntiles = tiles_per_b * B;
@@ -758,12 +1251,12 @@ __global__ __launch_bounds__(512) void mlp2_bwd_mfma_kernel(
         float tt = 0.f;
 #pragma unroll
         for (int o = 0; o < CO; ++o) {
-          const float w2v = CO == 1 ? W2r[0][v] : W2S[o * H + w * 32 + mfma_row(v, half)];
+          const float w2v = W2S[o * H + w * 32 + mfma_row(v, half)];
           tt = fmaf(w2v, gl[o], tt);
           acc2[o][v] = fmaf(gl[o], a, acc2[o][v]);
         }
         gh[v] = tt * d;
-        T[mfma_row(v, half) * kMlpTS + c] = gh[v];
+        T[mfma_row(v, half) * kMlpTurn + c] = gh[v];
       }
       v16f gacc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -776,7 +1269,7 @@ __global__ __launch_bounds__(512) void mlp2_bwd_mfma_kernel(
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int s = 0; s < 16; ++s)
-        accw = __builtin_amdgcn_mfma_f32_32x32x2f32(T[c * kMlpTS + 2 * s + half],
+        accw = __builtin_amdgcn_mfma_f32_32x32x2f32(T[c * kMlpTurn + 2 * s + half],
                                                     XS[c * kMlpXS + nb * 32 + 2 * s + half], accw, 0, 0, 0);
       __builtin_amdgcn_wave_barrier();
     }
@@ -789,7 +1282,7 @@ __global__ __launch_bounds__(512) void mlp2_bwd_mfma_kernel(
         if (p0 + col < N) gx[(b * Ci + i) * N + p0 + col] = sum;
       }
     }
-    if (++pass == kMlpFlush) {
+    if (++pass == kMlpFlush32) {
       pass = 0;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -812,11 +1305,11 @@ __global__ __launch_bounds__(512) void mlp2_bwd_mfma_kernel(
     if (o < Co) {
       __syncthreads();
 #pragma unroll
-      for (int v = 0; v < 16; ++v) T[mfma_row(v, half) * kMlpTS + c] = acc2[o][v];
+      for (int v = 0; v < 16; ++v) T[mfma_row(v, half) * kMlpTurn + c] = acc2[o][v];
       __syncthreads();
       if (half == 0) {
         double sum = 0.0;
-        for (int cc = 0; cc < 32; ++cc) sum += (double)T[c * kMlpTS + cc];
+        for (int cc = 0; cc < 32; ++cc) sum += (double)T[c * kMlpTurn + cc];
         ACC[H * (Ci + 1) + o * H + w * 32 + c] = sum;
       }
       float sg = accg[o];
@@ -1222,7 +1715,7 @@ hipError_t launch_pointwise_linear(int B, int Ci, int Co, int64_t np, const floa
   return hipGetLastError();
 }
 
-// The matrix-core projection kernels take hidden widths that are whole 32-row blocks, one wave
+// The fp32 adjoint of the projection takes hidden widths that are whole 32-row blocks, one wave
 // each, and tiles whose (c_in + c_out) x 64 values the block's threads stage in kMlpStage loads.
 bool mlp2_mfma_fits(int Ci, int H, int Co) {
   if (H % 32 != 0 || H < 32 || H > 256 || Ci > 31 || Co > 4 || Ci < 1 || Co < 1) return false;
@@ -1230,11 +1723,17 @@ bool mlp2_mfma_fits(int Ci, int H, int Co) {
 }
 
 size_t mlp2_bwd_mfma_lds(int Ci, int H, int Co) {
-  const int nw = H / 32, co = Co == 1 ? 1 : 4;
-  size_t floats = (size_t)32 * kMlpXS + (size_t)co * kMlpTile + (size_t)nw * 32 * kMlpTS + (size_t)nw * Ci * kMlpXS;
-  if (co > 1) floats += (size_t)co * H;
+  const int nw = H / 32;
+  size_t floats = (size_t)32 * kMlpXS + (size_t)4 * kMlpTile + (size_t)nw * 32 * kMlpTurn + (size_t)nw * Ci * kMlpXS +
+                  (size_t)4 * H;
   floats += floats & 1;
   return floats * 4 + ((size_t)H * (Ci + 1) + (size_t)Co * H + Co) * 8;
+}
+
+// LDS of the projection: the weights' three parts in operand order (a channel of ones joins the input channels) and W2
+size_t mlp2_split_lds(int Ci, int H, int Co) {
+  const size_t nh = (H + 31) / 32;
+  return nh * ((Ci + 16) / 16) * 3 * 64 * 16 + (size_t)(Co == 1 ? 1 : 4) * nh * 32 * 4;
 }
 
 hipError_t launch_pointwise_mlp2(int B, int Ci, int H, int Co, int64_t np, const float* x,
@@ -1243,17 +1742,21 @@ hipError_t launch_pointwise_mlp2(int B, int Ci, int H, int Co, int64_t np, const
   const int64_t nb = (np + kThreads - 1) / kThreads;
   if (nb > 0x7fffffffLL || B > 65535 || Co > 4 || Ci > 32) return hipErrorInvalidValue;
   if (nb == 0 || B == 0) return hipSuccess;
-  if (mlp2_mfma_fits(Ci, H, Co)) {
-    const int nw = H / 32;
-    const int64_t tiles = (int64_t)B * ((np + kMlpTile - 1) / kMlpTile);
-    const unsigned nblk = (unsigned)(tiles < 2048 ? tiles : 2048);
-    const int co = Co == 1 ? 1 : 4;
-    const size_t lds = (size_t)(32 * kMlpXS + nw * co * kMlpTile) * 4;
-#define FNO_MLPF(KSV, COV)                                                                              \
-  hipLaunchKernelGGL((mlp2_fwd_mfma_kernel<KSV, COV>), dim3(nblk), dim3(64 * nw), lds, s, B, Ci, H, Co, \
+  if (mlp2_split_lds(Ci, H, Co) <= (size_t)(150 * 1024)) {
+    const size_t lds = mlp2_split_lds(Ci, H, Co);
+    const int64_t tiles = (int64_t)B * ((np + 31) / 32), room = (int64_t)(160 * 1024 / lds);
+    const int64_t most = 256 * (room < 4 ? room : 4);
+    const unsigned nblk = (unsigned)((tiles + 3) / 4 < most ? (tiles + 3) / 4 : most);
+#define FNO_MLPF(NSV, COV)                                                                              \
+  hipLaunchKernelGGL((mlp2_fwd_split_kernel<NSV, COV>), dim3(nblk), dim3(kThreads), lds, s, B, Ci, H, Co, \
                      (long long)np, x, W1, b1, W2, b2, y)
-    if (Ci <= 21) { if (co == 1) FNO_MLPF(11, 1); else FNO_MLPF(11, 4); }
-    else { if (co == 1) FNO_MLPF(16, 1); else FNO_MLPF(16, 4); }
+#define FNO_MLPF_C(NSV) do { if (Co == 1) FNO_MLPF(NSV, 1); else FNO_MLPF(NSV, 4); } while (0)
+    if (Ci < 8) FNO_MLPF_C(4);
+    else if (Ci < 16) FNO_MLPF_C(8);
+    else if (Ci < 24) FNO_MLPF_C(12);
+    else if (Ci < 32) FNO_MLPF_C(16);
+    else FNO_MLPF_C(18);
+#undef FNO_MLPF_C
 #undef FNO_MLPF
     return hipGetLastError();
   }
@@ -1392,18 +1895,40 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
                                      float* gb1, float* gW2, float* gb2, void* ws, hipStream_t s) {
   if (Ci > 32 || Co > 4 || N <= 0) return hipErrorInvalidValue;
   const int nsum = H * (Ci + 1) + Co * H + Co;
-  if (mlp2_mfma_fits(Ci, H, Co) && mlp2_bwd_mfma_lds(Ci, H, Co) <= (size_t)(150 * 1024)) {
-    const int nw = H / 32, co = Co == 1 ? 1 : 4;
+  if (Co == 1 && H <= 256) {
+    const MlpBwd f{B, Ci, H, (H + 31) / 32, (long long)N};
+    const int npg = f.nwh <= 2 ? 2 : 1, nw = f.nwh * npg, kb = Ci < 16 ? 1 : 2;
+    const int64_t tiles = (int64_t)B * ((N + 63) / 64);
+    const int nblk = (int)(tiles < kMlpBlocks ? tiles : kMlpBlocks);
+    double* part = static_cast<double*>(ws);
+#define FNO_MLPB(NSV, NPGV)                                                                                       \
+  hipLaunchKernelGGL((mlp2_bwd_split_kernel<NSV, NPGV>), dim3((unsigned)nblk), dim3(64 * nw),                     \
+                     (size_t)kb * 6 * 64 * 16 + (size_t)2 * 64 * kMlpTS * 2 + (128 + (NSV == 18 ? 256 : 0) + (size_t)nw * mlp_region(NSV, NPGV)) * 4, \
+                     s, f, x, W1, b1, W2, g, gx, part)
+#define FNO_MLPB_N(NSV) do { if (npg == 2) FNO_MLPB(NSV, 2); else FNO_MLPB(NSV, 1); } while (0)
+    if (Ci < 8) FNO_MLPB_N(4);
+    else if (Ci < 16) FNO_MLPB_N(8);
+    else if (Ci < 24) FNO_MLPB_N(12);
+    else if (Ci < 32) FNO_MLPB_N(16);
+    else FNO_MLPB_N(18);
+#undef FNO_MLPB_N
+#undef FNO_MLPB
+    hipLaunchKernelGGL(reduce_ranges_kernel, dim3((nsum + kRedPairs - 1) / kRedPairs),
+                       dim3(kRedPairs * kRedGroups), 0, s, part, nblk, H * Ci, H, Co * H, Co, gW1, gb1, gW2, gb2);
+    return hipGetLastError();
+  }
+  if (Co > 1 && mlp2_mfma_fits(Ci, H, Co) && mlp2_bwd_mfma_lds(Ci, H, Co) <= (size_t)(150 * 1024)) {
+    const int nw = H / 32;
     const size_t lds = mlp2_bwd_mfma_lds(Ci, H, Co);
     const int64_t tiles = (int64_t)B * ((N + kMlpTile - 1) / kMlpTile);
     const int nblk = (int)(tiles < kMlpBlocks ? tiles : kMlpBlocks);
     double* part = static_cast<double*>(ws);
-#define FNO_MLPB(KSV, COV)                                                                                 \
-  hipLaunchKernelGGL((mlp2_bwd_mfma_kernel<KSV, COV>), dim3((unsigned)nblk), dim3(64 * nw), lds, s, B, Ci, \
-                     H, Co, (long long)N, x, W1, b1, W2, g, gx, part)
-    if (Ci <= 21) { if (co == 1) FNO_MLPB(11, 1); else FNO_MLPB(11, 4); }
-    else { if (co == 1) FNO_MLPB(16, 1); else FNO_MLPB(16, 4); }
-#undef FNO_MLPB
+    if (Ci <= 21)
+      hipLaunchKernelGGL((mlp2_bwd_mfma_kernel<11>), dim3((unsigned)nblk), dim3(64 * nw), lds, s, B, Ci, H, Co, (long long)N,
+                         x, W1, b1, W2, g, gx, part);
+    else
+      hipLaunchKernelGGL((mlp2_bwd_mfma_kernel<16>), dim3((unsigned)nblk), dim3(64 * nw), lds, s, B, Ci, H, Co, (long long)N,
+                         x, W1, b1, W2, g, gx, part);
     hipLaunchKernelGGL(reduce_ranges_kernel, dim3((nsum + kRedPairs - 1) / kRedPairs),
                        dim3(kRedPairs * kRedGroups), 0, s, part, nblk, H * Ci, H, Co * H, Co, gW1, gb1, gW2, gb2);
     return hipGetLastError();

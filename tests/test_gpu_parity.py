@@ -632,6 +632,62 @@ def test_pointwise_adjoints_match_oracle(shape):
         assert rel(host(got), want0[name]) <= TOL, name
 
 
+def _projection(batch, ci, h, co, npts, seed, sx=1.0, sg=1.0, sw2=1.0):
+    """Inputs of a projection, its float32 results and the float64 ones (torch, on the device)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    normal = lambda *shape: torch.randn(shape, device="cuda", generator=gen)
+    x, g = normal(batch, ci, npts) * sx, normal(batch, co, npts) * sg
+    W1, b1, W2, b2 = normal(h, ci) * ci ** -0.5 / (sx.T if torch.is_tensor(sx) else sx), normal(h) * 0.1, \
+        normal(co, h) * h ** -0.5 * sw2, normal(co) * 0.1
+    u, gx = torch.empty(batch, co, npts, device="cuda"), torch.empty_like(x)
+    grads = [torch.empty_like(p) for p in (W1, b1, W2, b2)]
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(ci, h, co) // 4 + 2, device="cuda")
+    B.fno_pointwise_mlp2(batch, ci, h, co, npts, x, W1, b1, W2, b2, u)
+    B.fno_pointwise_mlp2_bwd(batch, ci, h, co, npts, x, W1, b1, W2, g, gx, *grads, ws)
+    torch.cuda.synchronize()
+    xd = x.double().transpose(0, 1).reshape(ci, -1)
+    gd = g.double().transpose(0, 1).reshape(co, -1)
+    z = W1.double() @ xd + b1.double()[:, None]
+    cdf = 0.5 * torch.erfc(-z / 2 ** 0.5)
+    gh = (W2.double().T @ gd) * (cdf + z * torch.exp(-0.5 * z * z) / (2 * np.pi) ** 0.5)
+    wide = lambda a: a.reshape(a.shape[0], batch, npts).transpose(0, 1)
+    want = dict(u=wide(W2.double() @ (z * cdf) + b2.double()[:, None]), gx=wide(W1.double().T.contiguous() @ gh),
+                gW1=gh @ xd.T.contiguous(), gb1=gh.sum(1), gW2=gd @ (z * cdf).T.contiguous(), gb2=gd.sum(1))
+    # what the errors go with: the values themselves, and the root sum square of the terms of a sum over points
+    act, sq = z * cdf, lambda a, b: float((a ** 2 @ (b ** 2).T.contiguous()).sum().sqrt())
+    scale = dict(u=float(want["u"].norm()), gx=float(want["gx"].norm()), gW1=sq(gh, xd), gb1=float(gh.norm()),
+                 gW2=sq(gd, act), gb2=float(gd.norm()))
+    return dict(u=u, gx=gx, gW1=grads[0], gb1=grads[1], gW2=grads[2], gb2=grads[3]), want, scale
+
+
+# every tile of channels (1 .. 7, .. 15, .. 23, .. 31, 32) at its ends, hidden widths on and off the groups of 32 with one
+# and two waves each, ragged and single points, several batch entries and channels
+@pytest.mark.parametrize("batch, ci, h, co, npts", [
+    (1, 1, 32, 1, 33), (2, 7, 40, 1, 65), (1, 8, 64, 1, 64), (3, 15, 96, 1, 127), (1, 16, 128, 1, 2000), (1, 23, 100, 4, 31),
+    (1, 24, 160, 1, 1), (2, 31, 256, 1, 200), (1, 32, 32, 1, 63), (1, 32, 250, 1, 1000), (1, 20, 1, 1, 129), (1, 5, 300, 2, 70)])
+def test_projection_on_split_products(batch, ci, h, co, npts):
+    got, want, scale = _projection(batch, ci, h, co, npts, 7)
+    for name, ref in want.items():
+        # a hidden value and its slope are within about 2 units of 2^-23 (products of 24 bits, the fits of GELU); the sum over
+        # the hidden units may cancel to a quarter of its terms' size
+        assert float((got[name].double() - ref).norm()) <= 8 * 2.0 ** -23 * scale[name], name
+
+
+def test_projection_adjoint_with_channels_and_points_of_very_different_size():
+    # fp16 has five exponent bits: channels of x from 1e-9 to 1e2 (and weights to match), hidden units weighted 1e-4 to 1e4,
+    # cotangents that grow by 1e12 along the points, so that the scales follow them.  Every channel by itself, as above
+    sx = torch.logspace(-9, 2, 20, device="cuda")[:, None]
+    got, want, _ = _projection(1, 20, 128, 1, 100000, 8, sx=sx, sg=torch.logspace(-20, -8, 100000, device="cuda"),
+                               sw2=torch.logspace(-4, 4, 128, device="cuda"))
+    for name, dim in (("gx", 2), ("gW1", 0)):
+        err = (got[name].double() - want[name]).norm(dim=dim) / want[name].norm(dim=dim)
+        assert float(err.max()) <= 8 * 2.0 ** -23, name
+    first = slice(0, 5000)                              # the small cotangents alone
+    err = (got["gx"].double() - want["gx"])[..., first].norm(dim=2) / want["gx"][..., first].norm(dim=2)
+    assert float(err.max()) <= 8 * 2.0 ** -23
+
+
 def test_whole_network_training_step_matches_oracle():
     """Lift, two blocks, projection; relative L2 loss; backward through all of it; one Adam step.
 
