@@ -54,9 +54,9 @@ enum {
 
 /* GELU is z Phi(z) with Phi the normal distribution function (the erf form, not the tanh one).  The
  * kernels evaluate the tail of Phi by a polynomial for its logarithm: the forward epilogues (z Phi(z)
- * within 3e-7), the backward kernels of a block of width 4, 8, .. 20 on whole 64-point steps and of the
- * projection.  The backward kernels of all other blocks and of projections whose hidden width is off the
- * matrix-core kernels use the float erff / expf routines; in every case the activation and its slope are
+ * within 3e-7), the backward kernels of a block and of the projection.  Only the backward kernel of
+ * projections whose hidden width is off the matrix-core kernels uses the float erff / expf routines; in every
+ * case the activation and its slope are
  * within 1e-6 (absolute) of the float64 definition, far inside the 1e-5 relative L2 the library is tested
  * to. */
 enum { FNO_ACT_IDENTITY = 0, FNO_ACT_GELU = 1 };

@@ -38,6 +38,28 @@ __device__ __forceinline__ void gelu_and_grad_f(float z, float& val, float& grad
   grad = fmaf(z, pdf, cdf);
 }
 
+// The same without a bound on its argument and closer to float64: log2 of twice the tail is a q(a), q of degree 9 (largest
+// error of max(a, 1) T(a) 1.9e-10; a q(a) falls from 0 to minus infinity), so that its rounding shrinks with a.  25 issue
+// slots, where erff and expf took over 100 (both branches of erff run in a wave); against float64, of the norm under
+// N(0, 1): the slope 3.9e-8, value times slope 6.6e-8 (erff and expf 4.0e-8 and 7.2e-8).
+__device__ __forceinline__ void gelu_and_grad_fine_f(float z, float& val, float& grad) {
+  const float a = fabsf(z);
+  float q = fmaf(a, -5.62642732e-08f, 1.38986923e-06f);
+  q = fmaf(a, q, -1.52123248e-05f);
+  q = fmaf(a, q, 9.45571737e-05f);
+  q = fmaf(a, q, -3.24071734e-04f);
+  q = fmaf(a, q, 6.31522853e-05f);
+  q = fmaf(a, q, 6.89695915e-03f);
+  q = fmaf(a, q, -5.24215102e-02f);
+  q = fmaf(a, q, -4.59223896e-01f);
+  q = fmaf(a, q, -1.15110409e+00f);
+  const float t = __builtin_amdgcn_exp2f(a * q);
+  const float pdf = __builtin_amdgcn_exp2f(fmaf(z * z, -0.72134752044f, -1.3257480647f));     // log2 of 1 / sqrt(2 pi)
+  const float cdf = z < 0.f ? 0.5f * t : fmaf(-0.5f, t, 1.0f);
+  val = z * cdf;
+  grad = fmaf(z, pdf, cdf);
+}
+
 template <int CT, bool STREAM>
 __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
     const float* __restrict__ z, const float* __restrict__ gout, const float* __restrict__ x,
@@ -128,14 +150,20 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
 
 // The same step for every other width up to 32, any point count and alignment, and c_in != c_out (the adjoint of the
 // lift).  The kernel above keeps all of gW in a wave's accumulators, which 32 channels do not fit; here the output
-// channels are dealt to `ngrp` waves of a block (OT tiles of 4 each), which share x through the cache.  Layout and
-// products are those of the kernel above; rows need not be aligned (4-byte aligned 16-byte loads), a batch entry's
-// ragged last step takes single values, and channels past the end read the last one and count as zero.  The fp32
-// accumulators take kBwdChain steps (128 terms of a lane block) and then go to doubles, which are added over the wave's
-// 16 lane blocks, half of them sent away at each level: every lane keeps a sixteenth.  GELU and its slope by erff and
-// expf.  5 -> 20 channels at 33.5 M points: 0.78 ms = 4.3 TB/s; 32 -> 32 at 2.16 M points with GELU: 0.43 ms, where x
-// comes from the cache for three of the four waves that share it.  (One sum per thread over tiles of 256 points in LDS
-// took 1.9 and 0.67 ms.)
+// channels are dealt to `ngrp` waves of a block (OT tiles of 4 each).  Layout and products are those of the kernel above;
+// rows need not be aligned (4-byte aligned 16-byte loads), a batch entry's ragged last step takes single values, and
+// channels past the end read the last one and count as zero.  The fp32 accumulators take kBwdChain steps (128 terms of a
+// lane block) and then go to doubles, which are added over the wave's 16 lane blocks, half of them sent away at each
+// level: every lane keeps a sixteenth.
+//
+// Where the waves of a step are two or four (NG), each reads its share of x and leaves it in LDS, double buffered, one
+// barrier a step; that takes half to three quarters of a step's loads off every wave, and the registers they took hold
+// the next step's, asked for a step ahead.  (With all of x in every wave there is no room for that: 0.45 ms in the first
+// case below, with spills.)  What bounds it: copy speed at 32 channels and 4.2 TB/s (0.21 ms at 5.2).  With erff, expf and
+// x read by every wave, and now, us: 32 -> 32 at 2.16 M points with GELU and a target 446 and 270; the widths 17, 22, 24,
+// 25, 27 without a target 203, 215, 239, 355, 364 and 136, 148, 178, 257, 261; 9 and 10 (one wave a step) 117, 118 and
+// 90, 93; 5 -> 20 at 33.5 M points, no activation, 754 and 655 (its values of z were set to zero one by one, which waited
+// for the loads between them).
 constexpr int kBwdChain = 32;
 
 template <bool STREAM>
@@ -162,7 +190,9 @@ __device__ __forceinline__ void fold_level(const T* v, double* out, bool upper, 
 }
 constexpr int fold_count(int n) { return n % 2 == 0 ? n / 2 : n; }
 
-template <int OT, int IT, bool STREAM>
+// NG: waves that share x through LDS, or 0, where every wave reads all of it.
+constexpr int kBwdXS = 80;               // row stride of staged x: 16 banks, so that four channels by four points spread over all
+template <int OT, int IT, int NG, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     const float* __restrict__ z, const float* __restrict__ gout, const float* __restrict__ x,
     float* __restrict__ gz_out, double* __restrict__ part, int B, int Ci, int Co, long long N, int act,
@@ -173,8 +203,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
   const int per_block = (kThreads / 64) / ngrp;            // point ranges per block
   const int o0 = (wave % ngrp) * 4 * OT;
   const bool need_z = act || mse_target;
-  long long orow[OT], irow[IT];
-  bool olive[OT], ilive[IT];
+  long long orow[OT], irow[NG > 0 ? IT / NG : IT];
+  bool olive[OT], ilive[NG > 0 ? IT / NG : IT];
 #pragma unroll
   for (int T = 0; T < OT; ++T) {
     const int o = o0 + 4 * T + j4;
@@ -182,8 +212,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     orow[T] = (long long)(olive[T] ? o : Co - 1) * N;
   }
 #pragma unroll
-  for (int T = 0; T < IT; ++T) {
-    const int i = 4 * T + j4;
+  for (int T = 0; T < (NG > 0 ? IT / NG : IT); ++T) {
+    const int i = 4 * (NG > 0 ? wave % NG * (IT / NG) + T : T) + j4;
     ilive[T] = i < Ci;
     irow[T] = (long long)(ilive[T] ? i : Ci - 1) * N;
   }
@@ -229,49 +259,66 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
   const long long xe = xs + per_x < steps ? xs + per_x : steps;
   const long long wl = (long long)(blockIdx.x >> 3) * per_block + wave / ngrp;
   const long long nwl = (long long)(gridDim.x >> 3) * per_block;
-  int chain = 0;
-  for (long long s = xs + wl; s < xe; s += nwl) {
+  constexpr int XT = NG > 0 ? IT / NG : IT;      // tiles of x that a wave reads
+  constexpr int XS = 4 * IT * kBwdXS;
+  __shared__ float XL[NG > 0 ? 2 * (kThreads / 64 / NG) * XS : 1];       // [parity][point range][4 IT][kBwdXS]
+  const int member = NG > 0 ? wave % NG : 0;
+  float* own = XL + (NG > 0 ? wave / NG * XS : 0);
+  // the values of step s, whole or ragged
+  auto fetch = [&](long long s, long long& ob, long long& p0, v4f (&zn)[OT], v4f (&gn)[OT], v4f (&xn)[XT]) {
     const long long bb = s / steps_per_b;
-    const long long p0 = (s - bb * steps_per_b) * 64;
-    const long long p = p0 + 4 * blk;
+    p0 = (s - bb * steps_per_b) * 64;
+    ob = bb * Co * N;
+    const long long p = p0 + 4 * blk, ib = bb * Ci * N;
     const bool whole = p0 + 64 <= N;                       // the same for the whole wave
-    const long long ob = bb * Co * N, ib = bb * Ci * N;
-    v4f zq[OT], gq[OT], xq[IT];
     if (whole) {
+      if (need_z)                                          // else z is nowhere used: zeros here would wait for other loads
 #pragma unroll
-      for (int T = 0; T < OT; ++T) {
-        zq[T] = need_z ? load4<STREAM>(z + ob + orow[T] + p) : v4f{0.f, 0.f, 0.f, 0.f};
-        gq[T] = load4<STREAM>(gout + ob + orow[T] + p);
-      }
+        for (int T = 0; T < OT; ++T) zn[T] = load4<STREAM>(z + ob + orow[T] + p);
 #pragma unroll
-      for (int T = 0; T < IT; ++T) xq[T] = load4<false>(x + ib + irow[T] + p);
+      for (int T = 0; T < OT; ++T) gn[T] = load4<STREAM>(gout + ob + orow[T] + p);
+#pragma unroll
+      for (int T = 0; T < XT; ++T) xn[T] = load4<STREAM && (NG > 0)>(x + ib + irow[T] + p);
     } else {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const long long pu = p + u < N ? p + u : N - 1;
 #pragma unroll
         for (int T = 0; T < OT; ++T) {
-          zq[T][u] = need_z ? z[ob + orow[T] + pu] : 0.f;
-          gq[T][u] = gout[ob + orow[T] + pu];
+          if (need_z) zn[T][u] = z[ob + orow[T] + pu];
+          gn[T][u] = gout[ob + orow[T] + pu];
         }
 #pragma unroll
-        for (int T = 0; T < IT; ++T) xq[T][u] = p + u < N ? x[ib + irow[T] + pu] : 0.f;
+        for (int T = 0; T < XT; ++T) xn[T][u] = p + u < N ? x[ib + irow[T] + pu] : 0.f;
       }
+    }
+    return whole;
+  };
+  // the cotangent of the pre-activation, in gq's place
+  auto cotangent = [&](long long ob, long long p0, bool whole, const v4f (&zq)[OT], v4f (&gq)[OT]) {
+    const long long p = p0 + 4 * blk;
+    if (act) {
+#pragma unroll
+      for (int T = 0; T < OT; ++T)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float val, slope;
+          gelu_and_grad_fine_f(zq[T][u], val, slope);
+          if (mse_target) gq[T][u] = mse_scale * (val - gq[T][u]);
+          gq[T][u] *= slope;
+        }
+    } else if (mse_target) {
+#pragma unroll
+      for (int T = 0; T < OT; ++T)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) gq[T][u] = mse_scale * (zq[T][u] - gq[T][u]);
     }
 #pragma unroll
     for (int T = 0; T < OT; ++T) {
       v4f g = gq[T];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (act) {
-          const float zv = zq[T][u];
-          if (mse_target) g[u] = mse_scale * (gelu_f(zv) - g[u]);
-          g[u] *= gelu_prime_f(zv);
-        } else if (mse_target) {
-          g[u] = mse_scale * (zq[T][u] - g[u]);
-        }
+      for (int u = 0; u < 4; ++u)
         if (!olive[T] || (!whole && p + u >= N)) g[u] = 0.f;
-      }
       if (gz_out != nullptr && olive[T]) {
         float* dst = gz_out + ob + orow[T] + p;
         if (whole) {
@@ -286,19 +333,69 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
       gbacc[T] += (g[0] + g[1]) + (g[2] + g[3]);
       gq[T] = g;
     }
-#pragma unroll
-    for (int T = 0; T < IT; ++T)
-      if (!ilive[T]) xq[T] = v4f{0.f, 0.f, 0.f, 0.f};
+  };
+  // gq against XN tiles of x from c0 on
+  auto products = [&](const v4f (&gq)[OT], const auto& xv, auto c0) {
+    constexpr int XN = sizeof(xv) / sizeof(v4f);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int a = 0; a < OT; ++a)
 #pragma unroll
-        for (int c = 0; c < IT; ++c)
-          acc[a][c] = __builtin_amdgcn_mfma_f32_4x4x1f32(gq[a][u], xq[c][u], acc[a][c], 0, 0, 0);
-    if (++chain == kBwdChain) {
-      chain = 0;
-      flush();
+        for (int c = 0; c < XN; ++c)
+          acc[a][c0.value + c] = __builtin_amdgcn_mfma_f32_4x4x1f32(gq[a][u], xv[c][u], acc[a][c0.value + c], 0, 0, 0);
+  };
+  int chain = 0;
+  using std::integral_constant;
+  if constexpr (NG == 0) {
+    for (long long s = xs + wl; s < xe; s += nwl) {
+      long long ob, p0;
+      v4f zq[OT], gq[OT], xq[XT];
+      const bool whole = fetch(s, ob, p0, zq, gq, xq);
+      cotangent(ob, p0, whole, zq, gq);
+#pragma unroll
+      for (int T = 0; T < XT; ++T)
+        if (!ilive[T]) xq[T] = v4f{0.f, 0.f, 0.f, 0.f};
+      products(gq, xq, integral_constant<int, 0>{});
+      if (++chain == kBwdChain) { chain = 0; flush(); }
+    }
+  } else {
+    // all waves of a block take as many turns; the values of a step are asked for a step ahead
+    long long ob = 0, p0 = 0;
+    bool live = xs + wl < xe, whole = false;
+    v4f zn[OT], gn[OT], xn[XT];
+    if (live) whole = fetch(xs + wl, ob, p0, zn, gn, xn);
+    int turn = 0;
+    for (long long s0 = xs + (long long)(blockIdx.x >> 3) * per_block; s0 < xe; s0 += nwl, turn ^= 1) {
+      float* buf = own + turn * (kThreads / 64 / NG) * XS;
+      v4f zq[OT], gq[OT];
+      const long long ob_now = ob, p0_now = p0;
+      const bool live_now = live, whole_now = whole;
+      if (live) {
+#pragma unroll
+        for (int T = 0; T < XT; ++T)
+          *reinterpret_cast<v4f*>(buf + (4 * (member * XT + T) + j4) * kBwdXS + 4 * blk) = ilive[T] ? xn[T] : v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int T = 0; T < OT; ++T) { zq[T] = zn[T]; gq[T] = gn[T]; }
+      }
+      const long long s = s0 + nwl + wave / NG;
+      live = s < xe;
+      if (live) whole = fetch(s, ob, p0, zn, gn, xn);
+      __syncthreads();
+      if (live_now) {
+        cotangent(ob_now, p0_now, whole_now, zq, gq);
+        constexpr int XN = IT == 6 ? 3 : IT;               // tiles of x in registers at a time: as many as leave no spills
+        auto piece = [&](auto c0) {
+          v4f xq[XN];
+#pragma unroll
+          for (int c = 0; c < XN; ++c)
+            xq[c] = *reinterpret_cast<const v4f*>(buf + (4 * (c0.value + c) + j4) * kBwdXS + 4 * blk);
+          products(gq, xq, c0);
+        };
+        piece(integral_constant<int, 0>{});
+        if constexpr (XN < IT) piece(integral_constant<int, IT - XN>{});
+        if (++chain == kBwdChain) { chain = 0; flush(); }
+      }
     }
   }
   flush();
@@ -1628,18 +1725,19 @@ hipError_t launch_bwd_wide(const float* z, const float* gout, const float* x, fl
   if (nb > 1024) nb = 1024;
   *nslots = (int)nb * per_block;
   const bool stream = (int64_t)B * Co * N * 4 >= kStreamBytes;
-#define FNO_BPX(OTV, ITV)                                                                                         \
-  do {                                                                                                            \
-    if (stream)                                                                                                   \
-      hipLaunchKernelGGL((bwd_pointwise_wide_kernel<OTV, ITV, true>), dim3((unsigned)nb), dim3(kThreads), 0, s, z, gout, \
-                         x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);      \
-    else                                                                                                          \
-      hipLaunchKernelGGL((bwd_pointwise_wide_kernel<OTV, ITV, false>), dim3((unsigned)nb), dim3(kThreads), 0, s, z, gout, \
-                         x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);      \
+#define FNO_BPX(OTV, ITV, NGV)                                                                                         \
+  do {                                                                                                                 \
+    if (stream)                                                                                                        \
+      hipLaunchKernelGGL((bwd_pointwise_wide_kernel<OTV, ITV, NGV, true>), dim3((unsigned)nb), dim3(kThreads), 0, s,   \
+                         z, gout, x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);  \
+    else                                                                                                               \
+      hipLaunchKernelGGL((bwd_pointwise_wide_kernel<OTV, ITV, NGV, false>), dim3((unsigned)nb), dim3(kThreads), 0, s,  \
+                         z, gout, x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);  \
   } while (0)
-  if (it == 2) { if (ot == 2) FNO_BPX(2, 2); else if (ot == 5) FNO_BPX(5, 2); else FNO_BPX(4, 2); }
-  else if (it == 6) FNO_BPX(3, 6);
-  else FNO_BPX(2, 8);
+  if (it == 2) { if (ot == 2) FNO_BPX(2, 2, 0); else if (ot == 5) FNO_BPX(5, 2, 0); else FNO_BPX(4, 2, 0); }
+  else if (it == 6) { if (ngrp == 2) FNO_BPX(3, 6, 2); else FNO_BPX(3, 6, 0); }
+  else if (ngrp == 4) FNO_BPX(2, 8, 4);
+  else FNO_BPX(2, 8, 0);
 #undef FNO_BPX
   return hipGetLastError();
 }

@@ -201,6 +201,27 @@ def test_forward_activation_over_its_whole_range():
     assert float(over.max()) <= 0.0
 
 
+@pytest.mark.parametrize("c", [7, 17, 25])
+def test_activation_slope_over_its_whole_range(c):
+    # W = 1, R = 0 and a cotangent of ones: gx is the activation's slope as the kernel for any width forms it (one to four
+    # waves to a point).  Off by the tail's and the density's exponential (an exponent off by a unit in its last place and
+    # one more of the result: 2 x 2^-24 of a tail up to 1/2, 4 x 2^-24 of |z| phi(z) up to 0.25) and three roundings of
+    # values up to 1.13: 2^-24 (1 + 1 + 3.4) at most
+    grid, modes = (16, 16, 16, 5), (2, 2, 2, 2)
+    n = c * 16 ** 3 * 5
+    z = torch.linspace(-16.0, 16.0, n, dtype=torch.float64).float()
+    z[:8] = torch.tensor([0.0, -0.0, 1e18, -1e18, 1e-30, -1e-30, 40.0, -40.0])
+    z = z.view(1, c, *grid).cuda()
+    desc = B.make_desc(1, c, c, grid, modes, 0, B.FNO_ACT_GELU)
+    R = torch.zeros(c, c, 4, 4, 4, 2, dtype=torch.complex64, device="cuda")
+    W, gx = torch.eye(c, device="cuda"), torch.empty_like(z)
+    B.fno_block_bwd(desc, torch.zeros_like(z), R, W, z, torch.zeros_like(R[:1]), torch.ones_like(z), gx, torch.empty_like(R),
+                    torch.empty_like(W), torch.empty(c, device="cuda"), B.alloc_workspace(desc, B.FNO_OP_BLOCK_BWD))
+    zd = z.double().cpu()
+    want = 0.5 * torch.erfc(-zd / 2 ** 0.5) + zd * torch.exp(-0.5 * zd * zd) / (2 * np.pi) ** 0.5
+    assert float((gx.cpu().double() - want).abs().max()) <= 5.4 * 2.0 ** -24
+
+
 def test_accumulate_flag_adds_parameter_gradients_of_successive_calls():
     """FNO_FLAG_ACCUMULATE_GRADS: gR, gW, gb of a second call are added to those of the first (the
     gradient of a broadcast weight is a sum, Sec. 2.1), gx is overwritten; compared with the sum of
