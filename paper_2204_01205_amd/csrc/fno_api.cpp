@@ -253,7 +253,7 @@ int forward_chain(const Plan& p, void* ws, const float* field, int C, float2* sp
   float2* a1 = at<float2>(ws, p.off_a1);
   float2* a2 = at<float2>(ws, p.off_a2);
   FNO_STAGE(FNO_STAGE_TZ_FWD, s, fno::launch_tz_fwd(field, a1, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]),
-                             p.folded ? at<float>(ws, p.off_fold) : nullptr, bc * p.N[0] * p.N[1], p.ax[2], p.Nt, p.mt, s));
+                             p.folded ? at<float>(ws, p.off_fold) : nullptr, bc * p.N[0] * p.N[1], p.N[0] * p.N[1], p.ax[2], p.Nt, p.mt, s));
   const int64_t in_y = (int64_t)p.L[2] * p.mt;
   FNO_STAGE(FNO_STAGE_Y_FWD, s, axis_fwd(p, ws, 1, a1, a2, bc * p.N[0], in_y, s));
   const int64_t in_x = in_y * p.L[1];

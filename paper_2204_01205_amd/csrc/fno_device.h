@@ -127,6 +127,24 @@ __device__ __forceinline__ double swap_pair(double v) {
   return __builtin_bit_cast(double, b);
 }
 
+// A float as the exact sum of three bf16 values.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+__device__ __forceinline__ unsigned bf16_pair(float a, float b) {
+  const v2f v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+// the three parts of a and b, side by side
+__device__ __forceinline__ void bf16_split(float a, float b, unsigned (&part)[3]) {
+  part[0] = bf16_pair(a, b);
+  const float ra = a - bf16_low(part[0]), rb = b - bf16_high(part[0]);
+  part[1] = bf16_pair(ra, rb);
+  part[2] = bf16_pair(ra - bf16_low(part[1]), rb - bf16_high(part[1]));
+}
+
 // Thread blocks are dealt to the chip's eight XCDs round robin.  For a grid padded to a multiple of
 // eight blocks this is the work item of block `bid` under which every XCD walks a contiguous eighth
 // of the items, so that the memory it has in flight at one time spans an eighth of the pages

@@ -36,16 +36,16 @@ struct FoldPlan {
 FoldPlan fold_plan(AxisPlan az);
 hipError_t launch_plan_tables(const TableSet& ts, hipStream_t s);
 
-// Forward (t, z): x[planes][Nz][Nt] real  ->  out[planes][Lz][mt] complex.
+// Forward (t, z): x[planes][Nz][Nt] real  ->  out[planes][Lz][mt] complex; `field` planes make one (batch, channel) field.
 // ztab: the folded table of the z axis, or null where tz_fwd_fold_fits() says no.
 hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const float2* twz, const float* ztab,
-                         int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s);
+                         int64_t planes, int field, AxisPlan az, int Nt, int mt, hipStream_t s);
 
 // The same for any lengths (see fno_tz_fwd_fold.hip); ztab: the folded table of the z axis.
 bool tz_fwd_fold_fits(AxisPlan az, int Nt, int mt);
 bool tz_fwd_fold_pays(AxisPlan az, int Nt, int mt, int64_t planes);
 hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, const float* ztab,
-                              int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s);
+                              int64_t planes, int field, AxisPlan az, int Nt, int mt, hipStream_t s);
 
 // Complex pruned transform along the middle axis of [outer][N|L][inner].
 hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int64_t outer,

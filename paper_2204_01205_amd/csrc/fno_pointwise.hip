@@ -660,22 +660,6 @@ __device__ __forceinline__ int mfma_row(int v, int half) { return 8 * (v >> 2) +
 // rounding.  v_mfma_f32_32x32x16_bf16 takes half the cycles of v_mfma_f32_32x32x2 for eight times the terms, so the six
 // cost three eighths of the fp32 instruction, and unlike it they run beside the vector unit's work.
 // Lane l supplies A[l%32][8 (l/32) + j] and B[8 (l/32) + j][l%32], j < 8; the accumulator is laid out as mfma_row says.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
-__device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
-__device__ __forceinline__ unsigned bf16_pair(float a, float b) {
-  const v2f v = {a, b};
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-}
-// the three parts of a and b, side by side
-__device__ __forceinline__ void bf16_split(float a, float b, unsigned (&part)[3]) {
-  part[0] = bf16_pair(a, b);
-  const float ra = a - bf16_low(part[0]), rb = b - bf16_high(part[0]);
-  part[1] = bf16_pair(ra, rb);
-  part[2] = bf16_pair(ra - bf16_low(part[1]), rb - bf16_high(part[1]));
-}
 __device__ __forceinline__ v16f mfma_bf16(u32x4 a, u32x4 b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }

@@ -804,7 +804,7 @@ size_t tz_fast_lds(AxisPlan az, int Nt, int mt, int ppb) {
 }
 
 hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const float2* twz, const float* ztab,
-                         int64_t planes, AxisPlan az, int Nt, int mt, hipStream_t s) {
+                         int64_t planes, int field, AxisPlan az, int Nt, int mt, hipStream_t s) {
   if (planes <= 0) return hipSuccess;
   // in-register t stage: the power-of-two lengths, and 30 (the time steps of the paper's training samples)
   // as plain sums with compile-time twiddles
@@ -859,7 +859,7 @@ hipError_t launch_tz_fwd(const float* x, float2* out, const float2* twt, const f
     return hipGetLastError();
   }
   if (ztab != nullptr && tz_fwd_fold_fits(az, Nt, mt) && tz_fwd_fold_pays(az, Nt, mt, planes))
-    return launch_tz_fwd_fold(x, out, twt, ztab, planes, az, Nt, mt, s);
+    return launch_tz_fwd_fold(x, out, twt, ztab, planes, field, az, Nt, mt, s);
   int ppb = 1;
   // enough rows to occupy the block, within an LDS share that keeps several blocks per CU
   while (ppb * 2 * az.N <= 2 * kThreads && tz_fwd_lds(az, Nt, mt, ppb * 2) <= (size_t)(32 * 1024)) ppb *= 2;

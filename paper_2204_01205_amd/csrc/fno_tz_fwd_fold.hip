@@ -19,12 +19,19 @@
 // tile of the plane passes through LDS, no wave waits for another; LDS holds only the z table, which
 // a block's waves share over all planes they walk.
 //
-// The sums stay in fp32 but in short chains: two over t, blocks of eight pairs over z that are added up as they come,
+// The fp32 products' sums are in short chains: two over t, blocks of eight pairs over z that are added up as they come,
 // and the turn by the phase is in double.  One chain of Nz / 2 terms was off by up to 1.7 times what the FFT over z
 // that these kernels replaced is off by (128 x 20: 1.18e-7 with the FFT, 1.75e-7 in one chain, 1.07e-7 now).
 //
-// What bounds it: the matrix cores at 32 cycles per instruction (a 263 x 16 plane with 49 frequencies and
-// 8 bins: 9 tiles of 8 + 16 instructions) next to one read of the field.  Measured against the kernels it
+// Most shapes run both products on v_mfma_f32_16x16x32_bf16 instead (fold_split), with every float the exact sum of three
+// bf16 values and the six of nine products that count (what is left out is below 2^-25 of a product): fp32 matrix
+// instructions and vector instructions share one datapath, the 16-bit ones run beside it, and take 32 terms per rounding.
+// Splitting a value costs five and a half vector instructions.  A K step holds 32 values: of four values (KS <= 4, and
+// the rows of a tile) two parts each, so that three instructions make the six products, of eight one part.
+//
+// What bounds it: in fp32 the matrix cores at 32 cycles per instruction (a 263 x 16 plane with 49 frequencies and
+// 8 bins: 9 tiles of 8 + 16 instructions) next to one read of the field (20 channels, 68 x 118 columns: 0.85 ms); in parts
+// the vector unit's splits, 0.68 ms = 4.7 TB/s with the bins written.  Measured against the kernels it
 // replaced (mixed-radix and dense complex sums on tiles staged in LDS), us on 1536 columns: 64 x 20, 20 channels, 93 -> 53;
 // 128 x 24 202 -> 179; 80 x 40 375 -> 145; 263 x 16, 6 channels, 293 -> 102; two entries of 8 x 40 113 -> 44.
 #include "fno_device.h"
@@ -39,9 +46,53 @@ namespace {
 constexpr int fold_regs(int KS, int CT, int MT, int PP) {
   return KS * (4 + CT) + 8 * MT * CT * PP + (CT == 2 ? 16 : 6) * MT + 48;
 }
-constexpr int fold_waves(int KS, int CT, int MT, int PP) {
-  const int regs = fold_regs(KS, CT, MT, PP);
+// on bf16 parts: two row tiles in flight, the parts of the t table, the accumulators, the parts of a tile, addresses
+constexpr int split_regs(int KS, int CT, int MT) {
+  return KS * 2 + CT * (KS <= 4 ? 6 : 12 * ((KS + 7) / 8)) + 8 * MT * CT + (KS <= 4 ? 40 : 56) + 40;
+}
+constexpr int fold_waves(int KS, int CT, int MT, int PP, bool split) {
+  const int regs = split ? split_regs(KS, CT, MT) : fold_regs(KS, CT, MT, PP);
   return regs <= 64 ? 8 : (regs <= 72 ? 6 : (regs <= 96 ? 5 : (regs <= 128 ? 4 : (regs <= 168 ? 3 : 2))));
+}
+// words of a row of the table in parts (three bf16 a value): 4 modulo 8, so that the rows that a read covers spread over
+// all banks
+__host__ __device__ constexpr int split_stride(int stride) { return (6 * (stride >> 2) + 3) / 8 * 8 + 4; }
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ v4f mfma_split(u32x4 a, u32x4 b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// Four values in parts p[0] (large) to p[2], as the operands of the six products that count: against a table's (third,
+// first) parts (p0, p2), against its (first, second) ones (p1, p1) and (p0, p0).
+struct Quad { u32x4 p02, p11, p00; };
+template <int N>
+__device__ __forceinline__ void split_quad(const float (&v)[N], Quad& q) {
+  unsigned a[3], b[3];
+  bf16_split(v[0], N > 1 ? v[N > 1 ? 1 : 0] : 0.f, a);
+  bf16_split(N > 2 ? v[N > 2 ? 2 : 0] : 0.f, N > 3 ? v[N > 3 ? 3 : 0] : 0.f, b);
+  q.p02 = u32x4{a[0], b[0], a[2], b[2]};
+  q.p11 = u32x4{a[1], b[1], a[1], b[1]};
+  q.p00 = u32x4{a[0], b[0], a[0], b[0]};
+}
+// t: third, first and second parts of four entries of a table
+template <class F>
+__device__ __forceinline__ v4f quad_product(const u32x2 (&t)[3], const Quad& q, F mfma) {
+  const u32x4 t20 = {t[0][0], t[0][1], t[1][0], t[1][1]}, t01 = {t[1][0], t[1][1], t[2][0], t[2][1]};
+  v4f a = mfma(t20, q.p02, v4f{0.f, 0.f, 0.f, 0.f});
+  a = mfma(t01, q.p11, a);
+  return mfma(t01, q.p00, a);
+}
+// values s0 .. s0 + 7 of N in parts, zeros past the end
+template <int N>
+__device__ __forceinline__ void split_octet(const float (&v)[N], int s0, u32x4 (&p)[3]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    unsigned q[3];
+    const int s = s0 + 2 * j;
+    bf16_split(s < N ? v[s < N ? s : 0] : 0.f, s + 1 < N ? v[s + 1 < N ? s + 1 : 0] : 0.f, q);
+#pragma unroll
+    for (int h = 0; h < 3; ++h) p[h][j] = q[h];
+  }
 }
 
 // A row of Nt = 16 J + r floats (1 <= r <= 16): J runs of 16 (four per lane group) and a tail in which
@@ -49,15 +100,18 @@ constexpr int fold_waves(int KS, int CT, int MT, int PP) {
 // entries a lower group has already taken meet zeros in the t table.
 // PP planes of at most 16 / PP row pairs share a tile: row 4 g + v of it is pair (4 / PP) g + v % (4 / PP) of
 // plane v / (4 / PP), so that each register of the first product belongs to one plane.
-template <int J, int W, int CT, int MT, int PP, bool STREAM>
-__global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void tz_fwd_fold_kernel(
+// SPLIT: 1 the products on bf16 parts, 2 the same in blocks of eight waves.
+template <int J, int W, int CT, int MT, int PP, int SPLIT, bool STREAM>
+__global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 * J + W, CT, MT, PP, SPLIT > 0)) void tz_fwd_fold_kernel(
     const float* __restrict__ x, float* __restrict__ out, const float2* __restrict__ twt,
-    const float* __restrict__ ztab, long long planes, int Nz, int Nt, int Lz, int npos, int mt, int mrows,
+    const float* __restrict__ ztab, long long planes, int field, int Nz, int Nt, int Lz, int npos, int mt, int mrows,
     int pairs, int stride, int ngroups, int mgroups) {
   HIP_DYNAMIC_SHARED(float, smem)
+  constexpr int TH = SPLIT > 1 ? 2 * kThreads : kThreads;
   constexpr int KS = 4 * J + W;                 // K steps of the product over t
-  float* COS = smem;                            // [16 MT][stride]
-  float* SIN = smem + 16 * MT * stride;         // [16 MT][stride]
+  const int row = SPLIT ? split_stride(stride) : stride;       // words of a row of the table in LDS
+  float* COS = smem;                            // [16 MT][row]
+  float* SIN = smem + 16 * MT * row;            // [16 MT][row]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // uniform: plane addresses stay scalar
   const int c = lane & 15, g = lane >> 4;
@@ -69,12 +123,31 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
     const float4* cs = reinterpret_cast<const float4*>(ztab + (long long)m0 * stride);
     const float4* sn = reinterpret_cast<const float4*>(ztab + (long long)(mrows + m0) * stride);
     const int n4 = (16 * MT * stride) >> 2;
-    for (int i = tid; i < n4; i += kThreads) {
-      reinterpret_cast<float4*>(COS)[i] = cs[i];
-      reinterpret_cast<float4*>(SIN)[i] = sn[i];
+    if constexpr (SPLIT) {
+      // four pairs of a row at a time: their third, first and second parts
+      const int quads = stride >> 2;
+      for (int i = tid; i < n4; i += TH) {
+        const int r = i / quads, at = r * row + 6 * (i - r * quads);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float4 v = h ? sn[i] : cs[i];
+          unsigned a[3], b[3];
+          bf16_split(v.x, v.y, a);
+          bf16_split(v.z, v.w, b);
+          u32x2* d = reinterpret_cast<u32x2*>((h ? SIN : COS) + at);
+          d[0] = u32x2{a[2], b[2]};
+          d[1] = u32x2{a[0], b[0]};
+          d[2] = u32x2{a[1], b[1]};
+        }
+      }
+    } else {
+      for (int i = tid; i < n4; i += TH) {
+        reinterpret_cast<float4*>(COS)[i] = cs[i];
+        reinterpret_cast<float4*>(SIN)[i] = sn[i];
+      }
     }
   }
-  double2* ROT = reinterpret_cast<double2*>(SIN + 16 * MT * stride);    // [16 MT]
+  double2* ROT = reinterpret_cast<double2*>(SIN + 16 * MT * row);       // [16 MT]
   if (tid < 16 * MT) ROT[tid] = reinterpret_cast<const double2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
   const int r = Nt - 16 * J;
   const int t0 = min(W * g, r - W);             // start of this lane group's tail
@@ -94,14 +167,42 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
       tb[ct][s] = v;
     }
   }
+  // the same in parts: KS <= 4 third, first and second part of four values; else eight values a part
+  constexpr int KB = (KS + 7) / 8;
+  u32x2 t4[SPLIT && KS <= 4 ? CT : 1][3];
+  u32x4 t8[SPLIT && KS > 4 ? CT : 1][KB][3];
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      auto part2 = [&](int s0, unsigned (&q)[3]) { bf16_split(s0 < KS ? tb[ct][s0 < KS ? s0 : 0] : 0.f, s0 + 1 < KS ? tb[ct][s0 + 1 < KS ? s0 + 1 : 0] : 0.f, q); };
+      if constexpr (KS <= 4) {
+        unsigned a[3], b[3];
+        part2(0, a);
+        part2(2, b);
+        t4[ct][0] = u32x2{a[2], b[2]};
+        t4[ct][1] = u32x2{a[0], b[0]};
+        t4[ct][2] = u32x2{a[1], b[1]};
+      } else {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            unsigned q[3];
+            part2(8 * kb + 2 * j, q);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) t8[ct][kb][p][j] = q[p];
+          }
+      }
+    }
+  }
   const double sgn = (c & 1) ? -1.0 : 1.0;
   __syncthreads();
 
   // each XCD walks a contiguous eighth of the planes, its waves interleaved inside it
   const long long per_x = (planes + 7) >> 3;
   const long long pe = min(planes, (long long)(xcd + 1) * per_x);
-  const long long nwl = (long long)((gridDim.x >> 3) / ngroups) * (kThreads / 64) * PP;
-  long long p = (long long)xcd * per_x + ((long long)(local / ngroups) * (kThreads / 64) + wave) * PP;
+  const long long nwl = (long long)((gridDim.x >> 3) / ngroups) * (TH / 64) * PP;
+  long long p = (long long)xcd * per_x + ((long long)(local / ngroups) * (TH / 64) + wave) * PP;
   if (p >= pe) return;
   const int ntile = PP > 1 ? 1 : (pairs + 15) >> 4;
   constexpr int VP = 4 / PP;                    // registers of a lane that belong to one plane
@@ -129,7 +230,18 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
     for (int u = 0; u < W; ++u) { va[4 * J + u] = qa[u]; vb[4 * J + u] = qb[u]; }
   };
   load_tile(p, 0);
+  int at_field = SPLIT > 0 ? (int)(p % field) : 0;         // of the plane in its (batch, channel) field
+  const int step_field = SPLIT > 0 ? (int)(nwl % field) : 0;
   for (; p < pe; p += nwl) {
+    // The 16-bit instructions cut their sums towards minus infinity some bits below the rounding (0.004 units of the last
+    // place on average).  Planes add up over y and x, where the lowest frequencies of 48 x 32 planes of 108 x 33 were off
+    // by 3.3e-6 of a bin's size, fp32 products 8e-7.  Planes with an odd number of ones in their index within the field are
+    // worked with the other sign, which takes it out (6.5e-7).
+    const bool neg = SPLIT > 0 && (__builtin_popcount((unsigned)at_field) & 1);
+    if constexpr (SPLIT > 0) {
+      at_field += step_field;
+      if (at_field >= field) at_field -= field;
+    }
     v4f accC[PP][MT][CT], accS[PP][MT][CT];
 #pragma unroll
     for (int q = 0; q < PP; ++q)
@@ -142,10 +254,64 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
         }
     for (int tile = 0; tile < ntile; ++tile) {
       float e[KS], o[KS];
+      if (neg) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) { e[s] = va[s] + vb[s]; o[s] = va[s] - vb[s]; }
+        for (int s = 0; s < KS; ++s) { e[s] = -va[s] - vb[s]; o[s] = vb[s] - va[s]; }
+      } else {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) { e[s] = va[s] + vb[s]; o[s] = va[s] - vb[s]; }
+      }
       if (tile + 1 < ntile) load_tile(p, tile + 1);
       else if (p + nwl < pe) load_tile(p + nwl, 0);
+      if constexpr (SPLIT) {
+        const v4f zero = {0.f, 0.f, 0.f, 0.f};
+        v4f dE[CT], dO[CT];
+        if constexpr (KS <= 4) {
+          Quad qe, qo;
+          split_quad<KS>(e, qe);
+          split_quad<KS>(o, qo);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            dE[ct] = quad_product(t4[ct], qe, [](u32x4 t, u32x4 d, v4f a) { return mfma_split(d, t, a); });
+            dO[ct] = quad_product(t4[ct], qo, [](u32x4 t, u32x4 d, v4f a) { return mfma_split(d, t, a); });
+          }
+        } else {
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) dE[ct] = dO[ct] = zero;
+          u32x4 pe[KB][3], po[KB][3];
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) {
+            split_octet<KS>(e, 8 * kb, pe[kb]);
+            split_octet<KS>(o, 8 * kb, po[kb]);
+          }
+          constexpr int A[6] = {2, 0, 1, 1, 0, 0}, Bp[6] = {0, 2, 1, 0, 1, 0};       // the small products first
+#pragma unroll
+          for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+              for (int ct = 0; ct < CT; ++ct) {
+                dE[ct] = mfma_split(pe[kb][A[r]], t8[ct][kb][Bp[r]], dE[ct]);
+                dO[ct] = mfma_split(po[kb][A[r]], t8[ct][kb][Bp[r]], dO[ct]);
+              }
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          Quad qe, qo;
+          const float ve[4] = {dE[ct][0], dE[ct][1], dE[ct][2], dE[ct][3]}, vo[4] = {dO[ct][0], dO[ct][1], dO[ct][2], dO[ct][3]};
+          split_quad<4>(ve, qe);
+          split_quad<4>(vo, qo);
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            const u32x2* zc = reinterpret_cast<const u32x2*>(COS + (16 * m + c) * row + 6 * (4 * tile + g));
+            const u32x2* zs = reinterpret_cast<const u32x2*>(SIN + (16 * m + c) * row + 6 * (4 * tile + g));
+            const u32x2 tc[3] = {zc[0], zc[1], zc[2]}, ts[3] = {zs[0], zs[1], zs[2]};
+            accC[0][m][ct] += quad_product(tc, qe, [](u32x4 t, u32x4 d, v4f a) { return mfma_split(t, d, a); });
+            accS[0][m][ct] += quad_product(ts, qo, [](u32x4 t, u32x4 d, v4f a) { return mfma_split(t, d, a); });
+          }
+        }
+        continue;
+      }
       float ca[MT][VP], sa[MT][VP];
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
@@ -211,7 +377,8 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int kl = 16 * m + g4 + v, k = m0 + kl;
-          const double2 w = ROT[kl];
+          double2 w = ROT[kl];
+          if (neg) w = make_double2(-w.x, -w.y);
           const double ws = sgn * w.y;
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct) {
@@ -233,7 +400,26 @@ __global__ __launch_bounds__(kThreads, fold_waves(4 * J + W, CT, MT, PP)) void t
 
 constexpr size_t kFoldLds = 78 * 1024;      // two blocks per CU
 
-size_t fold_lds(const FoldPlan& f, int MT) { return (size_t)(2 * 16 * MT * f.stride + 4 * 16 * MT) * 4; }
+size_t fold_lds(const FoldPlan& f, int MT, int split = 0) {
+  return (size_t)(2 * 16 * MT * (split ? split_stride(f.stride) : f.stride) + 4 * 16 * MT) * 4;
+}
+
+// Which products: 0 fp32, 1 bf16 parts, 2 the same in blocks of eight waves.  The parts pay where the matrix work is what
+// a wave waits for: two tiles of bins or of frequencies, or whole K steps of the product over t (KS: a quarter of 16
+// points, or most of 32 and more).  Their table takes half as much LDS again, so that above 40 KiB a block has eight waves,
+// and only where four values a lane make a K step.  us, fp32 and parts, 8 channels, 24 x 24 columns: z of 118, 20 kept a
+// side, t of 8, 16, 24 and 48 with 3, 8, 12 and 16 bins 17.0, 20.2, 34.3, 47.4 and 15.1, 17.6, 25.0, 37.7; 64 x 64
+// columns: z of 60, 12 kept, t of 16, 24, 30 with 8, 12, 8 bins 40.2, 78.5, 85.5 and 38.3, 70.5, 76.9, but t of 8 and 10
+// with 3 and 4 bins 29.6, 32.4 and 31.2, 34.4; z of 263, 24 kept, t of 10 and 14 with 4 and 6 bins 162, 173 and 137, 146
+// (in blocks of four waves 181, 192), but 24 x 24 columns of 20 and 30 points of t 33 and 41 and, in blocks of eight, 39
+// and 47.
+int fold_split(const FoldPlan& f, int KS, int CT, int MT, int PP) {
+  const size_t lds = fold_lds(f, MT, 1);
+  if (PP > 1 || lds > kFoldLds) return 0;
+  if (CT == 2) return 1;
+  if (lds > 40 * 1024) return MT == 2 && KS <= 4 ? 2 : 0;
+  return MT == 2 || (f.pairs > 16 && (KS == 4 || KS >= 7)) ? 1 : 0;
+}
 
 }  // namespace
 
@@ -283,33 +469,45 @@ bool tz_fwd_fold_fits(AxisPlan az, int Nt, int mt) {
 }
 
 hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, const float* ztab, int64_t planes,
-                              AxisPlan az, int Nt, int mt, hipStream_t s) {
+                              int field, AxisPlan az, int Nt, int mt, hipStream_t s) {
   const FoldPlan f = fold_plan(az);
+  const int PP = f.pairs <= 4 ? 4 : (f.pairs <= 8 ? 2 : 1);      // more than one: also MT = 1, no more frequencies than rows
   const int CT = 2 * mt <= 16 ? 1 : 2, MT = f.rows >= 32 && fold_lds(f, 2) <= kFoldLds ? 2 : 1;
+  const int J = (Nt - 1) / 16, r = Nt - 16 * J, W = (r + 3) / 4;
+  const int split = fold_split(f, 4 * J + W, CT, MT, PP), threads = split > 1 ? 2 * kThreads : kThreads;
   const int mgroups = (f.rows + 16 * MT - 1) / (16 * MT), cgroups = (2 * mt + 16 * CT - 1) / (16 * CT);
   const int ngroups = mgroups * cgroups;
-  const size_t lds = fold_lds(f, MT);
+  const size_t lds = fold_lds(f, MT, split);
   // resident blocks only: each loads the z table once and walks planes
-  const int J = (Nt - 1) / 16, r = Nt - 16 * J, W = (r + 3) / 4;
-  const int PP = f.pairs <= 4 ? 4 : (f.pairs <= 8 ? 2 : 1);      // then also MT = 1: no more frequencies than rows
-  int64_t per_cu = fold_waves(4 * J + W, CT, MT, PP);
+  int64_t per_cu = fold_waves(4 * J + W, CT, MT, PP, split > 0) * kThreads / threads;
   if (per_cu > (int64_t)(160 * 1024 / lds)) per_cu = (int64_t)(160 * 1024 / lds);
-  int64_t per_x = ((planes + 7) / 8 + 4 * PP - 1) / (4 * PP);
+  const int64_t per_block = threads / 64 * PP;
+  int64_t per_x = ((planes + 7) / 8 + per_block - 1) / per_block;
   if (per_x > 32 * per_cu) per_x = 32 * per_cu;
   const dim3 grid((unsigned)(8 * per_x * ngroups));
   const bool stream = planes * (int64_t)az.N * Nt * 4 >= kStreamBytes;
-#define FNO_TZD_S(JV, WV, CTV, MTV, PPV, STRV)                                                                  \
-  hipLaunchKernelGGL((tz_fwd_fold_kernel<JV, WV, CTV, MTV, PPV, STRV>), grid, dim3(kThreads), lds, s, x,         \
-                     reinterpret_cast<float*>(out), twt, ztab, (long long)planes, az.N, Nt, az.L, az.npos, mt,  \
+#define FNO_TZD_S(JV, WV, CTV, MTV, PPV, SPV, STRV)                                                             \
+  hipLaunchKernelGGL((tz_fwd_fold_kernel<JV, WV, CTV, MTV, PPV, SPV, STRV>), grid, dim3(threads), lds, s, x,    \
+                     reinterpret_cast<float*>(out), twt, ztab, (long long)planes, field, az.N, Nt, az.L, az.npos, mt,  \
                      f.rows, f.pairs, f.stride, ngroups, mgroups)
-#define FNO_TZD_M(JV, WV, CTV, MTV, PPV)                                                                \
-  do {                                                                                                  \
-    if (stream) FNO_TZD_S(JV, WV, CTV, MTV, PPV, true); else FNO_TZD_S(JV, WV, CTV, MTV, PPV, false);   \
+#define FNO_TZD_M(JV, WV, CTV, MTV, PPV, SPV)                                                                    \
+  do {                                                                                                           \
+    if (stream) FNO_TZD_S(JV, WV, CTV, MTV, PPV, SPV, true); else FNO_TZD_S(JV, WV, CTV, MTV, PPV, SPV, false);  \
   } while (0)
-#define FNO_TZD_P(JV, WV, CTV)                                                                          \
-  do {                                                                                                  \
-    if (PP == 4) FNO_TZD_M(JV, WV, CTV, 1, 4); else if (PP == 2) FNO_TZD_M(JV, WV, CTV, 1, 2);          \
-    else if (MT == 1) FNO_TZD_M(JV, WV, CTV, 1, 1); else FNO_TZD_M(JV, WV, CTV, 2, 1);                  \
+#define FNO_TZD_P(JV, WV, CTV)                                                                                   \
+  do {                                                                                                           \
+    if (PP == 4) FNO_TZD_M(JV, WV, CTV, 1, 4, 0);                                                                \
+    else if (PP == 2) FNO_TZD_M(JV, WV, CTV, 1, 2, 0);                                                           \
+    else if (MT == 1) {                                                                                          \
+      if constexpr ((CTV) == 2 || 4 * (JV) + (WV) == 4 || 4 * (JV) + (WV) >= 7) {                                \
+        if (split) { FNO_TZD_M(JV, WV, CTV, 1, 1, 1); break; }                                                   \
+      }                                                                                                          \
+      FNO_TZD_M(JV, WV, CTV, 1, 1, 0);                                                                           \
+    } else if (split == 1) FNO_TZD_M(JV, WV, CTV, 2, 1, 1);                                                      \
+    else {                                                                                                       \
+      if constexpr ((CTV) == 1 && (JV) == 0) { if (split) { FNO_TZD_M(JV, WV, 1, 2, 1, 2); break; } }            \
+      FNO_TZD_M(JV, WV, CTV, 2, 1, 0);                                                                           \
+    }                                                                                                            \
   } while (0)
   // more than eight bins (CT = 2) need 16 points of t at least: no variant of shorter rows
 #define FNO_TZD_C(JV, WV)                                                           \

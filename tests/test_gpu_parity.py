@@ -1186,6 +1186,46 @@ def test_folded_forward_transform_sums_in_short_chains(nz, mz, nt, mt):
     assert rel(xh.reshape(want.shape), want) <= 1.1 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
 
 
+@pytest.mark.parametrize("nz, mz, nt, mt", [
+    (33, 5, 13, 5), (34, 6, 26, 8), (45, 8, 64, 7),         # one tile of frequencies: a K step of four values, of eight, two
+    (17, 5, 17, 9), (90, 16, 24, 12), (150, 30, 48, 16),    # two tiles of bins; of frequencies too
+    (99, 17, 1, 1), (118, 20, 20, 8),                       # two tiles of frequencies
+    (263, 24, 16, 8), (181, 20, 5, 2),                      # blocks of eight waves
+])
+def test_forward_transform_on_split_products(nz, mz, nt, mt):
+    """Products of exact three-way splits leave out less than 2^-25 of each, and an instruction sums 32 of them to its
+    accumulator; two roundings are counted for it.  Rounded are the fold, the table over t, the large products of at most
+    two K steps, the table over z, a tile's sum, the tiles' sum (a chain), and the phase: rms 0.42 x 2^-24 each, a fifth
+    for the scatter of the inputs.  Chains in fp32 (four terms an instruction) are a sixth (20 points of t, 118) to a half
+    (64 and 45) further off."""
+    L = Layer(64, 1, 1, (1, 1, nz, nt), (0, 0, mz, mt), 1)
+    _, xh = gpu_spectral_fwd(L)
+    n, k = np.arange(nz), np.array(O.mode_lists(L.spec)[2])
+    bins = np.fft.rfft(L.x.astype(np.float64).reshape(64, nz, nt), axis=2)[:, :, :mt]
+    want = np.einsum("kn,bnt->bkt", np.exp(-2j * np.pi * (np.outer(k, n) % nz) / nz), bins)
+    roundings = 1 + 1 + (3 if nt > 32 else 2) + 1 + 2 + (np.ceil(nz / 32) + 1) / 2 + 1
+    assert rel(xh.reshape(want.shape), want) <= 1.2 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
+
+
+@pytest.mark.parametrize("nz, nt", [(108, 33), (270, 14)])
+def test_split_products_leave_no_bias_in_the_lowest_frequencies(nz, nt):
+    """Planes add up over y and x.  An entry's error scatters with that of the norm (1.5e-7 of the bins' size; 6 times that
+    over 512 entries); a bias of each plane's sums, which the 16-bit instructions have, would add up to 3e-6 here."""
+    grid, m = (48, 32, nz, nt), 2
+    L_desc = B.make_desc(1, 8, 8, grid, (m, m, m, m), 0, 0)
+    gen = torch.Generator(device="cuda").manual_seed(nz)
+    x = torch.randn((1, 8) + grid, device="cuda", generator=gen)
+    xh = torch.empty((1, 8, 2 * m, 2 * m, 2 * m, m), dtype=torch.complex64, device="cuda")
+    R = torch.zeros((8, 8, 2 * m, 2 * m, 2 * m, m), dtype=torch.complex64, device="cuda")
+    B.fno_spectral_conv_fwd(L_desc, x, R, torch.empty_like(x), xh, B.alloc_workspace(L_desc, B.FNO_OP_SPECTRAL_CONV_FWD))
+    want = torch.fft.rfft(x.double(), dim=5)[..., :m]
+    for d in (4, 3, 2):
+        want = torch.fft.fft(want, dim=d)
+        want = torch.cat([want.narrow(d, 0, m), want.narrow(d, want.shape[d] - m, m)], dim=d)
+    size = float(want.abs().square().mean().sqrt())
+    assert float((xh.to(torch.complex128) - want).abs().max()) <= 9e-7 * size
+
+
 @pytest.mark.parametrize("nz, mz, nt, mt", [(64, 11, 20, 8), (96, 17, 20, 8), (128, 23, 10, 4), (160, 28, 24, 9),
                                             (263, 47, 20, 8)])
 def test_folded_inverse_transform_sums_in_short_chains(nz, mz, nt, mt):
