@@ -18,24 +18,26 @@ namespace {
 // over points and runs on the matrix cores: v_mfma_f32_4x4x1 block blk adds the outer product
 // gz[4To..4To+3][p] x[4Ti..4Ti+3][p] of its point p to its own 4x4 partial tile; the 16 blocks,
 // the waves and the thread blocks are summed at the end (per-wave partials in double, fixed order).
-// GELU and its slope: the upper tail as in gelu_fast_f, with a polynomial of degree 7 (the tail itself enters the slope;
-// largest error of max(a, 1) T(a) 6.2e-8, least value -57 at 9.75), and the density from an exponential of its own.  19 issue
-// slots (each exponential counts two), as many as the rational form 7.1.26 of Abramowitz & Stegun that stood here; against
-// float64, of the norm under N(0, 1): 5.8e-8 on z Phi(z) and 7.2e-8 on the slope (8.5e-8 and 9.9e-8).
+// GELU and its slope: with a = |z| and t = 1 / (1 + 0.4 a) the upper tail is exp(-a^2 / 2) t P(t), the form of Abramowitz &
+// Stegun 7.1.26, whose exponential is the density up to a constant.  P has degree 5 (7.1.26: 4) and is fitted over [0, 13]
+// to 3.5e-8 of max(a, 1) T(a) and to 1.7e-3 of the tail T itself, whichever is less, so that units that are all but off
+// keep their slope.  Against float64, of the norm, with 7.1.26 in brackets: under N(0, 1) 4.8e-8 on z Phi(z) and 6.9e-8 on
+// the slope (8.8e-8, 1.1e-7), at z = -5 7e-6 and 5e-7 (1.1e-3, 5e-5), at -9 5e-4 and 7e-6 (1.2e-2, 1.7e-4).  A polynomial
+// for the tail's logarithm, fitted in absolute error, was off by 7e-3 and 3e-4 at -5, by more than the value at -9, and
+// grew with |z| beyond 1e20.
 __device__ __forceinline__ void gelu_and_grad_f(float z, float& val, float& grad) {
-  const float a = __builtin_amdgcn_fmed3f(fabsf(z), 0.0f, 9.75f);
-  float p = fmaf(a, 6.1192263e-06f, -3.2478307e-05f);
-  p = fmaf(a, p, -4.9471017e-04f);
-  p = fmaf(a, p, 7.5082830e-03f);
-  p = fmaf(a, p, -5.2784692e-02f);
-  p = fmaf(a, p, -4.5912030e-01f);
-  p = fmaf(a, p, -1.1511149f);
-  p = fmaf(a, p, -9.9999982e-01f);
-  const float tail = __builtin_amdgcn_exp2f(p);
-  const float pdf = __builtin_amdgcn_exp2f(fmaf(z * z, -0.72134752044f, -1.3257480647f));     // log2 of 1 / sqrt(2 pi)
+  const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.4f, 1.0f));
+  float q = fmaf(t, 5.5231631e-02f, -2.5018391e-01f);
+  q = fmaf(t, q, 3.3274594e-01f);
+  q = fmaf(t, q, 1.8495135e-02f);
+  q = fmaf(t, q, 1.8670905e-01f);
+  q = fmaf(t, q, 1.5700214e-01f);
+  q *= t;
+  const float e = __builtin_amdgcn_exp2f((z * z) * -0.72134752044f);    // exp(-z^2 / 2)
+  const float tail = q * e;
   const float cdf = z < 0.f ? tail : 1.0f - tail;
   val = z * cdf;
-  grad = fmaf(z, pdf, cdf);
+  grad = fmaf(z, 0.39894228040143267794f * e, cdf);
 }
 
 // The same without a bound on its argument and closer to float64: log2 of twice the tail is a q(a), q of degree 9 (largest

@@ -222,6 +222,42 @@ def test_activation_slope_over_its_whole_range(c):
     assert float((gx.cpu().double() - want).abs().max()) <= 5.4 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("mse", [False, True])
+@pytest.mark.parametrize("c", [4, 20])
+def test_activation_and_slope_of_units_that_are_off(c, mse):
+    """W = 1, R = 0, widths and points of the matrix-core kernel: gx is the slope, with a target of zeros 2 / n times value times
+    slope.  The tail T is fitted to 3.5e-8 of max(|z|, 1) T and to 1.7e-3 of T; the exponential it shares with the
+    density is off by three roundings of z^2 / 2 and its own unit, and eight more roundings are counted."""
+    grid, modes, eps = (16, 16, 16, 5), (2, 2, 2, 2), 2.0 ** -24
+    n = c * 16 ** 3 * 5
+    z = torch.linspace(-8.0 if mse else -12.5, 16.0, n, dtype=torch.float64).float()
+    if not mse:
+        z[:4] = torch.tensor([-40.0, -1e18, -1e-30, 1e18])
+    z = z.view(1, c, *grid).cuda()
+    desc = B.make_desc(1, c, c, grid, modes, 0, B.FNO_ACT_GELU, B.FNO_FLAG_MSE_TARGET if mse else 0)
+    R = torch.zeros(c, c, 4, 4, 4, 2, dtype=torch.complex64, device="cuda")
+    W, gx = torch.eye(c, device="cuda"), torch.empty_like(z)
+    B.fno_block_bwd(desc, torch.zeros_like(z), R, W, z, torch.zeros_like(R[:1]), torch.zeros_like(z) if mse else torch.ones_like(z),
+                    gx, torch.empty_like(R), torch.empty_like(W), torch.empty(c, device="cuda"),
+                    B.alloc_workspace(desc, B.FNO_OP_BLOCK_BWD))
+    z = z.double().cpu()
+    a = z.abs()
+    tail, dens = 0.5 * torch.erfc(a / 2 ** 0.5), torch.exp(-0.5 * z * z) / (2 * np.pi) ** 0.5
+    cdf = torch.where(z < 0, tail, 1 - tail)
+    value, slope = z * cdf, cdf + z * dens
+    rounds = (1.5 * a * a).clamp(max=1e4) + 8
+    on = torch.where(z < 0, 0.0, 2 * eps)
+    tail_off = torch.minimum(3.6e-8 / a.clamp(min=1), 1.75e-3 * tail) + eps * rounds * tail
+    slope_off = tail_off + eps * rounds * a * dens + on
+    value_off = a * (tail_off + on)
+    if mse:
+        want = value * slope * (2.0 / n)
+        bound = (2.0 / n) * (value.abs() * slope_off + slope.abs() * value_off + value_off * slope_off + 4 * eps * (value * slope).abs())
+    else:
+        want, bound = slope, slope_off
+    assert float(((gx.cpu().double() - want).abs() - bound).max()) <= 0.0
+
+
 def test_accumulate_flag_adds_parameter_gradients_of_successive_calls():
     """FNO_FLAG_ACCUMULATE_GRADS: gR, gW, gb of a second call are added to those of the first (the
     gradient of a broadcast weight is a sum, Sec. 2.1), gx is overwritten; compared with the sum of
