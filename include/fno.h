@@ -53,12 +53,13 @@ enum {
 };
 
 /* GELU is z Phi(z) with Phi the normal distribution function (the erf form, not the tanh one).  The
- * kernels evaluate the tail of Phi by a polynomial for its logarithm: the forward epilogues (z Phi(z)
- * within 3e-7), the backward kernels of a block and of the projection.  Only the backward kernel of
- * projections whose hidden width is off the matrix-core kernels uses the float erff / expf routines; in every
- * case the activation and its slope are
- * within 1e-6 (absolute) of the float64 definition, far inside the 1e-5 relative L2 the library is tested
- * to. */
+ * forward epilogues evaluate the tail of Phi by a polynomial for its logarithm (z Phi(z) within 3e-7), the
+ * backward kernels of a block and of the projection by such a polynomial or by the density times one; projections
+ * whose weights or hidden width are off the matrix-core kernels use the float erff / expf routines.  In every case the
+ * activation and its slope are within 1e-6 (absolute) of the float64 definition for every finite argument, far
+ * inside the 1e-5 relative L2 the library is tested to; minus infinity gives NaN.  Where products run as sums of
+ * 16-bit parts (the projection, its adjoint, the forward transform), finite values from 3.39e38 on count as
+ * infinite, an infinite one gives NaN in what depends on it, and values below 1e-33 keep 8 to 24 bits. */
 enum { FNO_ACT_IDENTITY = 0, FNO_ACT_GELU = 1 };
 
 enum {

@@ -20,11 +20,11 @@ __device__ __forceinline__ float gelu_f(float z) {
 }
 // GELU for the forward epilogues without branches or erff: with a = |z| and the upper tail T(a) = (1 - erf(a / sqrt 2)) / 2,
 // z Phi(z) = max(z, 0) - a T(a), and log2 T(a) is so close to a parabola that a polynomial of degree 6, fitted so that
-// the largest error of a T(a) on [0, 6] is smallest, is within 5.1e-8 of it there.  It falls to -108 at 13.7 and turns
-// up beyond, hence the bound on its argument (|z| T is then below 3e-7 for |z| up to 1e26).  13 issue slots per value (the exponential counts four); 17 for the
-// rational form of Abramowitz & Stegun 7.1.28 that stood here, whose sixteenth power and reciprocal this saves.  Error
-// against the float64 definition, evaluated in float32: at most 2.8e-7 absolute, 6.2e-8 of the norm for N(0, 1)
-// (7.1.28: 7.1e-7 and 2.3e-7).
+// the largest error of a T(a) on [0, 6] is smallest, is within 5.1e-8 of it there.  It falls to -108 at 13.7 and would turn
+// up beyond: all but its last factor stop there, so that the whole goes on falling, by 7.8 a unit, and T is zero from 16.1
+// on.  10 instructions, one of them the exponential; 12 and a reciprocal for the rational form of Abramowitz & Stegun 7.1.28
+// that stood here.  Error against the float64 definition, evaluated in float32: at most 2.8e-7 absolute, 6.2e-8 of the norm
+// for N(0, 1) (7.1.28: 7.1e-7 and 2.3e-7).  Minus infinity gives NaN, as infinity times zero does.
 __device__ __forceinline__ float gelu_fast_f(float z) {
   const float a = __builtin_amdgcn_fmed3f(fabsf(z), 0.0f, 13.7f);
   float p = fmaf(a, 3.3092776e-05f, -7.6921936e-04f);
@@ -32,7 +32,7 @@ __device__ __forceinline__ float gelu_fast_f(float z) {
   p = fmaf(a, p, -5.3412102e-02f);
   p = fmaf(a, p, -4.5877096e-01f);
   p = fmaf(a, p, -1.1512017f);
-  p = fmaf(a, p, -9.9999309e-01f);
+  p = fmaf(fabsf(z), p, -9.9999309e-01f);
   const float t = __builtin_amdgcn_exp2f(p);            // v_exp_f32, 1 ulp
   // max(z, 0) on the bits, whose sign is z's: one instruction (a median of three with infinity, or fmaxf, first quiets a
   // signalling NaN, which is a second one).  |z| and not a: a NaN stays one
