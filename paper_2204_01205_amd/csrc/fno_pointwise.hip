@@ -809,43 +809,6 @@ __global__ __launch_bounds__(kThreads, 4) void mlp2_fwd_split_kernel(
   }
 }
 
-// The adjoint needs its own products split in registers, one hidden value at a time, so it uses two fp16 parts (2 x 11
-// bits, two vector instructions a value where three bf16 parts take five and a half) and all four products.  fp16 has
-// few exponents, so both operands are scaled by powers of two.
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ void f16_split(float a, float b, unsigned (&part)[2]) {
-  const v2f v = {a, b};
-  const f16x2 hi = __builtin_convertvector(v, f16x2);
-  const v2f r = {fmaf((float)hi[0], -1.f, a), fmaf((float)hi[1], -1.f, b)};      // v_fma_mix_f32
-  part[0] = __builtin_bit_cast(unsigned, hi);
-  part[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(r, f16x2));
-}
-__device__ __forceinline__ v16f mfma_f16(u32x4 a, u32x4 b, v16f c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-constexpr int kHalfA[4] = {1, 1, 0, 0}, kHalfB[4] = {1, 0, 1, 0};
-// the power of two that takes values up to v to 2^10 .. 2^11, where fp16 has room for values 16 times as large and for
-// the low parts of values 4096 times as small
-__device__ __forceinline__ int scale_exponent(float v) {
-  return 137 - (int)(__builtin_bit_cast(unsigned, v) >> 23 & 255u);
-}
-// the largest of a wave's non-negative values
-__device__ __forceinline__ float wave_max(float v) {
-  auto step = [&](auto ctrl, auto rows) {
-    const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl.value, rows.value, 0xf, false);
-    v = fmaxf(v, __builtin_bit_cast(float, o));
-  };
-  using std::integral_constant;
-  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});      // lanes 1, 2, 4, 8 to the left in rows of 16
-  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
-  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
-  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
-  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});      // the last lane of a row to the next row
-  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});      // that of the second row to the upper half
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-
 // 16-bit elements of LDS turned in reading: with rows of `stride` elements, lane l gets column l % 32 of rows
 // row0 + 8 (l/32) + 0 .. 7, two ds_read_b64_tr_b16 of four rows each (a group of 16 lanes reads 4 rows x 16 columns,
 // lane j of it the address of four elements of row j / 4, and keeps column j).
@@ -862,46 +825,57 @@ __device__ __forceinline__ u32x4 lds_turned(const unsigned short* base, int row0
 
 // Adjoint of the projection to one channel.  A block walks over tiles of 64 points, staged split in LDS; wave (wh, wp)
 // takes 32 hidden units, whose split weights stay in its registers, and both column blocks of 32 points or (two waves
-// per group of hidden units, when these are few) one of them.  With d = gelu'(h), M = diag(W2) W1 and Y = g [x ; 1],
+// per group of hidden units) one of them.  With d = gelu'(h), M = diag(W2) W1 and Y = g [x ; 1],
 //   h   = [W1 | b1] [x ; 1]
 //   gx  = g M^T d                      K runs over the hidden units in accumulator order: the parts of d are the right
 //                                      operand as they are packed
 //   gW1 | gb1 = diag(W2) d Y^T         K runs over the points; the parts of d are turned through LDS
-// so that neither g nor W2 multiplies anything per hidden value.  Every channel of M and of Y has a scale of its own.
-// Those of Y start anew with every flush of the accumulators and shrink, and the accumulators with them, when a tile
-// holds a value past fp16's range.
+// so that neither g nor W2 multiplies anything per hidden value.  All products are sums of three bf16 parts, which have
+// fp32's exponents: d of a unit that is off, a weight far below the largest and points with small values keep their 24
+// bits.  (Two fp16 parts with a scale for every channel of M and Y took 907 us where this takes 985, but have 2^-35 of the
+// largest value, and of d 2^-25, as their last place: hidden values of -5 gave gx off by 6e-4, of -7 by its whole size.)
 //
-// The fp32 accumulator of gW1 takes kMlpFlush tiles and then goes to doubles, and takes -Y every other time: the
+// The products for gW1 of a column block go to an accumulator of their own, which is added to the fp32 accumulator of the
+// tiles (vector additions, 64 between two flushes), and that to doubles.  Y has the other sign every other time: the matrix
 // instruction's sums are rounded to nearest after a cut towards minus infinity some bits below (measured: 0.004 units of
 // the accumulator's last place on average; single products rounded in fp32 show none), which adds up over millions of
-// points (4 million: gW1 off by 4.2e-6), and cancels in the difference (2.4e-7; in fp32 6.8e-7).
+// points (4 million: gW1 off by 4.2e-6), and cancels in the difference (1.7e-7; with fp32 instructions 5.4e-7).  With one
+// wave per group of hidden units the doubles stand in the block's slot of partial sums, in L2: 32 registers that the parts of d
+// need, at 2 % for a flush every 32 tiles (9 % every four).
 //
-// What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 1000 vector instructions
-// and 56 matrix instructions a wave and tile; the vector unit issues in 63 % of the cycles, the matrix unit in 26 %, 11 %
-// both.  20 -> 128 -> 1 at 4 million points, both ways' products on the fp32 instruction 1403 us, in three bf16 parts
-// 1095, now 950; against the scalar kernel (hidden or channel widths that the fp32 one did not fit) 20 -> 64 -> 1
-// 5637 -> 617 us, 32 -> 128 -> 1 at 2 million points 22300 -> 704 us.
+// What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 750 vector instructions
+// and 72 matrix instructions a wave and tile.  20 -> 128 -> 1 at 4 million points: 1370 us with both ways' products on the
+// fp32 instruction, now 985; against the scalar kernel (hidden or channel widths that the fp32 one did not fit)
+// 20 -> 64 -> 1 5815 and 588 us, 32 -> 128 -> 1 at 2 million points 23050 and 572 us.
 constexpr int kMlpTS = 36;               // row stride of turned tiles, in 16-bit elements: 18 banks, so that rows spread over all
 struct MlpBwd {
   int B, Ci, H, nwh;                     // nwh: groups of 32 hidden units
   long long N;
 };
-constexpr int kMlpFlush = 4;             // tiles between flushes of the fp32 weight-gradient accumulators
+constexpr int kMlpFlush = 32;            // tiles between flushes of the fp32 weight-gradient accumulators
 constexpr int mlp_rows(int NS) { return NS == 4 ? 8 : (NS == 8 ? 16 : (NS == 12 ? 24 : 32)); }      // rows of gx
-// LDS floats of a wave: the parts of d of its column blocks, then its share of gx
+// LDS floats of a wave: the parts of d of its column blocks, then in the same place its share of gx (32 channels, one column
+// block after the other: beside it)
+constexpr int mlp_buffers(int NS, int NPG) { return NPG == 2 || NS == 18 ? 1 : 2; }
 constexpr int mlp_region(int NS, int NPG) {
-  return mlp_rows(NS) * 64 > 64 / NPG * kMlpTS ? mlp_rows(NS) * 64 : 64 / NPG * kMlpTS;
+  const int parts = mlp_buffers(NS, NPG) * 48 * kMlpTS, share = mlp_rows(NS) * 64;
+  return NS == 18 && NPG == 1 ? parts + share : (share > parts ? share : parts);
 }
-template <int NS, int NPG>
+constexpr size_t mlp_bwd_lds(int NS, int NPG, int nw) {
+  return (size_t)(NS > 8 ? 2 : 1) * 6 * 64 * 16 + 3 * 64 * kMlpTS * 2 + 64 * 4 + (NS == 18 ? 256 * 4 : 0) +
+         (size_t)nw * mlp_region(NS, NPG) * 4;
+}
+// most pairs of channels that a wave of nw (or more) stages
+constexpr int mlp_stage(int NS, int nw) { return ((NS < 16 ? NS : 16) + nw - 1) / nw; }
+// NPG: waves per group of hidden units; SR: most pairs of channels that a wave stages
+template <int NS, int NPG, int SR>
 __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
     MlpBwd f, const float* __restrict__ x, const float* __restrict__ W1, const float* __restrict__ b1,
     const float* __restrict__ W2, const float* __restrict__ g, float* __restrict__ gx, double* __restrict__ part) {
   HIP_DYNAMIC_SHARED(float4, smem4)
   constexpr int KB = NS > 8 ? 2 : 1, ROWS = mlp_rows(NS), REG = mlp_region(NS, NPG);
   constexpr bool ALL = NS == 18;           // 32 input channels: no column left for gb1, the bias is where h starts
-  constexpr int PAIRS = NS < 16 ? NS : 16;
-  constexpr int SR = NPG == 2 ? PAIRS / 2 : (PAIRS + 2) / 3;     // most pairs of channels a wave stages: of two waves, or three
-  constexpr int NB = 2 / NPG;              // column blocks of a wave
+  constexpr int BUF = mlp_buffers(NS, NPG);                // column blocks that a wave works on at a time
   const int Ci = f.Ci, H = f.H;
   const long long N = f.N;
   const int nthreads = blockDim.x, nw = nthreads >> 6;
@@ -909,32 +883,30 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wp = w / f.nwh, wh = w - wp * f.nwh;
   u32x4* XS = reinterpret_cast<u32x4*>(smem4);                               // [KB][3][2][64]: octets of channels of a point
-  unsigned short* YS = reinterpret_cast<unsigned short*>(XS + KB * 6 * 64);  // [2][64][kMlpTS]: channels of a point
-  float* GS = reinterpret_cast<float*>(YS + 2 * 64 * kMlpTS);                // [64]
-  int* ES = reinterpret_cast<int*>(GS + 64);                                 // [32] exponents of Y's scales
-  int* EM = ES + 32;                                                         // [32] of M's
-  float* BS = reinterpret_cast<float*>(EM + 32);                             // [256] b1
+  unsigned short* YS = reinterpret_cast<unsigned short*>(XS + KB * 6 * 64);  // [3][64][kMlpTS]: channels of a point
+  float* GS = reinterpret_cast<float*>(YS + 3 * 64 * kMlpTS);                // [64]
+  float* BS = GS + 64;                                                       // [256] b1
   float* regions = BS + (ALL ? 256 : 0);
   float* own = regions + w * REG;
-  unsigned short* T = reinterpret_cast<unsigned short*>(own);                // [NB][2][32][kMlpTS]
+  unsigned short* T = reinterpret_cast<unsigned short*>(own);                // [BUF][3][32][kMlpTS]
+  float* share = own + (ALL && NPG == 1 ? BUF * 48 * kMlpTS : 0);            // [ROWS][64] of gx
   const int nsum = H * (Ci + 1) + H + 1;
   const int np = ALL ? 16 : Ci / 2 + 1;    // pairs with the channel of ones
   double* dst = part + (long long)blockIdx.x * nsum;       // gW1 | gb1 | gW2 | gb2
   for (int e = tid; e < KB * 6 * 64; e += nthreads) XS[e] = u32x4{0u, 0u, 0u, 0u};
+  for (int e = tid; e < 3 * 64 * kMlpTS / 2; e += nthreads) reinterpret_cast<unsigned*>(YS)[e] = 0u;
   if constexpr (ALL)
     for (int e = tid; e < 256; e += nthreads) BS[e] = b1 != nullptr && e < H ? b1[e] : 0.f;
-  // operands of h and gx; |M| of a channel is at most its largest |W1| times the largest |W2|
-  int m_exp = 0;
+  // M holds W2 by a power of two that makes the largest 1 .. 2 (the products with W1 keep W1's range); g takes it back
+  int w2_exp = 0;
   {
-    float m1 = 0.f, m2 = 0.f;
-#pragma unroll 8
-    for (int k = half; k < 32 * f.nwh; k += 2) m1 = fmaxf(m1, fabsf(W1[min(k, H - 1) * Ci + min(c, Ci - 1)]));
-    for (int k = lane; k < H; k += 64) m2 = fmaxf(m2, fabsf(W2[k]));
-    m1 = fmaxf(m1, __shfl_xor(m1, 32));
-    m_exp = scale_exponent(m1) + scale_exponent(wave_max(m2)) - 11;
-    if (tid < 32) EM[tid] = m_exp;
+    float m = 0.f;
+    for (int k = lane; k < H; k += 64) m = fmaxf(m, fabsf(W2[k]));
+#pragma unroll
+    for (int j = 1; j < 64; j <<= 1) m = fmaxf(m, __shfl_xor(m, j));
+    w2_exp = (int)(__builtin_bit_cast(unsigned, m) >> 23 & 255u) - 127;
   }
-  u32x4 a1[KB][3], am[2][2];
+  u32x4 a1[KB][3], am[2][3];
   {
     const int k = wh * 32 + c;
 #pragma unroll
@@ -958,24 +930,30 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const int kk = wh * 32 + mfma_row(v + q, half);
-        m[q] = (c < Ci && kk < H) ? (float)ldexp((double)W1[kk * Ci + c] * (double)W2[kk], m_exp) : 0.f;
+        m[q] = (c < Ci && kk < H) ? W1[kk * Ci + c] * ldexpf(W2[kk], -w2_exp) : 0.f;
       }
-      unsigned pt[2];
-      f16_split(m[0], m[1], pt);
+      unsigned pt[3];
+      bf16_split(m[0], m[1], pt);
 #pragma unroll
-      for (int p = 0; p < 2; ++p) am[v >> 3][p][(v & 7) / 2] = pt[p];
+      for (int p = 0; p < 3; ++p) am[v >> 3][p][(v & 7) / 2] = pt[p];
     }
   }
   v16f accw;
-  double accd[16], accgd = 0.0;
-  float acc2[16], accg = 0.f, accb[ALL ? 16 : 1];
+  double accg = 0.0;
+  float acc2[16], accb[ALL ? 16 : 1];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    accd[v] = 0.0;
-    acc2[v] = accw[v] = 0.f;
-  }
+  for (int v = 0; v < 16; ++v) acc2[v] = accw[v] = 0.f;
 #pragma unroll
   for (int v = 0; v < (ALL ? 16 : 1); ++v) accb[v] = 0.f;
+  // the doubles of accw: with two waves per group of hidden units in registers, else in the block's slot, of which every
+  // lane owns its entries
+  double accd[NPG == 2 ? 16 : 1];
+#pragma unroll
+  for (int v = 0; v < (NPG == 2 ? 16 : 1); ++v) accd[v] = 0.0;
+  const int slot_step = c < Ci ? Ci : 1;
+  double* slot = dst + (c < Ci ? c : H * Ci) + (wh * 32 + 4 * half) * slot_step;
+  auto in_slot = [&](int v) { return c <= Ci && wh * 32 + mfma_row(v, half) < H; };
+  bool begun = false;                      // the slot holds something
 
   const long long tiles_per_b = (N + 63) >> 6;
   long long t = blockIdx.x, b = t / tiles_per_b;
@@ -999,42 +977,46 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
   if (b < f.B) load();
   __syncthreads();                         // XS is clear
   float sign = blockIdx.x & 1 ? -1.f : 1.f;                // of Y
-  int y_exp = 0;                           // of the lane's column of accw
-  auto flush = [&]() {
+  // accw to its doubles; at the end these, times W2, go to the slot
+  auto flush = [&](bool last) {
+    double sum[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      accd[v] += ldexp((double)(sign * accw[v]), -y_exp);
-      accw[v] = 0.f;
+    for (int v = 0; v < 16; ++v) sum[v] = (double)(sign * accw[v]);
+    if constexpr (NPG == 2) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) accd[v] += sum[v];
+    } else {
+      int step = slot_step;
+      asm volatile("" : "+v"(step));       // else all sixteen addresses are kept over the loop
+      if (begun)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum[v] += in_slot(v) ? slot[mfma_row(v, 0) * step] : 0.0;
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (in_slot(v)) slot[mfma_row(v, 0) * step] = last ? sum[v] * (double)W2[wh * 32 + mfma_row(v, half)] : sum[v];
+      begun = true;
     }
-    accgd += (double)accg;
-    accg = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) accw[v] = 0.f;
     sign = -sign;
   };
-  int pass = 0, sc[SR][2];                 // scales of the channels that this wave stages
-#pragma unroll
-  for (int r = 0; r < SR; ++r) sc[r][0] = sc[r][1] = 0;
+  int pass = 0;
   while (b < f.B) {
     const float gp = pg, gs = pg * sign;
 #pragma unroll
     for (int r = 0; r < SR; ++r) {
       const int q = r * nw + w;
       if (q < np) {
-        unsigned pt[3], py[2];
+        unsigned pt[3], py[3];
         bf16_split(pv[r][0], pv[r][1], pt);
+        bf16_split(gs * pv[r][0], gs * pv[r][1], py);
         unsigned* xd = reinterpret_cast<unsigned*>(XS + ((q >> 3) * 6 + ((q >> 2) & 1)) * 64 + lane) + (q & 3);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) xd[p * 2 * 64 * 4] = pt[p];
-        const float y0 = gs * pv[r][0], y1 = gs * pv[r][1];
-        if (pass == 0 || __any(fmaxf(fabsf(ldexpf(y0, sc[r][0])), fabsf(ldexpf(y1, sc[r][1]))) > 32768.f)) {
-          const int e0 = scale_exponent(wave_max(fabsf(y0))), e1 = scale_exponent(wave_max(fabsf(y1)));
-          sc[r][0] = pass == 0 ? e0 : min(sc[r][0], e0);
-          sc[r][1] = pass == 0 ? e1 : min(sc[r][1], e1);
-          if (lane < 2) ES[2 * q + lane] = lane == 0 ? sc[r][0] : sc[r][1];
-        }
-        f16_split(ldexpf(y0, sc[r][0]), ldexpf(y1, sc[r][1]), py);
         unsigned* yd = reinterpret_cast<unsigned*>(YS + lane * kMlpTS) + q;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) yd[p * 64 * (kMlpTS / 2)] = py[p];
+        for (int p = 0; p < 3; ++p) {
+          xd[p * 2 * 64 * 4] = pt[p];
+          yd[p * 64 * (kMlpTS / 2)] = py[p];
+        }
       }
     }
     if (w == 0) GS[lane] = pg;
@@ -1043,20 +1025,13 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
     for (t += gridDim.x; t >= tiles_per_b && b < f.B; t -= tiles_per_b) ++b;
     const bool more = b < f.B;
     if (more) load();
-    {
-      const int e = ES[c];
-      if (__any(e != y_exp)) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) accw[v] = ldexpf(accw[v], e - y_exp);
-        y_exp = e;
-      }
-    }
     // Column block by column block.  The matrix instructions of one are dealt between the vector instructions of the
     // other by hand: left alone, the compiler keeps them together, and a wave waits for its own chain of products.
-    v16f ga[NB], hacc[NB];
-    u32x4 xs[KB][3], dp[NB][2][2], dt[2], yt[2];
-    auto read_x = [&](int nb) {
-      const int pc = (NPG == 2 ? wp : nb) * 32 + c;
+    v16f ga[BUF], hacc[BUF], gw_part;
+    u32x4 xs[KB][3], dp[BUF][2][3], dt[3], yt[3];
+    auto turn_buffer = [&](int u) { return T + u * 3 * 32 * kMlpTS; };
+    auto read_x = [&](int col) {
+      const int pc = col * 32 + c;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -1084,34 +1059,37 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
           hacc[nb] = mfma_bf16(a1[r % KB][kSplitA[r / KB]], xs[r % KB][kSplitB[r / KB]], hacc[nb]);
         }
     };
-    auto turned = [&](int nb, int m) {
+    auto turned = [&](int nb, int col, int m) {
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        dt[p] = lds_turned(T + (nb * 2 + p) * 32 * kMlpTS, 16 * m, kMlpTS);
-        yt[p] = lds_turned(YS + p * 64 * kMlpTS, (NPG == 2 ? wp : nb) * 32 + 16 * m, kMlpTS);
+      for (int p = 0; p < 3; ++p) {
+        dt[p] = lds_turned(turn_buffer(nb) + p * 32 * kMlpTS, 16 * m, kMlpTS);
+        yt[p] = lds_turned(YS + p * 64 * kMlpTS, col * 32 + 16 * m, kMlpTS);
       }
     };
-    auto products = [&](int nb, int step) {                // eighth `step` of the sixteen products with d
+    auto products = [&](int nb, int col, int step) {       // eighth `step` of the 24 products with d
 #pragma unroll
       for (int s = 0; s < 8; ++s) {
         if (s != step) continue;
         if (s == 0) clear(ga[nb]);
-        if (s == 2) turned(nb, 0);
-        if (s < 4) {
-          ga[nb] = mfma_f16(am[0][kHalfA[s]], dp[nb][0][kHalfB[s]], ga[nb]);
-          ga[nb] = mfma_f16(am[1][kHalfA[s]], dp[nb][1][kHalfB[s]], ga[nb]);
-        } else {
-          constexpr int two[4] = {0, 2, 0, 2};
-          const int r = two[s - 4];
-          accw = mfma_f16(dt[kHalfA[r]], yt[kHalfB[r]], accw);
-          accw = mfma_f16(dt[kHalfA[r + 1]], yt[kHalfB[r + 1]], accw);
-          if (s == 5) turned(nb, 1);
+        if (s == 2) turned(nb, col, 0);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          if (s < 4) {
+            const int r = (3 * s + j) / 2, m = (3 * s + j) % 2;
+            ga[nb] = mfma_bf16(am[m][kSplitA[r]], dp[nb][m][kSplitB[r]], ga[nb]);
+          } else {
+            const int r = 3 * (s & 1) + j;
+            if (s == 4 && j == 0) clear(gw_part);
+            gw_part = mfma_bf16(dt[kSplitA[r]], yt[kSplitB[r]], gw_part);
+          }
         }
+        if (s == 5) turned(nb, col, 1);
+        if (s == 7) accw += gw_part;
       }
     };
-    auto slopes = [&](int nb, auto&& beside) {
-      const float gl = GS[(NPG == 2 ? wp : nb) * 32 + c];
-      accg += half == 0 ? gl : 0.f;
+    auto slopes = [&](int nb, int col, auto&& beside) {
+      const float gl = GS[col * 32 + c];
+      accg += half == 0 ? (double)gl : 0.0;
 #pragma unroll
       for (int v = 0; v < 16; v += 2) {
         beside(v / 2);
@@ -1123,65 +1101,67 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
           acc2[v + q] = fmaf(gl, a, acc2[v + q]);
           if constexpr (ALL) accb[v + q] = fmaf(gl, d[q], accb[v + q]);
         }
-        unsigned pt[2];
-        f16_split(d[0], d[1], pt);
+        unsigned pt[3];
+        bf16_split(d[0], d[1], pt);
 #pragma unroll
-        for (int p = 0; p < 2; ++p) dp[nb][v >> 3][p][(v & 7) / 2] = pt[p];
+        for (int p = 0; p < 3; ++p) dp[nb][v >> 3][p][(v & 7) / 2] = pt[p];
         if ((v & 3) == 2) {                // rows 8 q + 4 half + 0 .. 3 of point c
           const int q = v >> 2;
 #pragma unroll
-          for (int p = 0; p < 2; ++p)
-            *reinterpret_cast<uint2*>(T + ((nb * 2 + p) * 32 + c) * kMlpTS + 8 * q + 4 * half) =
+          for (int p = 0; p < 3; ++p)
+            *reinterpret_cast<uint2*>(turn_buffer(nb) + (p * 32 + c) * kMlpTS + 8 * q + 4 * half) =
                 make_uint2(dp[nb][q >> 1][p][2 * (q & 1)], dp[nb][q >> 1][p][2 * (q & 1) + 1]);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    read_x(0);
-    hidden(0, 0, 6 * KB);
-    if constexpr (NB == 2 && ALL) {        // no registers for that
-      slopes(0, [](int) {});
-#pragma unroll
-      for (int u = 0; u < 8; ++u) products(0, u);
-      read_x(1);
-      hidden(1, 0, 6 * KB);
-      slopes(1, [](int) {});
-    } else if constexpr (NB == 2) {
-      read_x(1);
-      __builtin_amdgcn_sched_barrier(0);
-      slopes(0, [&](int u) { hidden(1, 6 * KB * u / 8, 6 * KB * (u + 1) / 8); });
-      slopes(1, [&](int u) { products(0, u); });
-    } else {
-      slopes(0, [](int) {});
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) products(NB - 1, u);
-    __builtin_amdgcn_wave_barrier();
-    if (gx != nullptr) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        float* share = own + 4 * half * 64 + (NPG == 2 ? wp : nb) * 32 + c;
+    auto share_gx = [&](int nb, int col) {
+      __builtin_amdgcn_wave_barrier();
+      float* dst = share + 4 * half * 64 + col * 32 + c;
+      if (gx != nullptr)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-          if (mfma_row(v, 0) < ROWS) share[mfma_row(v, 0) * 64] = ga[nb][v];
+          if (mfma_row(v, 0) < ROWS) dst[mfma_row(v, 0) * 64] = ga[nb][v];
+    };
+    if constexpr (BUF == 1) {              // one by one: 32 channels leave no registers for two
+#pragma unroll 1
+      for (int col = NPG == 2 ? wp : 0; col < (NPG == 2 ? wp + 1 : 2); ++col) {
+        read_x(col);
+        hidden(0, 0, 6 * KB);
+        slopes(0, col, [](int) {});
+#pragma unroll
+        for (int u = 0; u < 8; ++u) products(0, col, u);
+        share_gx(0, col);
       }
+    } else {
+      read_x(0);
+      hidden(0, 0, 6 * KB);
+      read_x(1);
+      __builtin_amdgcn_sched_barrier(0);
+      slopes(0, 0, [&](int u) { hidden(1, 6 * KB * u / 8, 6 * KB * (u + 1) / 8); });
+      slopes(1, 1, [&](int u) { products(0, 0, u); });
+#pragma unroll
+      for (int u = 0; u < 8; ++u) products(1, 1, u);
+      share_gx(0, 0);
+      share_gx(1, 1);
     }
     __syncthreads();
     if (gx != nullptr && po < N) {
-      const float* src = regions + (NPG == 2 ? half * f.nwh * REG : 0) + lane;
+      const float* src = regions + (share - own) + (NPG == 2 ? half * f.nwh * REG : 0) + lane;
+      const float gw = ldexpf(gp, w2_exp);
       for (int i = w; i < Ci; i += nw) {
         float sum = 0.f;
 #pragma unroll 4
         for (int ww = 0; ww < f.nwh; ++ww) sum += src[ww * REG + i * 64];
-        gx[(bo * Ci + i) * N + po] = ldexpf(sum, -EM[i]) * gp;
+        gx[(bo * Ci + i) * N + po] = sum * gw;
       }
     }
     if (++pass == kMlpFlush) {
       pass = 0;
-      flush();
+      flush(false);
     }
   }
-  flush();
+  flush(true);
   // the lanes of a row, then two waves with the same hidden units, meet in LDS in a fixed order
   __syncthreads();
   double* meet = reinterpret_cast<double*>(smem4) + wh * 64;
@@ -1192,13 +1172,11 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
     __syncthreads();
     return wp == 0 ? v + meet[lane] : 0.0;
   };
+  if constexpr (NPG == 2) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int k = wh * 32 + mfma_row(v, half);
-    const double s = joined(accd[v]) * (k < H ? (double)W2[k] : 0.0);
-    if (wp == 0 && k < H) {
-      if (c < Ci) dst[k * Ci + c] = s;
-      else if (c == Ci) dst[H * Ci + k] = s;
+    for (int v = 0; v < 16; ++v) {
+      const double sum = joined(accd[v]);
+      if (wp == 0 && in_slot(v)) slot[mfma_row(v, 0) * slot_step] = sum * (double)W2[wh * 32 + mfma_row(v, half)];
     }
   }
   auto row_sum = [&](const float (&a)[16]) {               // in lane l: over the lanes of register l / 2, half l % 2
@@ -1218,7 +1196,7 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
     const double sb = row_sum(accb);
     if (mine) dst[H * Ci + k] = sb * (double)W2[k];
   }
-  double sg = accgd;
+  double sg = accg;
 #pragma unroll
   for (int m = 1; m < 32; m <<= 1) sg += __shfl_xor(sg, m);
   sg = joined(sg);
@@ -1981,19 +1959,22 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
   const int nsum = H * (Ci + 1) + Co * H + Co;
   if (Co == 1 && H <= 256) {
     const MlpBwd f{B, Ci, H, (H + 31) / 32, (long long)N};
-    const int npg = f.nwh <= 2 ? 2 : 1, nw = f.nwh * npg, kb = Ci < 16 ? 1 : 2;
+    // two waves where groups of hidden units are few, and with 32 channels, whose wave takes its two column blocks one by one,
+    // as far as blocks of eight waves go: 32 -> 128 -> 1 at 2 million points 572 us, with one wave a group 776 (20 channels
+    // 545 and 495)
+    const int npg = f.nwh <= 2 || (Ci == 32 && f.nwh <= 4) ? 2 : 1, nw = f.nwh * npg;
     const int64_t tiles = (int64_t)B * ((N + 63) / 64);
     const int nblk = (int)(tiles < kMlpBlocks ? tiles : kMlpBlocks);
     double* part = static_cast<double*>(ws);
-#define FNO_MLPB(NSV, NPGV)                                                                                       \
-  hipLaunchKernelGGL((mlp2_bwd_split_kernel<NSV, NPGV>), dim3((unsigned)nblk), dim3(64 * nw),                     \
-                     (size_t)kb * 6 * 64 * 16 + (size_t)2 * 64 * kMlpTS * 2 + (128 + (NSV == 18 ? 256 : 0) + (size_t)nw * mlp_region(NSV, NPGV)) * 4, \
-                     s, f, x, W1, b1, W2, g, gx, part)
-#define FNO_MLPB_N(NSV) do { if (npg == 2) FNO_MLPB(NSV, 2); else FNO_MLPB(NSV, 1); } while (0)
+#define FNO_MLPB(NSV, NPGV, NWV)                                                                                  \
+  hipLaunchKernelGGL((mlp2_bwd_split_kernel<NSV, NPGV, mlp_stage(NSV, NWV)>), dim3((unsigned)nblk), dim3(64 * nw), \
+                     mlp_bwd_lds(NSV, NPGV, nw), s, f, x, W1, b1, W2, g, gx, part)
+#define FNO_MLPB_N(NSV) do { if (npg == 2) FNO_MLPB(NSV, 2, 2); else FNO_MLPB(NSV, 1, 3); } while (0)
     if (Ci < 8) FNO_MLPB_N(4);
     else if (Ci < 16) FNO_MLPB_N(8);
     else if (Ci < 24) FNO_MLPB_N(12);
     else if (Ci < 32) FNO_MLPB_N(16);
+    else if (npg == 2 && nw >= 6) FNO_MLPB(18, 2, 6);
     else FNO_MLPB_N(18);
 #undef FNO_MLPB_N
 #undef FNO_MLPB

@@ -648,7 +648,7 @@ def test_adam_steps_match_oracle_for_real_and_complex_parameters():
     (2, 5, 32, 1, 200),               # one 32-row block of hidden units on the matrix cores, ragged tile
     (2, 9, 64, 3, 1000),              # two blocks, three outputs, two batch elements
     (1, 24, 192, 4, 333),             # more than 21 input channels, six blocks
-    (1, 20, 128, 1, 64 * 512 * 17 + 7),  # every block flushes its weight-gradient accumulator once and goes on
+    (1, 20, 128, 1, 64 * 512 * 17 + 7),  # 17 and more tiles a block
 ])
 def test_pointwise_adjoints_match_oracle(shape):
     batch, c_in, hidden, c_out, npts = shape
@@ -750,8 +750,8 @@ def test_projection_on_split_products(batch, ci, h, co, npts):
 
 
 def test_projection_adjoint_with_channels_and_points_of_very_different_size():
-    # fp16 has five exponent bits: channels of x from 1e-9 to 1e2 (and weights to match), hidden units weighted 1e-4 to 1e4,
-    # cotangents that grow by 1e12 along the points, so that the scales follow them.  Every channel by itself, as above
+    # channels of x from 1e-9 to 1e2 (and weights to match), hidden units weighted 1e-4 to 1e4, cotangents that grow by 1e12
+    # along the points.  Every channel by itself, as above
     sx = torch.logspace(-9, 2, 20, device="cuda")[:, None]
     got, want, _ = _projection(1, 20, 128, 1, 100000, 8, sx=sx, sg=torch.logspace(-20, -8, 100000, device="cuda"),
                                sw2=torch.logspace(-4, 4, 128, device="cuda"))
@@ -761,6 +761,61 @@ def test_projection_adjoint_with_channels_and_points_of_very_different_size():
     first = slice(0, 5000)                              # the small cotangents alone
     err = (got["gx"].double() - want["gx"])[..., first].norm(dim=2) / want["gx"][..., first].norm(dim=2)
     assert float(err.max()) <= 8 * 2.0 ** -23
+
+
+@pytest.mark.parametrize("ci, h", [(20, 128), (32, 128), (9, 64)])
+@pytest.mark.parametrize("kind", ["off by 3", "off by 5", "off by 7", "a heavy unit without weights", "light units", "a plume"])
+def test_projection_adjoint_value_by_value(kind, ci, h):
+    """Units that are all but off, a large W2 beside weights W1 of zero, units 2^-25 as heavy as one that is off at the point, and
+    units that are off where the values are large and on where these are 2^-20 as large.  Every value by itself, against
+    the sum of the sizes of its terms: a term is off by its slope's fit and roundings (as for a block's), by what the
+    rounding of the hidden value makes of it, and by eight roundings of products and sums; forty in the sums over points."""
+    npts, eps = 3001, 2.0 ** -24
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(ci)
+    normal = lambda *shape: torch.randn(shape, device="cuda", generator=gen)
+    x, g = normal(1, ci, npts), normal(1, 1, npts) * 1e-3
+    W1, b1, W2 = normal(h, ci) * ci ** -0.5, normal(h) * 0.1, normal(1, h) * h ** -0.5
+    if kind.startswith("off"):
+        W1 *= 0.2
+        b1 -= float(kind[-1])
+    elif kind == "a heavy unit without weights":
+        W2[0, 3], W1[3] = 1e5, 0.0
+    elif kind == "light units":
+        W2[0, 1:] *= 2.0 ** -25
+        W1[0] = 0.0
+        W1[0, 0] = 8.0
+        x[:, 0] = torch.where(x[:, 0] < 0, -1.0, 1.0)
+    else:
+        W1[:, 0] = 8.0
+        x[:, 0], x[:, 1:, npts // 16:] = 1.0, x[:, 1:, npts // 16:] * 2.0 ** -20
+        x[:, 0, :npts // 16] = -1.0
+    gx, grads = torch.empty_like(x), [torch.empty_like(p) for p in (W1, b1, W2)]
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(ci, h, 1) // 4 + 2, device="cuda")
+    B.fno_pointwise_mlp2_bwd(1, ci, h, 1, npts, x, W1, b1, W2, g, gx, *grads, torch.empty(1, device="cuda"), ws)
+    torch.cuda.synchronize()
+    x, g, W1, b1, W2 = x[0].double(), g[0].double(), W1.double(), b1.double(), W2.double()
+    z, z_off = W1 @ x + b1[:, None], 6 * eps * (W1.abs() @ x.abs() + b1.abs()[:, None])
+    a, dens = z.abs(), torch.exp(-0.5 * z * z) / (2 * np.pi) ** 0.5
+    tail = 0.5 * torch.erfc(a / 2 ** 0.5)
+    slope = torch.where(z < 0, tail, 1 - tail) + z * dens
+    off = torch.minimum(3.6e-8 / a.clamp(min=1), 1.75e-3 * tail) + eps * (1.5 * a * a + 8) * (tail + a * dens) + \
+        (2 - z * z).abs() * dens * z_off * 1.1 + torch.where(z < 0, 0.0, 2 * eps)
+    M, Y = W1 * W2.T, torch.cat([x, torch.ones_like(x[:1])]) * g
+    pairs = [(gx[0], M.T.contiguous() @ slope * g, (M.abs().T.contiguous() @ (off + 8 * eps * slope.abs())) * g.abs())]
+    sums, bound = slope @ Y.T.contiguous() * W2.T, (off + 40 * eps * slope.abs()) @ Y.abs().T.contiguous() * W2.abs().T
+    pairs += [(grads[0], sums[:, :ci], bound[:, :ci]), (grads[1], sums[:, ci], bound[:, ci])]
+    for got, want, most in pairs:
+        worst = float(((got.double() - want).abs() / most.clamp(min=1e-40)).max())
+        assert worst <= 1.0
+
+
+@pytest.mark.parametrize("ci, h", [(20, 128), (32, 128), (32, 160), (20, 64), (7, 32)])
+def test_projection_adjoint_over_many_points(ci, h):
+    # 66 and more tiles a block: two flushes of the weight gradients and a rest, on one and two waves to a group of units
+    got, want, scale = _projection(1, ci, h, 1, 64 * 512 * 66 + 7, 11)
+    for name in ("gx", "gW1", "gb1", "gW2", "gb2"):
+        assert float((got[name].double() - want[name]).norm()) <= 8 * 2.0 ** -23 * scale[name], name
 
 
 def test_whole_network_training_step_matches_oracle():
