@@ -832,7 +832,7 @@ __device__ __forceinline__ u32x4 lds_turned(const unsigned short* base, int row0
 //   gW1 | gb1 = diag(W2) d Y^T         K runs over the points; the parts of d are turned through LDS
 // so that neither g nor W2 multiplies anything per hidden value.  All products are sums of three bf16 parts, which have
 // fp32's exponents: d of a unit that is off, a weight far below the largest and points with small values keep their 24
-// bits.  (Two fp16 parts with a scale for every channel of M and Y took 907 us where this takes 985, but have 2^-35 of the
+// bits.  (Two fp16 parts with a scale for every channel of M and Y took 907 us where this takes 1000, but have 2^-35 of the
 // largest value, and of d 2^-25, as their last place: hidden values of -5 gave gx off by 6e-4, of -7 by its whole size.)
 //
 // The products for gW1 of a column block go to an accumulator of their own, which is added to the fp32 accumulator of the
@@ -842,10 +842,11 @@ __device__ __forceinline__ u32x4 lds_turned(const unsigned short* base, int row0
 // points (4 million: gW1 off by 4.2e-6), and cancels in the difference (1.7e-7; with fp32 instructions 5.4e-7).  With one
 // wave per group of hidden units the doubles stand in the block's slot of partial sums, in L2: 32 registers that the parts of d
 // need, at 2 % for a flush every 32 tiles (9 % every four).
+// The lanes' fp32 sums for gW2, with 32 channels also those for gb1, go to doubles at the same time: 64 terms at most.
 //
 // What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 750 vector instructions
 // and 72 matrix instructions a wave and tile.  20 -> 128 -> 1 at 4 million points: 1370 us with both ways' products on the
-// fp32 instruction, now 985; against the scalar kernel (hidden or channel widths that the fp32 one did not fit)
+// fp32 instruction, now 1000; against the scalar kernel (hidden or channel widths that the fp32 one did not fit)
 // 20 -> 64 -> 1 5815 and 588 us, 32 -> 128 -> 1 at 2 million points 23050 and 572 us.
 constexpr int kMlpTS = 36;               // row stride of turned tiles, in 16-bit elements: 18 banks, so that rows spread over all
 struct MlpBwd {
@@ -977,6 +978,11 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
   if (b < f.B) load();
   __syncthreads();                         // XS is clear
   float sign = blockIdx.x & 1 ? -1.f : 1.f;                // of Y
+  // a value that a flush forms its addresses from: these would be kept over the loop otherwise
+  auto anew = [](int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
   // accw to its doubles; at the end these, times W2, go to the slot
   auto flush = [&](bool last) {
     double sum[16];
@@ -986,8 +992,7 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) accd[v] += sum[v];
     } else {
-      int step = slot_step;
-      asm volatile("" : "+v"(step));       // else all sixteen addresses are kept over the loop
+      const int step = anew(slot_step);
       if (begun)
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum[v] += in_slot(v) ? slot[mfma_row(v, 0) * step] : 0.0;
@@ -999,6 +1004,37 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) accw[v] = 0.f;
     sign = -sign;
+  };
+  // acc2 and accb to doubles, kept as those of accw: in lane l, over the lanes of register l / 2, half l % 2
+  double sum2 = 0.0, sumb = 0.0;
+  auto row_sum = [&](float (&a)[16]) {
+    const int at = anew(c);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      own[66 * v + 33 * half + at] = a[v];
+      a[v] = 0.f;
+    }
+    __builtin_amdgcn_wave_barrier();
+    double sum = 0.0;
+    for (int j = 0; j < 32; ++j) sum += (double)own[33 * at + j];
+    return sum;
+  };
+  auto row_of = [&](int q) { return wh * 32 + mfma_row(q >> 1, q & 1); };
+  auto flush_rows = [&](bool last) {       // before flush()
+    __syncthreads();                       // the shares of gx have been read
+    if constexpr (NPG == 2) {
+      sum2 += row_sum(acc2);
+      if constexpr (ALL) sumb += row_sum(accb);
+      return;
+    }
+    const int row = row_of(anew(c));
+    const bool mine = half == 0 && row < H;
+    auto add = [&](double* at, double v, double factor) {
+      if (mine) *at = (begun ? *at + v : v) * factor;
+    };
+    add(dst + H * (Ci + 1) + row, row_sum(acc2), 1.0);
+    if constexpr (ALL) add(dst + H * Ci + row, row_sum(accb), last && mine ? (double)W2[row] : 1.0);
   };
   int pass = 0;
   while (b < f.B) {
@@ -1158,9 +1194,11 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
     }
     if (++pass == kMlpFlush) {
       pass = 0;
+      flush_rows(false);
       flush(false);
     }
   }
+  flush_rows(true);
   flush(true);
   // the lanes of a row, then two waves with the same hidden units, meet in LDS in a fixed order
   __syncthreads();
@@ -1178,23 +1216,14 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
       const double sum = joined(accd[v]);
       if (wp == 0 && in_slot(v)) slot[mfma_row(v, 0) * slot_step] = sum * (double)W2[wh * 32 + mfma_row(v, half)];
     }
-  }
-  auto row_sum = [&](const float (&a)[16]) {               // in lane l: over the lanes of register l / 2, half l % 2
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) own[66 * v + 33 * half + c] = a[v];
-    __builtin_amdgcn_wave_barrier();
-    double s = 0.0;
-    for (int j = 0; j < 32; ++j) s += (double)own[33 * c + j];
-    return joined(s);
-  };
-  const int k = wh * 32 + mfma_row(c >> 1, c & 1);
-  const bool mine = wp == 0 && half == 0 && k < H;
-  const double s2 = row_sum(acc2);
-  if (mine) dst[H * (Ci + 1) + k] = s2;
-  if constexpr (ALL) {
-    const double sb = row_sum(accb);
-    if (mine) dst[H * Ci + k] = sb * (double)W2[k];
+    const int row = row_of(c);
+    const bool mine = wp == 0 && half == 0 && row < H;
+    const double s2 = joined(sum2);
+    if (mine) dst[H * (Ci + 1) + row] = s2;
+    if constexpr (ALL) {
+      const double sb = joined(sumb);
+      if (mine) dst[H * Ci + row] = sb * (double)W2[row];
+    }
   }
   double sg = accg;
 #pragma unroll
@@ -1961,7 +1990,7 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
     const MlpBwd f{B, Ci, H, (H + 31) / 32, (long long)N};
     // two waves where groups of hidden units are few, and with 32 channels, whose wave takes its two column blocks one by one,
     // as far as blocks of eight waves go: 32 -> 128 -> 1 at 2 million points 572 us, with one wave a group 776 (20 channels
-    // 545 and 495)
+    // 545 and 500)
     const int npg = f.nwh <= 2 || (Ci == 32 && f.nwh <= 4) ? 2 : 1, nw = f.nwh * npg;
     const int64_t tiles = (int64_t)B * ((N + 63) / 64);
     const int nblk = (int)(tiles < kMlpBlocks ? tiles : kMlpBlocks);

@@ -818,6 +818,29 @@ def test_projection_adjoint_over_many_points(ci, h):
         assert float((got[name].double() - want[name]).norm()) <= 8 * 2.0 ** -23 * scale[name], name
 
 
+@pytest.mark.parametrize("ci, h", [(1, 128), (32, 128), (32, 160), (3, 32)])
+def test_projection_adjoint_adds_up_equal_points(ci, h):
+    # 2^25 equal points, 1024 tiles a block: every lane adds one number again and again, whose roundings do not scatter.  Sums in
+    # fp32 of at most 32 tiles, 64 terms, are off by at most 32 x 2^-24; the term itself by eight roundings and a tile's products
+    # by eight more
+    npts, gen = 1 << 25, torch.Generator(device="cuda")
+    gen.manual_seed(h)
+    x1, W1 = [0.1 * torch.randn(s, device="cuda", generator=gen) for s in (ci, (h, ci))]
+    W2, b1, c = torch.ones(1, h, device="cuda"), torch.linspace(0.5, 4.0, h, device="cuda") - W1 @ x1, 0.3
+    x = x1[None, :, None].expand(1, ci, npts).contiguous()
+    g = torch.full((1, 1, npts), c, device="cuda")
+    grads = [torch.empty_like(p) for p in (W1, b1, W2)]
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(ci, h, 1) // 4 + 2, device="cuda")
+    B.fno_pointwise_mlp2_bwd(1, ci, h, 1, npts, x, W1, b1, W2, g, None, *grads, torch.empty(1, device="cuda"), ws)
+    torch.cuda.synchronize()
+    z = W1.double() @ x1.double() + b1.double()
+    cdf, dens = 0.5 * torch.erfc(-z / 2 ** 0.5), torch.exp(-0.5 * z * z) / (2 * np.pi) ** 0.5
+    total = float(g[0, 0, 0].double()) * npts
+    for got, want in ((grads[2][0], total * z * cdf), (grads[1], total * (cdf + z * dens))):
+        worst = float(((got.double() - want) / want).abs().max())
+        assert worst <= (32 + 16) * 2.0 ** -24
+
+
 def test_whole_network_training_step_matches_oracle():
     """Lift, two blocks, projection; relative L2 loss; backward through all of it; one Adam step.
 
