@@ -412,12 +412,14 @@ size_t fold_lds(const FoldPlan& f, int MT, int split = 0) {
 // columns: z of 60, 12 kept, t of 16, 24, 30 with 8, 12, 8 bins 40.2, 78.5, 85.5 and 38.3, 70.5, 76.9, but t of 8 and 10
 // with 3 and 4 bins 29.6, 32.4 and 31.2, 34.4; z of 263, 24 kept, t of 10 and 14 with 4 and 6 bins 162, 173 and 137, 146
 // (in blocks of four waves 181, 192), but 24 x 24 columns of 20 and 30 points of t 33 and 41 and, in blocks of eight, 39
-// and 47.
-int fold_split(const FoldPlan& f, int KS, int CT, int MT, int PP) {
+// and 47.  Blocks of eight waves need a plane for every wave of a chip full of them; with fewer, blocks of four take their
+// place: 263 x 16, 24 kept, 8 bins on 64, 256, 1024 and 2304 planes 12.6, 12.7, 14.1, 21.1 with eight waves, 11.1, 10.4, 12.2
+// with four (fp32 11.0, 11.0, 13.6, 21.4).
+int fold_split(const FoldPlan& f, int KS, int CT, int MT, int PP, int64_t planes) {
   const size_t lds = fold_lds(f, MT, 1);
   if (PP > 1 || lds > kFoldLds) return 0;
   if (CT == 2) return 1;
-  if (lds > 40 * 1024) return MT == 2 && KS <= 4 ? 2 : 0;
+  if (lds > 40 * 1024) return MT == 2 && KS <= 4 ? (planes >= 2048 ? 2 : 1) : 0;
   return MT == 2 || (f.pairs > 16 && (KS == 4 || KS >= 7)) ? 1 : 0;
 }
 
@@ -474,7 +476,7 @@ hipError_t launch_tz_fwd_fold(const float* x, float2* out, const float2* twt, co
   const int PP = f.pairs <= 4 ? 4 : (f.pairs <= 8 ? 2 : 1);      // more than one: also MT = 1, no more frequencies than rows
   const int CT = 2 * mt <= 16 ? 1 : 2, MT = f.rows >= 32 && fold_lds(f, 2) <= kFoldLds ? 2 : 1;
   const int J = (Nt - 1) / 16, r = Nt - 16 * J, W = (r + 3) / 4;
-  const int split = fold_split(f, 4 * J + W, CT, MT, PP), threads = split > 1 ? 2 * kThreads : kThreads;
+  const int split = fold_split(f, 4 * J + W, CT, MT, PP, planes), threads = split > 1 ? 2 * kThreads : kThreads;
   const int mgroups = (f.rows + 16 * MT - 1) / (16 * MT), cgroups = (2 * mt + 16 * CT - 1) / (16 * CT);
   const int ngroups = mgroups * cgroups;
   const size_t lds = fold_lds(f, MT, split);

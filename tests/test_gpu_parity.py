@@ -1322,7 +1322,7 @@ def test_folded_forward_transform_sums_in_short_chains(nz, mz, nt, mt):
     (33, 5, 13, 5), (34, 6, 26, 8), (45, 8, 64, 7),         # one tile of frequencies: a K step of four values, of eight, two
     (17, 5, 17, 9), (90, 16, 24, 12), (150, 30, 48, 16),    # two tiles of bins; of frequencies too
     (99, 17, 1, 1), (118, 20, 20, 8),                       # two tiles of frequencies
-    (263, 24, 16, 8), (181, 20, 5, 2),                      # blocks of eight waves
+    (263, 24, 16, 8), (181, 20, 5, 2),                      # long tables
 ])
 def test_forward_transform_on_split_products(nz, mz, nt, mt):
     """Products of exact three-way splits leave out less than 2^-25 of each, and an instruction sums 32 of them to its
@@ -1337,6 +1337,25 @@ def test_forward_transform_on_split_products(nz, mz, nt, mt):
     want = np.einsum("kn,bnt->bkt", np.exp(-2j * np.pi * (np.outer(k, n) % nz) / nz), bins)
     roundings = 1 + 1 + (3 if nt > 32 else 2) + 1 + 2 + (np.ceil(nz / 32) + 1) / 2 + 1
     assert rel(xh.reshape(want.shape), want) <= 1.2 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
+
+
+@pytest.mark.parametrize("planes, nz, mz, nt, mt", [
+    (2047, 181, 20, 5, 2), (2048, 181, 20, 5, 2), (2304, 263, 24, 16, 8),       # blocks of four waves, of eight
+    (16000, 263, 24, 16, 8), (24000, 118, 20, 24, 12), (38000, 60, 12, 30, 8),  # 256 MiB and more: streamed
+])
+def test_forward_transform_on_split_products_of_many_planes(planes, nz, mz, nt, mt):
+    """The bound of the test above, against torch in float64."""
+    desc = B.make_desc(planes, 1, 1, (1, 1, nz, nt), (0, 0, mz, mt), 1, 0)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(planes)
+    x = torch.randn((planes, 1, 1, 1, nz, nt), device="cuda", generator=gen)
+    xh = torch.empty((planes, 1, 1, 1, 2 * mz + 1, mt), dtype=torch.complex64, device="cuda")
+    R = torch.zeros((1, 1, 1, 1, 2 * mz + 1, mt), dtype=torch.complex64, device="cuda")
+    B.fno_spectral_conv_fwd(desc, x, R, torch.empty_like(x), xh, B.alloc_workspace(desc, B.FNO_OP_SPECTRAL_CONV_FWD))
+    want = torch.fft.fft(torch.fft.rfft(x.double(), dim=5)[..., :mt], dim=4)
+    want = torch.cat([want[..., :mz + 1, :], want[..., nz - mz:, :]], dim=4)
+    roundings = 1 + 1 + (3 if nt > 32 else 2) + 1 + 2 + (np.ceil(nz / 32) + 1) / 2 + 1
+    assert float((xh.to(torch.complex128) - want).norm() / want.norm()) <= 1.2 * 0.42 * 2.0 ** -24 * np.sqrt(roundings)
 
 
 @pytest.mark.parametrize("nz, nt", [(108, 33), (270, 14)])
