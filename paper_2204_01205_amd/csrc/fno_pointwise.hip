@@ -40,10 +40,10 @@ __device__ __forceinline__ void gelu_and_grad_f(float z, float& val, float& grad
   grad = fmaf(z, 0.39894228040143267794f * e, cdf);
 }
 
-// The same without a bound on its argument and closer to float64: log2 of twice the tail is a q(a), q of degree 9 (largest
-// error of max(a, 1) T(a) 1.9e-10; a q(a) falls from 0 to minus infinity), so that its rounding shrinks with a.  25 issue
-// slots, where erff and expf took over 100 (both branches of erff run in a wave); against float64, of the norm under
-// N(0, 1): the slope 3.9e-8, value times slope 6.6e-8 (erff and expf 4.0e-8 and 7.2e-8).
+// The same closer to float64 around zero: log2 of twice the tail is a q(a), q of degree 9 (largest
+// error of max(a, 1) T(a) 1.9e-10; a q(a) falls from 0 to minus infinity), so that its rounding shrinks with a.  20
+// instructions, where erff and expf took over 100 (both branches of erff run in a wave); against float64, of the norm under
+// N(0, 1): the slope 3.9e-8, value times slope 6.6e-8 (erff and expf 4.0e-8 and 7.2e-8); at z = -5 the slope 2e-6 (5e-4).
 __device__ __forceinline__ void gelu_and_grad_fine_f(float z, float& val, float& grad) {
   const float a = fabsf(z);
   float q = fmaf(a, -5.62642732e-08f, 1.38986923e-06f);
@@ -673,9 +673,9 @@ constexpr int kSplitA[6] = {0, 2, 1, 0, 1, 0}, kSplitB[6] = {2, 0, 1, 1, 0, 0};
 // channel of ones after the last), split once, and used against every group of hidden units, whose split weights the
 // block keeps in LDS.  Waves meet nowhere after the weights are there.
 //
-// What bounds it: the vector unit, 12 issue slots a hidden value (GELU and the product with W2) and a seventh of that for
-// loads and splits; it issues in 98 % of the cycles, the products' matrix instructions (38 %) run beside it, and the chip
-// holds 1.7 GHz.  20 -> 128 -> 1 at 4 million points 442 -> 312 us, off the measured rms error of the fp32 instruction
+// What bounds it: the vector unit, 13.5 instructions a hidden value (GELU 10, the product with W2 one, else loads and
+// splits); it issues in all of the cycles, the products' matrix instructions in 39 % of them run beside it, and the chip
+// holds 1.8 GHz.  20 -> 128 -> 1 at 4 million points 442 -> 312 us, off the measured rms error of the fp32 instruction
 // (2.2e-7, 1.1e-7 now); against the scalar kernel, which took the hidden and channel widths that one did not fit,
 // 20 -> 64 -> 1 862 -> 179 us, 32 -> 128 -> 1 at 2 million points 1352 -> 192 us.
 template <int NS, int CO>
@@ -844,8 +844,8 @@ __device__ __forceinline__ u32x4 lds_turned(const unsigned short* base, int row0
 // need, at 2 % for a flush every 32 tiles (9 % every four).
 // The lanes' fp32 sums for gW2, with 32 channels also those for gb1, go to doubles at the same time: 64 terms at most.
 //
-// What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 750 vector instructions
-// and 72 matrix instructions a wave and tile.  20 -> 128 -> 1 at 4 million points: 1370 us with both ways' products on the
+// What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 1020 vector instructions
+// and 72 matrix instructions a wave and tile; the vector unit issues in 61 % of the cycles, the matrix unit in 31 %, 13 % both.  20 -> 128 -> 1 at 4 million points: 1370 us with both ways' products on the
 // fp32 instruction, now 1000; against the scalar kernel (hidden or channel widths that the fp32 one did not fit)
 // 20 -> 64 -> 1 5815 and 588 us, 32 -> 128 -> 1 at 2 million points 23050 and 572 us.
 constexpr int kMlpTS = 36;               // row stride of turned tiles, in 16-bit elements: 18 banks, so that rows spread over all
