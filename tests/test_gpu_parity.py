@@ -1062,6 +1062,19 @@ def test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule):
 
 
 @pytest.mark.parametrize("c, nz, mz, nt, mt, rule", [
+    (20, 5, 2, 17, 6, 0),       # half a tile alone, the middle row its own pair, one step in the second tile of t
+    (6, 40, 7, 24, 8, 1),       # a whole tile and a half one; runs of three steps, none to spare
+    (7, 47, 9, 25, 9, 0),       # a half tile of exactly eight pairs, odd z; overlapping runs of four
+    (10, 33, 6, 29, 3, 0),      # an odd axis whose middle row opens the half tile
+    (20, 44, 8, 32, 11, 0),     # whole runs of four
+    (2, 21, 4, 18, 1, 1),       # one group of channels; the last lanes of the second tile of t have no step of their own
+])
+def test_inverse_transform_of_rows_in_two_tiles(c, nz, mz, nt, mt, rule):
+    """Folded inverse (z, t) stage, one task over both tiles of t: whole and half tiles of row pairs."""
+    test_inverse_transform_at_the_edges_of_its_tiles(c, nz, mz, nt, mt, rule)
+
+
+@pytest.mark.parametrize("c, nz, mz, nt, mt, rule", [
     # per-tile kernel: one residue class; padded channels; rows padded from 30 and 24 to 32 and from 12 to 16 points of t;
     # eight channel tiles; several groups of residue classes, most z frequencies kept; an odd number of them
     (20, 16, 4, 32, 8, 0), (7, 128, 30, 16, 9, 0), (18, 64, 12, 30, 9, 0), (13, 16, 8, 24, 11, 0), (24, 16, 3, 20, 7, 0),
