@@ -528,11 +528,14 @@ __global__ __launch_bounds__(kThreads) void tz_fwd_fast_kernel(
 // ------------------------------------------------------------------------------------------
 // Complex pruned transform along the middle axis of [outer][N][inner] -> [outer][L][inner]
 // ------------------------------------------------------------------------------------------
+// W = 2^wshift columns of [N][inner] per block.  The twiddles come from LDS or from memory by two copies of the code: read
+// through one pointer that may be either they are flat loads, each of which waits for memory and for LDS.
 template <int M, bool STREAM>
 __global__ __launch_bounds__(kThreads) void axis_fwd_kernel(
     const float2* __restrict__ in, float2* __restrict__ out, const float2* __restrict__ tw, int N,
-    int L, int npos, long long inner, int W, int ncb, int tw_lds) {
+    int L, int npos, long long inner, int wshift, int ncb, int tw_lds) {
   HIP_DYNAMIC_SHARED(float, smem)
+  const int W = 1 << wshift;
   float2* F = reinterpret_cast<float2*>(smem);          // [N][W]
   float2* TWs = F + N * W;                              // [L][P], only when tw_lds
   const int P = N / M;
@@ -545,7 +548,7 @@ __global__ __launch_bounds__(kThreads) void axis_fwd_kernel(
   if (tw_lds)
     for (int idx = tid; idx < L * P; idx += nthr) TWs[idx] = tw[idx];
   for (int idx = tid; idx < P * W; idx += nthr) {
-    const int col = idx % W, n2 = idx / W;
+    const int col = idx & (W - 1), n2 = idx >> wshift;
     if (col < wc) {
       const float2* src = in + (o * N + n2) * inner + c0 + col;
       float2 a[M];
@@ -557,31 +560,37 @@ __global__ __launch_bounds__(kThreads) void axis_fwd_kernel(
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < L * W; idx += nthr) {
-    const int col = idx % W, j = idx / W;
-    if (col < wc) {
-      const int mj = posmod(kfreq(j, L, npos), M);
-      const float2* base = F + (P * mj) * W + col;
-      const float2* w = (tw_lds ? TWs : tw) + j * P;
-      out[(o * L + j) * inner + c0 + col] = combine_terms(w, base, W, P);
+  auto combine = [&](const float2* twiddles) {
+    for (int idx = tid; idx < L * W; idx += nthr) {
+      const int col = idx & (W - 1), j = idx >> wshift;
+      if (col < wc) {
+        const int mj = kfreq(j, L, npos) & (M - 1);
+        out[(o * L + j) * inner + c0 + col] = combine_terms(twiddles + j * P, F + (P * mj) * W + col, W, P);
+      }
     }
-  }
+  };
+  if (tw_lds) combine(TWs); else combine(tw);
 }
 
-// [outer][L][inner] (kept frequencies, zero elsewhere) -> [outer][N][inner], exp(+i...)
+// [outer][L][inner] (kept frequencies, zero elsewhere) -> [outer][N][inner], exp(+i...).  neighbours: adjacent column
+// tiles are worked by one XCD (grid: a multiple of 8).  What bounds it: its writes, at copy speed for large tensors (256
+// points, 48 kept, 3.6 GB: 987 -> 660 us; 128 points, 32 kept, batch 4: 840 -> 700), since the reads of several bins go
+// out together and none is a flat load.
 template <int M, bool STREAM>
 __global__ __launch_bounds__(kThreads) void axis_inv_kernel(
     const float2* __restrict__ in, float2* __restrict__ out, const float2* __restrict__ tw, int N,
-    int L, int npos, long long inner, int W, int ncb, int tw_lds) {
+    int L, int npos, long long inner, int wshift, int ncb, int tw_lds, long long outer, int neighbours) {
   HIP_DYNAMIC_SHARED(float, smem)
+  const int W = 1 << wshift;
   float2* Y = reinterpret_cast<float2*>(smem);          // [L][W]
   float2* TWs = Y + L * W;                              // [L][P], only when tw_lds
-  const float2* twp = tw_lds ? TWs : tw;
   const int P = N / M;
   const int tid = threadIdx.x;
   const int nthr = blockDim.x;
-  const long long o = blockIdx.x / ncb;
-  const long long c0 = (long long)(blockIdx.x % ncb) * W;
+  const long long item = neighbours ? xcd_contiguous_item(blockIdx.x, gridDim.x) : blockIdx.x;
+  const long long o = item / ncb;
+  if (o >= outer) return;
+  const long long c0 = (item - o * ncb) * W;
   const int wc = (int)min((long long)W, inner - c0);
   const int kmin = npos - L, kmax = npos - 1;
 
@@ -592,35 +601,72 @@ __global__ __launch_bounds__(kThreads) void axis_inv_kernel(
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int idx = i0 + u * nthr;
-      const int col = idx % W, j = idx / W;
+      const int col = idx & (W - 1), j = idx >> wshift;
       v[u] = (idx < L * W && col < wc) ? in[(o * L + j) * inner + c0 + col] : make_float2(0.f, 0.f);
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int idx = i0 + u * nthr;
-      if (idx < L * W && idx % W < wc) Y[idx] = v[u];
+      if (idx < L * W && (idx & (W - 1)) < wc) Y[idx] = v[u];
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < P * W; idx += nthr) {
-    const int col = idx % W, n2 = idx / W;
-    if (col < wc) {
-      float2 g[M];
+  auto transform = [&](const float2* twiddles) {
+    // bin m takes the frequencies k = m modulo M; the reads of G bins (or of G terms of a bin) go out together
+    constexpr int G = M == 8 || M == 16 ? 8 : 4;
+    for (int idx = tid; idx < P * W; idx += nthr) {
+      const int col = idx & (W - 1), n2 = idx >> wshift;
+      if (col < wc) {
+        const float2* yc = Y + col;
+        const float2* wc2 = twiddles + n2;
+        auto entry = [&](int k) { return k >= 0 ? k : k + L; };
+        float2 g[M];
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        float2 acc = make_float2(0.f, 0.f);
-        for (int k = kmin + posmod(m - kmin, M); k <= kmax; k += M) {
-          const int j = k >= 0 ? k : k + L;
-          acc = cfmac(Y[j * W + col], twp[j * P + n2], acc);
+        for (int m = 0; m < M; ++m) g[m] = make_float2(0.f, 0.f);
+        if constexpr (M >= G) {
+          for (int k0 = kmin; k0 <= kmax; k0 += M) {
+#pragma unroll
+            for (int m0 = 0; m0 < M; m0 += G) {
+              float2 y[G], w[G];
+              bool any = false;
+#pragma unroll
+              for (int u = 0; u < G; ++u) any = any || k0 + ((m0 + u - kmin) & (M - 1)) <= kmax;
+              if (!any) continue;
+#pragma unroll
+              for (int u = 0; u < G; ++u) {
+                const int j = entry(min(k0 + ((m0 + u - kmin) & (M - 1)), kmax));
+                y[u] = yc[j << wshift];
+                w[u] = wc2[j * P];
+              }
+#pragma unroll
+              for (int u = 0; u < G; ++u)
+                if (k0 + ((m0 + u - kmin) & (M - 1)) <= kmax) g[m0 + u] = cfmac(y[u], w[u], g[m0 + u]);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int m = 0; m < M; ++m)
+            for (int k0 = kmin + ((m - kmin) & (M - 1)); k0 <= kmax; k0 += G * M) {
+              float2 y[G], w[G];
+#pragma unroll
+              for (int u = 0; u < G; ++u) {
+                const int j = entry(min(k0 + u * M, kmax));
+                y[u] = yc[j << wshift];
+                w[u] = wc2[j * P];
+              }
+#pragma unroll
+              for (int u = 0; u < G; ++u)
+                if (k0 + u * M <= kmax) g[m] = cfmac(y[u], w[u], g[m]);
+            }
         }
-        g[m] = acc;
-      }
-      fft_reg<M, +1>(g);
-      float2* dst = out + (o * N + n2) * inner + c0 + col;
+        fft_reg<M, +1>(g);
+        float2* dst = out + (o * N + n2) * inner + c0 + col;
 #pragma unroll
-      for (int n1 = 0; n1 < M; ++n1) st_once2<STREAM>(&dst[(long long)(P * n1) * inner], g[bitrev<M>(n1)]);
+        for (int n1 = 0; n1 < M; ++n1) st_once2<STREAM>(&dst[(long long)(P * n1) * inner], g[bitrev<M>(n1)]);
+      }
     }
-  }
+  };
+  if (tw_lds) transform(TWs); else transform(tw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -888,11 +934,11 @@ hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int6
   if (outer * ax.N * inner * 8 >= kStreamBytes) {
     FNO_DISPATCH_M(ax.M, hipLaunchKernelGGL((axis_fwd_kernel<MM, true>), dim3((unsigned)nblk),
                                             dim3(kThreads), lds, s, in, out, tw, ax.N, ax.L, ax.npos,
-                                            (long long)inner, W, (int)ncb, tw_lds));
+                                            (long long)inner, ilog2(W), (int)ncb, tw_lds));
   } else {
     FNO_DISPATCH_M(ax.M, hipLaunchKernelGGL((axis_fwd_kernel<MM, false>), dim3((unsigned)nblk),
                                             dim3(kThreads), lds, s, in, out, tw, ax.N, ax.L, ax.npos,
-                                            (long long)inner, W, (int)ncb, tw_lds));
+                                            (long long)inner, ilog2(W), (int)ncb, tw_lds));
   }
   return hipGetLastError();
 }
@@ -900,22 +946,27 @@ hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int6
 hipError_t launch_axis_inv(const float2* in, float2* out, const float2* tw, int64_t outer,
                            AxisPlan ax, int64_t inner, hipStream_t s) {
   if (outer <= 0 || inner <= 0) return hipSuccess;
-  const int W = axis_cols(ax, inner, ax.L, 32);          // 16 and 64 columns both measured slower
+  // Rows of the output that do not start on 64 bytes: column tiles meet in the middle of lines, which must come together
+  // in one L2 before they are written.  Adjacent tiles go to one XCD, wide ones if they are many, through plain stores.
+  // us, y axis of 64 points with 361 columns, of 24 with 561, of 128 with 91: 157, 208, 27 streamed by tiles of 32, 79,
+  // 146, 24 so; but 128 points with 216 columns (whole 64 bytes) 124 and 146.  Else 32 columns: 16 and 64 are slower.
+  const bool split = inner % 8 != 0;
+  const int W = axis_cols(ax, inner, ax.L, split && outer * ((inner + 63) / 64) >= 2048 ? 64 : 32);
   const int64_t ncb = (inner + W - 1) / W;
-  const int64_t nblk = outer * ncb;
+  const int64_t nblk = split ? (outer * ncb + 7) / 8 * 8 : outer * ncb;
   if (nblk > 0x7fffffffLL || ncb > 0x7fffffffLL) return hipErrorInvalidValue;
   const int tw_lds = (size_t)ax.L * ax.P * 8 <= (size_t)(8 * 1024);
   const size_t lds = (size_t)ax.L * W * 8 + (tw_lds ? (size_t)ax.L * ax.P * 8 : 0);
   const int thr = axis_threads(ax.P * W);
   // the output is written once: as a stream when it is larger than the caches
-  if (outer * ax.N * inner * 8 >= kStreamBytes) {
+  if (!split && outer * ax.N * inner * 8 >= kStreamBytes) {
     FNO_DISPATCH_M(ax.M, hipLaunchKernelGGL((axis_inv_kernel<MM, true>), dim3((unsigned)nblk),
                                             dim3(thr), lds, s, in, out, tw, ax.N, ax.L, ax.npos,
-                                            (long long)inner, W, (int)ncb, tw_lds));
+                                            (long long)inner, ilog2(W), (int)ncb, tw_lds, (long long)outer, split ? 1 : 0));
   } else {
     FNO_DISPATCH_M(ax.M, hipLaunchKernelGGL((axis_inv_kernel<MM, false>), dim3((unsigned)nblk),
                                             dim3(thr), lds, s, in, out, tw, ax.N, ax.L, ax.npos,
-                                            (long long)inner, W, (int)ncb, tw_lds));
+                                            (long long)inner, ilog2(W), (int)ncb, tw_lds, (long long)outer, split ? 1 : 0));
   }
   return hipGetLastError();
 }

@@ -1136,6 +1136,10 @@ def test_forward_transform_of_short_rows(nx, ny, nz, mz, nt, mt):
     (1, 2, 2, (14, 10, 12, 16), (1, 1, 3, 8), 1),
     (1, 2, 2, (6, 2, 12, 16), (2, 1, 3, 8), 0),
     (1, 2, 2, (4, 12, 47, 3), (1, 2, 23, 1), 1),
+    # inverse: more frequencies than bins (M = 32, 16); rows of 84 values, off the 64-byte grid, in 4096 wide tiles
+    (1, 2, 2, (64, 96, 3, 4), (31, 40, 1, 2), 1),
+    (1, 2, 1, (48, 16, 5, 6), (23, 7, 2, 3), 1),
+    (2, 8, 8, (128, 16, 22, 8), (2, 3, 10, 4), 1),
 ])
 def test_fft_axis_kernels_match_oracle(case):
     test_spectral_conv_fwd_matches_oracle(case)
