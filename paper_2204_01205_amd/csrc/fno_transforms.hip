@@ -979,8 +979,10 @@ hipError_t launch_mix_fwd(const float2* xh, const float2* R, float2* yh, int B, 
   // four output channels and up to four batch entries per thread (a tile of one or two entries for
   // batches that small: 3 % faster than four with unused rows); wider output tiles (10 or 20
   // channels for a single batch entry, which would read the input spectrum less often) measured slower.
-  // R is read once per call: as a stream when it is larger than the caches
-  const bool stream = (int64_t)Ci * Co * K * 8 >= kStreamBytes;
+  // R is read once per call: as a stream from half the size of the memory-side cache on, which it would otherwise share
+  // with the spectra and fields around it (us, one batch entry: 217 MB 63 -> 51, 147 MB 39 -> 33; the adjoint, which
+  // writes as much as it reads, is no faster below the whole size)
+  const bool stream = (int64_t)Ci * Co * K * 8 >= kStreamBytes / 2;
 #define FNO_MIX(KBV, STRV)                                                                                  \
   hipLaunchKernelGGL((mix_fwd_kernel<KBV, 4, STRV>), dim3((unsigned)nb, (unsigned)((Co + 3) / 4)), dim3(thr), \
                      0, s, xh, R, yh, B, Ci, Co, (long long)K, mt, Nt, (float)invN)
