@@ -844,10 +844,13 @@ __device__ __forceinline__ u32x4 lds_turned(const unsigned short* base, int row0
 // need, at 2 % for a flush every 32 tiles (9 % every four).
 // The lanes' fp32 sums for gW2, with 32 channels also those for gb1, go to doubles at the same time: 64 terms at most.
 //
-// What bounds it: issue at two waves per SIMD (the weight gradients' registers allow no more), 1020 vector instructions
-// and 72 matrix instructions a wave and tile; the vector unit issues in 61 % of the cycles, the matrix unit in 31 %, 13 % both.  20 -> 128 -> 1 at 4 million points: 1370 us with both ways' products on the
-// fp32 instruction, now 1000; against the scalar kernel (hidden or channel widths that the fp32 one did not fit)
-// 20 -> 64 -> 1 5815 and 588 us, 32 -> 128 -> 1 at 2 million points 23050 and 572 us.
+// What bounds it: issue at two waves per SIMD (the parts of d, of the weights and of x, and LDS, allow no more), 1050 vector
+// instructions (64 of them transcendental, at half rate) and 72 matrix instructions of 32 cycles a wave and tile.  Equal
+// priorities left the vector unit idle in 32 % of the cycles, both units in 13 %.  20 -> 128 -> 1 at 4 million points: 1370
+// us with both ways' products on the fp32 instruction, 945 with sums for gW2 that the compiler kept back to the tile's
+// end (64 registers), a select of every value of x as it was asked for (which waited for it) and one priority, now 870;
+// 16, 24, 32 channels at 2 million 422, 522, 582 and 376, 430, 521; against the scalar kernel (hidden or channel widths
+// that the fp32 one did not fit) 20 -> 64 -> 1 5815 and 540 us, 32 -> 128 -> 1 at 2 million points 23050 and 521 us.
 constexpr int kMlpTS = 36;               // row stride of turned tiles, in 16-bit elements: 18 banks, so that rows spread over all
 struct MlpBwd {
   int B, Ci, H, nwh;                     // nwh: groups of 32 hidden units
@@ -961,7 +964,8 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
   t -= b * tiles_per_b;
   // a wave stages pairs of channels w, w + nw, ..; its lanes are the points
   float pv[SR][2], pg;
-  // (lanes past the last point read it again, under g = 0; pairs past the last channel are not used)
+  // (lanes past the last point read it again, under g = 0; pairs past the last channel are not used).  Nothing is done
+  // with the values before they are staged, a tile later: a select here waits for them here.
   auto load = [&]() {
     const long long p = (t << 6) + lane, pc = min(p, N - 1);
     const float* xb = x + b * Ci * N + pc;
@@ -970,14 +974,15 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
       const int i = 2 * (r * nw + w);
       pv[r][0] = xb[min(i, Ci - 1) * N];
       pv[r][1] = xb[min(i + 1, Ci - 1) * N];
-      if (i == Ci) pv[r][0] = 1.f;
-      if (i + 1 == Ci) pv[r][1] = 1.f;
     }
-    pg = p < N ? g[b * N + pc] : 0.f;
+    pg = g[b * N + pc];
   };
   if (b < f.B) load();
   __syncthreads();                         // XS is clear
   float sign = blockIdx.x & 1 ? -1.f : 1.f;                // of Y
+  // sums that only a flush reads are added to here and now: left alone they move behind the tile's last barrier, and
+  // hidden values, distribution values and products stay in 80 registers until then
+  auto now = [](float& v) { asm volatile("" : "+v"(v)); };
   // a value that a flush forms its addresses from: these would be kept over the loop otherwise
   auto anew = [](int v) {
     asm volatile("" : "+v"(v));
@@ -1038,14 +1043,16 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
   };
   int pass = 0;
   while (b < f.B) {
-    const float gp = pg, gs = pg * sign;
+    const long long bo = b, to = t;
+    const float gp = (to << 6) + lane < N ? pg : 0.f, gs = gp * sign;
 #pragma unroll
     for (int r = 0; r < SR; ++r) {
       const int q = r * nw + w;
       if (q < np) {
+        const float v0 = 2 * q == Ci ? 1.f : pv[r][0], v1 = 2 * q + 1 == Ci ? 1.f : pv[r][1];
         unsigned pt[3], py[3];
-        bf16_split(pv[r][0], pv[r][1], pt);
-        bf16_split(gs * pv[r][0], gs * pv[r][1], py);
+        bf16_split(v0, v1, pt);
+        bf16_split(gs * v0, gs * v1, py);
         unsigned* xd = reinterpret_cast<unsigned*>(XS + ((q >> 3) * 6 + ((q >> 2) & 1)) * 64 + lane) + (q & 3);
         unsigned* yd = reinterpret_cast<unsigned*>(YS + lane * kMlpTS) + q;
 #pragma unroll
@@ -1055,12 +1062,17 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
         }
       }
     }
-    if (w == 0) GS[lane] = pg;
+    if (w == 0) GS[lane] = gp;
     __syncthreads();
-    const long long bo = b, po = (t << 6) + lane;
     for (t += gridDim.x; t >= tiles_per_b && b < f.B; t -= tiles_per_b) ++b;
     const bool more = b < f.B;
-    if (more) load();
+    // The next tile's values are asked for when the slopes are done, which need all registers: the last products and what
+    // follows them are as long as the loads take.
+    auto ask = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) load();
+      __builtin_amdgcn_sched_barrier(0);
+    };
     // Column block by column block.  The matrix instructions of one are dealt between the vector instructions of the
     // other by hand: left alone, the compiler keeps them together, and a wave waits for its own chain of products.
     v16f ga[BUF], hacc[BUF], gw_part;
@@ -1120,7 +1132,11 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
           }
         }
         if (s == 5) turned(nb, col, 1);
-        if (s == 7) accw += gw_part;
+        if (s == 7) {
+          accw += gw_part;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(accw[v]));
+        }
       }
     };
     auto slopes = [&](int nb, int col, auto&& beside) {
@@ -1135,7 +1151,11 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
           float a;
           gelu_and_grad_f(hacc[nb][v + q], a, d[q]);
           acc2[v + q] = fmaf(gl, a, acc2[v + q]);
-          if constexpr (ALL) accb[v + q] = fmaf(gl, d[q], accb[v + q]);
+          now(acc2[v + q]);
+          if constexpr (ALL) {
+            accb[v + q] = fmaf(gl, d[q], accb[v + q]);
+            now(accb[v + q]);
+          }
         }
         unsigned pt[3];
         bf16_split(d[0], d[1], pt);
@@ -1164,7 +1184,10 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
       for (int col = NPG == 2 ? wp : 0; col < (NPG == 2 ? wp + 1 : 2); ++col) {
         read_x(col);
         hidden(0, 0, 6 * KB);
+        __builtin_amdgcn_s_setprio(1);
         slopes(0, col, [](int) {});
+        __builtin_amdgcn_s_setprio(0);
+        if (NPG == 2 || col == 1) ask();
 #pragma unroll
         for (int u = 0; u < 8; ++u) products(0, col, u);
         share_gx(0, col);
@@ -1174,23 +1197,48 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
       hidden(0, 0, 6 * KB);
       read_x(1);
       __builtin_amdgcn_sched_barrier(0);
+      // The wave with slopes to work goes before the one (of the other block) in its chains of products, which wait for
+      // one another anyhow: 10 % over equal priorities, which leave the products ahead as often as not.
+      __builtin_amdgcn_s_setprio(1);
       slopes(0, 0, [&](int u) { hidden(1, 6 * KB * u / 8, 6 * KB * (u + 1) / 8); });
       slopes(1, 1, [&](int u) { products(0, 0, u); });
+      ask();
+      __builtin_amdgcn_s_setprio(0);
 #pragma unroll
       for (int u = 0; u < 8; ++u) products(1, 1, u);
       share_gx(0, 0);
       share_gx(1, 1);
     }
     __syncthreads();
-    if (gx != nullptr && po < N) {
-      const float* src = regions + (share - own) + (NPG == 2 ? half * f.nwh * REG : 0) + lane;
-      const float gw = ldexpf(gp, w2_exp);
-      for (int i = w; i < Ci; i += nw) {
-        float sum = 0.f;
-#pragma unroll 4
-        for (int ww = 0; ww < f.nwh; ++ww) sum += src[ww * REG + i * 64];
-        gx[(bo * Ci + i) * N + po] = sum * gw;
+    const int point = __lane_id();         // made anew: kept over the products it would be in scratch, whose wait is for x too
+    if (gx != nullptr && (to << 6) + point < N) {
+      const float* src = regions + (share - own) + (NPG == 2 ? (point >> 5) * f.nwh * REG : 0) + point;
+      const float gw = ldexpf(GS[point], w2_exp);
+      // the channels of this wave, two shares of all of them at a time: the reads go out together
+      float sum[2 * SR];
+#pragma unroll
+      for (int r = 0; r < 2 * SR; ++r) sum[r] = 0.f;
+#pragma unroll 1
+      for (int ww = 0; ww < f.nwh; ww += 2) {
+        float one[2 * SR], two[2 * SR];
+        const float* s1 = src + ww * REG;
+        const float* s2 = src + min(ww + 1, f.nwh - 1) * REG;
+#pragma unroll
+        for (int r = 0; r < 2 * SR; ++r) {
+          const int i = min(w + r * nw, Ci - 1) * 64;
+          one[r] = s1[i];
+          two[r] = s2[i];
+        }
+#pragma unroll
+        for (int r = 0; r < 2 * SR; ++r) {
+          sum[r] += one[r];
+          if (ww + 1 < f.nwh) sum[r] += two[r];
+        }
       }
+      float* tile = gx + bo * Ci * N + (to << 6);
+#pragma unroll
+      for (int r = 0; r < 2 * SR; ++r)
+        if (w + r * nw < Ci) tile[(w + r * nw) * N + point] = sum[r] * gw;
     }
     if (++pass == kMlpFlush) {
       pass = 0;
@@ -1990,7 +2038,7 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
     const MlpBwd f{B, Ci, H, (H + 31) / 32, (long long)N};
     // two waves where groups of hidden units are few, and with 32 channels, whose wave takes its two column blocks one by one,
     // as far as blocks of eight waves go: 32 -> 128 -> 1 at 2 million points 572 us, with one wave a group 776 (20 channels
-    // 545 and 500)
+    // 545 and 500; before the sums were kept in place)
     const int npg = f.nwh <= 2 || (Ci == 32 && f.nwh <= 4) ? 2 : 1, nw = f.nwh * npg;
     const int64_t tiles = (int64_t)B * ((N + 63) / 64);
     const int nblk = (int)(tiles < kMlpBlocks ? tiles : kMlpBlocks);
@@ -1998,7 +2046,8 @@ hipError_t launch_pointwise_mlp2_bwd(int B, int Ci, int H, int Co, int64_t N, co
 #define FNO_MLPB(NSV, NPGV, NWV)                                                                                  \
   hipLaunchKernelGGL((mlp2_bwd_split_kernel<NSV, NPGV, mlp_stage(NSV, NWV)>), dim3((unsigned)nblk), dim3(64 * nw), \
                      mlp_bwd_lds(NSV, NPGV, nw), s, f, x, W1, b1, W2, g, gx, part)
-#define FNO_MLPB_N(NSV) do { if (npg == 2) FNO_MLPB(NSV, 2, 2); else FNO_MLPB(NSV, 1, 3); } while (0)
+#define FNO_MLPB_N(NSV) \
+  do { if (npg == 2) FNO_MLPB(NSV, 2, 2); else if (nw == 3) FNO_MLPB(NSV, 1, 3); else FNO_MLPB(NSV, 1, 4); } while (0)
     if (Ci < 8) FNO_MLPB_N(4);
     else if (Ci < 16) FNO_MLPB_N(8);
     else if (Ci < 24) FNO_MLPB_N(12);

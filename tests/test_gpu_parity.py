@@ -740,7 +740,9 @@ def _projection(batch, ci, h, co, npts, seed, sx=1.0, sg=1.0, sw2=1.0):
 # and two waves each, ragged and single points, several batch entries and channels
 @pytest.mark.parametrize("batch, ci, h, co, npts", [
     (1, 1, 32, 1, 33), (2, 7, 40, 1, 65), (1, 8, 64, 1, 64), (3, 15, 96, 1, 127), (1, 16, 128, 1, 2000), (1, 23, 100, 4, 31),
-    (1, 24, 160, 1, 1), (2, 31, 256, 1, 200), (1, 32, 32, 1, 63), (1, 32, 250, 1, 1000), (1, 20, 1, 1, 129), (1, 5, 300, 2, 70)])
+    (1, 24, 160, 1, 1), (2, 31, 256, 1, 200), (1, 32, 32, 1, 63), (1, 32, 250, 1, 1000), (1, 20, 1, 1, 129), (1, 5, 300, 2, 70),
+    # the most channels that four and three waves stage in their rounds
+    (1, 7, 128, 1, 65), (1, 15, 128, 1, 66), (2, 23, 128, 1, 200), (1, 31, 128, 1, 130), (1, 23, 96, 1, 129)])
 def test_projection_on_split_products(batch, ci, h, co, npts):
     got, want, scale = _projection(batch, ci, h, co, npts, 7)
     for name, ref in want.items():
