@@ -32,6 +32,7 @@ struct Plan {
   // workspace offsets in bytes
   bool folded;           // the folded z table is there
   bool ax_folded[2];     // x, y as folded products: off_tw holds the folded table
+  bool xmix, xmix_bwd;   // x stages and mode mix in one launch, forward and adjoint
   size_t off_ztab, off_twt, off_tw[3], off_twf[2], off_fold, off_a1, off_a2, off_s1, off_s2, off_s3, off_gz, off_part, total;
   int part_blocks;
 };
@@ -111,6 +112,9 @@ int make_plan(const fno_desc* d, bool need_block, bool need_bwd_block, Plan* p) 
     if (!ok) { set_detail("an Nz x Nt plane with this many channels does not fit the LDS tiles"); return FNO_EUNSUPPORTED; }
     p->ax[2] = az;
   }
+
+  p->xmix = fno::xmix_fits(p->B, p->Ci, p->Co, p->ax[0], (int64_t)p->L[1] * p->L[2] * p->L[3], false);
+  p->xmix_bwd = fno::xmix_fits(p->B, p->Ci, p->Co, p->ax[0], (int64_t)p->L[1] * p->L[2] * p->L[3], true);
 
   // workspace
   size_t off = 0;
@@ -247,7 +251,7 @@ hipError_t axis_inv(const Plan& p, void* ws, int a, const float2* in, float2* ou
   return fno::launch_axis_inv(in, out, at<float2>(ws, p.off_tw[a]), outer, p.ax[a], inner, s);
 }
 
-// real field [B*C][grid] -> kept spectrum [B*C][K]
+// real field [B*C][grid] -> a2 [B*C][Nx][Ly][Lz][mt], and, where spec is not null, on to the kept spectrum [B*C][K]
 int forward_chain(const Plan& p, void* ws, const float* field, int C, float2* spec, hipStream_t s) {
   const int64_t bc = (int64_t)p.B * C;
   float2* a1 = at<float2>(ws, p.off_a1);
@@ -257,11 +261,11 @@ int forward_chain(const Plan& p, void* ws, const float* field, int C, float2* sp
   const int64_t in_y = (int64_t)p.L[2] * p.mt;
   FNO_STAGE(FNO_STAGE_Y_FWD, s, axis_fwd(p, ws, 1, a1, a2, bc * p.N[0], in_y, s));
   const int64_t in_x = in_y * p.L[1];
-  FNO_STAGE(FNO_STAGE_X_FWD, s, axis_fwd(p, ws, 0, a2, spec, bc, in_x, s));
+  if (spec != nullptr) FNO_STAGE(FNO_STAGE_X_FWD, s, axis_fwd(p, ws, 0, a2, spec, bc, in_x, s));
   return FNO_OK;
 }
 
-// scaled spectrum [B*C][K] -> real field through the epilogue
+// scaled spectrum [B*C][K] (null: a2 holds the field after the x stage) -> real field through the epilogue
 int inverse_chain(const Plan& p, void* ws, const float2* spec, int C, float* out, fno::Epilogue ep,
                   hipStream_t s) {
   const int64_t bc = (int64_t)p.B * C;
@@ -269,7 +273,7 @@ int inverse_chain(const Plan& p, void* ws, const float2* spec, int C, float* out
   float2* a2 = at<float2>(ws, p.off_a2);
   const int64_t in_y = (int64_t)p.L[2] * p.mt;
   const int64_t in_x = in_y * p.L[1];
-  FNO_STAGE(FNO_STAGE_X_INV, s, axis_inv(p, ws, 0, spec, a2, bc, in_x, s));
+  if (spec != nullptr) FNO_STAGE(FNO_STAGE_X_INV, s, axis_inv(p, ws, 0, spec, a2, bc, in_x, s));
   FNO_STAGE(FNO_STAGE_Y_INV, s, axis_inv(p, ws, 1, a2, a1, bc * p.N[0], in_y, s));
   FNO_STAGE(FNO_STAGE_ZT_INV, s, fno::launch_zt_inv(a1, out, at<float2>(ws, p.off_twt), at<float2>(ws, p.off_tw[2]),
                              p.folded ? at<float>(ws, p.off_fold) : nullptr, p.B, C,
@@ -281,6 +285,15 @@ int conv_fwd_common(const Plan& p, const float* x, const float* R, float* out, f
                     void* ws, fno::Epilogue ep, bool tables_ready, hipStream_t s) {
   int rc = build_tables(p, ws, s, tables_ready);
   if (rc != FNO_OK) return rc;
+  if (p.xmix) {
+    rc = forward_chain(p, ws, x, p.Ci, nullptr, s);
+    if (rc != FNO_OK) return rc;
+    float2* a2 = at<float2>(ws, p.off_a2);
+    FNO_STAGE(FNO_STAGE_MIX, s, fno::launch_xmix_fwd(a2, reinterpret_cast<const float2*>(R),
+                                reinterpret_cast<float2*>(xhat_save), a2, p.B, p.Ci, p.Co, p.ax[0],
+                                p.K / p.L[0], p.mt, p.Nt, 1.0 / double(p.Npts), s));
+    return inverse_chain(p, ws, nullptr, p.Co, out, ep, s);
+  }
   float2* xh = xhat_save != nullptr ? reinterpret_cast<float2*>(xhat_save) : at<float2>(ws, p.off_s1);
   rc = forward_chain(p, ws, x, p.Ci, xh, s);
   if (rc != FNO_OK) return rc;
@@ -303,6 +316,16 @@ int conv_bwd_common(const Plan& p, const float* x, const float* xhat_saved, cons
     xh = s3;
   }
   if (xh == nullptr) xh = at<float2>(ws, p.off_s3);   // unread when gR is null
+  if (p.xmix_bwd) {
+    rc = forward_chain(p, ws, gz, p.Co, nullptr, s);
+    if (rc != FNO_OK) return rc;
+    float2* a2 = at<float2>(ws, p.off_a2);
+    FNO_STAGE(FNO_STAGE_MIX_BWD, s, fno::launch_xmix_bwd(a2, reinterpret_cast<const float2*>(R), xh,
+                                    reinterpret_cast<float2*>(gR), gx != nullptr ? a2 : nullptr, p.B, p.Ci, p.Co, p.ax[0],
+                                    p.K / p.L[0], p.mt, p.Nt, 1.0 / double(p.Npts), accumulate, s));
+    if (gx != nullptr) return inverse_chain(p, ws, nullptr, p.Ci, gx, ep, s);
+    return FNO_OK;
+  }
   float2* gh = at<float2>(ws, p.off_s1);
   rc = forward_chain(p, ws, gz, p.Co, gh, s);
   if (rc != FNO_OK) return rc;

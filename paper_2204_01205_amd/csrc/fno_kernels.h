@@ -68,6 +68,14 @@ hipError_t launch_mix_bwd(const float2* xh, const float2* R, const float2* gh, f
                           float2* gxh, int B, int Ci, int Co, int64_t K, int mt, int Nt,
                           double invN, int accumulate, hipStream_t s);
 
+// Small layers: x stage, mode mix and x stage back in one launch (fno_xmix.hip); `out` may be `in`.  xh, R, gR and
+// accumulate as in launch_mix_fwd and launch_mix_bwd; xh nullable in the forward, gR and out in the adjoint.
+bool xmix_fits(int B, int Ci, int Co, AxisPlan ax, int64_t inner, bool adjoint);
+hipError_t launch_xmix_fwd(const float2* in, const float2* R, float2* xh, float2* out, int B, int Ci, int Co, AxisPlan ax,
+                           int64_t inner, int mt, int Nt, double invN, hipStream_t s);
+hipError_t launch_xmix_bwd(const float2* in, const float2* R, const float2* xh, float2* gR, float2* out, int B, int Ci, int Co,
+                           AxisPlan ax, int64_t inner, int mt, int Nt, double invN, int accumulate, hipStream_t s);
+
 struct Epilogue {
   const float* u;      // [B][Cu][grid] tensor the channel-linear term acts on, or nullptr
   int Cu;              // its channel count

@@ -1148,6 +1148,53 @@ def test_fft_axis_kernels_match_oracle(case):
     test_spectral_conv_bwd_matches_oracle(case)
 
 
+@pytest.mark.parametrize("case", [
+    # x stages and mode mix in one launch: tiles of four columns with one to spare, of eight; one and two points, every
+    # frequency kept; odd and even axes; more and fewer channels out than in; one to four entries
+    (1, 3, 5, (1, 3, 4, 5), (0, 1, 1, 1), 1),
+    (4, 2, 2, (2, 4, 4, 4), (1, 1, 1, 3), 0),
+    (3, 4, 4, (9, 6, 5, 6), (4, 2, 2, 3), 1),
+    (2, 5, 3, (14, 7, 6, 5), (7, 3, 2, 3), 0),
+    (2, 3, 5, (11, 6, 5, 6), (3, 2, 1, 2), 1),
+    (1, 2, 2, (10, 17, 17, 10), (2, 8, 8, 5), 1),
+    (1, 17, 32, (6, 5, 4, 4), (1, 1, 1, 2), 0),
+    # one step past it: kernels of their own for one to five entries
+    (1, 12, 16, (30, 9, 8, 6), (7, 2, 2, 3), 0),
+    (2, 12, 16, (30, 9, 8, 6), (7, 2, 2, 3), 0),
+    (3, 6, 6, (32, 9, 8, 6), (8, 2, 2, 3), 0),
+    (5, 2, 3, (9, 6, 5, 6), (2, 2, 2, 3), 1),
+])
+def test_x_stages_and_mode_mix_of_small_layers(case):
+    test_spectral_conv_fwd_matches_oracle(case)
+    test_spectral_conv_bwd_matches_oracle(case)
+    if case[1] == case[2]:
+        test_block_fwd_and_bwd_match_oracle(case, B.FNO_ACT_GELU)
+
+
+@pytest.mark.parametrize("n, m", [(80, 13), (12, 2), (20, 3), (14, 1), (6, 2), (4, 1), (36, 6), (45, 10), (28, 5), (16, 4)])
+def test_x_stage_kernels_of_five_entries(n, m):
+    """Short x axes on the kernels of the stage itself: batches above four are never in one launch with the mix."""
+    test_fft_axis_kernels_match_oracle((5, 2, 2, (n, 5, 12, 16), (m, 1, 3, 8), 0))
+
+
+def test_one_launch_adds_to_the_weight_gradient():
+    """FNO_FLAG_ACCUMULATE_GRADS on a small layer: gR is added to what the buffer holds, gx is not."""
+    L = Layer(2, 3, 4, (8, 6, 5, 6), (2, 2, 1, 2))
+    gy = dev(synth.normal_field(1, synth.T_GOUT, 2, 4, L.spec.grid))
+    ws = B.alloc_workspace(L.desc, B.FNO_OP_SPECTRAL_CONV_BWD)
+    got = []
+    for flags in (0, B.FNO_FLAG_ACCUMULATE_GRADS):
+        gx = torch.full((2, 3) + L.spec.grid, 7.0, device="cuda")
+        gR = torch.full((3, 4) + L.counts, 0.5 - 2j, dtype=torch.complex64, device="cuda")
+        desc = B.make_desc(2, 3, 4, L.spec.grid, L.spec.modes, 0, 0, flags)
+        B.fno_spectral_conv_bwd(desc, dev(L.x), None, dev(L.R), gy, gx, gR, ws)
+        torch.cuda.synchronize()
+        got.append((host(gx), host(gR)))
+    assert np.array_equal(got[0][0], got[1][0])
+    # two fp32 additions more, each within 2^-24 of a sum of size 2
+    assert np.abs(got[1][1] - got[0][1] - (0.5 - 2j)).max() <= 4 * 2.0 ** -24 * max(2.1, np.abs(got[1][1]).max())
+
+
 @pytest.mark.parametrize("c_in, c_out, npts, batch", [
     (1, 1, 3, 1), (8, 8, 64, 2), (5, 20, 65, 2), (8, 32, 127, 1), (9, 12, 66, 3), (24, 24, 193, 1), (7, 25, 640, 2),
     (25, 8, 130, 1), (26, 16, 129, 2), (32, 32, 1001, 1), (32, 17, 64, 1),
