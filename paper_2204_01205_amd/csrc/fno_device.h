@@ -115,6 +115,49 @@ __device__ __forceinline__ void store_run(void* p, const float* v) {
   }
 }
 
+// Loads and stores at 32-bit offsets from a base in scalar registers (uniform, below 2 GiB).  Lanes whose offset lies past
+// the end read zeros and store nothing, so that no access needs a branch and every way through a loop has as many: wait
+// counts are the smallest over all ways.  (A pointer that goes through an asm statement loses its address space, and
+// flat loads count as LDS accesses too.)
+constexpr unsigned kNowhere = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+// W consecutive floats per lane
+template <int W, bool STREAM>
+__device__ __forceinline__ void buffer_load(__amdgpu_buffer_rsrc_t r, unsigned at, float (&y)[W]) {
+  constexpr int aux = STREAM ? 2 : 0;            // nontemporal
+  if constexpr (W == 1) {
+    y[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, aux));
+  } else {
+    typedef unsigned vec __attribute__((ext_vector_type(W)));
+    vec q;
+    if constexpr (W == 2) q = __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, aux);
+    if constexpr (W == 3) q = __builtin_amdgcn_raw_buffer_load_b96(r, at, 0, aux);
+    if constexpr (W == 4) q = __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, aux);
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      const unsigned e = q[v];
+      y[v] = __builtin_bit_cast(float, e);
+    }
+  }
+}
+template <int W, bool STREAM>
+__device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t r, unsigned at, const float (&y)[W]) {
+  constexpr int aux = STREAM ? 2 : 0;
+  if constexpr (W == 1) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, y[0]), r, at, 0, aux);
+  } else {
+    typedef unsigned vec __attribute__((ext_vector_type(W)));
+    vec q;
+#pragma unroll
+    for (int v = 0; v < W; ++v) q[v] = __builtin_bit_cast(unsigned, y[v]);
+    if constexpr (W == 2) __builtin_amdgcn_raw_buffer_store_b64(q, r, at, 0, aux);
+    if constexpr (W == 3) __builtin_amdgcn_raw_buffer_store_b96(q, r, at, 0, aux);
+    if constexpr (W == 4) __builtin_amdgcn_raw_buffer_store_b128(q, r, at, 0, aux);
+  }
+}
+
 // the value of lane ^ 1: the other part of a complex number
 __device__ __forceinline__ float swap_pair(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));

@@ -29,6 +29,13 @@
 // Splitting a value costs five and a half vector instructions.  A K step holds 32 values: of four values (KS <= 4, and
 // the rows of a tile) two parts each, so that three instructions make the six products, of eight one part.
 //
+// A tile's rows become sums and differences before the next tile is asked for, and those are made behind the stores of the
+// plane before, whose number does not vary: the loads of a tile are on their way over the products of the one before it,
+// and no wait is for stores.  (Left alone, the compiler put the sums behind the next loads, and a wave waited for these
+// first.)  The t table of a wave is asked for in one go, its first tile before the tables.  us, before and after: 50 x 45
+// columns of 40 x 24, 32 channels, 105 -> 88; 64 x 20, 20 channels, 4096 columns 127 -> 122; 21 x 14, 24 fields of 810
+// columns 22 -> 19; 263 x 16 690 and 692.
+//
 // What bounds it: in fp32 the matrix cores at 32 cycles per instruction (a 263 x 16 plane with 49 frequencies and
 // 8 bins: 9 tiles of 8 + 16 instructions) next to one read of the field (20 channels, 68 x 118 columns: 0.85 ms); in parts
 // the vector unit's splits, 0.68 ms = 4.7 TB/s with the bins written.  Measured against the kernels it
@@ -119,6 +126,40 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
   const int grp = local % ngroups;
   const int m0 = 16 * MT * (grp % mgroups), c0 = 16 * CT * (grp / mgroups);
+  const int r = Nt - 16 * J;
+  const int t0 = min(W * g, r - W);             // start of this lane group's tail
+  // each XCD walks a contiguous eighth of the planes, its waves interleaved inside it
+  const long long per_x = (planes + 7) >> 3;
+  const long long pe = min(planes, (long long)(xcd + 1) * per_x);
+  const long long nwl = (long long)((gridDim.x >> 3) / ngroups) * (TH / 64) * PP;
+  long long p = (long long)xcd * per_x + ((long long)(local / ngroups) * (TH / 64) + wave) * PP;
+  const int ntile = PP > 1 ? 1 : (pairs + 15) >> 4;
+  constexpr int VP = 4 / PP;                    // registers of a lane that belong to one plane
+  const int lp = (c & 3) / VP, ln = VP * (c >> 2) + (c & (VP - 1));      // plane and pair of tile row c (PP > 1)
+
+  float va[KS], vb[KS];                         // this lane's part of row n and of row Nz - 1 - n
+  // (there: else nothing is read and the values are zeros)
+  auto load_tile = [&](long long plane, int tile, bool there) {
+    const int n = min(PP > 1 ? ln : 16 * tile + c, pairs - 1);
+    const int first = PP > 1 ? min(lp, (int)min((long long)PP, planes - plane) - 1) * Nz : 0;      // row of the lane's plane
+    const __amdgpu_buffer_rsrc_t base = buffer_of(x + plane * (Nz * Nt), there ? PP * Nz * Nt * 4 : 0);
+    const unsigned ra = (unsigned)((first + n) * Nt) * 4u, rb = (unsigned)((first + Nz - 1 - n) * Nt) * 4u;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      float qa[4], qb[4];
+      buffer_load<4, STREAM>(base, ra + 64u * j + 16u * g, qa);
+      buffer_load<4, STREAM>(base, rb + 64u * j + 16u * g, qb);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { va[4 * j + u] = qa[u]; vb[4 * j + u] = qb[u]; }
+    }
+    float qa[W], qb[W];
+    buffer_load<W, STREAM>(base, ra + 64u * J + 4u * t0, qa);
+    buffer_load<W, STREAM>(base, rb + 64u * J + 4u * t0, qb);
+#pragma unroll
+    for (int u = 0; u < W; ++u) { va[4 * J + u] = qa[u]; vb[4 * J + u] = qb[u]; }
+  };
+  const bool any = p < pe;
+  load_tile(any ? p : 0, 0, any);                // on its way while the tables are made
   {
     const float4* cs = reinterpret_cast<const float4*>(ztab + (long long)m0 * stride);
     const float4* sn = reinterpret_cast<const float4*>(ztab + (long long)(mrows + m0) * stride);
@@ -149,22 +190,18 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
   }
   double2* ROT = reinterpret_cast<double2*>(SIN + 16 * MT * row);       // [16 MT]
   if (tid < 16 * MT) ROT[tid] = reinterpret_cast<const double2*>(ztab + (long long)2 * mrows * stride)[m0 + tid];
-  const int r = Nt - 16 * J;
-  const int t0 = min(W * g, r - W);             // start of this lane group's tail
   float tb[CT][KS];                             // t table, the right operand of every K step
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + c, kt = col >> 1;
+    // all of them asked for before the first is looked at
+    const float* part = reinterpret_cast<const float*>(twt + min(kt, mt - 1) * Nt) + (col & 1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) tb[ct][s] = part[2 * (s < 4 * J ? 16 * (s >> 2) + 4 * g + (s & 3) : 16 * J + t0 + (s - 4 * J))];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const int t = s < 4 * J ? 16 * (s >> 2) + 4 * g + (s & 3) : 16 * J + t0 + (s - 4 * J);
-      const bool dup = s >= 4 * J && t < 16 * J + W * g;
-      float v = 0.f;
-      if (kt < mt && !dup) {
-        const float2 w = twt[kt * Nt + t];
-        v = (col & 1) ? w.y : w.x;
-      }
-      tb[ct][s] = v;
+      const bool dup = s >= 4 * J && t0 + (s - 4 * J) < W * g;
+      tb[ct][s] = kt < mt && !dup ? tb[ct][s] : 0.f;
     }
   }
   // the same in parts: KS <= 4 third, first and second part of four values; else eight values a part
@@ -197,47 +234,33 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
   }
   const double sgn = (c & 1) ? -1.0 : 1.0;
   __syncthreads();
+  if (!any) return;
 
-  // each XCD walks a contiguous eighth of the planes, its waves interleaved inside it
-  const long long per_x = (planes + 7) >> 3;
-  const long long pe = min(planes, (long long)(xcd + 1) * per_x);
-  const long long nwl = (long long)((gridDim.x >> 3) / ngroups) * (TH / 64) * PP;
-  long long p = (long long)xcd * per_x + ((long long)(local / ngroups) * (TH / 64) + wave) * PP;
-  if (p >= pe) return;
-  const int ntile = PP > 1 ? 1 : (pairs + 15) >> 4;
-  constexpr int VP = 4 / PP;                    // registers of a lane that belong to one plane
-  const int lp = (c & 3) / VP, ln = VP * (c >> 2) + (c & (VP - 1));      // plane and pair of tile row c (PP > 1)
-
-  float va[KS], vb[KS];                         // this lane's part of row n and of row Nz - 1 - n
-  auto load_tile = [&](long long plane, int tile) {
-    const int n = min(PP > 1 ? ln : 16 * tile + c, pairs - 1);
-    const int first = PP > 1 ? min(lp, (int)min((long long)PP, planes - plane) - 1) * Nz : 0;      // row of the lane's plane
-    const float* base = x + plane * (Nz * Nt);
-    const float* ra = base + (first + n) * Nt;
-    const float* rb = base + (first + Nz - 1 - n) * Nt;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      float qa[4], qb[4];
-      load_run<4, STREAM>(ra + 16 * j + 4 * g, qa);
-      load_run<4, STREAM>(rb + 16 * j + 4 * g, qb);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { va[4 * j + u] = qa[u]; vb[4 * j + u] = qb[u]; }
-    }
-    float qa[W], qb[W];
-    load_run<W, STREAM>(ra + 16 * J + t0, qa);
-    load_run<W, STREAM>(rb + 16 * J + t0, qb);
-#pragma unroll
-    for (int u = 0; u < W; ++u) { va[4 * J + u] = qa[u]; vb[4 * J + u] = qb[u]; }
-  };
-  load_tile(p, 0);
   int at_field = SPLIT > 0 ? (int)(p % field) : 0;         // of the plane in its (batch, channel) field
   const int step_field = SPLIT > 0 ? (int)(nwl % field) : 0;
+  // Sums and differences of the tile's rows.  They are made behind the stores of the plane before, of which there are
+  // always as many, so that the wait for the tile's loads is not one for stores; and here and now, so that the next loads
+  // take the places of these values.
+  float e[KS], o[KS];
+  bool neg;
+  auto fold_rows = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      float sum = neg ? -va[s] - vb[s] : va[s] + vb[s], diff = neg ? vb[s] - va[s] : va[s] - vb[s];
+      asm volatile("" : "+v"(sum), "+v"(diff));
+      e[s] = sum;
+      o[s] = diff;
+    }
+  };
+  neg = SPLIT > 0 && (__builtin_popcount((unsigned)at_field) & 1);
+  fold_rows();
   for (; p < pe; p += nwl) {
     // The 16-bit instructions cut their sums towards minus infinity some bits below the rounding (0.004 units of the last
     // place on average).  Planes add up over y and x, where the lowest frequencies of 48 x 32 planes of 108 x 33 were off
     // by 3.3e-6 of a bin's size, fp32 products 8e-7.  Planes with an odd number of ones in their index within the field are
     // worked with the other sign, which takes it out (6.5e-7).
-    const bool neg = SPLIT > 0 && (__builtin_popcount((unsigned)at_field) & 1);
+    const bool turned = neg;                     // neg is the next plane's from the last tile on
     if constexpr (SPLIT > 0) {
       at_field += step_field;
       if (at_field >= field) at_field -= field;
@@ -252,17 +275,9 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
           accC[q][m][ct] = v4f{0.f, 0.f, 0.f, 0.f};
           accS[q][m][ct] = v4f{0.f, 0.f, 0.f, 0.f};
         }
-    for (int tile = 0; tile < ntile; ++tile) {
-      float e[KS], o[KS];
-      if (neg) {
-#pragma unroll
-        for (int s = 0; s < KS; ++s) { e[s] = -va[s] - vb[s]; o[s] = vb[s] - va[s]; }
-      } else {
-#pragma unroll
-        for (int s = 0; s < KS; ++s) { e[s] = va[s] + vb[s]; o[s] = va[s] - vb[s]; }
-      }
-      if (tile + 1 < ntile) load_tile(p, tile + 1);
-      else if (p + nwl < pe) load_tile(p + nwl, 0);
+    // the products of a tile's rows, while the next tile's are on their way
+    auto products = [&](int tile) __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
       if constexpr (SPLIT) {
         const v4f zero = {0.f, 0.f, 0.f, 0.f};
         v4f dE[CT], dO[CT];
@@ -310,7 +325,7 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
             accS[0][m][ct] += quad_product(ts, qo, [](u32x4 t, u32x4 d, v4f a) { return mfma_split(t, d, a); });
           }
         }
-        continue;
+        return;
       }
       float ca[MT][VP], sa[MT][VP];
 #pragma unroll
@@ -363,22 +378,33 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
           }
         }
       }
+    };
+    // the plane's last tile apart: on its way the next plane's first is asked for, and stores come between
+    if constexpr (PP == 1) {
+#pragma unroll 1
+      for (int tile = 0; tile + 1 < ntile; ++tile) {
+        load_tile(p, tile + 1, true);
+        products(tile);
+        fold_rows();
+      }
     }
+    load_tile(p + nwl < pe ? p + nwl : p, 0, p + nwl < pe);
+    products(ntile - 1);
     // X[+-k] from C, S: real and imaginary parts sit in neighbouring lanes
     // the phases and the store offsets are worked out again for every plane, not kept in registers
     int g4 = 4 * g;
     asm volatile("" : "+v"(g4)::"memory");
 #pragma unroll
     for (int q = 0; q < PP; ++q) {
-      if (PP > 1 && p + q >= pe) break;
-      float* dst = out + (p + q) * (Lz * mt * 2);
+      // lanes and planes without a place have an offset past the end
+      const __amdgpu_buffer_rsrc_t dst = buffer_of(out + (p + q) * (Lz * mt * 2), PP == 1 || p + q < pe ? Lz * mt * 8 : 0);
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int kl = 16 * m + g4 + v, k = m0 + kl;
           double2 w = ROT[kl];
-          if (neg) w = make_double2(-w.x, -w.y);
+          if (turned) w = make_double2(-w.x, -w.y);
           const double ws = sgn * w.y;
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct) {
@@ -388,13 +414,14 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
             const double D = swap_pair(fc), it = sgn * fs;
             const double yp = fma(C + is, w.x, -ws * (D - it));
             const double ym = fma(C - is, w.x, ws * (D + it));
-            if (col < 2 * mt) {
-              if (k < npos) dst[k * mt * 2 + col] = (float)yp;
-              if (k >= 1 && k <= Lz - npos) dst[(Lz - k) * mt * 2 + col] = (float)ym;
-            }
+            const float p1[1] = {(float)yp}, m1[1] = {(float)ym};
+            buffer_store<1, false>(dst, col < 2 * mt && k < npos ? (unsigned)(k * mt * 2 + col) * 4u : kNowhere, p1);
+            buffer_store<1, false>(dst, col < 2 * mt && k >= 1 && k <= Lz - npos ? (unsigned)((Lz - k) * mt * 2 + col) * 4u : kNowhere, m1);
           }
         }
     }
+    if constexpr (SPLIT > 0) neg = __builtin_popcount((unsigned)at_field) & 1;
+    fold_rows();
   }
 }
 

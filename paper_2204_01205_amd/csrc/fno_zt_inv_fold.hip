@@ -71,7 +71,6 @@ constexpr int fold_inv_ns(int W, int CI) { return 2 * W * CI <= 160 ? 2 : 1; }
 constexpr int fold_inv_low(int CI) { return CI <= 8 ? 1 : (CI == 32 ? 25 : CI - 3); }
 
 // Where a lane's points of one task lie: NU runs of W points, of the two rows of a pair or of one row.
-constexpr unsigned kNowhere = 0x80000000u;       // past the end of every column
 template <int NU> struct FoldTile {
   int n;                 // pair of rows
   bool second;           // one row per lane: it is Nz-1-n
@@ -103,53 +102,12 @@ __device__ __forceinline__ FoldTile<NU> fold_inv_place(const FoldInv& f, int tas
   return q;
 }
 
-// A column of one channel as a buffer: loads and stores at 32-bit offsets from a base in scalar registers.  (A pointer
-// that goes through an asm statement loses its address space: the flat loads that this kernel had then count as LDS
-// accesses too, and every wait for LDS waits for them.)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t fold_inv_column(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
 // the waves of a block meet once their LDS accesses are done; what is on its way from and to memory stays so
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-// W consecutive floats per lane; lanes whose offset lies past the end store nothing.
-template <int W, bool STREAM>
-__device__ __forceinline__ void fold_inv_load(__amdgpu_buffer_rsrc_t r, unsigned at, float (&y)[W]) {
-  constexpr int aux = STREAM ? 2 : 0;            // nontemporal
-  if constexpr (W == 1) {
-    y[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, aux));
-  } else {
-    typedef unsigned vec __attribute__((ext_vector_type(W)));
-    vec q;
-    if constexpr (W == 2) q = __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, aux);
-    if constexpr (W == 3) q = __builtin_amdgcn_raw_buffer_load_b96(r, at, 0, aux);
-    if constexpr (W == 4) q = __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, aux);
-#pragma unroll
-    for (int v = 0; v < W; ++v) {
-      const unsigned e = q[v];
-      y[v] = __builtin_bit_cast(float, e);
-    }
-  }
-}
-template <int W, bool STREAM>
-__device__ __forceinline__ void fold_inv_store(__amdgpu_buffer_rsrc_t r, unsigned at, const float (&y)[W]) {
-  constexpr int aux = STREAM ? 2 : 0;
-  if constexpr (W == 1) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, y[0]), r, at, 0, aux);
-  } else {
-    typedef unsigned vec __attribute__((ext_vector_type(W)));
-    vec q;
-#pragma unroll
-    for (int v = 0; v < W; ++v) q[v] = __builtin_bit_cast(unsigned, y[v]);
-    if constexpr (W == 2) __builtin_amdgcn_raw_buffer_store_b64(q, r, at, 0, aux);
-    if constexpr (W == 3) __builtin_amdgcn_raw_buffer_store_b96(q, r, at, 0, aux);
-    if constexpr (W == 4) __builtin_amdgcn_raw_buffer_store_b128(q, r, at, 0, aux);
-  }
-}
-
 // u of the lane's points, every input channel (up: channel 0 of the column)
 template <int NU, int W, int CI, bool STREAM>
 __device__ __forceinline__ void fold_inv_load_u(const unsigned (&at)[NU], const char* up, unsigned bytes, int Cu, long long chan_bytes,
@@ -157,9 +115,9 @@ __device__ __forceinline__ void fold_inv_load_u(const unsigned (&at)[NU], const 
 #pragma unroll
   for (int i = 0; i < CI; ++i) {
     // channels past the last: nothing to read, zeros
-    const __amdgpu_buffer_rsrc_t r = fold_inv_column(up, i < fold_inv_low(CI) || i < Cu ? bytes : 0);
+    const __amdgpu_buffer_rsrc_t r = buffer_of(up, i < fold_inv_low(CI) || i < Cu ? bytes : 0);
 #pragma unroll
-    for (int s = 0; s < NU; ++s) fold_inv_load<W, STREAM>(r, at[s], u[i][s]);
+    for (int s = 0; s < NU; ++s) buffer_load<W, STREAM>(r, at[s], u[i][s]);
     up += chan_bytes;
     asm volatile("" : "+s"(up));                 // one running base, not one per channel
   }
@@ -237,7 +195,7 @@ __device__ __forceinline__ void fold_inv_t(const float (&tb)[NS], v4f C, v4f S, 
 template <int NS>
 __device__ __forceinline__ void fold_inv_load_z(const FoldInv& f, const float* ztab, const FoldTile<NS>& q, float* ZT) {
   const int g = (threadIdx.x & 63) >> 4, plane = f.mrows * f.stride * 4, at = (g * f.stride + q.n) * 4;
-  const __amdgpu_buffer_rsrc_t r = fold_inv_column(ztab, 2 * plane);
+  const __amdgpu_buffer_rsrc_t r = buffer_of(ztab, 2 * plane);
   for (int s = 0; s < f.ks; ++s) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(ZT + 128 * s), 4, at,
                                              16 * s * f.stride, 0, 0);
@@ -349,13 +307,13 @@ __device__ __forceinline__ void fold_inv_tile(const FoldInv& f, const EpiArgs& e
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         // the column of one channel; nothing for a channel past the last
-        const __amdgpu_buffer_rsrc_t r = fold_inv_column(dst + base + w * f.Npts, o + w < f.Co ? f.Nz * f.Nt * 4 : 0);
+        const __amdgpu_buffer_rsrc_t r = buffer_of(dst + base + w * f.Npts, o + w < f.Co ? f.Nz * f.Nt * 4 : 0);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
           float y[W];
 #pragma unroll
           for (int v = 0; v < W; ++v) y[v] = acc[s][v][w];
-          fold_inv_store<W, STREAM>(r, q.at[s], y);
+          buffer_store<W, STREAM>(r, q.at[s], y);
         }
       }
     };
@@ -523,7 +481,7 @@ __global__ __launch_bounds__(kThreads, fold_inv_waves(W, CI)) void zt_inv_fold_k
   lds_barrier();
   // The number of memory instructions that a wait may leave open is the smallest over all ways to its place.  On the way
   // from the last task there are a group's stores after u; here, as many that store nothing.
-  const __amdgpu_buffer_rsrc_t none = fold_inv_column(out, 0);
+  const __amdgpu_buffer_rsrc_t none = buffer_of(out, 0);
 #pragma unroll
   for (int s = 0; s < 4 * NS; ++s) {
     __builtin_amdgcn_raw_buffer_store_b32(0u, none, 4 * s, 0, 0);
