@@ -153,19 +153,18 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
 // The same step for every other width up to 32, any point count and alignment, and c_in != c_out (the adjoint of the
 // lift).  The kernel above keeps all of gW in a wave's accumulators, which 32 channels do not fit; here the output
 // channels are dealt to `ngrp` waves of a block (OT tiles of 4 each).  Layout and products are those of the kernel above;
-// rows need not be aligned (4-byte aligned 16-byte loads), a batch entry's ragged last step takes single values, and
-// channels past the end read the last one and count as zero.  The fp32 accumulators take kBwdChain steps (128 terms of a
-// lane block) and then go to doubles, which are added over the wave's 16 lane blocks, half of them sent away at each
-// level: every lane keeps a sixteenth.
+// rows need not be aligned (4-byte aligned 16-byte loads), points past the end of a batch entry and channels past the last
+// count as zero.  The fp32 accumulators take kBwdChain steps (128 terms of a lane block) and then go to doubles, which are
+// added over the wave's 16 lane blocks, half of them sent away at each level: every lane keeps a sixteenth.
 //
 // Where the waves of a step are two or four (NG), each reads its share of x and leaves it in LDS, double buffered, one
 // barrier a step; that takes half to three quarters of a step's loads off every wave, and the registers they took hold
 // the next step's, asked for a step ahead.  (With all of x in every wave there is no room for that: 0.45 ms in the first
-// case below, with spills.)  What bounds it: copy speed at 32 channels and 4.2 TB/s (0.21 ms at 5.2).  With erff, expf and
-// x read by every wave, and now, us: 32 -> 32 at 2.16 M points with GELU and a target 446 and 270; the widths 17, 22, 24,
-// 25, 27 without a target 203, 215, 239, 355, 364 and 136, 148, 178, 257, 261; 9 and 10 (one wave a step) 117, 118 and
-// 90, 93; 5 -> 20 at 33.5 M points, no activation, 754 and 655 (its values of z were set to zero one by one, which waited
-// for the loads between them).
+// case below, with spills.)  What bounds it: memory at 32 channels, 4.5 TB/s (0.21 ms at the 5.2 of a large copy).  At
+// 2.16 M points with GELU, us: 32, 27, 25, 24, 22, 17 channels 248, 225, 217, 189, 173, 150; with a ragged step, a last
+// step and channels past the last on ways of their own, where the loads of the next step were waited for as they were
+// sent, 289, 273, 265, 189, 176, 152.  9 and 10 (one wave a step) 90, 93; 5 -> 20 at 33.5 M points, no activation, 655
+// (754 where values of z that are not needed were set to zero one by one, which waited for the loads between them).
 constexpr int kBwdChain = 32;
 
 template <bool STREAM>
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     float* __restrict__ gz_out, double* __restrict__ part, int B, int Ci, int Co, long long N, int act,
     int mse_target, float mse_scale, int ngrp) {
   constexpr int R0 = 4 * OT * IT, R1 = fold_count(R0), R2 = fold_count(R1), R3 = fold_count(R2), R4 = fold_count(R3);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int j4 = lane & 3, blk = lane >> 2;
   const int per_block = (kThreads / 64) / ngrp;            // point ranges per block
   const int o0 = (wave % ngrp) * 4 * OT;
@@ -297,8 +296,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     return whole;
   };
   // the cotangent of the pre-activation, in gq's place
-  auto cotangent = [&](long long ob, long long p0, bool whole, const v4f (&zq)[OT], v4f (&gq)[OT]) {
-    const long long p = p0 + 4 * blk;
+  auto cotangent_of = [&](const v4f (&zq)[OT], v4f (&gq)[OT]) {
     if (act) {
 #pragma unroll
       for (int T = 0; T < OT; ++T)
@@ -315,6 +313,11 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
 #pragma unroll
         for (int u = 0; u < 4; ++u) gq[T][u] = mse_scale * (zq[T][u] - gq[T][u]);
     }
+  };
+  // and stored
+  auto cotangent = [&](long long ob, long long p0, bool whole, const v4f (&zq)[OT], v4f (&gq)[OT]) {
+    const long long p = p0 + 4 * blk;
+    cotangent_of(zq, gq);
 #pragma unroll
     for (int T = 0; T < OT; ++T) {
       v4f g = gq[T];
@@ -347,6 +350,12 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
         for (int c = 0; c < XN; ++c)
           acc[a][c0.value + c] = __builtin_amdgcn_mfma_f32_4x4x1f32(gq[a][u], xv[c][u], acc[a][c0.value + c], 0, 0, 0);
   };
+  // the waves of a block meet once their LDS accesses are done; what is on its way from and to memory stays so
+  auto lds_meet = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
   int chain = 0;
   using std::integral_constant;
   if constexpr (NG == 0) {
@@ -362,30 +371,119 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
       if (++chain == kBwdChain) { chain = 0; flush(); }
     }
   } else {
-    // all waves of a block take as many turns; the values of a step are asked for a step ahead
-    long long ob = 0, p0 = 0;
-    bool live = xs + wl < xe, whole = false;
+    // All waves of a block take as many turns; the values of a step are asked for a step ahead.  One way through a turn, with
+    // as many loads and stores whatever the step: where a ragged step's loads, a last step without a next one or channels
+    // past the last were ways of their own, the values met in copies that waited for them at once.  So a step past the last
+    // is the last again, a lane past the row's last four points takes those and shifts them when they are there, and what
+    // is not to be stored has an offset past the end.  (N from 4 to 2^27: 32-bit offsets over four rows.)
+    auto step_of = [&](long long s, long long& ob, long long& ib, long long& p0) {
+      s = s < steps ? s : steps - 1;
+      const long long bb = s / steps_per_b;
+      p0 = (s - bb * steps_per_b) * 64;
+      ob = bb * Co * N;
+      ib = bb * Ci * N;
+    };
+    const long long Nall = (long long)B * N;
+    // rows first .. first + 3 of a tensor of C channels, from point p0 of an entry on: a base and the lane's offset
+    auto tile_of = [&](const float* t, long long base, int C, int first, long long p0) {
+      const int row = first < C ? first : C - 1;
+      const long long at = base + row * N + p0, left = (Nall * C - at) * 4;
+      return buffer_of(t + at, (unsigned)(left < 0x7fffffffLL ? left : 0x7fffffffLL));
+    };
+    auto offset_of = [&](int C, int first, int point) {
+      const int row = first < C ? first : C - 1, mine = first + j4 < C ? first + j4 : C - 1;
+      return ((unsigned)(mine - row) * (unsigned)N + (unsigned)point) * 4u;
+    };
+    auto four = [&](__amdgpu_buffer_rsrc_t r, unsigned at) {
+      float q[4];
+      buffer_load<4, STREAM>(r, at, q);
+      return v4f{q[0], q[1], q[2], q[3]};
+    };
+    const int i0 = 4 * member * XT;
     v4f zn[OT], gn[OT], xn[XT];
-    if (live) whole = fetch(xs + wl, ob, p0, zn, gn, xn);
+    auto ask = [&](long long s) {
+      long long ob, ib, p0;
+      step_of(s, ob, ib, p0);
+      const long long from = p0 > 0 ? p0 - 4 : 0;          // the last four points start at p0 - 3 at the earliest
+      const int at = (int)(min(p0 + 4 * blk, N - 4) - from);
+      if (need_z)
+#pragma unroll
+        for (int T = 0; T < OT; ++T) zn[T] = four(tile_of(z, ob, Co, o0 + 4 * T, from), offset_of(Co, o0 + 4 * T, at));
+#pragma unroll
+      for (int T = 0; T < OT; ++T) gn[T] = four(tile_of(gout, ob, Co, o0 + 4 * T, from), offset_of(Co, o0 + 4 * T, at));
+#pragma unroll
+      for (int T = 0; T < XT; ++T) xn[T] = four(tile_of(x, ib, Ci, i0 + 4 * T, from), offset_of(Ci, i0 + 4 * T, at));
+    };
+    ask(xs + wl);
     int turn = 0;
-    for (long long s0 = xs + (long long)(blockIdx.x >> 3) * per_block; s0 < xe; s0 += nwl, turn ^= 1) {
+    long long s = xs + wl;
+    for (long long s0 = xs + (long long)(blockIdx.x >> 3) * per_block; s0 < xe; s0 += nwl, s += nwl, turn ^= 1) {
       float* buf = own + turn * (kThreads / 64 / NG) * XS;
-      v4f zq[OT], gq[OT];
-      const long long ob_now = ob, p0_now = p0;
-      const bool live_now = live, whole_now = whole;
-      if (live) {
+      const bool live = s < xe;
+      long long ob, ib, p0;
+      step_of(s, ob, ib, p0);
+      const bool whole = p0 + 64 <= N;
+      if (!whole) {
+        // the lane's first point is `d` further on in what it read
+        const int d = (int)(4 * blk - min((long long)(4 * blk), N - 4 - p0));
+        auto shift = [&](v4f& v) {
+          const v4f q = v;
 #pragma unroll
-        for (int T = 0; T < XT; ++T)
-          *reinterpret_cast<v4f*>(buf + (4 * (member * XT + T) + j4) * kBwdXS + 4 * blk) = ilive[T] ? xn[T] : v4f{0.f, 0.f, 0.f, 0.f};
+          for (int u = 0; u < 4; ++u) {
+            float r = d == 0 ? q[u] : 0.f;
 #pragma unroll
-        for (int T = 0; T < OT; ++T) { zq[T] = zn[T]; gq[T] = gn[T]; }
+            for (int e = 1; u + e < 4; ++e) r = d == e ? q[u + e] : r;
+            v[u] = r;
+          }
+        };
+#pragma unroll
+        for (int T = 0; T < OT; ++T) {
+          if (need_z) shift(zn[T]);
+          shift(gn[T]);
+        }
+#pragma unroll
+        for (int T = 0; T < XT; ++T) shift(xn[T]);
       }
-      const long long s = s0 + nwl + wave / NG;
-      live = s < xe;
-      if (live) whole = fetch(s, ob, p0, zn, gn, xn);
-      __syncthreads();
-      if (live_now) {
-        cotangent(ob_now, p0_now, whole_now, zq, gq);
+      v4f gq[OT];
+#pragma unroll
+      for (int T = 0; T < XT; ++T)
+        *reinterpret_cast<v4f*>(buf + (4 * (member * XT + T) + j4) * kBwdXS + 4 * blk) = ilive[T] ? xn[T] : v4f{0.f, 0.f, 0.f, 0.f};
+      // the slopes before the next step's values are asked for, which take the places of these
+      cotangent_of(zn, gn);
+#pragma unroll
+      for (int T = 0; T < OT; ++T) {
+        gq[T] = gn[T];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float v = gq[T][u];
+          asm volatile("" : "+v"(v));
+          gq[T][u] = v;
+        }
+      }
+      ask(s + nwl);
+#pragma unroll
+      for (int T = 0; T < OT; ++T) {
+        const int row = o0 + 4 * T;
+        const long long at = ob + (row < Co ? row : Co - 1) * N + p0, left = (Nall * Co - at) * 4;
+        const __amdgpu_buffer_rsrc_t r = buffer_of(gz_out + at, live && gz_out != nullptr && row < Co ? (unsigned)(left < 0x7fffffffLL ? left : 0x7fffffffLL) : 0u);
+        const unsigned to = olive[T] ? offset_of(Co, row, 4 * blk) : kNowhere;
+        if (whole) {
+          const float gs[4] = {gq[T][0], gq[T][1], gq[T][2], gq[T][3]};
+          buffer_store<4, STREAM>(r, to, gs);
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float g1[1] = {gq[T][u]};
+            buffer_store<1, false>(r, p0 + 4 * blk + u < N ? to + 4u * u : kNowhere, g1);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (!live || !olive[T] || p0 + 4 * blk + u >= N) gq[T][u] = 0.f;
+        gbacc[T] += (gq[T][0] + gq[T][1]) + (gq[T][2] + gq[T][3]);
+      }
+      lds_meet();
+      if (live) {
         constexpr int XN = IT == 6 ? 3 : IT;               // tiles of x in registers at a time: as many as leave no spills
         auto piece = [&](auto c0) {
           v4f xq[XN];
@@ -1766,6 +1864,8 @@ hipError_t launch_bwd_wide(const float* z, const float* gout, const float* x, fl
   if (nb > 1024) nb = 1024;
   *nslots = (int)nb * per_block;
   const bool stream = (int64_t)B * Co * N * 4 >= kStreamBytes;
+  // a lane's four points within an entry, and 32-bit offsets over four rows of one: else every wave reads all of x
+  const bool ahead = N >= 4 && N <= (1ll << 27);
 #define FNO_BPX(OTV, ITV, NGV)                                                                                         \
   do {                                                                                                                 \
     if (stream)                                                                                                        \
@@ -1776,8 +1876,8 @@ hipError_t launch_bwd_wide(const float* z, const float* gout, const float* x, fl
                          z, gout, x, gz_out, part, B, Ci, Co, (long long)N, act, mse_target, (float)mse_scale, ngrp);  \
   } while (0)
   if (it == 2) { if (ot == 2) FNO_BPX(2, 2, 0); else if (ot == 5) FNO_BPX(5, 2, 0); else FNO_BPX(4, 2, 0); }
-  else if (it == 6) { if (ngrp == 2) FNO_BPX(3, 6, 2); else FNO_BPX(3, 6, 0); }
-  else if (ngrp == 4) FNO_BPX(2, 8, 4);
+  else if (it == 6) { if (ngrp == 2 && ahead) FNO_BPX(3, 6, 2); else FNO_BPX(3, 6, 0); }
+  else if (ngrp == 4 && ahead) FNO_BPX(2, 8, 4);
   else FNO_BPX(2, 8, 0);
 #undef FNO_BPX
   return hipGetLastError();

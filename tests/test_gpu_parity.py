@@ -1219,6 +1219,25 @@ def test_sums_over_points_of_every_tile_shape(c_in, c_out, npts, batch):
     assert rel(host(gb), gd.sum(axis=(0, 2))) <= TOL
 
 
+@pytest.mark.parametrize("c_in, c_out", [(24, 24), (17, 13), (32, 32), (27, 25)])
+def test_sums_over_points_of_a_short_last_step(c_in, c_out):
+    """Widths whose waves share a step: entries of fewer points than a lane takes at once, and last steps whose points
+    end 1, 2 or 3 into a lane's four, before and after the first step, so that lanes read points in front of theirs."""
+    for npts in (1, 2, 3, 4, 5, 6, 7, 61, 62, 63, 65, 66, 67, 68, 190):
+        test_sums_over_points_of_every_tile_shape(c_in, c_out, npts, 2)
+
+
+@pytest.mark.parametrize("case", [
+    (2, 32, 32, (3, 3, 9, 5), (1, 1, 2, 2), 0),        # 405 points: 5 lanes of four and a point in the last step
+    (2, 27, 27, (3, 3, 5, 3), (1, 1, 1, 1), 0),        # 135: a lane and 3 points, a ragged channel tile
+    (1, 24, 24, (1, 2, 11, 3), (0, 0, 2, 1), 1),       # 66: 2 points
+    (3, 18, 18, (1, 1, 2, 3), (0, 0, 0, 1), 1),        # 6: less than a step
+])
+def test_block_adjoint_of_a_short_last_step(case):
+    for activation in (B.FNO_ACT_GELU, B.FNO_ACT_IDENTITY):
+        test_block_fwd_and_bwd_match_oracle(case, activation)
+
+
 @pytest.mark.parametrize("c_in, c_out", [(5, 8), (24, 24), (32, 7)])
 def test_sums_over_points_reach_doubles_after_128_terms(c_in, c_out):
     """Whole numbers whose 128-term chains stay below 2^24 (128 x 255 x 255 < 8.4e6) and are therefore exact in fp32,
