@@ -199,7 +199,10 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     float* __restrict__ gz_out, double* __restrict__ part, int B, int Ci, int Co, long long N, int act,
     int mse_target, float mse_scale, int ngrp) {
   constexpr int R0 = 4 * OT * IT, R1 = fold_count(R0), R2 = fold_count(R1), R3 = fold_count(R2), R4 = fold_count(R3);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // scalar where buffer loads need it; alone it costs: with scalar branches the loads of a step (5 -> 20 channels) wait for
+  // one another, 662 -> 702 us
+  const int tid = threadIdx.x, wave = NG > 0 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+  const int lane = tid & 63;
   const int j4 = lane & 3, blk = lane >> 2;
   const int per_block = (kThreads / 64) / ngrp;            // point ranges per block
   const int o0 = (wave % ngrp) * 4 * OT;
