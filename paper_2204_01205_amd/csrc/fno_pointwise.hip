@@ -967,7 +967,7 @@ constexpr int mlp_region(int NS, int NPG) {
   return NS == 18 && NPG == 1 ? parts + share : (share > parts ? share : parts);
 }
 constexpr size_t mlp_bwd_lds(int NS, int NPG, int nw) {
-  return (size_t)(NS > 8 ? 2 : 1) * 6 * 64 * 16 + 3 * 64 * kMlpTS * 2 + 64 * 4 + (NS == 18 ? 256 * 4 : 0) +
+  return (size_t)(NS > 8 ? 2 : 1) * 6 * 64 * 16 + 3 * 64 * kMlpTS * 2 + 2 * 64 * 4 + (NS == 18 ? 256 * 4 : 0) +
          (size_t)nw * mlp_region(NS, NPG) * 4;
 }
 // most pairs of channels that a wave of nw (or more) stages
@@ -989,8 +989,8 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
   const int wp = w / f.nwh, wh = w - wp * f.nwh;
   u32x4* XS = reinterpret_cast<u32x4*>(smem4);                               // [KB][3][2][64]: octets of channels of a point
   unsigned short* YS = reinterpret_cast<unsigned short*>(XS + KB * 6 * 64);  // [3][64][kMlpTS]: channels of a point
-  float* GS = reinterpret_cast<float*>(YS + 3 * 64 * kMlpTS);                // [64]
-  float* BS = GS + 64;                                                       // [256] b1
+  float* GS2 = reinterpret_cast<float*>(YS + 3 * 64 * kMlpTS);               // [2][64] cotangents, tile by tile in turn
+  float* BS = GS2 + 2 * 64;                                                  // [256] b1
   float* regions = BS + (ALL ? 256 : 0);
   float* own = regions + w * REG;
   unsigned short* T = reinterpret_cast<unsigned short*>(own);                // [BUF][3][32][kMlpTS]
@@ -1143,8 +1143,13 @@ __global__ __launch_bounds__(512, 2) void mlp2_bwd_split_kernel(
     if constexpr (ALL) add(dst + H * Ci + row, row_sum(accb), last && mine ? (double)W2[row] : 1.0);
   };
   int pass = 0;
+  static_assert(kMlpFlush % 2 == 0, "passes take the two halves of GS2 in turn");
   while (b < f.B) {
     const long long bo = b, to = t;
+    // The cotangents are read after the tile's last barrier, when wave 0 may be at the next tile already: that one has the
+    // other half.  This half is written again a tile later, behind the next tile's first barrier, which every wave reaches
+    // with its reads done.  (One array: a wave held up took another tile's cotangents.)
+    float* GS = GS2 + 64 * (pass & 1);
     const float gp = (to << 6) + lane < N ? pg : 0.f, gs = gp * sign;
 #pragma unroll
     for (int r = 0; r < SR; ++r) {

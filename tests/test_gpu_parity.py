@@ -765,6 +765,25 @@ def test_projection_adjoint_with_channels_and_points_of_very_different_size():
     assert float(err.max()) <= 8 * 2.0 ** -23
 
 
+@pytest.mark.parametrize("batch, ci, h", [
+    (1, 20, 128), (1, 7, 128), (1, 31, 128),               # four waves, two column blocks each
+    (1, 20, 96), (1, 23, 96),                              # three waves
+    (1, 32, 128), (1, 32, 96), (1, 20, 64), (2, 15, 32),   # two waves a group of hidden units
+    (1, 32, 256), (2, 24, 160),                            # eight and five waves
+])
+def test_projection_adjoint_tile_by_tile(batch, ci, h):
+    """512 blocks of several tiles of 64 points each, past a flush of the sums (32 tiles) with two waves a group: the
+    cotangents of a block's tiles differ by 2^20 from one to the next, and every tile's gx is held against its own size."""
+    npts = 64 * 512 * (35 if h <= 64 else 5) // batch + 7
+    tiles = (npts + 63) // 64
+    turn = (torch.arange(batch, device="cuda")[:, None] * tiles + torch.arange(npts, device="cuda") // 64) // 512
+    got, want, _ = _projection(batch, ci, h, 1, npts, 9, sg=torch.where(turn % 2 == 0, 1.0, 2.0 ** -20)[:, None])
+    pad = lambda t: torch.nn.functional.pad(t, (0, tiles * 64 - npts)).reshape(batch, ci, tiles, 64).norm(dim=(1, 3))
+    err = pad(got["gx"].double() - want["gx"]) / pad(want["gx"])
+    # as for the whole field above: the smallest tile has 7 points of at least 7 channels
+    assert float(err.max()) <= 8 * 2.0 ** -23
+
+
 @pytest.mark.parametrize("ci, h", [(20, 128), (32, 128), (9, 64)])
 @pytest.mark.parametrize("kind", ["off by 3", "off by 5", "off by 7", "a heavy unit without weights", "light units", "a plume"])
 def test_projection_adjoint_value_by_value(kind, ci, h):
