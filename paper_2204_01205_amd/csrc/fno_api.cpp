@@ -311,8 +311,12 @@ int conv_bwd_common(const Plan& p, const float* x, const float* xhat_saved, cons
   const float2* xh = reinterpret_cast<const float2*>(xhat_saved);
   if (gR != nullptr && xh == nullptr) {
     float2* s3 = at<float2>(ws, p.off_s3);
-    rc = forward_chain(p, ws, x, p.Ci, s3, s);
+    rc = forward_chain(p, ws, x, p.Ci, p.xmix ? nullptr : s3, s);
     if (rc != FNO_OK) return rc;
+    // the kernel that the forward call takes: a spectrum has the same bits saved and worked out again
+    if (p.xmix)
+      FNO_STAGE(FNO_STAGE_X_FWD, s, fno::launch_xmix_fwd(at<float2>(ws, p.off_a2), nullptr, s3, nullptr, p.B, p.Ci, p.Co,
+                                    p.ax[0], p.K / p.L[0], p.mt, p.Nt, 1.0 / double(p.Npts), s));
     xh = s3;
   }
   if (xh == nullptr) xh = at<float2>(ws, p.off_s3);   // unread when gR is null

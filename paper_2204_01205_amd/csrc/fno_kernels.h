@@ -69,7 +69,8 @@ hipError_t launch_mix_bwd(const float2* xh, const float2* R, const float2* gh, f
                           double invN, int accumulate, hipStream_t s);
 
 // Small layers: x stage, mode mix and x stage back in one launch (fno_xmix.hip); `out` may be `in`.  xh, R, gR and
-// accumulate as in launch_mix_fwd and launch_mix_bwd; xh nullable in the forward, gR and out in the adjoint.
+// accumulate as in launch_mix_fwd and launch_mix_bwd; xh nullable in the forward, as are out and R together (the spectrum
+// alone), gR and out in the adjoint.
 bool xmix_fits(int B, int Ci, int Co, AxisPlan ax, int64_t inner, bool adjoint);
 hipError_t launch_xmix_fwd(const float2* in, const float2* R, float2* xh, float2* out, int B, int Ci, int Co, AxisPlan ax,
                            int64_t inner, int mt, int Nt, double invN, hipStream_t s);

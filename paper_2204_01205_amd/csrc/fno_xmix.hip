@@ -108,7 +108,8 @@ __device__ __forceinline__ void xmix_inverse(const XMix& f, const float2* Y, int
   }
 }
 
-// in, out [B C][N][inner]; xh (nullable) [B Ci][L][inner].  One batch entry per block.
+// in, out [B C][N][inner]; xh (nullable) [B Ci][L][inner]; out null: the spectrum alone, R is not read then.  One batch entry
+// per block.
 __global__ __launch_bounds__(kXmixThreads) void xmix_fwd_kernel(const float2* in, const float2* __restrict__ R,
                                                                 float2* __restrict__ xh, float2* out, XMix f) {
   HIP_DYNAMIC_SHARED(float4, smem4)
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(kXmixThreads) void xmix_fwd_kernel(const float2* in
   xmix_roots(f, roots);
   xmix_forward(f, in + (long long)b * f.Ci * f.N * f.inner + c0, f.Ci, wc, roots, A, X,
                xh != nullptr ? xh + (long long)b * f.Ci * K + c0 : nullptr);
+  if (out == nullptr) return;
   __syncthreads();
   float2* Y = A;
   for (int idx = tid; idx < f.Co * f.L * W; idx += kXmixThreads) {

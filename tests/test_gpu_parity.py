@@ -1196,6 +1196,29 @@ def test_x_stage_kernels_of_five_entries(n, m):
     test_fft_axis_kernels_match_oracle((5, 2, 2, (n, 5, 12, 16), (m, 1, 3, 8), 0))
 
 
+@pytest.mark.parametrize("case", [
+    (1, 3, 5, (1, 3, 4, 5), (0, 1, 1, 1), 1),          # x stages and mode mix in one launch, forward and adjoint
+    (2, 4, 4, (9, 6, 5, 6), (4, 2, 2, 3), 1),
+    (4, 16, 16, (12, 9, 8, 6), (3, 2, 2, 3), 0),       # the forward alone
+    (2, 3, 5, (11, 6, 5, 6), (3, 2, 1, 2), 1),         # the adjoint alone
+    (2, 12, 16, (30, 9, 8, 6), (7, 2, 2, 3), 0),       # neither
+])
+def test_weight_gradient_from_a_spectrum_saved_and_worked_out_again(case):
+    """The adjoint without the forward's spectrum takes the forward's kernels: the same bits."""
+    L = Layer(*case)
+    gy = dev(synth.normal_field(1, synth.T_GOUT, case[0], case[2], L.spec.grid))
+    x, R = dev(L.x), dev(L.R)
+    ws = B.alloc_workspace(L.desc, B.FNO_OP_SPECTRAL_CONV_BWD)
+    xh = torch.empty((case[0], case[1]) + L.counts, dtype=torch.complex64, device="cuda")
+    B.fno_spectral_conv_fwd(L.desc, x, R, torch.empty_like(gy), xh, ws)
+    gR = [torch.empty_like(R) for _ in range(2)]
+    B.fno_spectral_conv_bwd(L.desc, x, xh, R, gy, None, gR[0], ws)
+    B.fno_spectral_conv_bwd(L.desc, x, None, R, gy, None, gR[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(gR[0], gR[1])
+    assert rel(host(gR[1]), O.spectral_conv_bwd(L.x, L.R, host(gy), L.spec)[1]) <= TOL
+
+
 def test_one_launch_adds_to_the_weight_gradient():
     """FNO_FLAG_ACCUMULATE_GRADS on a small layer: gR is added to what the buffer holds, gx is not."""
     L = Layer(2, 3, 4, (8, 6, 5, 6), (2, 2, 1, 2))
