@@ -228,22 +228,32 @@ bool xmix_geometry(int B, int from, int to, AxisPlan ax, int64_t inner, int* wsh
 
 }  // namespace
 
-// Where one launch is faster than three: as long as the chip is far from full (values of the pruned field) and a block's own
-// work, in multiply-adds of its sums per column, is no longer than the launches saved.  us, three launches and one, forward
-// and (in brackets) forward and adjoint: 8 -> 8 channels, 16 points, 8 kept, 192 columns 35.6, 28.6 (70, 56); 12 -> 12, 12
-// points, 2 kept, 240 columns 42, 35 (87, 70); batch 4, 16 -> 16, 9 points, 336 columns 58, 49 (123, 108); 8 -> 16, 34
-// points, 10 kept, 320 columns (4512 multiply-adds) 53, 52 (111, 103); but batch 2, 32 -> 32, 20 points, 8 kept, 144
-// columns (6016, in the adjoint 12032) 78, 82 (163, 176); 8 -> 16, 60 points, 24 kept (18140) 64, 72 (133, 150); 16 -> 16,
-// 19 points, 1296 columns (394 thousand values) 67, 66 (135, 134).  The forward's choice is the same for one to four
-// entries, each of which has blocks of its own; an adjoint's block works all of them.
+// Where one launch is faster than three: as long as the chip is far from full (values of the pruned field), a block's own
+// work is no longer than the launches saved, and the weights, which every batch entry's blocks read in runs of one tile,
+// are few.  The work per column: multiply-adds of the sums (`sums`) and products of the mix.  us, three launches and one,
+// forward and (in brackets) forward and adjoint: 8 -> 8 channels, 16 points, 8 kept, 192 columns 35.6, 28.6 (70, 56); 12 ->
+// 12, 12 points, 2 kept, 240 columns 42, 35 (87, 70); batch 4, 16 -> 16, 9 points, 336 columns 58, 49 (123, 108); 8 -> 16,
+// 34 points, 10 kept, 320 columns (4512 multiply-adds) 53, 52 (111, 103); but batch 2, 32 -> 32, 20 points, 8 kept, 144
+// columns (6016, in the adjoint 12032) 78, 82 (163, 176); 16 -> 16, 19 points, 1296 columns (394 thousand values) 67, 66
+// (135, 134).  The mix alone, one entry: 32 -> 32, 12 points, 11 kept, 105 columns (11264 products beside 4768 multiply-
+// adds; 9.5 MB) 45, 57 (adjoint 54, 71); weights alone, batch 3: 24 -> 24, 6 points, 5 kept, 845 columns (20 MB) 64, 85.
+// An adjoint's block works all entries in turn: batch 4, 2 -> 2 channels, 52 points (208 of the field in a chain) 57, 65;
+// about 96 in a chain are as fast either way.  Over 17 thousand random layers that the sums and values alone would let in,
+// 4.4 % of the forwards and 2.8 % of the adjoints were more than 3 % slower in one launch, 0.9 and 0.5 % are with the
+// whole rule.
+//
+// The forward's choice is the same for one to four entries of as many channels out as in, each of which has blocks of its
+// own; else the result has no place for several entries.
 bool xmix_fits(int B, int Ci, int Co, AxisPlan ax, int64_t inner, bool adjoint) {
+  const int from = adjoint ? Co : Ci, to = adjoint ? Ci : Co, most = Ci > Co ? Ci : Co;
   const int64_t K1 = 1 + (ax.npos - 1 > ax.L - ax.npos ? ax.npos - 1 : ax.L - ax.npos);
-  const int64_t sums = Ci * K1 * ax.N + Co * (int64_t)(ax.N / 2 + 1) * ax.L;
-  if (B > 4 || sums > 5000 || inner > 150000 || (int64_t)(Ci > Co ? Ci : Co) * ax.N * inner > 150000) return false;
-  if (adjoint && (B * sums > 5000 || (int64_t)B * (Ci > Co ? Ci : Co) * ax.N * inner > 300000)) return false;
+  const int64_t sums = from * K1 * ax.N + to * (int64_t)(ax.N / 2 + 1) * ax.L, mix = (int64_t)Ci * Co * ax.L;
+  if (B > 4 || sums > 5000 || 4 * sums + 3 * mix > 28000) return false;
+  if (inner > 150000 || most * ax.N * inner > 150000 || mix * inner > (adjoint ? 1500000 : 1000000)) return false;
+  if (adjoint && (B * sums > 5000 || B * most * ax.N * inner > 300000 || (B > 1 && B * ax.N > 96))) return false;
   if (!adjoint && B > 1 && Ci != Co) return false;
   int s;
-  return adjoint ? xmix_geometry(B, Co, Ci, ax, inner, &s) : xmix_geometry(1, Ci, Co, ax, inner, &s);
+  return xmix_geometry(adjoint ? B : 1, from, to, ax, inner, &s);
 }
 
 namespace {

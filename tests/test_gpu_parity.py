@@ -1182,6 +1182,10 @@ def test_fft_axis_kernels_match_oracle(case):
     (2, 12, 16, (30, 9, 8, 6), (7, 2, 2, 3), 0),
     (3, 6, 6, (32, 9, 8, 6), (8, 2, 2, 3), 0),
     (5, 2, 3, (9, 6, 5, 6), (2, 2, 2, 3), 1),
+    # past it by the products of the mix alone, by the weights' size, and (adjoint) by the points of all entries
+    (1, 32, 32, (11, 5, 4, 4), (5, 1, 1, 2), 1),
+    (1, 28, 28, (6, 24, 16, 8), (2, 6, 4, 4), 1),
+    (3, 2, 2, (33, 6, 5, 6), (2, 2, 1, 3), 0),
 ])
 def test_x_stages_and_mode_mix_of_small_layers(case):
     test_spectral_conv_fwd_matches_oracle(case)
