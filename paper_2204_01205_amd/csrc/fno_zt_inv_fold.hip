@@ -552,8 +552,11 @@ FoldInvLoad zt_inv_fold_load(AxisPlan az, int Nt, int mt, int Co, int Cu) {
   size_t lds;
   if (!fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds)) return {0, 0};
   const int waves = fold_inv_waves(fold_inv_run(Nt, f.tt), fold_inv_bucket(Cu)), room = (int)((size_t)160 * 1024 / lds);
-  const int wc = 1 << f.wc_shift;
-  return {(room < waves ? room : waves) * (4 / wc) * (f.ntask < wc ? f.ntask : wc),
+  // A block's short last tile over both tiles of t counts as two tasks, which it is with u for both.  us, 4096 columns of 16 x
+  // 24, 24 channels with the linear term, 5 kept, 12 bins: per tile 235, folded 167; 16 x 22, 12 channels, 8 kept, 11 bins
+  // 115 and 79; but convolutions, 20 channels, 16 x 22, 9 and 11 bins, 79 and 84 per tile, 108 and 123 folded.
+  const int wc = 1 << f.wc_shift, tasks = f.ntask + (f.two_t && Cu > 0 ? f.half_last : 0);
+  return {(room < waves ? room : waves) * (4 / wc) * (tasks < wc ? tasks : wc),
           (2 * mt + 2) / 4 * (2 * f.ks + 8) * f.nchunk};
 }
 
