@@ -521,8 +521,10 @@ bool fold_inv_geometry(AxisPlan az, int Nt, int mt, int Co, int Cu, FoldInv* out
   const int CT = (Co + 3) / 4;
   // Waves per column: two tasks each, so that the second one's u values load under the first (64 x 20, one block
   // forward and back: 0.71 ms with one task per wave, 0.68 with two); more waves when the columns of a block then
-  // fit the LDS share of its resident waves; then fewer output channels per block.
-  const int wc0 = f.ntask >= 8 ? 2 : (f.ntask >= 4 ? 1 : 0);
+  // fit the LDS share of its resident waves; then fewer output channels per block.  A short last tile over both tiles of t
+  // counts as two (us, 20 channels with the linear term, 220 columns of 40 x 18: its three tasks on one wave 58, on two 41;
+  // up to 2400 columns of 33 to 48 points of z 3 to 19 % faster on two, from 2500 on 1 % slower).
+  const int tasks = f.ntask + (f.two_t ? f.half_last : 0), wc0 = tasks >= 8 ? 2 : (tasks >= 4 ? 1 : 0);
   for (int nchunk = 1; nchunk <= CT; ++nchunk) {
     f.ct = (CT + nchunk - 1) / nchunk;
     f.nchunk = (CT + f.ct - 1) / f.ct;
