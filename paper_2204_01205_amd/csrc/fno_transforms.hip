@@ -612,8 +612,9 @@ __global__ __launch_bounds__(kThreads) void axis_inv_kernel(
   }
   __syncthreads();
   auto transform = [&](const float2* twiddles) {
-    // bin m takes the frequencies k = m modulo M; the reads of G bins (or of G terms of a bin) go out together
-    constexpr int G = M == 8 || M == 16 ? 8 : 4;
+    // bin m takes the frequencies k = m modulo M; the reads of G bins (or of G terms of a bin) go out together, bins that no
+    // frequency falls into among them (of 16 bins eight at a time were up to 4 % slower in the mean, where few frequencies are kept)
+    constexpr int G = 4;
     for (int idx = tid; idx < P * W; idx += nthr) {
       const int col = idx & (W - 1), n2 = idx >> wshift;
       if (col < wc) {
@@ -642,6 +643,12 @@ __global__ __launch_bounds__(kThreads) void axis_inv_kernel(
               for (int u = 0; u < G; ++u)
                 if (k0 + ((m0 + u - kmin) & (M - 1)) <= kmax) g[m0 + u] = cfmac(y[u], w[u], g[m0 + u]);
             }
+          }
+        } else if (L <= M) {                     // a term a bin: nothing to read together
+#pragma unroll
+          for (int m = 0; m < M; ++m) {
+            const int k = kmin + ((m - kmin) & (M - 1));
+            if (k <= kmax) g[m] = cfmac(yc[entry(k) << wshift], wc2[entry(k) * P], g[m]);
           }
         } else {
 #pragma unroll
@@ -946,14 +953,18 @@ hipError_t launch_axis_fwd(const float2* in, float2* out, const float2* tw, int6
 hipError_t launch_axis_inv(const float2* in, float2* out, const float2* tw, int64_t outer,
                            AxisPlan ax, int64_t inner, hipStream_t s) {
   if (outer <= 0 || inner <= 0) return hipSuccess;
-  // Rows of the output that do not start on 64 bytes: column tiles meet in the middle of lines, which must come together
-  // in one L2 before they are written.  Adjacent tiles go to one XCD, wide ones if they are many, through plain stores.
-  // us, y axis of 64 points with 361 columns, of 24 with 561, of 128 with 91: 157, 208, 27 streamed by tiles of 32, 79,
-  // 146, 24 so; but 128 points with 216 columns (whole 64 bytes) 124 and 146.  Else 32 columns: 16 and 64 are slower.
-  const bool split = inner % 8 != 0;
+  // Rows of the output that are not whole lines of 128 bytes: column tiles meet in the middle of lines, which must come
+  // together in one L2 before they are written, so adjacent tiles go to one XCD; where rows are not even whole 64 bytes also
+  // through plain stores, and by wide tiles if they are many.  Only outputs that outgrow the L2s (32 MB together): smaller
+  // ones are merged there however they come.  us, y axis of 64 points with 361 columns, of 24 with 561: 157 and 208 streamed
+  // by tiles of 32, 79 and 146 so; 128 points with 216 columns (13.5 lines) 125 and 121; but 256 points with 288 (18 lines)
+  // 626 and 646, and 16 points with 26 columns (13 MB) 10.3 and 13.8.  Over 16 thousand outputs of up to 200 MB whose rows
+  // are not whole 64 bytes it was up to 4 % slower in the mean below 32 MB, 5 to 14 % faster above.  Else 32 columns: 16
+  // and 64 are slower.
+  const bool big = outer * ax.N * inner * 8 >= (int64_t)32 << 20, split = big && inner % 8 != 0, near = big && inner % 16 != 0;
   const int W = axis_cols(ax, inner, ax.L, split && outer * ((inner + 63) / 64) >= 2048 ? 64 : 32);
   const int64_t ncb = (inner + W - 1) / W;
-  const int64_t nblk = split ? (outer * ncb + 7) / 8 * 8 : outer * ncb;
+  const int64_t nblk = near ? (outer * ncb + 7) / 8 * 8 : outer * ncb;
   if (nblk > 0x7fffffffLL || ncb > 0x7fffffffLL) return hipErrorInvalidValue;
   const int tw_lds = (size_t)ax.L * ax.P * 8 <= (size_t)(8 * 1024);
   const size_t lds = (size_t)ax.L * W * 8 + (tw_lds ? (size_t)ax.L * ax.P * 8 : 0);
@@ -962,11 +973,11 @@ hipError_t launch_axis_inv(const float2* in, float2* out, const float2* tw, int6
   if (!split && outer * ax.N * inner * 8 >= kStreamBytes) {
     FNO_DISPATCH_M(ax.M, hipLaunchKernelGGL((axis_inv_kernel<MM, true>), dim3((unsigned)nblk),
                                             dim3(thr), lds, s, in, out, tw, ax.N, ax.L, ax.npos,
-                                            (long long)inner, ilog2(W), (int)ncb, tw_lds, (long long)outer, split ? 1 : 0));
+                                            (long long)inner, ilog2(W), (int)ncb, tw_lds, (long long)outer, near ? 1 : 0));
   } else {
     FNO_DISPATCH_M(ax.M, hipLaunchKernelGGL((axis_inv_kernel<MM, false>), dim3((unsigned)nblk),
                                             dim3(thr), lds, s, in, out, tw, ax.N, ax.L, ax.npos,
-                                            (long long)inner, ilog2(W), (int)ncb, tw_lds, (long long)outer, split ? 1 : 0));
+                                            (long long)inner, ilog2(W), (int)ncb, tw_lds, (long long)outer, near ? 1 : 0));
   }
   return hipGetLastError();
 }
