@@ -32,9 +32,10 @@
 // A tile's rows become sums and differences before the next tile is asked for, and those are made behind the stores of the
 // plane before, whose number does not vary: the loads of a tile are on their way over the products of the one before it,
 // and no wait is for stores.  (Left alone, the compiler put the sums behind the next loads, and a wave waited for these
-// first.)  The t table of a wave is asked for in one go, its first tile before the tables.  us, before and after: 50 x 45
-// columns of 40 x 24, 32 channels, 105 -> 88; 64 x 20, 20 channels, 4096 columns 127 -> 122; 21 x 14, 24 fields of 810
-// columns 22 -> 19; 263 x 16 690 and 692.
+// first.)  us, before and after: 50 x 45 columns of 40 x 24, 32 channels, 95 -> 80; 21 x 14, 24 fields of 810 columns 19 ->
+// 17; 64 x 20, 20 channels, 4096 columns 123 and 122; 263 x 16 666 and 678.  Planes that share a tile have many stores
+// without a lane to store, which are left out there; a wave's first tile is asked for behind its tables, since the waits
+// for these would be for the tile as well.  (8 x 40, 16 bins, 3726 planes 9.9 us, 11.5 in the order before all of this.)
 //
 // What bounds it: in fp32 the matrix cores at 32 cycles per instruction (a 263 x 16 plane with 49 frequencies and
 // 8 bins: 9 tiles of 8 + 16 instructions) next to one read of the field (20 channels, 68 x 118 columns: 0.85 ms); in parts
@@ -158,8 +159,6 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
 #pragma unroll
     for (int u = 0; u < W; ++u) { va[4 * J + u] = qa[u]; vb[4 * J + u] = qb[u]; }
   };
-  const bool any = p < pe;
-  load_tile(any ? p : 0, 0, any);                // on its way while the tables are made
   {
     const float4* cs = reinterpret_cast<const float4*>(ztab + (long long)m0 * stride);
     const float4* sn = reinterpret_cast<const float4*>(ztab + (long long)(mrows + m0) * stride);
@@ -194,14 +193,13 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const int col = c0 + 16 * ct + c, kt = col >> 1;
-    // all of them asked for before the first is looked at
     const float* part = reinterpret_cast<const float*>(twt + min(kt, mt - 1) * Nt) + (col & 1);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) tb[ct][s] = part[2 * (s < 4 * J ? 16 * (s >> 2) + 4 * g + (s & 3) : 16 * J + t0 + (s - 4 * J))];
-#pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const bool dup = s >= 4 * J && t0 + (s - 4 * J) < W * g;
-      tb[ct][s] = kt < mt && !dup ? tb[ct][s] : 0.f;
+      const int t = s < 4 * J ? 16 * (s >> 2) + 4 * g + (s & 3) : 16 * J + t0 + (s - 4 * J);
+      const bool dup = s >= 4 * J && t < 16 * J + W * g;
+      tb[ct][s] = 0.f;
+      if (kt < mt && !dup) tb[ct][s] = part[2 * t];
     }
   }
   // the same in parts: KS <= 4 third, first and second part of four values; else eight values a part
@@ -234,7 +232,8 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
   }
   const double sgn = (c & 1) ? -1.0 : 1.0;
   __syncthreads();
-  if (!any) return;
+  if (p >= pe) return;
+  load_tile(p, 0, true);                        // (behind the tables, whose waits would be for it too)
 
   int at_field = SPLIT > 0 ? (int)(p % field) : 0;         // of the plane in its (batch, channel) field
   const int step_field = SPLIT > 0 ? (int)(nwl % field) : 0;
@@ -402,6 +401,8 @@ __global__ __launch_bounds__(SPLIT > 1 ? 2 * kThreads : kThreads, fold_waves(4 *
       for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
+          // no lane has a frequency (with one plane a tile, whose wait for the next loads counts the stores, these stay)
+          if (PP > 1 && m0 + 16 * m + v >= npos && m0 + 16 * m + v > Lz - npos) continue;
           const int kl = 16 * m + g4 + v, k = m0 + kl;
           double2 w = ROT[kl];
           if (turned) w = make_double2(-w.x, -w.y);
