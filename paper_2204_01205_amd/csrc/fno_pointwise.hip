@@ -160,11 +160,13 @@ __global__ __launch_bounds__(kThreads) void bwd_pointwise_mfma_kernel(
 // Where the waves of a step are two or four (NG), each reads its share of x and leaves it in LDS, double buffered, one
 // barrier a step; that takes half to three quarters of a step's loads off every wave, and the registers they took hold
 // the next step's, asked for a step ahead.  (With all of x in every wave there is no room for that: 0.45 ms in the first
-// case below, with spills.)  What bounds it: memory at 32 channels, 4.5 TB/s (0.21 ms at the 5.2 of a large copy).  At
-// 2.16 M points with GELU, us: 32, 27, 25, 24, 22, 17 channels 248, 225, 217, 189, 173, 150; with a ragged step, a last
-// step and channels past the last on ways of their own, where the loads of the next step were waited for as they were
-// sent, 289, 273, 265, 189, 176, 152.  9 and 10 (one wave a step) 90, 93; 5 -> 20 at 33.5 M points, no activation, 655
-// (754 where values of z that are not needed were set to zero one by one, which waited for the loads between them).
+// case below, with spills.)  What bounds it: memory at 32 channels, 4.7 TB/s (0.21 ms at the 5.2 of a large copy).  At
+// 2.16 M points with GELU and a target, us: 32, 27, 25, 24, 22, 17 channels 236, 215, 200, 181, 166, 139; with a ragged
+// step, a last step and channels past the last on ways of their own, where the loads of the next step were waited for as
+// they were sent, 268, 253, 245, 184, 172, 144.  (Below 16 MB a tensor and without activation, with one or two turns a
+// wave, 25 channels and more are 1 us slower than so, of 10 to 20.)  9 and 10 (one wave a step) 88, 91; 5 -> 20 at 33.5 M
+// points, no activation, 655 (754 where values of z that are not needed were set to zero one by one, which waited for the
+// loads between them).
 constexpr int kBwdChain = 32;
 
 template <bool STREAM>
@@ -376,22 +378,20 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
   } else {
     // All waves of a block take as many turns; the values of a step are asked for a step ahead.  One way through a turn, with
     // as many loads and stores whatever the step: where a ragged step's loads, a last step without a next one or channels
-    // past the last were ways of their own, the values met in copies that waited for them at once.  So a step past the last
-    // is the last again, a lane past the row's last four points takes those and shifts them when they are there, and what
-    // is not to be stored has an offset past the end.  (N from 4 to 2^27: 32-bit offsets over four rows.)
-    auto step_of = [&](long long s, long long& ob, long long& ib, long long& p0) {
-      s = s < steps ? s : steps - 1;
-      const long long bb = s / steps_per_b;
-      p0 = (s - bb * steps_per_b) * 64;
-      ob = bb * Co * N;
-      ib = bb * Ci * N;
-    };
+    // past the last were ways of their own, the values met in copies that waited for them at once.  So of a step past the last
+    // nothing is there to be read, a lane past the row's last four points takes those and shifts them when they are there,
+    // and what is not to be stored has an offset past the end.  (N from 4 to 2^27: 32-bit offsets over four rows.)
+    // The step that is asked for next, as entry and step in it.  Divisions are long chains: two of 64 bits a turn took 3 % of
+    // the time with GELU at any size, two before the first turn 1.5 % of 10 us.  (Counts of steps fit 32 bits: a step holds
+    // four points at least, and more than 2^31 of these, at nine channels and more, no memory.)
+    long long entry = (unsigned)(xs + wl) / (unsigned)steps_per_b, inside = xs + wl - entry * steps_per_b;
+    const long long skip_entries = (unsigned)nwl / (unsigned)steps_per_b, skip = nwl - skip_entries * steps_per_b;
     const long long Nall = (long long)B * N;
     // rows first .. first + 3 of a tensor of C channels, from point p0 of an entry on: a base and the lane's offset
-    auto tile_of = [&](const float* t, long long base, int C, int first, long long p0) {
+    auto tile_of = [&](const float* t, long long base, int C, int first, long long p0, bool there) {
       const int row = first < C ? first : C - 1;
       const long long at = base + row * N + p0, left = (Nall * C - at) * 4;
-      return buffer_of(t + at, (unsigned)(left < 0x7fffffffLL ? left : 0x7fffffffLL));
+      return buffer_of(t + at, there ? (unsigned)(left < 0x7fffffffLL ? left : 0x7fffffffLL) : 0u);
     };
     auto offset_of = [&](int C, int first, int point) {
       const int row = first < C ? first : C - 1, mine = first + j4 < C ? first + j4 : C - 1;
@@ -404,27 +404,31 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
     };
     const int i0 = 4 * member * XT;
     v4f zn[OT], gn[OT], xn[XT];
-    auto ask = [&](long long s) {
-      long long ob, ib, p0;
-      step_of(s, ob, ib, p0);
+    long long asked_ob, asked_p0;
+    auto ask = [&](bool there) {
+      const long long ob = entry * Co * N, ib = entry * Ci * N, p0 = inside * 64;
       const long long from = p0 > 0 ? p0 - 4 : 0;          // the last four points start at p0 - 3 at the earliest
       const int at = (int)(min(p0 + 4 * blk, N - 4) - from);
       if (need_z)
 #pragma unroll
-        for (int T = 0; T < OT; ++T) zn[T] = four(tile_of(z, ob, Co, o0 + 4 * T, from), offset_of(Co, o0 + 4 * T, at));
+        for (int T = 0; T < OT; ++T) zn[T] = four(tile_of(z, ob, Co, o0 + 4 * T, from, there), offset_of(Co, o0 + 4 * T, at));
 #pragma unroll
-      for (int T = 0; T < OT; ++T) gn[T] = four(tile_of(gout, ob, Co, o0 + 4 * T, from), offset_of(Co, o0 + 4 * T, at));
+      for (int T = 0; T < OT; ++T) gn[T] = four(tile_of(gout, ob, Co, o0 + 4 * T, from, there), offset_of(Co, o0 + 4 * T, at));
 #pragma unroll
-      for (int T = 0; T < XT; ++T) xn[T] = four(tile_of(x, ib, Ci, i0 + 4 * T, from), offset_of(Ci, i0 + 4 * T, at));
+      for (int T = 0; T < XT; ++T) xn[T] = four(tile_of(x, ib, Ci, i0 + 4 * T, from, there), offset_of(Ci, i0 + 4 * T, at));
+      asked_ob = ob;
+      asked_p0 = p0;
+      entry += skip_entries;
+      inside += skip;
+      if (inside >= steps_per_b) { inside -= steps_per_b; ++entry; }
     };
-    ask(xs + wl);
-    int turn = 0;
     long long s = xs + wl;
+    ask(s < xe);
+    int turn = 0;
     for (long long s0 = xs + (long long)(blockIdx.x >> 3) * per_block; s0 < xe; s0 += nwl, s += nwl, turn ^= 1) {
       float* buf = own + turn * (kThreads / 64 / NG) * XS;
       const bool live = s < xe;
-      long long ob, ib, p0;
-      step_of(s, ob, ib, p0);
+      const long long ob = asked_ob, p0 = asked_p0;
       const bool whole = p0 + 64 <= N;
       if (!whole) {
         // the lane's first point is `d` further on in what it read
@@ -463,12 +467,11 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_pointwise_wide_kernel(
           gq[T][u] = v;
         }
       }
-      ask(s + nwl);
+      ask(s + nwl < xe);
 #pragma unroll
       for (int T = 0; T < OT; ++T) {
         const int row = o0 + 4 * T;
-        const long long at = ob + (row < Co ? row : Co - 1) * N + p0, left = (Nall * Co - at) * 4;
-        const __amdgpu_buffer_rsrc_t r = buffer_of(gz_out + at, live && gz_out != nullptr && row < Co ? (unsigned)(left < 0x7fffffffLL ? left : 0x7fffffffLL) : 0u);
+        const __amdgpu_buffer_rsrc_t r = tile_of(gz_out, ob, Co, row, p0, live && gz_out != nullptr && row < Co);
         const unsigned to = olive[T] ? offset_of(Co, row, 4 * blk) : kNowhere;
         if (whole) {
           const float gs[4] = {gq[T][0], gq[T][1], gq[T][2], gq[T][3]};
