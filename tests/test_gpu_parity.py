@@ -1273,6 +1273,32 @@ def test_sums_over_points_of_a_short_last_step(c_in, c_out):
         test_sums_over_points_of_every_tile_shape(c_in, c_out, npts, 2)
 
 
+@pytest.mark.parametrize("npts", [2 ** 27, 2 ** 27 + 1])
+@pytest.mark.parametrize("c_in, c_out", [(9, 13), (9, 25)])
+def test_sums_over_points_of_the_longest_entries(c_in, c_out, npts):
+    """The most points that four rows of a tensor may have for 32-bit offsets (two and four waves a step), and one more (every
+    wave reads all of x, at 64-bit addresses), against float64 sums made piece by piece on the device."""
+    gen = torch.Generator(device="cuda").manual_seed(c_out)
+    x = torch.randn((1, c_in, npts), device="cuda", generator=gen)
+    g = torch.randn((1, c_out, npts), device="cuda", generator=gen)
+    gW, gb = torch.empty((c_out, c_in), device="cuda"), torch.empty(c_out, device="cuda")
+    ws = torch.empty(B.fno_pointwise_bwd_workspace_bytes(c_in, 0, c_out) // 4 + 2, device="cuda")
+    B.fno_pointwise_linear_bwd(1, c_in, c_out, npts, x, torch.ones_like(gW), g, None, gW, gb, ws)
+    want, sq, wantb, sqb = (torch.zeros(*shape, device="cuda", dtype=torch.float64)
+                            for shape in ((c_out, c_in), (c_out, c_in), (c_out,), (c_out,)))
+    for p in range(0, npts, 2 ** 22):
+        gd, xd = g[0, :, p:p + 2 ** 22].double(), x[0, :, p:p + 2 ** 22].double()
+        for i in range(c_in):
+            term = gd * xd[i]
+            want[:, i] += term.sum(1)
+            sq[:, i] += term.square_().sum(1)
+        wantb += gd.sum(1)
+        sqb += gd.square().sum(1)
+    # as above: an entry is off by a few 2^-24 of its terms' root sum square
+    assert float(((gW - want).abs() / torch.maximum(sq.sqrt(), want.abs())).max()) <= TOL
+    assert float(((gb - wantb).abs() / torch.maximum(sqb.sqrt(), wantb.abs())).max()) <= TOL
+
+
 @pytest.mark.parametrize("case", [
     (2, 32, 32, (3, 3, 9, 5), (1, 1, 2, 2), 0),        # 405 points: 5 lanes of four and a point in the last step
     (2, 27, 27, (3, 3, 5, 3), (1, 1, 1, 1), 0),        # 135: a lane and 3 points, a ragged channel tile
