@@ -1132,6 +1132,19 @@ def test_forward_transform_of_long_z_axes(c, nz, mz, nt, mt):
     assert rel(xh, xho) <= TOL and rel(y, yo) <= TOL
 
 
+@pytest.mark.parametrize("nz, mz, nt, mt", [
+    (16, 3, 16, 9), (128, 20, 16, 9), (64, 12, 32, 17), (8, 2, 64, 33), (32, 5, 64, 33), (64, 9, 30, 16),      # every bin of t
+    (64, 12, 32, 9), (64, 30, 64, 12), (64, 9, 30, 15), (128, 16, 32, 8), (128, 3, 64, 10), (128, 20, 30, 7),  # 4 and 8 residues
+    (256, 20, 16, 5), (64, 32, 16, 8), (128, 1, 16, 3), (32, 4, 32, 5),                                        # any count of them
+])
+def test_forward_transform_of_whole_rows(nz, mz, nt, mt):
+    """The kernel with a row per thread; 15 planes: blocks of several have one left over."""
+    L = Layer(1, 1, 1, (5, 3, nz, nt), (2, 1, mz, mt))
+    y, xh = gpu_spectral_fwd(L)
+    yo, xho = O.spectral_conv_fwd(L.x, L.R, L.spec, return_xhat=True)
+    assert rel(xh, xho) <= TOL and rel(y, yo) <= TOL
+
+
 @pytest.mark.parametrize("nz, mz, nt, mt", [(12, 2, 4, 2), (20, 4, 5, 2), (8, 2, 6, 3), (24, 4, 7, 3), (16, 3, 8, 3),
                                             (32, 5, 5, 2), (10, 3, 5, 2)])
 @pytest.mark.parametrize("nx, ny", [(63, 61), (24, 32)])
