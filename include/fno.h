@@ -109,7 +109,14 @@ int fno_plan_tables(const fno_desc* desc, int op, void* ws, size_t ws_bytes, voi
  * out_k (host, nullable) receives *out_n values; out_n (host) receives the count. */
 int fno_mode_indices(const fno_desc* desc, int axis, int32_t* out_k, int32_t* out_n);
 
-/* Spectral convolution, eq. (3):  y = K(phi) x.
+/* What the bits of a result depend on.  A call repeated with the same descriptor, values and alignment gives the same
+ * bits.  An entry of a batch may differ in its last bits from the same entry in a batch of another size: kernels are
+ * chosen by sizes, the batch among them (the (z,t) stages by their number of columns; small layers take the x stages and
+ * the mode mix in one launch, whose sums are in double, up to four entries, or to one where c_in != c_out, and their
+ * adjoint as long as all entries together are small).  The spectrum that an adjoint works out again from x has the bits
+ * that the forward call saves with the same descriptor.
+ *
+ * Spectral convolution, eq. (3):  y = K(phi) x.
  *   x         in   float  [B][Cin][Nx][Ny][Nz][Nt]
  *   R         in   cfloat [Cin][Cout][Lx][Ly][Lz][mt]
  *   y         out  float  [B][Cout][Nx][Ny][Nz][Nt]
@@ -246,7 +253,10 @@ int fno_spectral_conv_fwd_static(const fno_desc* desc, const float* x, const flo
  * for every stage, 0 to switch timing off: an event pair costs a few microseconds of idle time
  * between kernels, so a caller that times a whole step and wants one kernel's duration from the
  * same run enables that stage alone.  fno_timing_read waits for the recorded events, returns up to `capacity` records in
- * launch order (stage id FNO_STAGE_*, elapsed milliseconds; host arrays) and clears the log.
+ * launch order (stage id FNO_STAGE_*, elapsed milliseconds; host arrays) and clears the log.  Small layers run the
+ * x stage, the mode mix and the x stage back as one launch, recorded under FNO_STAGE_MIX or FNO_STAGE_MIX_BWD: these
+ * stages then hold the x transforms, and no record has an x stage's id (but for an adjoint that works the spectrum of x
+ * out again: its x stage keeps FNO_STAGE_X_FWD).
  * This log is the library's only process-wide state and is not thread-safe; leave it disabled
  * under graph capture.  At most 8192 records are kept between reads. */
 enum {

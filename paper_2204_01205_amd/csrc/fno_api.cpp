@@ -215,7 +215,8 @@ void timing_end(hipStream_t s) {
 template <class T> T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws) + off); }
 
 // The twiddle tables depend on the descriptor only (grid, kept modes, mode rule).  tables_ready: the
-// caller states that fno_plan_tables wrote them into this workspace and nothing overwrote them.
+// caller states that fno_plan_tables wrote them into this workspace and nothing overwrote them.  (The x tables are made for
+// small layers too, whose one launch reads none: the same tables may serve another batch, which is not one.)
 int build_tables(const Plan& p, void* ws, hipStream_t s, bool tables_ready = false) {
   if (tables_ready) return FNO_OK;
   fno::TableSet ts{};
