@@ -511,8 +511,9 @@ __global__ __launch_bounds__(kThreads, fold_inv_waves(W, CI)) void zt_inv_fold_k
 int fold_inv_bucket(int Cu) { return Cu <= 0 ? 0 : (Cu <= 8 ? 8 : (Cu <= 20 ? (Cu + 3) / 4 * 4 : (Cu <= 24 ? 24 : 32))); }
 int fold_inv_run(int Nt, int tt) { return (Nt + 4 * tt - 1) / (4 * tt); }      // points of t per lane
 
-// everything but the number of columns; false where no split fits the LDS
-bool fold_inv_geometry(AxisPlan az, int Nt, int mt, int Co, int Cu, FoldInv* out, size_t* lds) {
+// everything but the number of columns, which only has a say in how many waves share one (0: any); false where no split
+// fits the LDS
+bool fold_inv_geometry(AxisPlan az, int Nt, int mt, int Co, int Cu, int64_t ncols, FoldInv* out, size_t* lds) {
   if (Co > kMaxCo || Cu > 32 || (int64_t)az.N * Nt > (1 << 28) || !tz_fwd_fold_fits(az, Nt, mt)) return false;
   const FoldPlan fp = fold_plan(az);
   FoldInv f{};
@@ -535,8 +536,13 @@ bool fold_inv_geometry(AxisPlan az, int Nt, int mt, int Co, int Cu, FoldInv* out
   // forward and back: 0.71 ms with one task per wave, 0.68 with two); more waves when the columns of a block then
   // fit the LDS share of its resident waves; then fewer output channels per block.  A short last tile over both tiles of t
   // counts as two (us, 20 channels with the linear term, 220 columns of 40 x 18: its three tasks on one wave 58, on two 41;
-  // up to 2400 columns of 33 to 48 points of z 3 to 19 % faster on two, from 2500 on 1 % slower).
-  const int tasks = f.ntask + (f.two_t ? f.half_last : 0), wc0 = tasks >= 8 ? 2 : (tasks >= 4 ? 1 : 0);
+  // up to 2400 columns of 33 to 48 points of z 3 to 19 % faster on two, from 2500 on 1 % slower), but not where three tasks on
+  // one wave a column fill the chip once and twice the waves would come to little less than two rounds (us on one and on two,
+  // 16 channels, 40 x 20: 1280 columns 66 and 63, 1664 67 and 77, 2000 75 and 81, 2208 past one round 108 and 101).
+  const auto share = [](int tasks) { return tasks >= 8 ? 2 : (tasks >= 4 ? 1 : 0); };
+  const int64_t room = (int64_t)256 * 4 * fold_inv_waves(W, CI);
+  const bool once = f.ntask == 3 && ncols <= room && 4 * ncols > 3 * room;
+  const int wc0 = share(f.ntask + (f.two_t && !once ? f.half_last : 0));
   for (int nchunk = 1; nchunk <= CT; ++nchunk) {
     f.ct = (CT + nchunk - 1) / nchunk;
     f.nchunk = (CT + f.ct - 1) / f.ct;
@@ -558,13 +564,13 @@ bool fold_inv_geometry(AxisPlan az, int Nt, int mt, int Co, int Cu, FoldInv* out
 bool zt_inv_fold_fits(AxisPlan az, int Nt, int mt, int Co, int Cu) {
   FoldInv f;
   size_t lds;
-  return fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds);
+  return fold_inv_geometry(az, Nt, mt, Co, Cu, 0, &f, &lds);
 }
 
 FoldInvLoad zt_inv_fold_load(AxisPlan az, int Nt, int mt, int Co, int Cu) {
   FoldInv f;
   size_t lds;
-  if (!fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds)) return {0, 0};
+  if (!fold_inv_geometry(az, Nt, mt, Co, Cu, 0, &f, &lds)) return {0, 0};
   const int waves = fold_inv_waves(fold_inv_run(Nt, f.tt), fold_inv_bucket(Cu)), room = (int)((size_t)160 * 1024 / lds);
   // A block's short last tile over both tiles of t counts as two tasks, which it is with u for both.  us, 4096 columns of 16 x
   // 24, 24 channels with the linear term, 5 kept, 12 bins: per tile 235, folded 167; 16 x 22, 12 channels, 8 kept, 11 bins
@@ -579,7 +585,7 @@ hipError_t launch_zt_inv_fold(const float2* a, float* out, const float2* twt, co
   FoldInv f{};
   size_t lds = 0;
   const int Cu = e.u != nullptr ? e.Cu : 0;
-  if (!fold_inv_geometry(az, Nt, mt, Co, Cu, &f, &lds)) return hipErrorInvalidValue;
+  if (!fold_inv_geometry(az, Nt, mt, Co, Cu, ncols, &f, &lds)) return hipErrorInvalidValue;
   f.ncols = ncols; f.NxNy = NxNy; f.Npts = (int64_t)NxNy * az.N * Nt;
   const int W = fold_inv_run(Nt, f.tt), CI = fold_inv_bucket(Cu);
   const int cb = 4 >> f.wc_shift;
