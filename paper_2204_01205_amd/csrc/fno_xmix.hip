@@ -230,17 +230,19 @@ bool xmix_geometry(int B, int from, int to, AxisPlan ax, int64_t inner, int* wsh
 
 // Where one launch is faster than three: as long as the chip is far from full (values of the pruned field), a block's own
 // work is no longer than the launches saved, and the weights, which every batch entry's blocks read in runs of one tile,
-// are few.  The work per column: multiply-adds of the sums (`sums`) and products of the mix.  us, three launches and one,
+// are few.  The work per column: multiply-adds of the sums, over all entries in an adjoint, and products of the mix, which
+// weigh three quarters of one.  us, three launches and one,
 // forward and (in brackets) forward and adjoint: 8 -> 8 channels, 16 points, 8 kept, 192 columns 35.6, 28.6 (70, 56); 12 ->
 // 12, 12 points, 2 kept, 240 columns 42, 35 (87, 70); batch 4, 16 -> 16, 9 points, 336 columns 58, 49 (123, 108); 8 -> 16,
-// 34 points, 10 kept, 320 columns (4512 multiply-adds) 53, 52 (111, 103); but batch 2, 32 -> 32, 20 points, 8 kept, 144
-// columns (6016, in the adjoint 12032) 78, 82 (163, 176); 16 -> 16, 19 points, 1296 columns (394 thousand values) 67, 66
-// (135, 134).  The mix alone, one entry: 32 -> 32, 12 points, 11 kept, 105 columns (11264 products beside 4768 multiply-
-// adds; 9.5 MB) 45, 57 (adjoint 54, 71); weights alone, batch 3: 24 -> 24, 6 points, 5 kept, 845 columns (20 MB) 64, 85.
-// An adjoint's block works all entries in turn: batch 4, 2 -> 2 channels, 52 points (208 of the field in a chain) 57, 65;
-// about 96 in a chain are as fast either way.  Over 17 thousand random layers that the sums and values alone would let in,
-// 4.4 % of the forwards and 2.8 % of the adjoints were more than 3 % slower in one launch, 0.9 and 0.5 % are with the
-// whole rule.
+// 34 points, 10 kept, 320 columns (4512 multiply-adds) 53, 52 (111, 103); 20 -> 10, 36 points, 8 kept, 16 columns (in the
+// adjoint 5120) forward and adjoint 80, 73; 29 -> 29, 16 points, 7 kept, batch 4 (3683 and 5887 products) 74, 66; but
+// batch 2, 32 -> 32, 20 points, 8 kept, 144 columns (6016 and 8192, in the adjoint 12032) 78, 82 (163, 176); 16 -> 16, 19
+// points, 1296 columns (394 thousand values) 67, 66 (135, 134).  The mix alone, one entry: 32 -> 32, 12 points, 11 kept, 105
+// columns (11264 products beside 4768 multiply-adds; 9.5 MB) 45, 57 (adjoint 54, 71); weights alone, batch 3: 24 -> 24, 6
+// points, 5 kept, 845 columns (20 MB) 64, 85.  An adjoint's block works all entries in turn: batch 4, 2 -> 2 channels, 52
+// points (208 of the field in a chain) 57, 65; about 96 in a chain are as fast either way.  Over 7500 random forwards and
+// 8700 adjoints of 2 to 32 channels, 6 to 72 points and up to 8 thousand columns, 0.2 and 0.7 % are more than 3 % slower in
+// one launch than in three, 2.2 and 3.1 % the other way (0.1, 0.3, 7.1 and 7.6 % with the sums bounded apart, at 5000).
 //
 // The forward's choice is the same for one to four entries of as many channels out as in, each of which has blocks of its
 // own; else the result has no place for several entries.
@@ -248,9 +250,9 @@ bool xmix_fits(int B, int Ci, int Co, AxisPlan ax, int64_t inner, bool adjoint) 
   const int from = adjoint ? Co : Ci, to = adjoint ? Ci : Co, most = Ci > Co ? Ci : Co;
   const int64_t K1 = 1 + (ax.npos - 1 > ax.L - ax.npos ? ax.npos - 1 : ax.L - ax.npos);
   const int64_t sums = from * K1 * ax.N + to * (int64_t)(ax.N / 2 + 1) * ax.L, mix = (int64_t)Ci * Co * ax.L;
-  if (B > 4 || sums > 5000 || 4 * sums + 3 * mix > 28000) return false;
+  if (B > 4 || 4 * (adjoint ? B : 1) * sums + 3 * mix > 33600) return false;
   if (inner > 150000 || most * ax.N * inner > 150000 || mix * inner > (adjoint ? 1500000 : 1000000)) return false;
-  if (adjoint && (B * sums > 5000 || B * most * ax.N * inner > 300000 || (B > 1 && B * ax.N > 96))) return false;
+  if (adjoint && (B * most * ax.N * inner > 300000 || (B > 1 && B * ax.N > 96))) return false;
   if (!adjoint && B > 1 && Ci != Co) return false;
   int s;
   return xmix_geometry(adjoint ? B : 1, from, to, ax, inner, &s);

@@ -1190,6 +1190,9 @@ def test_fft_axis_kernels_match_oracle(case):
     (2, 3, 5, (11, 6, 5, 6), (3, 2, 1, 2), 1),
     (1, 2, 2, (10, 17, 17, 10), (2, 8, 8, 5), 1),
     (1, 17, 32, (6, 5, 4, 4), (1, 1, 1, 2), 0),
+    # one step inside it: many sums in an adjoint, many products of the mix
+    (1, 20, 10, (36, 4, 8, 6), (4, 1, 2, 2), 0),
+    (4, 29, 29, (16, 5, 5, 4), (3, 1, 1, 2), 1),
     # one step past it: kernels of their own for one to five entries
     (1, 12, 16, (30, 9, 8, 6), (7, 2, 2, 3), 0),
     (2, 12, 16, (30, 9, 8, 6), (7, 2, 2, 3), 0),
