@@ -39,7 +39,7 @@
 // add up, within a wave and between waves), else its traffic in part (64 x 30, three streams: 28 and 25 %, 3.8 TB/s): u
 // in registers allows two waves per SIMD; streaming u past accumulators for all output channels takes as many, and one
 // row at a time, with three waves, was no faster.  us before and after the whole rows and the waits: 64 x 30, 3600 columns of 20
-// channels, forward with the pre-activation 495 -> 435, adjoint 372 -> 332; 263 x 16, 8024 columns, 1730 -> 1640.
+// channels, forward with the pre-activation 495 -> 435, adjoint 372 -> 332; 263 x 16, 8024 columns, 1730 -> 1650.
 // Measured against the kernels that this one replaced (mixed-radix or dense sums with LDS staging, and
 // 4x4x1 tiles of one residue class), milliseconds: 20 channels, 68 x 118 columns of 263 x 16 3.95 -> 1.68; one block
 // forward and back: 20 channels, 64^3 x 20 0.89 -> 0.68, x 30 0.95 -> 0.81, 32 channels, 50 x 45 x 40 x 24
