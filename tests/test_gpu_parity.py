@@ -1120,6 +1120,13 @@ def test_many_columns_of_a_large_folded_spectrum(c, nz, mz, nt, mt):
     test_block_fwd_and_bwd_match_oracle((1, c, c, (28, 28, nz, nt), (1, 1, mz, mt), 0), B.FNO_ACT_GELU)
 
 
+@pytest.mark.parametrize("nx, ny", [(48, 32), (29, 53), (64, 32), (50, 41)])
+def test_short_last_tiles_of_columns_that_fill_the_chip_once(nx, ny):
+    """Folded inverse (z, t) stage with 12 channels, three tasks a column: on two waves at three quarters of the 2048 columns that
+    one wave each has on the chip at a time (1536) and past them (2050), on one wave between (1537, 2048)."""
+    test_block_fwd_and_bwd_match_oracle((1, 12, 12, (nx, ny, 35, 18), (1, 1, 5, 4), 0), B.FNO_ACT_GELU)
+
+
 @pytest.mark.parametrize("c, nz, mz, nt, mt", [
     (2, 611, 30, 4, 2), (1, 1215, 300, 3, 2), (2, 609, 304, 5, 3),      # folded, one row tile per block
     (3, 128, 64, 10, 5), (2, 160, 30, 24, 4), (2, 256, 100, 20, 9),     # mixed radix: many frequencies
